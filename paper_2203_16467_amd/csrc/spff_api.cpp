@@ -53,8 +53,8 @@ inline bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
 struct Layout {
   // ctl: two control blocks per slot (ticks alternate; the host uses the
-  // first); prow: two halves of row-forward partials (ticks alternate)
-  size_t ctl, prm, ptr, twx, twy, prow, prow1, pcol, pinv, list, bad, prof, seq, rec, kt, ktsum;
+  // first); prow: two halves of row partials (ticks alternate)
+  size_t ctl, prm, ptr, twx, twy, prow, prow1, pcol, list, bad, prof, seq, rec, kt, ktsum;
   size_t slot0, slot_bytes;
   // offsets inside a slot
   size_t E, phi, phi_ref, eps, theta, rm, pm, spec;
@@ -282,8 +282,10 @@ LaunchGeom geom_from_plan(const spff_config* c, int S, size_t csize, const spff_
   G.ngr = c->ny / pl.rows;
   G.threads = pl.row_threads;
   G.row_reg = pl.row_kind == SPFF_FFT_REG ? 1 : (pl.row_kind == SPFF_FFT_REG4 ? 2 : 0);
-  G.lds_row = G.row_reg ? ((size_t)pl.rows * (M + M / 8) + (size_t)M * (pl.rows + 1)) * csize
+  const size_t xch = (size_t)pl.rows * (M + M / 8), tile = (size_t)M * (pl.rows + 1);
+  G.lds_row = G.row_reg ? (M >= 1024 ? std::max(xch, tile) : xch + tile) * csize  // RowLds in spff_kernels.hip
                         : 3 * (size_t)pl.rows * (M + PAD) * csize;
+  if (G.row_reg) G.lds_row += (size_t)M * csize;  // twiddle factors
   G.W = pl.cols;
   G.ngc = M / pl.cols;
   G.threads_col = pl.col_threads;
@@ -292,6 +294,7 @@ LaunchGeom geom_from_plan(const spff_config* c, int S, size_t csize, const spff_
   G.nyq_free = c->nyquist == SPFF_NYQ_FREE ? 1 : 0;
   G.lds_col = G.col_reg ? (size_t)pl.cols * (c->ny + c->ny / 8) * csize
                         : 3 * (size_t)pl.cols * (c->ny + PAD) * csize;
+  if (G.col_reg) G.lds_col += (size_t)(c->ny / 2) * csize;
   return G;
 }
 
@@ -315,7 +318,6 @@ Layout layout(const spff_config* c, int S, size_t rsize, bool scratch_only = fal
   L.prow = take(sizeof(double) * S * c->ny * NP_ROW);
   L.prow1 = take(sizeof(double) * S * c->ny * NP_ROW);
   L.pcol = take(sizeof(double) * S * (c->nx / 2) * NP_COL);
-  L.pinv = take(sizeof(double) * S * c->ny * NP_INV);
   L.list = take(sizeof(int32_t) * S);
   L.bad = take(64);
   L.prof = take(sizeof(double) * 3 * S);
@@ -405,7 +407,6 @@ TickBufs<real> tick_bufs(const spff_problem* p) {
   B.prow[0] = reinterpret_cast<double*>(p->ws + p->L.prow);
   B.prow[1] = reinterpret_cast<double*>(p->ws + p->L.prow1);
   B.pcol = reinterpret_cast<double*>(p->ws + p->L.pcol);
-  B.pinv = reinterpret_cast<double*>(p->ws + p->L.pinv);
   B.prof = p->prof_on ? p->d_prof() : nullptr;
   B.seqs = p->d_seq();
   B.recs = p->d_rec();
@@ -424,6 +425,15 @@ hipError_t enqueue_block(spff_problem* p, int k, hipStream_t st, int b) {
     if (e != hipSuccess) return e;
   }
   return launch_close<real>(p->geoms[b], B, k, st);
+}
+
+// one tick of a diagnostic phase and the row kernel that finishes it (the
+// caller restores the control blocks)
+template <typename real>
+hipError_t enqueue_operator(spff_problem* p, hipStream_t st, int b) {
+  const TickBufs<real> B = tick_bufs<real>(p);
+  hipError_t e = launch_tick<real>(p->geoms[b], B, 0, st);
+  return e != hipSuccess ? e : launch_tick<real>(p->geoms[b], B, 1, st, true);
 }
 
 hipError_t enqueue_ticks(spff_problem* p, int k, hipStream_t st, int b) {
@@ -755,7 +765,8 @@ spff_status run_diag(spff_problem* p, int phase, const std::vector<int32_t>& slo
   if (lst != SPFF_OK) return lst;
   const bool prof = p->prof_on;
   p->prof_on = false;
-  hipError_t e = enqueue_ticks(p, 1, p->stream, b);
+  hipError_t e = p->cfg.precision == SPFF_FP64 ? enqueue_operator<double>(p, p->stream, b)
+                                               : enqueue_operator<float>(p, p->stream, b);
   p->prof_on = prof;
   if (e != hipSuccess) return fail(SPFF_E_DEVICE, "operator launch failed: %s", hipGetErrorString(e));
   for (int s : slots)
@@ -1377,7 +1388,6 @@ spff_status static_step(const spff_config* cfg, const Layout& L, const LaunchGeo
   B.prow[0] = reinterpret_cast<double*>(ws + L.prow);
   B.prow[1] = reinterpret_cast<double*>(ws + L.prow1);
   B.pcol = reinterpret_cast<double*>(ws + L.pcol);
-  B.pinv = reinterpret_cast<double*>(ws + L.pinv);
   const int K = cfg->ticks_per_sync;
   for (;;) {
     for (int i = 0; i < K; ++i) {

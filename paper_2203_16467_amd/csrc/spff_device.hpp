@@ -218,8 +218,23 @@ __device__ __forceinline__ void group_sync() {
 
 // LDS index of element i of an exchange area (one pad slot per 8 elements,
 // so that the stride-RD writes of a pass spread over the banks)
-__device__ __forceinline__ int xpad(int i) { return i + (i >> 3); }
+__device__ __forceinline__ constexpr int xpad(int i) { return i + (i >> 3); }
 template <int N> struct XArea { static constexpr int size = N + N / 8; };
+// xpad(base + q NS) - xpad(base) for the outputs base = (j - k) RD + k,
+// k = j mod NS, of a radix-RD pass: known at compile time, so that one
+// register addresses a butterfly's outputs (and one a lane's inputs; an
+// address each kept the registers of the row kernels' data).
+template <int NS, int RD>
+__device__ __forceinline__ constexpr int xdisp(int q) {
+  static_assert(NS % 8 == 0 || NS == 1 || (NS == 4 && RD == 4), "padding of this pass");
+  return NS % 8 == 0 ? q * (NS + NS / 8) : (NS == 1 ? q : 4 * q + (q >> 1));
+}
+// The same value, which the compiler takes for a new one: what is computed
+// from it is computed again instead of being kept in registers.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 
 template <bool INV, int RD, typename V>
 __device__ __forceinline__ void dft_small(V (&u)[RD]) {
@@ -277,9 +292,9 @@ __device__ __forceinline__ void reg_pass(cplx<real> (&v)[E], cplx<real>* x, int 
 #pragma unroll
       for (int q = 0; q < RD; ++q) o[t + q * B] = u[q];
     } else {
-      const int base = (j - k) * RD + k;
+      cplx<real>* wr = x + xpad((j - k) * RD + k);
 #pragma unroll
-      for (int q = 0; q < RD; ++q) x[xpad(base + q * NS)] = u[q];
+      for (int q = 0; q < RD; ++q) wr[xdisp<NS, RD>(q)] = u[q];
     }
   }
   if constexpr (LAST) {
@@ -287,8 +302,10 @@ __device__ __forceinline__ void reg_pass(cplx<real> (&v)[E], cplx<real>* x, int 
     for (int m = 0; m < E; ++m) v[m] = o[m];
   } else {
     group_sync<L>();
+    static_assert(L % 8 == 0, "a lane's inputs are a whole number of pad groups apart");
+    const cplx<real>* rd = x + xpad(lane);
 #pragma unroll
-    for (int m = 0; m < E; ++m) v[m] = x[xpad(lane + m * L)];
+    for (int m = 0; m < E; ++m) v[m] = rd[m * (L + L / 8)];
     group_sync<L>();
   }
 }
@@ -433,52 +450,53 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[NP], double* re
   }
 }
 
-// Sums (or maxima: bit j of max_mask) of NA arrays of partials, array j
-// being p[j][0..cnt[j]), by one wavefront in a fixed order: lane l runs
-// through p[j][l], p[j][l + 64], ... in index order, then a butterfly; every
-// lane returns the same values.  Used identically by the controller and by
-// kernels that need a scalar of the same tick.  The partials are loaded 512
-// at a time (eight per lane) for all NA arrays before any of them is summed,
-// so the arrays of one controller step cost one memory round trip per 512
-// work-groups rather than one per array and per 256.
-template <int NA>
-__device__ __forceinline__ void wave_reduce_partials_n(const double* const (&p)[NA], const int (&cnt)[NA],
-                                                       double (&out)[NA], unsigned max_mask = 0u) {
+// Sums over the work-groups' partials by one wavefront, in a fixed order:
+// lane l runs through p[l], p[l + 64], ... in index order, then the
+// wavefront combines; every lane returns the same values.  Array j of the
+// row partials is pr[j ngr .. (j + 1) ngr), j < nrow <= NP (array MAXSLOT, if
+// >= 0, is a maximum); the column partials are pc[0 .. ncol).  Four values per
+// lane and array (256 work-groups) are loaded for all arrays before any of
+// them is summed: one memory round trip per 256 work-groups, in one piece of
+// code for every phase (the controller step is part of every row
+// work-group, and its instructions are fetched cold in each launch).
+template <int NP>
+__device__ __forceinline__ void reduce_partials(const double* __restrict__ pr, int ngr, int nrow, int maxslot,
+                                                const double* __restrict__ pc, int ncol, double (&out)[NP],
+                                                double* outc) {
   const int lane = threadIdx.x & 63;
-  double s[NA];
-  int cmax = 0;
+  constexpr int NK = 4;
+  double s[NP], sc = 0.0;
 #pragma unroll
-  for (int j = 0; j < NA; ++j) {
-    s[j] = ((max_mask >> j) & 1u) ? -1.0e300 : 0.0;
-    cmax = cnt[j] > cmax ? cnt[j] : cmax;
-  }
-  for (int base = 0; base < cmax; base += 512) {
-    double a[NA][8];
+  for (int j = 0; j < NP; ++j) s[j] = j == maxslot ? -1.0e300 : 0.0;
+  const int cmax = ncol > ngr ? ncol : ngr;
+  for (int base = lane; base < cmax; base += 64 * NK) {
+    double a[NP][NK], c[NK];
 #pragma unroll
-    for (int j = 0; j < NA; ++j)
+    for (int k = 0; k < NK; ++k) c[k] = base + 64 * k < ncol ? pc[base + 64 * k] : 0.0;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int i = base + lane + 64 * k;
-        a[j][k] = i < cnt[j] ? p[j][i] : 0.0;
+    for (int j = 0; j < NP; ++j) {
+      if (j < nrow) {
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+          a[j][k] = base + 64 * k < ngr ? pr[j * ngr + base + 64 * k] : (j == maxslot ? -1.0e300 : 0.0);
       }
+    }
 #pragma unroll
-    for (int j = 0; j < NA; ++j)
+    for (int k = 0; k < NK; ++k) sc += c[k];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (base + lane + 64 * k < cnt[j]) s[j] = ((max_mask >> j) & 1u) ? fmax(s[j], a[j][k]) : s[j] + a[j][k];
+    for (int j = 0; j < NP; ++j) {
+      if (j < nrow) {
+#pragma unroll
+        for (int k = 0; k < NK; ++k) s[j] = j == maxslot ? fmax(s[j], a[j][k]) : s[j] + a[j][k];
       }
+    }
   }
 #pragma unroll
-  for (int j = 0; j < NA; ++j) out[j] = ((max_mask >> j) & 1u) ? wave_max(s[j]) : wave_sum(s[j]);
-}
-
-__device__ __forceinline__ double wave_reduce_partials(const double* __restrict__ p, int count,
-                                                       bool is_max = false) {
-  const double* const ps[1] = {p};
-  const int cs[1] = {count};
-  double o[1];
-  wave_reduce_partials_n<1>(ps, cs, o, is_max ? 1u : 0u);
-  return o[0];
+  for (int j = 0; j < NP; ++j) {
+    out[j] = 0.0;
+    if (j < nrow) out[j] = j == maxslot ? wave_max(s[j]) : wave_sum(s[j]);
+  }
+  *outc = ncol > 0 ? wave_sum(sc) : 0.0;
 }
 
 // ---------------------------------------------------------------------------

@@ -12,18 +12,26 @@
 //   AM_CHK  ||phi_n+1 - phi_n||_1 (Sec. 3.2.1)
 //   STATS   energies, mean stress, phi statistics
 //
-// The host advances all slots together in "ticks": one tick launches the
-// row-forward, column and row-inverse FFT kernels (each does the part of the
-// current phase that belongs to it, or nothing).  The controller step of a
-// tick -- reduce the tick's partial sums in a fixed order, compute the FP64
-// scalars (alpha, beta, norms) and move the slot to its next phase -- runs
-// at the start of the next tick's row-forward kernel, redundantly in every
-// work-group of the slot (same inputs, same order: same result), and for
-// the last tick of a block in a closing kernel.  The control block is
-// double-buffered across ticks: the row-forward kernel of tick i reads
-// block (i & 1), the group of row block 0 writes the advanced one to block
-// ((i + 1) & 1), which the column and row-inverse kernels of tick i read.
-// Ticks contain no host round trip, so blocks of ticks can be replayed as a
+// The host advances all slots together in "ticks".  A tick is two kernels:
+// the row kernel finishes the previous tick's phase (inverse row transforms
+// and its pointwise part) and starts the next one (its pointwise part and
+// the forward row transforms) in one pass over the rows, and the column
+// kernel applies the phase's operator per mode.  Both parts of a row kernel
+// can share a pass because every scalar the second part needs is known
+// before it: the mechanics residual is kept and updated in Fourier space, so
+// the column kernel gives ||r|| and with it beta; the BCCG transforms r and
+// the previous p, and the column kernel combines their spectra once it
+// knows beta.
+//
+// The controller step of a tick -- reduce the tick's partial sums in a fixed
+// order, compute the FP64 scalars (alpha, beta, norms) and move the slot to
+// its next phase -- runs at the start of the next tick's row kernel,
+// redundantly in every work-group of the slot (same inputs, same order: same
+// result), and for the last tick of a block in a closing kernel.  The
+// control block is double-buffered across ticks: the row kernel of tick i
+// reads block (i & 1), the group of row block 0 writes the advanced one to
+// block ((i + 1) & 1), which the column kernel of tick i reads.  Ticks
+// contain no host round trip, so blocks of ticks can be replayed as a
 // captured HIP graph; the host polls phases between blocks (the closing
 // kernel leaves the current block in buffer 0).
 #pragma once
@@ -44,13 +52,15 @@ enum Phase : int32_t {
   PH_X_LAP = 9,   // diagnostic: rm[0] = -lap theta[0]
   PH_TD_RESTORE = 10,  // time-discretized evolution: phi <- phi_n before a retry with dt/2
   PH_X_DISP = 11,      // diagnostic: rm[0..1] = displacement u* of the strain field in theta (3 planes)
+  // nothing to start: the row kernel only finishes the phase before
+  PH_PF_WAIT = 12, // PF_ASM of a near-equilibrium check
+  PH_X_END = 13,   // a diagnostic operator
 };
 
 // ctl.flags bits
 enum : int32_t {
   FL_FIRST_OF_STEP = 1,   // next M_RES copies phi -> phi_ref
-  FL_THETA_PENDING = 2,   // next M_RES applies eps* += theta
-  FL_CG_FIRST = 4,        // next M_CG is the first of a Newton step
+  FL_THETA_PENDING = 2,   // next M_RES applies eps* += theta + alpha p
   FL_INIT_SOLVE = 8,      // phase-field solve at zero strain (phi_init)
   FL_MECH_STARTED = 16,   // reference norm of the current mechanics solve set
   FL_NOT_CONVERGED = 32,  // an iteration cap was hit during the step
@@ -59,6 +69,7 @@ enum : int32_t {
   FL_STALLED = 256,       // BCCG residual stopped improving (stall guard)
   FL_NE_CHECK = 512,      // near-equilibrium: this PF_ASM evaluates -F_phi(phi_n, eps_n)
   FL_NE_SCALE = 1024,     // near-equilibrium: this PF_ASM first scales eps* by gamma
+  FL_THETA_FIRST = 2048,  // the CG iteration being finished was its Newton step's first: theta = 0
 };
 
 // Per-slot physical and solver parameters (read-only during a step).
@@ -92,6 +103,7 @@ struct SlotCtl {
   int32_t cg_newton, pf_it;         // CG iterations of the current Newton step, BCCG of the current solve
   int32_t newton_solve;             // Newton steps of the current mechanics solve
   int32_t pending;                  // the controller step of the last tick is still to run
+  int32_t inv, pad1;                // phase that the row kernel finishes before it starts `phase` (0: none)
   uint64_t t_start;                 // device wall clock at the start of the step
   int32_t ticks, status;
   double eps_bar[3];
@@ -111,6 +123,7 @@ struct SlotCtl {
   // near-equilibrium evolution: strain scaling of the step, largest -F_phi
   // before it, trigger flag (kept between load steps)
   double gamma, fmax_ne;
+  double dmax;                      // largest -h'(phi_n) psi0+ of the checked assembly
   int32_t ne_flag, pad2;
   // statistics of the finished step
   double F_e, F_f, sbar[3], phi_sum, phi_max, crack_px;
@@ -119,7 +132,7 @@ struct SlotCtl {
 // Per-slot device pointers (resident state + scratch).  Scratch planes are
 // shared between the mechanics and phase-field phases, which never overlap:
 //   theta[0..2] (mech update)      | d, b, phi_am   (phase field)
-//   rm[0..2]    (mech residual)    | r_pf = rm[0]
+//   rm[0..2]    (mech residual, half spectra [3][nx/2][ny]) | r_pf = rm[0]
 //   pm[0..2]    (mech direction)   | p_pf = pm[0], mask = bytes of pm[1]
 template <typename real>
 struct SlotPtr {
@@ -154,16 +167,19 @@ struct StepRec {
   double eps_bar[3];
 };
 
-// Device-side kernel timing (profiling) of one kernel: every work-group
-// lowers one of KT_LINES `start` words to its first clock reading and raises
-// one of KT_LINES `end` words to its last (hashed by work-group, one word per
-// 128-byte line, so that thousands of groups do not contend on one address).
-// Ticks alternate between two sets of three (one per FFT kernel).  An extra
-// work-group of the next tick's column kernel (or the closing kernel, for
-// the last tick of a block) folds, per FFT kernel, its activity (last end -
-// first start) and its span (first start to the next kernel's first start:
-// activity plus the dead time of its drain, write-back and the next
-// dispatch), and resets the words.
+// Device-side kernel timing (profiling) of one part of a tick: every
+// work-group lowers one of KT_LINES `start` words to its first clock reading
+// and raises one of KT_LINES `end` words to its last (hashed by work-group,
+// one word per 128-byte line, so that thousands of groups do not contend on
+// one address).  A tick has three parts: the row kernel's inverse part (its
+// start to the point where a group's inverse transforms are done), the row
+// kernel's forward part (from there to its end) and the column kernel.
+// Ticks alternate between two sets of three (row-forward, column,
+// row-inverse).  An extra work-group of the next tick's column kernel (or
+// the closing kernel, for the last tick of a block) folds, per part, its
+// activity (last end - first start) and its span (first start to the next
+// part's first start: for the column kernel that includes the dead time of
+// its drain, write-back and the next dispatch), and resets the words.
 constexpr int KT_LINES = 64;
 constexpr int KT_STRIDE = 16;  // 64-bit words per line
 struct KTime {
@@ -174,6 +190,5 @@ struct KTime {
 // Number of FP64 partials per work-group written by each kernel.
 constexpr int NP_ROW = 8;
 constexpr int NP_COL = 2;
-constexpr int NP_INV = 4;
 
 }  // namespace spff

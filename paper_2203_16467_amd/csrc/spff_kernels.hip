@@ -1,7 +1,7 @@
-// Solver kernels for gfx950.  One tick = k_rowfwd -> k_col -> k_rowinv over
-// all listed slots of a handle; the row-forward kernel first advances each
-// slot's control block by the controller step of the previous tick, and a
-// block of ticks ends with k_close (the controller step of its last tick).
+// Solver kernels for gfx950.  One tick = k_row -> k_col over all listed slots
+// of a handle; the row kernel first advances each slot's control block by the
+// controller step of the previous tick, and a block of ticks ends with
+// k_close (the controller step of its last tick).
 // Every kernel looks up the phase of its slot and does that phase's share of
 // the work (or returns).
 //
@@ -31,54 +31,6 @@ constexpr int THREADS = 256;
 constexpr int MAXE = 8;   // FFT elements per thread per chunk: M <= 2048
 constexpr int PAD = 1;    // complex padding per LDS row (bank spread)
 constexpr double TWO_PI = 6.283185307179586476925286766559;
-
-__device__ __forceinline__ int phase_comps_row(int phase) {
-  switch (phase) {
-    case PH_M_RES:
-    case PH_M_CG:
-    case PH_X_PROJ:
-    case PH_X_DISP:
-      return 3;
-    case PH_PF_ASM:
-    case PH_PF_PQ:
-    case PH_PF_R:
-    case PH_STATS:
-    case PH_X_LAP:
-      return 1;
-    default:
-      return 0;
-  }
-}
-
-// Number of FP64 partial sums a kernel's phase produces for the controller
-// (the leading entries of its accumulator array).
-__device__ __forceinline__ int nacc_rowfwd(int phase) {
-  switch (phase) {
-    case PH_M_RES:
-    case PH_PF_PQ:
-    case PH_PF_ASM:
-      return 2;
-    case PH_M_CG:
-    case PH_AM_CHK:
-      return 1;
-    case PH_STATS:
-      return NP_ROW;
-    default:
-      return 0;
-  }
-}
-__device__ __forceinline__ int nacc_rowinv(int phase) {
-  switch (phase) {
-    case PH_M_RES:
-    case PH_M_CG:
-      return 1;
-    case PH_PF_ASM:
-    case PH_PF_R:
-      return NP_INV;
-    default:
-      return 0;
-  }
-}
 
 // Row-kernel coordinates (row group g, list index si) of this work-group.
 // Work-groups are dispatched to the 8 XCDs round-robin by linear id; the
@@ -117,37 +69,63 @@ template <>
 struct Pair<double> {
   typedef double type __attribute__((ext_vector_type(2)));
 };
+// A pixel of a plane: a lane's byte offset plus a displacement in elements
+// that is known at compile time.  With the plane's base in scalar registers
+// this is the address form base + 32-bit lane offset + immediate: one vector
+// register addresses every plane and pixel pair of a lane (64-bit lane
+// addresses took more registers than the data and set the row kernels'
+// occupancy).  A plane holds less than 4 GiB.
+struct At {
+  unsigned b;
+  int d;
+};
+__device__ __forceinline__ At operator+(At o, int d) { return {o.b, o.d + d}; }
 template <typename real>
-__device__ __forceinline__ V2<real> ld2(const real* p) {
+__device__ __forceinline__ At at(int o) {
+  return {(unsigned)o * (unsigned)sizeof(real), 0};
+}
+template <typename T>
+__device__ __forceinline__ SPFF_GLOBAL T* gat(const void* p, unsigned b, int disp) {
+  return (SPFF_GLOBAL T*)((SPFF_GLOBAL char*)const_cast<void*>(p) + b + disp);
+}
+template <typename real>
+__device__ __forceinline__ V2<real> ld2(const real* p, At o) {
   using T = typename Pair<real>::type;
-  const T v = *(const SPFF_GLOBAL T*)(p);
+  const T v = *gat<const T>(p, o.b, o.d * (int)sizeof(real));
   return {v.x, v.y};
 }
 template <typename real>
-__device__ __forceinline__ void st2(real* p, real a, real b) {
+__device__ __forceinline__ void st2(real* p, At o, real a, real b) {
   using T = typename Pair<real>::type;
   T v;
   v.x = a;
   v.y = b;
-  *(SPFF_GLOBAL T*)(p) = v;
+  *gat<T>(p, o.b, o.d * (int)sizeof(real)) = v;
 }
-// one complex value of a spectrum
+// one complex value of a spectrum, element i + d (d known at compile time)
 template <typename real>
-__device__ __forceinline__ cplx<real> ldc(const cplx<real>* p) {
+__device__ __forceinline__ cplx<real> ldc(const cplx<real>* p, unsigned i, int d = 0) {
   using T = typename Pair<real>::type;
-  const T v = *(const SPFF_GLOBAL T*)(p);
+  const T v = *gat<const T>(p, i * (unsigned)sizeof(T), d * (int)sizeof(T));
   return mk<cplx<real>>(v.x, v.y);
 }
 template <typename real>
-__device__ __forceinline__ void stc(cplx<real>* p, const cplx<real>& c) {
+__device__ __forceinline__ void stc(cplx<real>* p, unsigned i, const cplx<real>& c, int d = 0) {
   using T = typename Pair<real>::type;
   T v;
   v.x = c.x;
   v.y = c.y;
-  *(SPFF_GLOBAL T*)(p) = v;
+  *gat<T>(p, i * (unsigned)sizeof(T), d * (int)sizeof(T)) = v;
 }
-__device__ __forceinline__ unsigned char ldb(const unsigned char* p) { return *(const SPFF_GLOBAL unsigned char*)(p); }
-__device__ __forceinline__ void stb(unsigned char* p, unsigned char v) { *(SPFF_GLOBAL unsigned char*)(p) = v; }
+// active-set bytes of a pixel pair (even pixel first)
+template <typename real>
+__device__ __forceinline__ unsigned short ldm(const unsigned char* p, At o) {
+  return *gat<const unsigned short>(p, o.b / (unsigned)sizeof(real), o.d);
+}
+template <typename real>
+__device__ __forceinline__ void stm(unsigned char* p, At o, bool a, bool b) {
+  *gat<unsigned short>(p, o.b / (unsigned)sizeof(real), o.d) = (unsigned short)((a ? 1u : 0u) | (b ? 0x100u : 0u));
+}
 
 template <typename real>
 __device__ __forceinline__ real lower_bound(real pref, const SlotParam& P) {
@@ -155,409 +133,500 @@ __device__ __forceinline__ real lower_bound(real pref, const SlotParam& P) {
   return pref >= real(P.threshold) ? pref : real(0);
 }
 
-// Per-slot scalars of a tick shared by the row prologue and epilogue.
+// What a row kernel does in one pass over its rows: finish the previous
+// tick's phase (its pointwise part works on inverse-transformed rows) and
+// start the next one (its pointwise part gives the rows to transform).
+enum RowOp : int {
+  RO_NONE = 0,
+  RO_RES,       // -> M_RES
+  RO_RES_CG,    // M_RES -> M_CG (the first iteration of a Newton step)
+  RO_CG_CG,     // M_CG -> M_CG
+  RO_ASM,       // -> PF_ASM
+  RO_ASM_PQ,    // PF_ASM -> PF_PQ (the first iteration)
+  RO_ASM_WAIT,  // PF_ASM -> PF_WAIT
+  RO_R_PQ,      // PF_R -> PF_PQ
+  RO_PQ,        // -> PF_PQ (the first iteration), after PF_WAIT
+  RO_PFR,       // -> PF_R
+  RO_AM,        // -> AM_CHK
+  RO_RESTORE,   // -> TD_RESTORE
+  RO_STATS,     // -> STATS
+  RO_X_IN,      // -> a diagnostic operator
+  RO_X_OUT,     // a diagnostic operator -> X_END
+};
+__device__ __forceinline__ int row_op(int inv, int phase) {
+  switch (phase) {
+    case PH_M_RES: return RO_RES;
+    case PH_M_CG: return inv == PH_M_RES ? RO_RES_CG : RO_CG_CG;
+    case PH_PF_ASM: return RO_ASM;
+    case PH_PF_PQ: return inv == PH_PF_ASM ? RO_ASM_PQ : (inv == PH_PF_R ? RO_R_PQ : RO_PQ);
+    case PH_PF_WAIT: return RO_ASM_WAIT;
+    case PH_PF_R: return RO_PFR;
+    case PH_AM_CHK: return RO_AM;
+    case PH_TD_RESTORE: return RO_RESTORE;
+    case PH_STATS: return RO_STATS;
+    case PH_X_PROJ:
+    case PH_X_DISP:
+    case PH_X_LAP: return RO_X_IN;
+    case PH_X_END: return RO_X_OUT;
+    default: return RO_NONE;
+  }
+}
+// components that arrive from / leave for the column kernel
+__device__ __forceinline__ constexpr int op_comps_in(int op, int inv) {
+  switch (op) {
+    case RO_RES_CG:
+    case RO_CG_CG: return 3;
+    case RO_ASM_PQ:
+    case RO_ASM_WAIT:
+    case RO_R_PQ: return 1;
+    case RO_X_OUT: return inv == PH_X_LAP ? 1 : 3;
+    default: return 0;
+  }
+}
+__device__ __forceinline__ constexpr int op_comps_out(int op, int phase) {
+  switch (op) {
+    case RO_RES:
+    case RO_RES_CG:
+    case RO_CG_CG: return 3;
+    case RO_R_PQ: return 2;
+    case RO_ASM:
+    case RO_ASM_PQ:
+    case RO_PQ:
+    case RO_PFR:
+    case RO_STATS: return 1;
+    case RO_X_IN: return phase == PH_X_LAP ? 1 : 3;
+    default: return 0;
+  }
+}
+// FP64 partial sums an op leaves for the controller (the leading entries of
+// its accumulators; RP_* below), and the entry that is a maximum
+__device__ __forceinline__ constexpr int op_nacc(int op) {
+  switch (op) {
+    case RO_RES:
+    case RO_ASM: return 2;
+    case RO_RES_CG:
+    case RO_CG_CG: return 1;
+    case RO_ASM_PQ:
+    case RO_PQ: return 5;
+    case RO_ASM_WAIT: return 4;
+    case RO_R_PQ:
+    case RO_STATS: return 8;
+    case RO_AM: return 1;
+    default: return 0;
+  }
+}
+__device__ __forceinline__ constexpr int op_maxslot(int op) {
+  return op == RO_STATS ? 3 : ((op == RO_ASM || op == RO_ASM_WAIT || op == RO_ASM_PQ) ? 1 : -1);
+}
+// M_RES: 0 ||sigma(eps_bar)||^2, 1 ||sigma||^2.  M_CG: 0 p.Cp.
+// PF_ASM: 0 ||b||^2, 1 max -h'(phi_n) psi0+.
+// Residual of PF_ASM / PF_R and PF_PQ (r: residual, m p: the direction on
+// the inactive pixels): 0 ||r||^2, 1 r.r_old (PF_R) or max -F_phi (PF_ASM),
+// 2 ||phi||^2, 3 ||d phi||^2, 4 sum d r^2, 5 sum d r mp, 6 sum d mp^2,
+// 7 r.mp.
+
+// Per-slot scalars of a tick used by the row kernels' pointwise work.
 template <typename real>
 struct RowCtx {
-  int phase, flags, split, contact, n, ncomp;  // split: driving-force model, contact: stress model
-  real lt, mt, kres, eb0, eb1, eb2, beta_m, beta_pf, alpha_pf;
+  int op, flags, split, contact, n, nin, nout;  // split: driving-force model, contact: stress model
+  real lt, mt, kres, eb0, eb1, eb2, alpha_m, beta_m, beta_pf, alpha_pf;
   real ne_gamma;  // near-equilibrium strain scaling (FL_NE_SCALE)
   double eta_dt;
 };
 
+// A value that every lane holds alike (read from LDS), in scalar registers:
+// the branches on it are then scalar branches.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ double uni(double v) { return read_lane(v, 0); }
+__device__ __forceinline__ float uni(float v) { return __int_as_float(uni(__float_as_int(v))); }
+
 template <typename real>
-__device__ __forceinline__ RowCtx<real> row_ctx(const SlotCtl& ctl, const SlotParam& P, int phase, int ncomp, int n) {
+__device__ __forceinline__ RowCtx<real> row_ctx(const SlotCtl& ctl, const SlotParam& P, int n) {
   RowCtx<real> X;
-  X.phase = phase;
-  X.flags = ctl.flags;
+  const int inv = uni(ctl.inv), phase = uni(ctl.phase);
+  X.op = row_op(inv, phase);
+  X.flags = uni(ctl.flags);
   X.split = P.split;
   X.contact = P.contact;
   X.n = n;
-  X.ncomp = ncomp;
+  X.nin = op_comps_in(X.op, inv);
+  X.nout = op_comps_out(X.op, phase);
   X.lt = real(P.lam_t);
   X.mt = real(P.mu_t);
   X.kres = real(P.k_res);
-  X.eb0 = real(ctl.eps_bar[0]);
-  X.eb1 = real(ctl.eps_bar[1]);
-  X.eb2 = real(ctl.eps_bar[2]);
-  X.beta_m = real(ctl.beta_m);
-  X.beta_pf = real(ctl.beta_pf);
-  X.alpha_pf = real(ctl.alpha_pf);
-  X.eta_dt = ctl.eta_dt;
-  X.ne_gamma = real(ctl.gamma);
+  X.eb0 = uni(real(ctl.eps_bar[0]));
+  X.eb1 = uni(real(ctl.eps_bar[1]));
+  X.eb2 = uni(real(ctl.eps_bar[2]));
+  X.alpha_m = uni(real(ctl.alpha_m));
+  X.beta_m = uni(real(ctl.beta_m));
+  X.beta_pf = uni(real(ctl.beta_pf));
+  X.alpha_pf = uni(real(ctl.alpha_pf));
+  X.eta_dt = uni(ctl.eta_dt);
+  X.ne_gamma = uni(real(ctl.gamma));
   return X;
 }
 
-// Row-forward prologue for the pixel pair (o, o + 1): the phase's pointwise
-// work, the values entering the transforms (val[c][0..1]) and the FP64
-// partial sums.
-// Inputs of the row prologue for one pixel pair, loaded ahead of the
-// arithmetic (see row_prologue_n); the slots each phase uses are listed
-// with pro_load_chunk.
+// Field planes of a slot, restrict-qualified through the kernel's call chain
+// so that loads of later pixel pairs may be issued before stores of earlier
+// ones (the pairs never overlap).
+#define SPFF_PLANES                                                                                        \
+  const real *__restrict__ Ep, real *__restrict__ phip, real *__restrict__ prefp, real *__restrict__ epsp, \
+      real *__restrict__ thp, real *__restrict__ rmp, real *__restrict__ pmp
+#define SPFF_PLANE_ARGS Ep, phip, prefp, epsp, thp, rmp, pmp
+
+// Inputs of one pixel pair: field values and two active-set bytes.  The
+// slots each op uses are those of pair_load / pair_work.
 template <typename real>
-struct ProIn {
+struct RowIn {
   V2<real> a[11];
-  unsigned char m[2];
+  unsigned short m;
 };
 
-template <typename real, int PH = -1, bool PRE = false>
-__device__ __forceinline__ void row_prologue(const RowCtx<real>& X, const SlotParam& P, const real* __restrict__ Ep,
-                                             real* __restrict__ phip, real* __restrict__ prefp,
-                                             real* __restrict__ epsp, real* __restrict__ thp,
-                                             real* __restrict__ rmp, real* __restrict__ pmp, int o,
-                                             real (&val)[3][2], double (&acc)[NP_ROW],
-                                             const ProIn<real>& in = ProIn<real>{}) {
-  // PH >= 0: the phase is known at compile time (the other cases fold away).
-  // PRE: the inputs of this pair were loaded into `in` (PH one of M_RES,
-  // M_CG, PF_ASM, PF_PQ, PF_R)
-  const int phase = PH >= 0 ? PH : X.phase;
-  const int flags = X.flags, split = X.split, contact = X.contact, n = X.n, ncomp = X.ncomp;
-  const real lt = X.lt, mt = X.mt, kres = X.kres, eb0 = X.eb0, eb1 = X.eb1, eb2 = X.eb2;
+// The CG vector updates of one pixel pair and tensor component, which need
+// nothing of the other components: of the register kinds they run right
+// after the component's inverse transform, so that one component's vectors
+// are in registers at a time.  q: the inverse-transformed residual r;
+// receives the direction p.
+//   M_RES -> M_CG   p = r
+//   M_CG  -> M_CG   theta += alpha p, p = r + beta p (theta = 0 before a
+//                   Newton step's first iteration: FL_THETA_FIRST)
+template <typename real>
+struct CompIn {
+  V2<real> p, th;
+};
+template <typename real, int OP, int NQ, int OSTEP>
+__device__ __forceinline__ void comp_load(const RowCtx<real>& X, const real* __restrict__ pk,
+                                          const real* __restrict__ tk, At o0, CompIn<real> (&in)[NQ]) {
+  if constexpr (OP == RO_CG_CG) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) val[0][q] = val[1][q] = val[2][q] = real(0);
-  switch (phase) {
-    case PH_M_RES: {
-      const V2<real> E = PRE ? in.a[0] : ld2(Ep + o), ph = PRE ? in.a[1] : ld2(phip + o);
-      if (flags & FL_FIRST_OF_STEP) st2(prefp + o, ph.a, ph.b);
-      V2<real> ex = PRE ? in.a[2] : ld2(epsp + o), ey = PRE ? in.a[3] : ld2(epsp + n + o),
-               exy = PRE ? in.a[4] : ld2(epsp + 2 * n + o);
-      if (flags & FL_THETA_PENDING) {
-        const V2<real> tx = PRE ? in.a[5] : ld2(thp + o), ty = PRE ? in.a[6] : ld2(thp + n + o),
-                       txy = PRE ? in.a[7] : ld2(thp + 2 * n + o);
-        ex = {ex.a + tx.a, ex.b + tx.b};
-        ey = {ey.a + ty.a, ey.b + ty.b};
-        exy = {exy.a + txy.a, exy.b + txy.b};
-        st2(epsp + o, ex.a, ex.b);
-        st2(epsp + n + o, ey.a, ey.b);
-        st2(epsp + 2 * n + o, exy.a, exy.b);
-      }
-      const real Ev[2] = {E.a, E.b}, pv[2] = {ph.a, ph.b};
-      const real xv[2] = {ex.a, ex.b}, yv[2] = {ey.a, ey.b}, sv[2] = {exy.a, exy.b};
+    for (int i = 0; i < NQ; ++i) in[i].p = ld2(pk, o0 + i * OSTEP);
+    if (!(X.flags & FL_THETA_FIRST)) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const real lam = lt * Ev[q], mu = mt * Ev[q];
-        const real hk = (real(1) - pv[q]) * (real(1) - pv[q]) + kres;
-        const Sym<real> e = {eb0 + xv[q], eb1 + yv[q], eb2 + sv[q]};
-        const Sym<real> sg = stress(e, lam, mu, hk, contact);
-        const Sym<real> eh = {eb0, eb1, eb2};
-        const Sym<real> sh = stress(eh, lam, mu, hk, contact);
-        acc[0] += double(ddot(sh, sh));
-        acc[1] += double(ddot(sg, sg));
-        val[0][q] = sg.xx;
-        val[1][q] = sg.yy;
-        val[2][q] = sg.xy;
-      }
-      break;
+      for (int i = 0; i < NQ; ++i) in[i].th = ld2(tk, o0 + i * OSTEP);
     }
-    case PH_M_CG: {
-      const V2<real> E = PRE ? in.a[0] : ld2(Ep + o), ph = PRE ? in.a[1] : ld2(phip + o);
-      V2<real> px = PRE ? in.a[2] : ld2(rmp + o), py = PRE ? in.a[3] : ld2(rmp + n + o),
-               pxy = PRE ? in.a[4] : ld2(rmp + 2 * n + o);
-      if (!(flags & FL_CG_FIRST)) {
-        const real bt = real(X.beta_m);
-        const V2<real> qx = PRE ? in.a[5] : ld2(pmp + o), qy = PRE ? in.a[6] : ld2(pmp + n + o),
-                       qxy = PRE ? in.a[7] : ld2(pmp + 2 * n + o);
-        px = {px.a + bt * qx.a, px.b + bt * qx.b};
-        py = {py.a + bt * qy.a, py.b + bt * qy.b};
-        pxy = {pxy.a + bt * qxy.a, pxy.b + bt * qxy.b};
-      }
-      st2(pmp + o, px.a, px.b);
-      st2(pmp + n + o, py.a, py.b);
-      st2(pmp + 2 * n + o, pxy.a, pxy.b);
-      V2<real> ex = {0, 0}, ey = {0, 0}, exy = {0, 0};
-      if (contact != 0) {
-        ex = PRE ? in.a[8] : ld2(epsp + o);
-        ey = PRE ? in.a[9] : ld2(epsp + n + o);
-        exy = PRE ? in.a[10] : ld2(epsp + 2 * n + o);
-      }
-      const real Ev[2] = {E.a, E.b}, pv[2] = {ph.a, ph.b};
-      const real xv[2] = {ex.a, ex.b}, yv[2] = {ey.a, ey.b}, sv[2] = {exy.a, exy.b};
-      const real pxv[2] = {px.a, px.b}, pyv[2] = {py.a, py.b}, psv[2] = {pxy.a, pxy.b};
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const real lam = lt * Ev[q], mu = mt * Ev[q];
-        const real hk = (real(1) - pv[q]) * (real(1) - pv[q]) + kres;
-        const Sym<real> e = {eb0 + xv[q], eb1 + yv[q], eb2 + sv[q]};
-        const Sym<real> p = {pxv[q], pyv[q], psv[q]};
-        const Sym<real> cp = tangent(e, p, lam, mu, hk, contact);
-        acc[0] += double(ddot(p, cp));
-        val[0][q] = cp.xx;
-        val[1][q] = cp.yy;
-        val[2][q] = cp.xy;
-      }
-      break;
-    }
-    case PH_PF_ASM: {
-      const V2<real> E = PRE ? in.a[0] : ld2(Ep + o), ph = PRE ? in.a[1] : ld2(phip + o),
-                     pr = PRE ? in.a[2] : ld2(prefp + o);
-      V2<real> ex = PRE ? in.a[3] : ld2(epsp + o), ey = PRE ? in.a[4] : ld2(epsp + n + o),
-               exy = PRE ? in.a[5] : ld2(epsp + 2 * n + o);
-      if (flags & FL_NE_SCALE) {
-        // near-equilibrium evolution: eps* <- gamma eps* (eps_bar was scaled
-        // by the controller)
-        const real g = X.ne_gamma;
-        ex = {g * ex.a, g * ex.b};
-        ey = {g * ey.a, g * ey.b};
-        exy = {g * exy.a, g * exy.b};
-        st2(epsp + o, ex.a, ex.b);
-        st2(epsp + n + o, ey.a, ey.b);
-        st2(epsp + 2 * n + o, exy.a, exy.b);
-      }
-      const real Ev[2] = {E.a, E.b}, pv[2] = {ph.a, ph.b}, rv[2] = {pr.a, pr.b};
-      const real xv[2] = {ex.a, ex.b}, yv[2] = {ey.a, ey.b}, sv[2] = {exy.a, exy.b};
-      real dv[2], bv[2], cv[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const real lam = lt * Ev[q], mu = mt * Ev[q];
-        const Sym<real> e = {eb0 + xv[q], eb1 + yv[q], eb2 + sv[q]};
-        real pp, pm;
-        energies(e, lam, mu, split, &pp, &pm);
-        dv[q] = real(2) * pp + real(P.cwl * P.wpp + X.eta_dt);
-        // crack driving force -h'(phi_n) psi0+ (near-equilibrium trigger)
-        if (flags & FL_NE_CHECK) acc[1] = fmax(acc[1], double(real(2) * (real(1) - rv[q]) * pp));
-        bv[q] = real(2) * pp - real(P.cwl * P.dw0) + real(X.eta_dt) * rv[q];
-        const real lo = lower_bound(rv[q], P);
-        cv[q] = fmin(fmax(pv[q], lo), real(1));
-        acc[0] += double(bv[q]) * double(bv[q]);
-        val[0][q] = cv[q];
-      }
-      st2(thp + o, dv[0], dv[1]);
-      st2(thp + n + o, bv[0], bv[1]);
-      st2(thp + 2 * n + o, ph.a, ph.b);  // phi at the start of this PF solve
-      st2(phip + o, cv[0], cv[1]);
-      break;
-    }
-    case PH_PF_PQ: {
-      const V2<real> r = PRE ? in.a[0] : ld2(rmp + o), d = PRE ? in.a[1] : ld2(thp + o);
-      V2<real> p;
-      if (flags & FL_PF_FIRST) {
-        p = {-r.a, -r.b};
-      } else {
-        const V2<real> po = PRE ? in.a[2] : ld2(pmp + o);
-        const real bt = real(X.beta_pf);
-        p = {-r.a + bt * po.a, -r.b + bt * po.b};
-      }
-      const unsigned char* mask = reinterpret_cast<const unsigned char*>(pmp + n);
-      if (PRE ? in.m[0] : ldb(mask + o)) p.a = real(0);
-      if (PRE ? in.m[1] : ldb(mask + o + 1)) p.b = real(0);
-      st2(pmp + o, p.a, p.b);
-      acc[0] += double(d.a) * double(p.a) * double(p.a) + double(d.b) * double(p.b) * double(p.b);
-      acc[1] += double(r.a) * double(p.a) + double(r.b) * double(p.b);
-      val[0][0] = p.a;
-      val[0][1] = p.b;
-      break;
-    }
-    case PH_PF_R: {
-      const V2<real> ph = PRE ? in.a[0] : ld2(phip + o), p = PRE ? in.a[1] : ld2(pmp + o),
-                     pr = PRE ? in.a[2] : ld2(prefp + o);
-      const real al = real(X.alpha_pf);
-      const real a0 = fmin(fmax(ph.a + al * p.a, lower_bound(pr.a, P)), real(1));
-      const real a1 = fmin(fmax(ph.b + al * p.b, lower_bound(pr.b, P)), real(1));
-      st2(phip + o, a0, a1);
-      val[0][0] = a0;
-      val[0][1] = a1;
-      break;
-    }
-    case PH_TD_RESTORE: {
-      const V2<real> pr = ld2(prefp + o);
-      st2(phip + o, pr.a, pr.b);
-      break;
-    }
-    case PH_AM_CHK: {
-      const V2<real> ph = ld2(phip + o), pa = ld2(thp + 2 * n + o);
-      acc[0] += fabs(double(ph.a) - double(pa.a)) + fabs(double(ph.b) - double(pa.b));
-      break;
-    }
-    case PH_STATS: {
-      const V2<real> E = ld2(Ep + o), ph = ld2(phip + o);
-      const V2<real> ex = ld2(epsp + o), ey = ld2(epsp + n + o), exy = ld2(epsp + 2 * n + o);
-      const real Ev[2] = {E.a, E.b}, pv[2] = {ph.a, ph.b};
-      const real xv[2] = {ex.a, ex.b}, yv[2] = {ey.a, ey.b}, sv[2] = {exy.a, exy.b};
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const real lam = lt * Ev[q], mu = mt * Ev[q];
-        const real hk = (real(1) - pv[q]) * (real(1) - pv[q]) + kres;
-        const Sym<real> e = {eb0 + xv[q], eb1 + yv[q], eb2 + sv[q]};
-        real pp, pm;
-        energies(e, lam, mu, contact, &pp, &pm);  // elastic energy of the stress model
-        const Sym<real> sg = stress(e, lam, mu, hk, contact);
-        acc[0] += double(hk) * double(pp) + double(pm);
-        acc[1] += P.at == 1 ? double(pv[q]) : double(pv[q]) * double(pv[q]);
-        acc[2] += double(pv[q]);
-        acc[3] = fmax(acc[3], double(pv[q]));
-        acc[4] += pv[q] > real(0.9) ? 1.0 : 0.0;
-        acc[5] += double(sg.xx);
-        acc[6] += double(sg.yy);
-        acc[7] += double(sg.xy);
-        val[0][q] = pv[q];
-      }
-      break;
-    }
-    case PH_X_PROJ:
-    case PH_X_DISP:
-    case PH_X_LAP: {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (c < ncomp) {
-          const V2<real> t = ld2(thp + c * n + o);
-          val[c][0] = t.a;
-          val[c][1] = t.b;
-        }
-      }
-      break;
-    }
-    default:
-      break;
   }
 }
+template <typename real, int OP>
+__device__ __forceinline__ void comp_update(const RowCtx<real>& X, real* __restrict__ pk, real* __restrict__ tk, At o,
+                                            const CompIn<real>& in, cplx<real>& q) {
+  using C = cplx<real>;
+  if constexpr (OP == RO_CG_CG) {
+    const bool first = X.flags & FL_THETA_FIRST;
+    st2(tk, o, (first ? real(0) : in.th.a) + X.alpha_m * in.p.a, (first ? real(0) : in.th.b) + X.alpha_m * in.p.b);
+    q = mk<C>(q.x + X.beta_m * in.p.a, q.y + X.beta_m * in.p.b);
+  }
+  st2(pk, o, q.x, q.y);
+}
 
-// The prologue for NQ pixel pairs o0 + q OSTEP of one lane.  The field
-// pointers are restrict-qualified here so that the loads of later pairs may
-// be issued before the stores of earlier ones (the pairs never overlap).
-// Loads the prologue inputs of CH pixel pairs o0 + c OSTEP of phase PH, all
-// before any of them is used: the arithmetic of a pair branches (the
-// spectral split), which keeps the compiler from issuing the next pair's
-// loads early, so without this every pair cost a memory round trip.  Loads
-// that depend on the phase's flags are grouped under one test per chunk.
-template <typename real, int PH, int CH, int OSTEP>
-__device__ __forceinline__ void pro_load_chunk(const RowCtx<real>& X, const real* __restrict__ Ep,
-                                               const real* __restrict__ phip, const real* __restrict__ prefp,
-                                               const real* __restrict__ epsp, const real* __restrict__ thp,
-                                               const real* __restrict__ rmp, const real* __restrict__ pmp, int o0,
-                                               ProIn<real> (&in)[CH]) {
+// Loads the inputs of the CH pixel pairs o0 + c OSTEP, all before any of
+// them is used: the arithmetic of a pair branches (the spectral split) and
+// ends in stores, and on this GPU a wait for a load also waits for the
+// stores issued before it, so a pair at a time costs a memory round trip
+// each.  Loads that depend on the flags are grouped under one test.
+// PNEW: the direction that comp_update stored is read back (from the L2)
+// rather than kept in registers.
+template <typename real, int OP, int CH, int OSTEP, bool PNEW>
+__device__ __forceinline__ void pair_load(const RowCtx<real>& X, SPFF_PLANES, At o0, RowIn<real> (&in)[CH]) {
   const int n = X.n, flags = X.flags;
-  if constexpr (PH == PH_M_RES) {
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int o = o0 + c * OSTEP;
-      in[c].a[0] = ld2(Ep + o);
-      in[c].a[1] = ld2(phip + o);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) in[c].a[2 + k] = ld2(epsp + k * n + o);
-    }
+#define SPFF_EACH(...)                  \
+  _Pragma("unroll") for (int c = 0; c < CH; ++c) { \
+    const At o = o0 + c * OSTEP;       \
+    RowIn<real>& I = in[c];             \
+    __VA_ARGS__                         \
+  }
+#define SPFF_LD3(S, PL) _Pragma("unroll") for (int k = 0; k < 3; ++k) I.a[(S) + k] = ld2((PL) + k * n, o);
+  if constexpr (OP == RO_RES || OP == RO_RES_CG || OP == RO_CG_CG || OP == RO_ASM || OP == RO_STATS) {
+    SPFF_EACH(I.a[0] = ld2(Ep, o); I.a[1] = ld2(phip, o);)
+    if (OP == RO_RES || OP == RO_ASM || OP == RO_STATS || X.contact != 0) SPFF_EACH(SPFF_LD3(2, epsp))
+  }
+  if constexpr (OP == RO_RES) {
     if (flags & FL_THETA_PENDING) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) in[c].a[5 + k] = ld2(thp + k * n + o0 + c * OSTEP);
+      if (!(flags & FL_THETA_FIRST)) SPFF_EACH(SPFF_LD3(5, thp))
+      SPFF_EACH(SPFF_LD3(8, pmp))
     }
-  } else if constexpr (PH == PH_M_CG) {
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int o = o0 + c * OSTEP;
-      in[c].a[0] = ld2(Ep + o);
-      in[c].a[1] = ld2(phip + o);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) in[c].a[2 + k] = ld2(rmp + k * n + o);
-    }
-    if (!(flags & FL_CG_FIRST)) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) in[c].a[5 + k] = ld2(pmp + k * n + o0 + c * OSTEP);
-    }
-    if (X.contact != 0) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) in[c].a[8 + k] = ld2(epsp + k * n + o0 + c * OSTEP);
-    }
-  } else if constexpr (PH == PH_PF_ASM) {
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int o = o0 + c * OSTEP;
-      in[c].a[0] = ld2(Ep + o);
-      in[c].a[1] = ld2(phip + o);
-      in[c].a[2] = ld2(prefp + o);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) in[c].a[3 + k] = ld2(epsp + k * n + o);
-    }
-  } else if constexpr (PH == PH_PF_PQ) {
+  }
+  if constexpr (PNEW && (OP == RO_RES_CG || OP == RO_CG_CG)) SPFF_EACH(SPFF_LD3(8, pmp))
+  if constexpr (OP == RO_ASM) SPFF_EACH(I.a[5] = ld2(prefp, o);)
+  if constexpr (OP == RO_ASM_PQ || OP == RO_ASM_WAIT || OP == RO_R_PQ) {
+    SPFF_EACH(I.a[0] = ld2(phip, o); I.a[1] = ld2(thp, o); I.a[2] = ld2(thp + n, o); I.a[3] = ld2(prefp, o);
+              if constexpr (OP == RO_R_PQ) {
+                I.a[4] = ld2(rmp, o);
+                I.a[5] = ld2(pmp, o);
+              })
+  }
+  if constexpr (OP == RO_PQ) SPFF_EACH(I.a[0] = ld2(rmp, o); I.a[1] = ld2(thp, o);)
+  if constexpr (OP == RO_PFR) {
     const unsigned char* mask = reinterpret_cast<const unsigned char*>(pmp + n);
+    SPFF_EACH(I.a[0] = ld2(phip, o); I.a[1] = ld2(prefp, o); I.a[2] = ld2(rmp, o);)
+    if (!(flags & FL_PF_FIRST)) SPFF_EACH(I.a[3] = ld2(pmp, o); I.m = ldm<real>(mask, o);)
+  }
+  if constexpr (OP == RO_AM) SPFF_EACH(I.a[0] = ld2(phip, o); I.a[1] = ld2(thp + 2 * n, o);)
+  if constexpr (OP == RO_RESTORE) SPFF_EACH(I.a[0] = ld2(prefp, o);)
+  if constexpr (OP == RO_X_IN) SPFF_EACH(for (int k = 0; k < 3; ++k) if (k < X.nout) I.a[k] = ld2(thp + k * n, o);)
+#undef SPFF_EACH
+#undef SPFF_LD3
+}
+
+// The pointwise work of one pixel pair (o, o + 1): q holds the
+// inverse-transformed values of the finished phase (x: o, y: o + 1; for the
+// CG ops the direction p that comp_update made of them) and receives the
+// values that enter the next phase's transforms.
+template <typename real, int OP>
+__device__ __forceinline__ void pair_work(const RowCtx<real>& X, const SlotParam& P, SPFF_PLANES, At o,
+                                          const RowIn<real>& in, cplx<real> (&q)[3], double (&acc)[NP_ROW]) {
+  using C = cplx<real>;
+  const int n = X.n, flags = X.flags;
+  [[maybe_unused]] const real eb[3] = {X.eb0, X.eb1, X.eb2};
+  // two pixels of three planes as tensors
+  [[maybe_unused]] auto tens = [](V2<real> x, V2<real> y, V2<real> s, int k) {
+    return Sym<real>{k ? x.b : x.a, k ? y.b : y.a, k ? s.b : s.a};
+  };
+  [[maybe_unused]] auto el = [](V2<real> v, int k) { return k ? v.b : v.a; };
+  if constexpr (OP == RO_RES) {
+    V2<real> e[3] = {in.a[2], in.a[3], in.a[4]};
+    if (flags & FL_FIRST_OF_STEP) st2(prefp, o, in.a[1].a, in.a[1].b);
+    if (flags & FL_THETA_PENDING) {
+      // the CG's last step alpha p is not in theta yet
+      const bool first = flags & FL_THETA_FIRST;
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int o = o0 + c * OSTEP;
-      in[c].a[0] = ld2(rmp + o);
-      in[c].a[1] = ld2(thp + o);
-      in[c].m[0] = ldb(mask + o);
-      in[c].m[1] = ldb(mask + o + 1);
+      for (int k = 0; k < 3; ++k) {
+        const V2<real> to = in.a[5 + k], po = in.a[8 + k];
+        const V2<real> th = {(first ? real(0) : to.a) + X.alpha_m * po.a, (first ? real(0) : to.b) + X.alpha_m * po.b};
+        e[k] = {e[k].a + th.a, e[k].b + th.b};
+        st2(epsp + k * n, o, e[k].a, e[k].b);
+      }
     }
+    // ||sigma(eps_bar)|| is the reference of a solve's first residual only
+    const bool ref = !(flags & FL_MECH_STARTED);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const real E = el(in.a[0], k), ph = el(in.a[1], k);
+      const real lam = X.lt * E, mu = X.mt * E;
+      const real hk = (real(1) - ph) * (real(1) - ph) + X.kres;
+      const Sym<real> t = tens(e[0], e[1], e[2], k);
+      const Sym<real> eps = {eb[0] + t.xx, eb[1] + t.yy, eb[2] + t.xy};
+      const Sym<real> sg = stress(eps, lam, mu, hk, X.contact);
+      if (ref) {
+        const Sym<real> eh = {eb[0], eb[1], eb[2]};
+        const Sym<real> sh = stress(eh, lam, mu, hk, X.contact);
+        acc[0] += double(ddot(sh, sh));
+      }
+      acc[1] += double(ddot(sg, sg));
+      (k ? q[0].y : q[0].x) = sg.xx;
+      (k ? q[1].y : q[1].x) = sg.yy;
+      (k ? q[2].y : q[2].x) = sg.xy;
+    }
+  }
+  if constexpr (OP == RO_RES_CG || OP == RO_CG_CG) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const real E = el(in.a[0], k), ph = el(in.a[1], k);
+      const real lam = X.lt * E, mu = X.mt * E;
+      const real hk = (real(1) - ph) * (real(1) - ph) + X.kres;
+      Sym<real> eps = {eb[0], eb[1], eb[2]};
+      if (X.contact != 0) {
+        const Sym<real> t = tens(in.a[2], in.a[3], in.a[4], k);
+        eps = {eb[0] + t.xx, eb[1] + t.yy, eb[2] + t.xy};
+      }
+      const Sym<real> pv = {k ? q[0].y : q[0].x, k ? q[1].y : q[1].x, k ? q[2].y : q[2].x};
+      const Sym<real> cp = tangent(eps, pv, lam, mu, hk, X.contact);
+      acc[0] += double(ddot(pv, cp));
+      (k ? q[0].y : q[0].x) = cp.xx;
+      (k ? q[1].y : q[1].x) = cp.yy;
+      (k ? q[2].y : q[2].x) = cp.xy;
+    }
+  }
+  if constexpr (OP == RO_ASM) {
+    V2<real> e[3] = {in.a[2], in.a[3], in.a[4]};
+    if (flags & FL_NE_SCALE) {
+      // near-equilibrium evolution: eps* <- gamma eps* (eps_bar was scaled
+      // by the controller)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        e[k] = {X.ne_gamma * e[k].a, X.ne_gamma * e[k].b};
+        st2(epsp + k * n, o, e[k].a, e[k].b);
+      }
+    }
+    real dv[2], bv[2], cv[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const real E = el(in.a[0], k), ph = el(in.a[1], k), rv = el(in.a[5], k);
+      const real lam = X.lt * E, mu = X.mt * E;
+      const Sym<real> t = tens(e[0], e[1], e[2], k);
+      const Sym<real> eps = {eb[0] + t.xx, eb[1] + t.yy, eb[2] + t.xy};
+      real pp, pm;
+      energies(eps, lam, mu, X.split, &pp, &pm);
+      dv[k] = real(2) * pp + real(P.cwl * P.wpp + X.eta_dt);
+      // crack driving force -h'(phi_n) psi0+ (near-equilibrium trigger)
+      if (flags & FL_NE_CHECK) acc[1] = fmax(acc[1], double(real(2) * (real(1) - rv) * pp));
+      bv[k] = real(2) * pp - real(P.cwl * P.dw0) + real(X.eta_dt) * rv;
+      cv[k] = fmin(fmax(ph, lower_bound(rv, P)), real(1));
+      acc[0] += double(bv[k]) * double(bv[k]);
+    }
+    st2(thp, o, dv[0], dv[1]);
+    st2(thp + n, o, bv[0], bv[1]);
+    st2(thp + 2 * n, o, in.a[1].a, in.a[1].b);  // phi at the start of this PF solve
+    st2(phip, o, cv[0], cv[1]);
+    q[0] = mk<C>(cv[0], cv[1]);
+  }
+  if constexpr (OP == RO_ASM_PQ || OP == RO_ASM_WAIT || OP == RO_R_PQ) {
+    const C lap = q[0];
+    const V2<real> ph = in.a[0], d = in.a[1], b = in.a[2], pr = in.a[3];
+    const real rr0 = d.a * ph.a + lap.x - b.a;
+    const real rr1 = d.b * ph.b + lap.y - b.b;
+    const real lo0 = lower_bound(pr.a, P), lo1 = lower_bound(pr.b, P);
+    const bool a0 = (ph.a <= lo0 && rr0 > real(0)) || (ph.a >= real(1) && rr0 < real(0));
+    const bool a1 = (ph.b <= lo1 && rr1 > real(0)) || (ph.b >= real(1) && rr1 < real(0));
+    const real r0 = a0 ? real(0) : rr0, r1 = a1 ? real(0) : rr1;
+    if constexpr (OP == RO_ASM_WAIT) {
+      // near-equilibrium evolution: phi = phi_n here, so the unmasked
+      // residual is F_phi(phi_n, eps_n); keep it for the search of x*
+      st2(rmp + n, o, rr0, rr1);
+      acc[1] = fmax(acc[1], fmax(-double(rr0), -double(rr1)));
+    }
+    st2(rmp, o, r0, r1);
+    acc[0] += double(r0) * r0 + double(r1) * r1;
+    acc[2] += double(ph.a) * ph.a + double(ph.b) * ph.b;
+    acc[3] += double(d.a * ph.a) * double(d.a * ph.a) + double(d.b * ph.b) * double(d.b * ph.b);
+    if constexpr (OP != RO_ASM_WAIT) {
+      acc[4] += double(d.a) * double(r0) * double(r0) + double(d.b) * double(r1) * double(r1);
+      q[0] = mk<C>(r0, r1);
+    }
+    if constexpr (OP == RO_R_PQ) {
+      unsigned char* mask = reinterpret_cast<unsigned char*>(pmp + n);
+      stm<real>(mask, o, a0, a1);
+      const V2<real> ro = in.a[4];
+      const real m0 = a0 ? real(0) : in.a[5].a, m1 = a1 ? real(0) : in.a[5].b;
+      acc[1] += double(r0) * ro.a + double(r1) * ro.b;
+      acc[5] += double(d.a) * double(r0) * double(m0) + double(d.b) * double(r1) * double(m1);
+      acc[6] += double(d.a) * double(m0) * double(m0) + double(d.b) * double(m1) * double(m1);
+      acc[7] += double(r0) * m0 + double(r1) * m1;
+      q[1] = mk<C>(m0, m1);
+    }
+  }
+  if constexpr (OP == RO_PQ) {
+    const V2<real> r = in.a[0], d = in.a[1];
+    acc[0] += double(r.a) * r.a + double(r.b) * r.b;
+    acc[4] += double(d.a) * double(r.a) * double(r.a) + double(d.b) * double(r.b) * double(r.b);
+    q[0] = mk<C>(r.a, r.b);
+  }
+  if constexpr (OP == RO_PFR) {
+    const V2<real> ph = in.a[0], pr = in.a[1], r = in.a[2];
+    V2<real> p = {-r.a, -r.b};
     if (!(flags & FL_PF_FIRST)) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c) in[c].a[2] = ld2(pmp + o0 + c * OSTEP);
+      p = {-r.a + X.beta_pf * in.a[3].a, -r.b + X.beta_pf * in.a[3].b};
+      if (in.m & 0xffu) p.a = real(0);
+      if (in.m >> 8) p.b = real(0);
     }
-  } else if constexpr (PH == PH_PF_R) {
+    st2(pmp, o, p.a, p.b);
+    const real a0 = fmin(fmax(ph.a + X.alpha_pf * p.a, lower_bound(pr.a, P)), real(1));
+    const real a1 = fmin(fmax(ph.b + X.alpha_pf * p.b, lower_bound(pr.b, P)), real(1));
+    st2(phip, o, a0, a1);
+    q[0] = mk<C>(a0, a1);
+  }
+  if constexpr (OP == RO_RESTORE) st2(phip, o, in.a[0].a, in.a[0].b);
+  if constexpr (OP == RO_AM)
+    acc[0] += fabs(double(in.a[0].a) - double(in.a[1].a)) + fabs(double(in.a[0].b) - double(in.a[1].b));
+  if constexpr (OP == RO_STATS) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const real E = el(in.a[0], k), pv = el(in.a[1], k);
+      const real lam = X.lt * E, mu = X.mt * E;
+      const real hk = (real(1) - pv) * (real(1) - pv) + X.kres;
+      const Sym<real> t = tens(in.a[2], in.a[3], in.a[4], k);
+      const Sym<real> eps = {eb[0] + t.xx, eb[1] + t.yy, eb[2] + t.xy};
+      real pp, pm;
+      energies(eps, lam, mu, X.contact, &pp, &pm);  // elastic energy of the stress model
+      const Sym<real> sg = stress(eps, lam, mu, hk, X.contact);
+      acc[0] += double(hk) * double(pp) + double(pm);
+      acc[1] += P.at == 1 ? double(pv) : double(pv) * double(pv);
+      acc[2] += double(pv);
+      acc[3] = fmax(acc[3], double(pv));
+      acc[4] += pv > real(0.9) ? 1.0 : 0.0;
+      acc[5] += double(sg.xx);
+      acc[6] += double(sg.yy);
+      acc[7] += double(sg.xy);
+      (k ? q[0].y : q[0].x) = pv;
+    }
+  }
+  if constexpr (OP == RO_X_IN) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < X.nout) q[k] = mk<C>(in.a[k].a, in.a[k].b);
+  }
+  if constexpr (OP == RO_X_OUT) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < X.nin) st2(rmp + k * n, o, q[k].x, q[k].y);
+  }
+}
+
+// Makes the compiler finish the sums so far: it would otherwise put the FP64
+// additions of all of a lane's pixels off to the end and keep their FP32
+// terms in registers until then.
+template <int NP>
+__device__ __forceinline__ void settle(double (&acc)[NP], int first, int last) {
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+    if (i >= first && i < last) asm volatile("" : "+v"(acc[i]));
+}
+
+// Calls F<op>() for the op of this tick.
+#define SPFF_ROW_SWITCH(op, F) \
+  switch (op) {                \
+    case RO_RES: F(RO_RES); break;           \
+    case RO_RES_CG: F(RO_RES_CG); break;     \
+    case RO_CG_CG: F(RO_CG_CG); break;       \
+    case RO_ASM: F(RO_ASM); break;           \
+    case RO_ASM_PQ: F(RO_ASM_PQ); break;     \
+    case RO_ASM_WAIT: F(RO_ASM_WAIT); break; \
+    case RO_R_PQ: F(RO_R_PQ); break;         \
+    case RO_PQ: F(RO_PQ); break;             \
+    case RO_PFR: F(RO_PFR); break;           \
+    case RO_AM: F(RO_AM); break;             \
+    case RO_RESTORE: F(RO_RESTORE); break;   \
+    case RO_STATS: F(RO_STATS); break;       \
+    case RO_X_IN: F(RO_X_IN); break;         \
+    case RO_X_OUT: F(RO_X_OUT); break;       \
+    default: break;                          \
+  }
+
+// The pointwise work of a lane's NQ pixel pairs o0 + i OSTEP, in chunks of
+// CH pairs that are loaded in full before their arithmetic.
+template <typename real, int OP, int NQ, int CH, int OSTEP, bool PNEW>
+__device__ __forceinline__ void row_pairs(const RowCtx<real>& X, const SlotParam& P, SPFF_PLANES, At o0,
+                                          cplx<real> (&v)[3][NQ], double (&acc)[NP_ROW]) {
+  static_assert(NQ % CH == 0, "pairs per lane in whole chunks");
+#pragma unroll
+  for (int q0 = 0; q0 < NQ; q0 += CH) {
+    RowIn<real> in[CH];
+    if (q0) asm volatile("" ::: "memory");  // keeps later chunks' loads out of this chunk's registers
+    pair_load<real, OP, CH, OSTEP, PNEW>(X, SPFF_PLANE_ARGS, o0 + q0 * OSTEP, in);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-      const int o = o0 + c * OSTEP;
-      in[c].a[0] = ld2(phip + o);
-      in[c].a[1] = ld2(pmp + o);
-      in[c].a[2] = ld2(prefp + o);
-    }
-  }
-}
-
-template <typename real, int NQ, int OSTEP>
-__device__ __forceinline__ void row_prologue_n(const RowCtx<real>& X, const SlotParam& P, const real* __restrict__ Ep,
-                                               real* __restrict__ phip, real* __restrict__ prefp,
-                                               real* __restrict__ epsp, real* __restrict__ thp,
-                                               real* __restrict__ rmp, real* __restrict__ pmp, int o0,
-                                               real (&val)[NQ][3][2], double (&acc)[NP_ROW]) {
-#define SPFF_PRO_CASE(PHC)                                                                                 \
-  case PHC:                                                                                               \
-    _Pragma("unroll") for (int q = 0; q < NQ; ++q)                                                        \
-        row_prologue<real, PHC>(X, P, Ep, phip, prefp, epsp, thp, rmp, pmp, o0 + q * OSTEP, val[q], acc); \
-    break;
-  // the phases a solve iterates on: chunks of up to four pairs, each loaded
-  // in full before its arithmetic (with sixteen pairs per lane, 2048-point
-  // rows, the registers are spent and the per-pair path is faster)
-  constexpr bool CHUNK = NQ <= 8;
-  constexpr int CH = NQ < 4 ? NQ : 4;
-  static_assert(NQ % CH == 0, "pairs per lane in whole chunks");
-#define SPFF_PRO_HOT(PHC)                                                                                    \
-  case PHC:                                                                                                 \
-    if constexpr (CHUNK) {                                                                                  \
-      _Pragma("unroll") for (int q0 = 0; q0 < NQ; q0 += CH) {                                               \
-        ProIn<real> in[CH];                                                                                 \
-        pro_load_chunk<real, PHC, CH, OSTEP>(X, Ep, phip, prefp, epsp, thp, rmp, pmp, o0 + q0 * OSTEP, in); \
-        _Pragma("unroll") for (int c = 0; c < CH; ++c)                                                      \
-            row_prologue<real, PHC, true>(X, P, Ep, phip, prefp, epsp, thp, rmp, pmp,                       \
-                                          o0 + (q0 + c) * OSTEP, val[q0 + c], acc, in[c]);                  \
-      }                                                                                                     \
-    } else {                                                                                                \
-      _Pragma("unroll") for (int q = 0; q < NQ; ++q)                                                        \
-          row_prologue<real, PHC>(X, P, Ep, phip, prefp, epsp, thp, rmp, pmp, o0 + q * OSTEP, val[q], acc); \
-    }                                                                                                       \
-    break;
-  switch (X.phase) {
-    SPFF_PRO_HOT(PH_M_RES)
-    SPFF_PRO_HOT(PH_M_CG)
-    SPFF_PRO_HOT(PH_PF_ASM)
-    SPFF_PRO_HOT(PH_PF_PQ)
-    SPFF_PRO_HOT(PH_PF_R)
-    SPFF_PRO_CASE(PH_AM_CHK)
-    SPFF_PRO_CASE(PH_TD_RESTORE)
-    SPFF_PRO_CASE(PH_STATS)
-    SPFF_PRO_CASE(PH_X_PROJ)
-    SPFF_PRO_CASE(PH_X_DISP)
-    SPFF_PRO_CASE(PH_X_LAP)
-    default:
+      cplx<real> q[3];
 #pragma unroll
-      for (int q = 0; q < NQ; ++q)
-        val[q][0][0] = val[q][0][1] = val[q][1][0] = val[q][1][1] = val[q][2][0] = val[q][2][1] = real(0);
-      break;
+      for (int k = 0; k < 3; ++k) {
+        if constexpr (PNEW && (OP == RO_RES_CG || OP == RO_CG_CG))
+          q[k] = mk<cplx<real>>(in[c].a[8 + k].a, in[c].a[8 + k].b);
+        else
+          q[k] = v[k][q0 + c];
+      }
+      pair_work<real, OP>(X, P, SPFF_PLANE_ARGS, o0 + (q0 + c) * OSTEP, in[c], q, acc);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[k][q0 + c] = q[k];
+    }
+    settle(acc, 0, op_nacc(OP));
   }
-#undef SPFF_PRO_CASE
-#undef SPFF_PRO_HOT
 }
 
-// Inputs of the controller step that a row-forward kernel runs for the
-// previous tick (and the closing kernel for the last tick of a block).
+// Inputs of the controller step that a row kernel runs for the previous
+// tick (and the closing kernel for the last tick of a block).
 struct CtrlArgs {
   const SlotCtl* ctl_in;  // control blocks as the previous tick left them
-  SlotCtl* ctl_out;       // advanced blocks, read by this tick's other kernels
+  SlotCtl* ctl_out;       // advanced blocks, read by this tick's column kernel
   const double* prow;     // partial sums of the previous tick
   const double* pcol;
-  const double* pinv;
   double* prof;
   SlotSeq* seqs;
   StepRec* recs;
@@ -568,9 +637,46 @@ template <typename real>
 __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict__ ptrs,
                                           const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
                                           const double* __restrict__ prow, const double* __restrict__ pcol,
-                                          const double* __restrict__ pinv, double* __restrict__ prof,
-                                          SlotSeq* __restrict__ seqs, StepRec* __restrict__ recs, int nx, int ny,
-                                          int ngr, int ngc);
+                                          double* __restrict__ prof, SlotSeq* __restrict__ seqs,
+                                          StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc);
+
+// Timers of a row kernel's two parts (null when profiling is off).
+struct RowTimers {
+  KTime* inv;
+  KTime* fwd;
+};
+__device__ __forceinline__ void row_middle(const RowTimers& T);
+
+__device__ __forceinline__ void init_acc(int op, double (&acc)[NP_ROW]) {
+#pragma unroll
+  for (int i = 0; i < NP_ROW; ++i) acc[i] = 0.0;
+  if (op == RO_STATS) acc[3] = -1.0e300;
+  if (op == RO_ASM_WAIT || op == RO_ASM_PQ) acc[1] = -1.0e300;
+}
+
+// Twiddle factors of a register kind's transforms in LDS.  A global load waits for
+// every load and store that its wavefront issued before it, so twiddles read
+// from memory made each transform wait for the field stores ahead of it; LDS
+// reads are counted apart.  The loads are issued first thing in the kernel,
+// the table is stored once the control block is known.
+template <typename real, int NT>
+struct TwLoad {
+  cplx<real> t[NT];
+  __device__ __forceinline__ void load(const cplx<real>* tw, int count) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const int i = threadIdx.x + k * blockDim.x;
+      if (i < count) t[k] = ldc<real>(tw, (unsigned)i);
+    }
+  }
+  __device__ __forceinline__ void store(cplx<real>* tab, int count) const {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const int i = threadIdx.x + k * blockDim.x;
+      if (i < count) tab[i] = t[k];
+    }
+  }
+};
 
 // Control block of slot s for this tick, in `lc` (LDS): a copy of the input
 // block, advanced by the controller step of the previous tick if that is
@@ -578,12 +684,13 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
 // same inputs reduced in the same order); the one that owns row block 0
 // (`writer`) publishes it to ctl_out and records the step.  The input block
 // is not written, so groups that start late read what the early ones read.
-// Every thread of the group calls this (it synchronises the group).
-template <typename real>
+// Every thread of the group calls this (it synchronises the group); `also`
+// runs in every thread before the last synchronisation.
+template <typename real, typename Also>
 __device__ __forceinline__ void tick_control(int s, bool writer, const CtrlArgs& A,
                                              const SlotPtr<real>* __restrict__ ptrs,
                                              const SlotParam* __restrict__ prms, int nx, int ny, int ngr,
-                                             SlotCtl& lc) {
+                                             SlotCtl& lc, Also also) {
   constexpr int NW = (int)(sizeof(SlotCtl) / sizeof(int));
   static_assert(sizeof(SlotCtl) % sizeof(int) == 0, "the control block is copied as words");
   const int* src = reinterpret_cast<const int*>(A.ctl_in + s);
@@ -592,11 +699,11 @@ __device__ __forceinline__ void tick_control(int s, bool writer, const CtrlArgs&
   __syncthreads();
   if (threadIdx.x < 64) {
     if (lc.pending)
-      ctrl_slot<real>(s, ptrs, prms, lc, writer, A.prow, A.pcol, A.pinv, A.prof, A.seqs, A.recs, nx, ny, ngr,
-                      A.ngc);
+      ctrl_slot<real>(s, ptrs, prms, lc, writer, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc);
     // the slot's controller step after this tick is pending if it works
     if (threadIdx.x == 0) lc.pending = lc.phase != PH_IDLE ? 1 : 0;
   }
+  also();
   __syncthreads();
   if (writer) {
     int* out = reinterpret_cast<int*>(A.ctl_out + s);
@@ -605,15 +712,15 @@ __device__ __forceinline__ void tick_control(int s, bool writer, const CtrlArgs&
 }
 
 // ===========================================================================
-// Row-forward kernel: prologue (per phase) -> R2C row FFTs -> transposed
-// store of the half spectra; FP64 partial sums per work-group.
+// Row kernel (LDS kind): transposed load of the half spectra -> C2R row FFTs
+// -> pointwise work -> R2C row FFTs -> transposed store; FP64 partial sums
+// per work-group.  Each part runs if the slot's phases need it.
 // ===========================================================================
 template <typename real>
-__device__ __forceinline__ void k_rowfwd_body(const int* __restrict__ list,
-                                                    const SlotPtr<real>* __restrict__ ptrs,
-                                                    const SlotParam* __restrict__ prms, const CtrlArgs A,
-                                                    const cplx<real>* __restrict__ twx, double* __restrict__ part,
-                                                    int nx, int ny, int R, int ngr) {
+__device__ __forceinline__ void k_row_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
+                                           const SlotParam* __restrict__ prms, const CtrlArgs A,
+                                           const cplx<real>* __restrict__ twx, double* __restrict__ part, int nx,
+                                           int ny, int R, int ngr, const RowTimers T) {
   using C = cplx<real>;
   extern __shared__ unsigned char smem_raw[];
   __shared__ double red[(THREADS / 64) * NP_ROW];
@@ -622,54 +729,69 @@ __device__ __forceinline__ void k_rowfwd_body(const int* __restrict__ list,
   row_coords(ngr, g, si);
   const int s = list[si];
   if (s < 0) return;
-  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl);
-  const SlotCtl& ctl = lctl;
-  const int phase = ctl.phase;
-  const int ncomp = phase_comps_row(phase);
-  if (phase != PH_AM_CHK && phase != PH_TD_RESTORE && ncomp == 0) return;
+  const int M = nx >> 1, stride = M + PAD;
+  C* buf = reinterpret_cast<C*>(smem_raw);
+  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl, []() {});
   const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
-  const int flags = ctl.flags;
-  const int M = nx >> 1, stride = M + PAD;
-  const int y0 = g * R;
   const int n = nx * ny;
-  C* buf = reinterpret_cast<C*>(smem_raw);
-  double acc[NP_ROW];
-#pragma unroll
-  for (int i = 0; i < NP_ROW; ++i) acc[i] = 0.0;
-  if (phase == PH_STATS) acc[3] = -1.0e300;
-
-  const RowCtx<real> X = row_ctx<real>(ctl, P, phase, ncomp, n);
-
+  const RowCtx<real> X = row_ctx<real>(lctl, P, n);
+  if (X.op == RO_NONE) return;
+  const int y0 = g * R;
+  C* spec = reinterpret_cast<C*>(F.spec);
   const int logM = ilog2(M), logR = ilog2(R);
-  for (int idx = threadIdx.x; idx < R * M; idx += blockDim.x) {
-    const int r = idx >> logM, h = idx & (M - 1);
-    const int o = (y0 + r) * nx + 2 * h;
-    const int li = r * stride + h;  // LDS index of component 0
-    real val[3][2];
-    row_prologue<real>(X, P, F.E, F.phi, F.phi_ref, F.eps, F.theta, F.rm, F.pm, o, val, acc);
-    if (ncomp > 0) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (c < ncomp) buf[c * R * stride + li] = mk<C>(val[c][0], val[c][1]);
-    }
-  }
-  if (ncomp > 0) {
-    __syncthreads();
-    fft_lds<real, false, MAXE>(buf, M, ncomp * R, stride, twx, 2);
-    r2c_post<real>(buf, M, ncomp * R, stride, twx);
-    // transposed store: spec[c][kx][y0 + r]
-    C* spec = reinterpret_cast<C*>(F.spec);
-    const int tot = ncomp * M * R;
+  if (X.nin > 0) {
+    const int tot = X.nin * M * R;
     for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
       const int r = idx & (R - 1);
       const int rest = idx >> logR;
       const int kx = rest & (M - 1), c = rest >> logM;
-      stc<real>(spec + (size_t)(rest) * ny + y0 + r, buf[(c * R + r) * stride + kx]);
+      buf[(c * R + r) * stride + kx] = ldc<real>(spec, (unsigned)(rest * ny + y0 + r));
+    }
+    __syncthreads();
+    c2r_pre<real>(buf, M, X.nin * R, stride, twx);
+    fft_lds<real, true, MAXE>(buf, M, X.nin * R, stride, twx, 2);
+  }
+  row_middle(T);
+  double acc[NP_ROW];
+  init_acc(X.op, acc);
+  const real *Ep = F.E;
+  real *phip = F.phi, *prefp = F.phi_ref, *epsp = F.eps, *thp = F.theta, *rmp = F.rm, *pmp = F.pm;
+#define SPFF_ROW_LOOP(OPC)                                                                       \
+  for (int idx = threadIdx.x; idx < R * M; idx += blockDim.x) {                                  \
+    const int r = idx >> logM, h = idx & (M - 1);                                                \
+    const At o = at<real>((y0 + r) * nx + 2 * h);                                                \
+    C* b = buf + r * stride + h;                                                                 \
+    RowIn<real> in[1];                                                                           \
+    pair_load<real, OPC, 1, 1, false>(X, SPFF_PLANE_ARGS, o, in);                                \
+    C q[3];                                                                                      \
+    _Pragma("unroll") for (int c = 0; c < 3; ++c) q[c] = c < X.nin ? b[c * R * stride] : mk<C>(real(0), real(0)); \
+    if constexpr (OPC == RO_RES_CG || OPC == RO_CG_CG) {                                         \
+      CompIn<real> ci[3][1];                                                                     \
+      _Pragma("unroll") for (int c = 0; c < 3; ++c)                                              \
+          comp_load<real, OPC, 1, 1>(X, pmp + c * n, thp + c * n, o, ci[c]);                     \
+      _Pragma("unroll") for (int c = 0; c < 3; ++c)                                              \
+          comp_update<real, OPC>(X, pmp + c * n, thp + c * n, o, ci[c][0], q[c]);                \
+    }                                                                                            \
+    pair_work<real, OPC>(X, P, SPFF_PLANE_ARGS, o, in[0], q, acc);                               \
+    _Pragma("unroll") for (int c = 0; c < 3; ++c) if (c < X.nout) b[c * R * stride] = q[c];      \
+  }
+  SPFF_ROW_SWITCH(X.op, SPFF_ROW_LOOP)
+#undef SPFF_ROW_LOOP
+  if (X.nout > 0) {
+    __syncthreads();
+    fft_lds<real, false, MAXE>(buf, M, X.nout * R, stride, twx, 2);
+    r2c_post<real>(buf, M, X.nout * R, stride, twx);
+    // transposed store: spec[c][kx][y0 + r]
+    const int tot = X.nout * M * R;
+    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
+      const int r = idx & (R - 1);
+      const int rest = idx >> logR;
+      const int kx = rest & (M - 1), c = rest >> logM;
+      stc<real>(spec, (unsigned)(rest * ny + y0 + r), buf[(c * R + r) * stride + kx]);
     }
   }
-  block_reduce_store<NP_ROW>(acc, red, part + (size_t)s * NP_ROW * ngr + g, ngr, nacc_rowfwd(phase),
-                             phase == PH_STATS ? 3 : (phase == PH_PF_ASM ? 1 : -1));
+  block_reduce_store<NP_ROW>(acc, red, part + (size_t)s * NP_ROW * ngr + g, ngr, op_nacc(X.op), op_maxslot(X.op));
 }
 
 // ===========================================================================
@@ -739,47 +861,100 @@ __device__ __forceinline__ void disp3(cplx<real>* v, real fx, real fy, real scal
   v[2] = mk<C>(real(0), real(0));
 }
 
+// What the column kernel does for a phase.  combine: the search direction's
+// spectrum is -R + beta Q, R and Q the transforms of the residual and of the
+// previous direction (components 0 and 1).
+enum ColMode : int {
+  CM_PROJECT = 0,  // G^, for a diagnostic
+  CM_LAP,          // Laplacian symbol
+  CM_SUM,          // Parseval reduction of the Laplacian's quadratic form
+  CM_DISP,         // displacement
+  CM_RES,          // residual r^ = -G^ sigma^ and its norm
+  CM_CG,           // r^ -= alpha G^ (C p)^ and its norm
+};
+struct ColOp {
+  int ncomp, mode;
+  bool combine;
+};
+__device__ __forceinline__ ColOp col_op(const SlotCtl& ctl) {
+  switch (ctl.phase) {
+    case PH_M_RES: return {3, CM_RES, false};
+    case PH_M_CG: return {3, CM_CG, false};
+    case PH_X_PROJ: return {3, CM_PROJECT, false};
+    case PH_X_DISP: return {3, CM_DISP, false};
+    case PH_X_LAP:
+    case PH_PF_ASM:
+    case PH_PF_R: return {1, CM_LAP, false};
+    case PH_PF_PQ: return {1, CM_SUM, ctl.inv == PH_PF_R};
+    case PH_STATS: return {1, CM_SUM, false};
+    default: return {0, 0, false};
+  }
+}
+
+// BCCG direction coefficient of Algorithm 1 from ||r||^2 and r.r_old.
+__device__ __forceinline__ double bccg_beta(double r2, double rro, const SlotCtl& C) {
+  return (r2 - rro) / (C.alpha_pf * C.pq);
+}
+
+// CG step length from p.Cp and ||r||^2.
+__device__ __forceinline__ double cg_alpha(double pcp, double rr) {
+  return (pcp > 0.0 && isfinite(pcp)) ? rr / pcp : 0.0;
+}
+
+// The coefficient of a CM_CG (alpha) or combining CM_SUM (beta) column kernel
+// from this tick's row partials, for every thread of the group (which it
+// synchronises); the controller reduces the same partials in the same order
+// and gets the same value.
+__device__ __forceinline__ double col_coef(const double* __restrict__ pr, int ngr, const SlotCtl& ctl, bool combine) {
+  __shared__ double coef;
+  if (threadIdx.x < 64) {
+    double o[2], oc;
+    reduce_partials<2>(pr, ngr, combine ? 2 : 1, -1, nullptr, 0, o, &oc);
+    if (threadIdx.x == 0) coef = combine ? bccg_beta(o[0], o[1], ctl) : cg_alpha(o[0], ctl.rr);
+  }
+  __syncthreads();
+  return coef;
+}
+
+// The mechanics residual of a mode (three components a, packed or not):
+// r = -a, or r - alpha a with the stored r; stores r, leaves r / n in a and
+// returns r:r.  The residual lives in Fourier space (in the planes rm, laid
+// out as the spectrum): its norm is known when the column kernel ends, so
+// that the row kernel after it can update the direction at once, and every
+// iteration's residual is compatible up to one transform's rounding (in
+// real space the rounding of each update stays, its incompatible part for
+// good).
+template <typename real>
+__device__ __forceinline__ double col_residual(cplx<real>* a, cplx<real>* rhat, unsigned at, int d, size_t plane, bool cg,
+                                               real alpha, const cplx<real>* r0, real inv_n) {
+  using C = cplx<real>;
+  double w = 0.0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const C r = cg ? mk<C>(r0[c].x - alpha * a[c].x, r0[c].y - alpha * a[c].y) : mk<C>(-a[c].x, -a[c].y);
+    stc<real>(rhat + c * plane, at, r, d);
+    w += (c == 2 ? 2.0 : 1.0) * (double(r.x) * r.x + double(r.y) * r.y);
+    a[c] = cscale(r, inv_n);
+  }
+  return w;
+}
+
 template <typename real>
 __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                                  const SlotParam* __restrict__ prms,
                                                  const SlotCtl* __restrict__ ctls,
-                                                 const cplx<real>* __restrict__ twy, double* __restrict__ part,
-                                                 int nx, int ny, int W, int ngc, int nyq_free) {
+                                                 const cplx<real>* __restrict__ twy,
+                                                 const double* __restrict__ part_row, double* __restrict__ part,
+                                                 int nx, int ny, int W, int ngr, int ngc, int nyq_free) {
   using C = cplx<real>;
   extern __shared__ unsigned char smem_raw[];
   __shared__ double red[(THREADS / 64) * NP_COL];
   const int s = list[blockIdx.y], g = blockIdx.x;
   if (s < 0) return;
-  const int phase = ctls[s].phase;
-  int ncomp, mode;  // mode 0: projection, 1: Laplacian, 2: Parseval reduction, 3: displacement
-  switch (phase) {
-    case PH_M_RES:
-    case PH_M_CG:
-    case PH_X_PROJ:
-      ncomp = 3;
-      mode = 0;
-      break;
-    case PH_X_DISP:
-      ncomp = 3;
-      mode = 3;
-      break;
-    case PH_X_LAP:
-      ncomp = 1;
-      mode = 1;
-      break;
-    case PH_PF_ASM:
-    case PH_PF_R:
-      ncomp = 1;
-      mode = 1;
-      break;
-    case PH_PF_PQ:
-    case PH_STATS:
-      ncomp = 1;
-      mode = 2;
-      break;
-    default:
-      return;
-  }
+  const SlotCtl& ctl = ctls[s];
+  const ColOp op = col_op(ctl);
+  if (op.ncomp == 0) return;
+  const int phase = ctl.phase, ncomp = op.ncomp, mode = op.mode;
   const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
   const int M = nx >> 1, stride = ny + PAD;
@@ -792,10 +967,31 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
   // load W columns of each component
   const int tot = ncomp * W * ny;
   const int logny = ilog2(ny), logW = ilog2(W);
+  const bool mech = mode == CM_RES || mode == CM_CG;
+  const real coef = (op.combine || mode == CM_CG)
+                        ? real(col_coef(part_row + (size_t)s * NP_ROW * ngr, ngr, ctl, op.combine))
+                        : real(0);
+  C* rhat = reinterpret_cast<C*>(F.rm);
+  // one mode of the mechanics residual
+  auto mech_mode = [&](C* a, int kx, int ky) {
+    const unsigned at = (unsigned)(kx * ny + ky);
+    C r0[3];
+    if (mode == CM_CG) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) r0[c] = ldc<real>(rhat + (size_t)c * M * ny, at);
+    }
+    return col_residual<real>(a, rhat, at, 0, (size_t)M * ny, mode == CM_CG, coef, r0, inv_n);
+  };
   for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
     const int y = idx & (ny - 1), rest = idx >> logny;
     const int w = rest & (W - 1), c = rest >> logW;
-    buf[rest * stride + y] = ldc<real>(spec + (size_t)(c * M + kx0 + w) * ny + y);
+    const unsigned at = (unsigned)((c * M + kx0 + w) * ny + y);
+    C z = ldc<real>(spec, at);
+    if (op.combine) {
+      const C zq = ldc<real>(spec + (size_t)M * ny, at);
+      z = mk<C>(coef * zq.x - z.x, coef * zq.y - z.y);
+    }
+    buf[rest * stride + y] = z;
   }
   __syncthreads();
   fft_lds<real, false, MAXE>(buf, ny, ncomp * W, stride, twy, 1);
@@ -812,25 +1008,33 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
     const real fy_grad = (2 * ky == ny) ? real(0) : fy_true;
     if (kx > 0) {
       const real fx = real(kx) / real(nx);
-      if (mode == 3) {
+      if (mode == CM_DISP) {
         C a[3] = {buf[(0 * W + w) * stride + ky], buf[(1 * W + w) * stride + ky], buf[(2 * W + w) * stride + ky]};
         disp3(a, fx, fy_grad, inv_n);
 #pragma unroll
         for (int c = 0; c < 3; ++c) buf[(c * W + w) * stride + ky] = a[c];
-      } else if (mode == 0) {
+      } else if (mode == CM_PROJECT || mech) {
         C* a0 = buf + (0 * W + w) * stride + ky;
         C* a1 = buf + (1 * W + w) * stride + ky;
         C* a2 = buf + (2 * W + w) * stride + ky;
         real re[3] = {a0->x, a1->x, a2->x}, im[3] = {a0->y, a1->y, a2->y};
         project3_mode(re, fx, fy_grad, 2 * ky == ny, nyq_free);
         project3_mode(im, fx, fy_grad, 2 * ky == ny, nyq_free);
-        *a0 = mk<C>(re[0] * inv_n, im[0] * inv_n);
-        *a1 = mk<C>(re[1] * inv_n, im[1] * inv_n);
-        *a2 = mk<C>(re[2] * inv_n, im[2] * inv_n);
+        if (mech) {
+          C a[3] = {mk<C>(re[0], im[0]), mk<C>(re[1], im[1]), mk<C>(re[2], im[2])};
+          acc[0] += 2.0 * mech_mode(a, kx, ky);
+          *a0 = a[0];
+          *a1 = a[1];
+          *a2 = a[2];
+        } else {
+          *a0 = mk<C>(re[0] * inv_n, im[0] * inv_n);
+          *a1 = mk<C>(re[1] * inv_n, im[1] * inv_n);
+          *a2 = mk<C>(re[2] * inv_n, im[2] * inv_n);
+        }
       } else {
         const real L = two_pi * two_pi * (fx * fx + fy_true * fy_true);
         C* a = buf + w * stride + ky;
-        if (mode == 1) {
+        if (mode == CM_LAP) {
           *a = cscale(*a, L * lap_scale);
         } else {
           const C v = *a;
@@ -843,7 +1047,7 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
       const bool self = (km == ky);
       // split packed column into A (kx = 0 column) and B (kx = nx/2 column)
       const real fxN_true = real(0.5);
-      if (mode == 3) {
+      if (mode == CM_DISP) {
         C Aa[3], Bb[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -860,7 +1064,7 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
           buf[(c * W + w) * stride + ky] = cadd(Aa[c], cmuli(Bb[c]));
           if (!self) buf[(c * W + w) * stride + km] = cadd(cconj(Aa[c]), cmuli(cconj(Bb[c])));
         }
-      } else if (mode == 0) {
+      } else if (mode == CM_PROJECT || mech) {
         C Aa[3], Bb[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -876,11 +1080,29 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
         // kx = nx/2: gradient wavevector x-component is zero (Nyquist)
         project3_mode(br, real(0), fy_grad, true, nyq_free);
         project3_mode(bi, real(0), fy_grad, true, nyq_free);
+        C zp[3], zm[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const C A = mk<C>(ar[c] * inv_n, ai[c] * inv_n), B = mk<C>(br[c] * inv_n, bi[c] * inv_n);
-          buf[(c * W + w) * stride + ky] = cadd(A, cmuli(B));
-          if (!self) buf[(c * W + w) * stride + km] = cadd(cconj(A), cmuli(cconj(B)));
+          const C A = mk<C>(ar[c], ai[c]), B = mk<C>(br[c], bi[c]);
+          zp[c] = cadd(A, cmuli(B));
+          zm[c] = cadd(cconj(A), cmuli(cconj(B)));
+        }
+        if (mech) {
+          // the packed column's norm is that of its two halves (the cross
+          // terms of Hermitian A and B cancel over +-ky)
+          acc[0] += mech_mode(zp, 0, ky);
+          if (!self) acc[0] += mech_mode(zm, 0, km);
+        } else {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            zp[c] = cscale(zp[c], inv_n);
+            zm[c] = cscale(zm[c], inv_n);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          buf[(c * W + w) * stride + ky] = zp[c];
+          if (!self) buf[(c * W + w) * stride + km] = zm[c];
         }
       } else {
         const C cp = buf[w * stride + ky];
@@ -889,7 +1111,7 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
         const C B = cscale(cmulni(csub(cp, cm)), real(0.5));
         const real L0 = two_pi * two_pi * (fy_true * fy_true);
         const real LN = two_pi * two_pi * (fxN_true * fxN_true + fy_true * fy_true);
-        if (mode == 1) {
+        if (mode == CM_LAP) {
           const C A2 = cscale(A, L0 * lap_scale), B2 = cscale(B, LN * lap_scale);
           buf[w * stride + ky] = cadd(A2, cmuli(B2));
           if (!self) buf[w * stride + km] = cadd(cconj(A2), cmuli(cconj(B2)));
@@ -902,15 +1124,15 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
     }
   }
   __syncthreads();
-  if (mode != 2) {
+  if (mode != CM_SUM) {
     fft_lds<real, true, MAXE>(buf, ny, ncomp * W, stride, twy, 1);
     for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
       const int y = idx & (ny - 1), rest = idx >> logny;
       const int w = rest & (W - 1), c = rest >> logW;
-      stc<real>(spec + (size_t)(c * M + kx0 + w) * ny + y, buf[rest * stride + y]);
+      stc<real>(spec, (unsigned)((c * M + kx0 + w) * ny + y), buf[rest * stride + y]);
     }
   }
-  block_reduce_store<NP_COL>(acc, red, part + (size_t)s * NP_COL * ngc + g, ngc, mode == 2 ? 1 : 0);
+  block_reduce_store<NP_COL>(acc, red, part + (size_t)s * NP_COL * ngc + g, ngc, (mech || mode == CM_SUM) ? 1 : 0);
 }
 
 // Column kernel with register-resident transforms (ny = N in {128, ...,
@@ -924,8 +1146,8 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
 template <typename real, int N, int E>
 __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                             const SlotParam* __restrict__ prms, const SlotCtl* __restrict__ ctls,
-                                            const cplx<real>* __restrict__ twy, double* __restrict__ part, int nx,
-                                            int ngc, int nyq_free) {
+                                            const cplx<real>* __restrict__ twy, const double* __restrict__ part_row,
+                                            double* __restrict__ part, int nx, int ngr, int ngc, int nyq_free) {
   using C = cplx<real>;
   // E = 8 points per lane up to 512-point columns; 1024 and 2048 points
   // take 16 (one or two wavefronts per column) or 8 (two or four: twice
@@ -937,41 +1159,23 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
   static_assert(L <= 64 || N >= 1024, "groups wider than a wavefront are 1024- or 2048-point columns");
   extern __shared__ unsigned char smem_raw[];
   __shared__ double red[(THREADS / 64) * NP_COL];
+  TwLoad<real, (N / 2 + 63) / 64> tl;
+  tl.load(twy, N / 2);
   const int s = list[blockIdx.y], g = blockIdx.x;
   if (s < 0) return;
-  const int phase = ctls[s].phase;
-  int ncomp, mode;  // mode 0: projection, 1: Laplacian, 2: Parseval reduction, 3: displacement
-  switch (phase) {
-    case PH_M_RES:
-    case PH_M_CG:
-    case PH_X_PROJ:
-      ncomp = 3;
-      mode = 0;
-      break;
-    case PH_X_DISP:
-      ncomp = 3;
-      mode = 3;
-      break;
-    case PH_X_LAP:
-    case PH_PF_ASM:
-    case PH_PF_R:
-      ncomp = 1;
-      mode = 1;
-      break;
-    case PH_PF_PQ:
-    case PH_STATS:
-      ncomp = 1;
-      mode = 2;
-      break;
-    default:
-      return;
-  }
+  const SlotCtl& ctl = ctls[s];
+  const ColOp op = col_op(ctl);
+  if (op.ncomp == 0) return;
+  const int phase = ctl.phase, ncomp = op.ncomp, mode = op.mode;
   const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
   const int M = nx >> 1;
   const int W = blockDim.x / L;
+  C* tw = reinterpret_cast<C*>(smem_raw) + W * XArea<N>::size;
+  tl.store(tw, N / 2);
   const int col = threadIdx.x / L, lane = threadIdx.x & (L - 1);
   const int kx = g * W + col;
+  const unsigned at = (unsigned)(kx * N + lane);
   C* x = reinterpret_cast<C*>(smem_raw) + col * XArea<N>::size;
   C* spec = reinterpret_cast<C*>(F.spec);
   const real inv_n = real(1.0 / (double(nx) * double(N)));
@@ -982,14 +1186,27 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     if (c < ncomp) {
-      const C* src = spec + (size_t)(c * M + kx) * N + lane;
 #pragma unroll
-      for (int m = 0; m < E; ++m) v[c][m] = ldc<real>(src + m * L);
+      for (int m = 0; m < E; ++m) v[c][m] = ldc<real>(spec + (size_t)c * M * N, at, m * L);
     }
   }
+  if (op.combine) {
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[1][m] = ldc<real>(spec + (size_t)M * N, at, m * L);
+  }
+  const bool mech = mode == CM_RES || mode == CM_CG;
+  real coef = 0;
+  if (op.combine || mode == CM_CG)
+    coef = real(col_coef(part_row + (size_t)s * NP_ROW * ngr, ngr, ctl, op.combine));
+  if (op.combine) {
+#pragma unroll
+    for (int m = 0; m < E; ++m) v[0][m] = mk<C>(coef * v[1][m].x - v[0][m].x, coef * v[1][m].y - v[0][m].y);
+  }
+  C* rhat = reinterpret_cast<C*>(F.rm);
+  __syncthreads();  // the twiddle table
 #pragma unroll
   for (int c = 0; c < 3; ++c)
-    if (c < ncomp) reg_fft<real, false, N, E>(v[c], x, lane, twy, 1);
+    if (c < ncomp) reg_fft<real, false, N, E>(v[c], x, lane, tw, 1);
 
   double acc[NP_COL] = {0.0, 0.0};
   if (kx > 0) {
@@ -1000,20 +1217,20 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
       const int kys = ky < N / 2 ? ky : ky - N;
       const real fy_true = real(kys) / real(N);
       const real fy_grad = (2 * ky == N) ? real(0) : fy_true;
-      if (mode == 3) {
+      if (mode == CM_DISP) {
         C a[3] = {v[0][m], v[1][m], v[2][m]};
         disp3(a, fx, fy_grad, inv_n);
 #pragma unroll
         for (int c = 0; c < 3; ++c) v[c][m] = a[c];
-      } else if (mode == 0) {
+      } else if (mode == CM_PROJECT || mech) {
         real re[3] = {v[0][m].x, v[1][m].x, v[2][m].x}, im[3] = {v[0][m].y, v[1][m].y, v[2][m].y};
         project3_mode(re, fx, fy_grad, 2 * ky == N, nyq_free);
         project3_mode(im, fx, fy_grad, 2 * ky == N, nyq_free);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) v[c][m] = mk<C>(re[c] * inv_n, im[c] * inv_n);
+        for (int c = 0; c < 3; ++c) v[c][m] = mk<C>(re[c], im[c]);
       } else {
         const real Lk = two_pi * two_pi * (fx * fx + fy_true * fy_true);
-        if (mode == 1) {
+        if (mode == CM_LAP) {
           v[0][m] = cscale(v[0][m], Lk * lap_scale);
         } else {
           acc[0] += 2.0 * double(Lk) * (double(v[0][m].x) * double(v[0][m].x) + double(v[0][m].y) * double(v[0][m].y));
@@ -1039,10 +1256,10 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
           // the partner lane may sit in the other wavefront: exchange
           // through the column's LDS area (free between transforms)
 #pragma unroll
-          for (int i = 0; i < E; ++i) x[xpad(lane + i * L)] = v[c][i];
+          for (int i = 0; i < E; ++i) x[xpad(lane) + i * (L + L / 8)] = v[c][i];
           group_sync<L>();
 #pragma unroll
-          for (int i = 0; i < E; ++i) Pn[c][E - 1 - i] = x[xpad(src + i * L)];
+          for (int i = 0; i < E; ++i) Pn[c][E - 1 - i] = x[xpad(src) + i * (L + L / 8)];
           group_sync<L>();
         }
         if (lane == 0) {
@@ -1057,7 +1274,7 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
       const int kys = ky < N / 2 ? ky : ky - N;
       const real fy_true = real(kys) / real(N);
       const real fy_grad = (2 * ky == N) ? real(0) : fy_true;
-      if (mode == 3) {
+      if (mode == CM_DISP) {
         C Aa[3], Bb[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -1069,7 +1286,7 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
         disp3(Bb, real(0), fy_grad, inv_n);
 #pragma unroll
         for (int c = 0; c < 3; ++c) v[c][m] = cadd(Aa[c], cmuli(Bb[c]));
-      } else if (mode == 0) {
+      } else if (mode == CM_PROJECT || mech) {
         real ar[3], ai[3], br[3], bi[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -1087,17 +1304,14 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
         project3_mode(br, real(0), fy_grad, true, nyq_free);
         project3_mode(bi, real(0), fy_grad, true, nyq_free);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const C A = mk<C>(ar[c] * inv_n, ai[c] * inv_n), Bq = mk<C>(br[c] * inv_n, bi[c] * inv_n);
-          v[c][m] = cadd(A, cmuli(Bq));
-        }
+        for (int c = 0; c < 3; ++c) v[c][m] = cadd(mk<C>(ar[c], ai[c]), cmuli(mk<C>(br[c], bi[c])));
       } else {
         const C cp = v[0][m], cm = cconj(Pn[0][m]);
         const C A = cscale(cadd(cp, cm), real(0.5));
         const C Bq = cscale(cmulni(csub(cp, cm)), real(0.5));
         const real L0 = two_pi * two_pi * (fy_true * fy_true);
         const real LN = two_pi * two_pi * (real(0.25) + fy_true * fy_true);
-        if (mode == 1) {
+        if (mode == CM_LAP) {
           v[0][m] = cadd(cscale(A, L0 * lap_scale), cmuli(cscale(Bq, LN * lap_scale)));
         } else {
           acc[0] += double(L0) * (double(A.x) * double(A.x) + double(A.y) * double(A.y)) +
@@ -1106,208 +1320,69 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
       }
     }
   }
-  if (mode != 2) {
+  if (mech) {
+    // (a packed column's norm is that of its two halves: the cross terms of
+    // the Hermitian A and B cancel over +-ky)
+    const double w = kx > 0 ? 2.0 : 1.0;
+    constexpr int CH = 4;  // modes whose residual is loaded ahead
+#pragma unroll
+    for (int m0 = 0; m0 < E; m0 += CH) {
+      C r0[CH][3];
+      if (mode == CM_CG) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) r0[i][c] = ldc<real>(rhat + (size_t)c * M * N, at, (m0 + i) * L);
+      }
+#pragma unroll
+      for (int i = 0; i < CH; ++i) {
+        C a[3] = {v[0][m0 + i], v[1][m0 + i], v[2][m0 + i]};
+        acc[0] += w * col_residual<real>(a, rhat, at, (m0 + i) * L, (size_t)M * N, mode == CM_CG, coef, r0[i], inv_n);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c][m0 + i] = a[c];
+      }
+      settle(acc, 0, 1);
+    }
+  } else if (mode == CM_PROJECT) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int m = 0; m < E; ++m) v[c][m] = cscale(v[c][m], inv_n);
+  }
+  if (mode != CM_SUM) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       if (c < ncomp) {
-        reg_fft<real, true, N, E>(v[c], x, lane, twy, 1);
-        C* dst = spec + (size_t)(c * M + kx) * N + lane;
+        reg_fft<real, true, N, E>(v[c], x, lane, tw, 1);
 #pragma unroll
-        for (int m = 0; m < E; ++m) stc<real>(dst + m * L, v[c][m]);
+        for (int m = 0; m < E; ++m) stc<real>(spec + (size_t)c * M * N, at, v[c][m], m * L);
       }
     }
   }
-  block_reduce_store<NP_COL>(acc, red, part + (size_t)s * NP_COL * ngc + g, ngc, mode == 2 ? 1 : 0);
-}
-
-// Row-inverse epilogue for the pixel pair (o, o + 1): q[c] holds the
-// transformed values of component c at the pair (x: o, y: o + 1).
-// Inputs of the row epilogue for one pixel pair, loaded ahead of the
-// arithmetic (see epi_load_chunk for the slots of each phase).
-template <typename real>
-struct EpiIn {
-  V2<real> a[9];
-};
-
-template <typename real, int PH = -1, bool PRE = false>
-__device__ __forceinline__ void row_epilogue(const RowCtx<real>& X, const SlotParam& P, real* __restrict__ phip,
-                                             real* __restrict__ prefp, real* __restrict__ thp,
-                                             real* __restrict__ rmp, real* __restrict__ pmp, int o,
-                                             const cplx<real> (&q)[3], real alpha, double (&acc)[NP_INV],
-                                             const EpiIn<real>& in = EpiIn<real>{}) {
-  // PRE: the inputs of this pair were loaded into `in` (PH one of M_CG,
-  // PF_ASM, PF_R; see row_epilogue_n)
-  using C = cplx<real>;
-  const int phase = PH >= 0 ? PH : X.phase;
-  const int n = X.n, ncomp = X.ncomp;
-  switch (phase) {
-    case PH_M_RES: {
-      const C q0 = q[0], q1 = q[1], q2 = q[2];
-      st2(rmp + o, -q0.x, -q0.y);
-      st2(rmp + n + o, -q1.x, -q1.y);
-      st2(rmp + 2 * n + o, -q2.x, -q2.y);
-      acc[0] += double(q0.x) * q0.x + double(q0.y) * q0.y + double(q1.x) * q1.x + double(q1.y) * q1.y +
-                2.0 * (double(q2.x) * q2.x + double(q2.y) * q2.y);
-      break;
-    }
-    case PH_M_CG: {
-      const bool first = X.flags & FL_CG_FIRST;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const V2<real> p = PRE ? in.a[c] : ld2(pmp + c * n + o);
-        V2<real> r2 = PRE ? in.a[3 + c] : ld2(rmp + c * n + o);
-        V2<real> th = first ? V2<real>{0, 0} : (PRE ? in.a[6 + c] : ld2(thp + c * n + o));
-        th = {th.a + alpha * p.a, th.b + alpha * p.b};
-        r2 = {r2.a - alpha * q[c].x, r2.b - alpha * q[c].y};
-        st2(thp + c * n + o, th.a, th.b);
-        st2(rmp + c * n + o, r2.a, r2.b);
-        const double wc = c == 2 ? 2.0 : 1.0;
-        acc[0] += wc * (double(r2.a) * r2.a + double(r2.b) * r2.b);
-      }
-      break;
-    }
-    case PH_PF_ASM:
-    case PH_PF_R: {
-      const C lap = q[0];
-      const V2<real> ph = PRE ? in.a[0] : ld2(phip + o), d = PRE ? in.a[1] : ld2(thp + o),
-                     b = PRE ? in.a[2] : ld2(thp + n + o);
-      const V2<real> pr = PRE ? in.a[3] : ld2(prefp + o);
-      const real rr0 = d.a * ph.a + lap.x - b.a;
-      const real rr1 = d.b * ph.b + lap.y - b.b;
-      const real lo0 = lower_bound(pr.a, P), lo1 = lower_bound(pr.b, P);
-      const bool a0 = (ph.a <= lo0 && rr0 > real(0)) || (ph.a >= real(1) && rr0 < real(0));
-      const bool a1 = (ph.b <= lo1 && rr1 > real(0)) || (ph.b >= real(1) && rr1 < real(0));
-      const real r0 = a0 ? real(0) : rr0, r1 = a1 ? real(0) : rr1;
-      if (phase == PH_PF_ASM && (X.flags & FL_NE_CHECK)) {
-        // near-equilibrium evolution: phi = phi_n here, so the unmasked
-        // residual is F_phi(phi_n, eps_n); keep it for the search of x*
-        st2(rmp + n + o, rr0, rr1);
-        acc[1] = fmax(acc[1], fmax(-double(rr0), -double(rr1)));
-      }
-      if (phase == PH_PF_R) {
-        const V2<real> ro = PRE ? in.a[4] : ld2(rmp + o);
-        acc[1] += double(r0) * ro.a + double(r1) * ro.b;
-      }
-      st2(rmp + o, r0, r1);
-      unsigned char* mask = reinterpret_cast<unsigned char*>(pmp + n);
-      stb(mask + o, a0 ? 1 : 0);
-      stb(mask + o + 1, a1 ? 1 : 0);
-      acc[0] += double(r0) * r0 + double(r1) * r1;
-      acc[2] += double(ph.a) * ph.a + double(ph.b) * ph.b;
-      acc[3] += double(d.a * ph.a) * double(d.a * ph.a) + double(d.b * ph.b) * double(d.b * ph.b);
-      break;
-    }
-    case PH_X_PROJ:
-    case PH_X_DISP:
-    case PH_X_LAP: {
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (c < ncomp) st2(rmp + c * n + o, q[c].x, q[c].y);
-      break;
-    }
-    default:
-      break;
-  }
-}
-
-// Loads the epilogue inputs of CH pixel pairs o0 + c OSTEP of phase PH
-// before any store of the chunk: on this GPU a wait for a load also waits
-// for the stores issued before it, so interleaved per-pair loads and stores
-// cost a round trip per pair.
-template <typename real, int PH, int CH, int OSTEP>
-__device__ __forceinline__ void epi_load_chunk(const RowCtx<real>& X, const real* __restrict__ phip,
-                                               const real* __restrict__ prefp, const real* __restrict__ thp,
-                                               const real* __restrict__ rmp, const real* __restrict__ pmp, int o0,
-                                               EpiIn<real> (&in)[CH]) {
-  const int n = X.n;
-  if constexpr (PH == PH_M_CG) {
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        in[c].a[k] = ld2(pmp + k * n + o0 + c * OSTEP);
-        in[c].a[3 + k] = ld2(rmp + k * n + o0 + c * OSTEP);
-      }
-    if (!(X.flags & FL_CG_FIRST)) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) in[c].a[6 + k] = ld2(thp + k * n + o0 + c * OSTEP);
-    }
-  } else if constexpr (PH == PH_PF_ASM || PH == PH_PF_R) {
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int o = o0 + c * OSTEP;
-      in[c].a[0] = ld2(phip + o);
-      in[c].a[1] = ld2(thp + o);
-      in[c].a[2] = ld2(thp + n + o);
-      in[c].a[3] = ld2(prefp + o);
-      if constexpr (PH == PH_PF_R) in[c].a[4] = ld2(rmp + o);
-    }
-  }
-}
-
-// The epilogue for NQ pixel pairs o0 + q OSTEP of one lane (restrict
-// pointers: see row_prologue_n).
-template <typename real, int NQ, int OSTEP>
-__device__ __forceinline__ void row_epilogue_n(const RowCtx<real>& X, const SlotParam& P, real* __restrict__ phip,
-                                               real* __restrict__ prefp, real* __restrict__ thp,
-                                               real* __restrict__ rmp, real* __restrict__ pmp, int o0,
-                                               const cplx<real> (&q)[NQ][3], real alpha, double (&acc)[NP_INV]) {
-#define SPFF_EPI_CASE(PHC)                                                                             \
-  case PHC:                                                                                           \
-    _Pragma("unroll") for (int i = 0; i < NQ; ++i)                                                    \
-        row_epilogue<real, PHC>(X, P, phip, prefp, thp, rmp, pmp, o0 + i * OSTEP, q[i], alpha, acc); \
-    break;
-  // up to four pairs per lane (launches with few problems): all loaded
-  // before their stores; with more pairs the registers this takes would
-  // cost occupancy, and the per-pair path stays
-  constexpr bool CHUNK = NQ <= 4;
-#define SPFF_EPI_HOT(PHC)                                                                                    \
-  case PHC:                                                                                                   \
-    if constexpr (CHUNK) {                                                                                    \
-      EpiIn<real> in[NQ];                                                                                     \
-      epi_load_chunk<real, PHC, NQ, OSTEP>(X, phip, prefp, thp, rmp, pmp, o0, in);                            \
-      _Pragma("unroll") for (int c = 0; c < NQ; ++c)                                                          \
-          row_epilogue<real, PHC, true>(X, P, phip, prefp, thp, rmp, pmp, o0 + c * OSTEP, q[c], alpha, acc,   \
-                                        in[c]);                                                               \
-    } else {                                                                                                  \
-      _Pragma("unroll") for (int i = 0; i < NQ; ++i)                                                          \
-          row_epilogue<real, PHC>(X, P, phip, prefp, thp, rmp, pmp, o0 + i * OSTEP, q[i], alpha, acc);       \
-    }                                                                                                         \
-    break;
-  switch (X.phase) {
-    SPFF_EPI_CASE(PH_M_RES)
-    SPFF_EPI_HOT(PH_M_CG)
-    SPFF_EPI_HOT(PH_PF_ASM)
-    SPFF_EPI_HOT(PH_PF_R)
-    SPFF_EPI_CASE(PH_X_PROJ)
-    SPFF_EPI_CASE(PH_X_DISP)
-    SPFF_EPI_CASE(PH_X_LAP)
-    default:
-      break;
-  }
-#undef SPFF_EPI_CASE
-#undef SPFF_EPI_HOT
+  block_reduce_store<NP_COL>(acc, red, part + (size_t)s * NP_COL * ngc + g, ngc, (mech || mode == CM_SUM) ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------
-// Row kernels with register-resident transforms (M = nx/2 in {64 .. 1024},
+// Row kernel with register-resident transforms (M = nx/2 in {64 .. 1024},
 // FP32): a group of L = M/E lanes (E = 4, 8, or 16 for M = 1024) owns one row
 // (R = blockDim/L rows per work-group); lane l holds z[h] = x[2h] + i x[2h+1]
-// for h = l + m L.  The
-// prologue / epilogue run per pixel pair on the registers; the real <->
-// half-spectrum step pairs bin k with M - k by a cross-lane shuffle (same
-// pattern as the packed column); the transposed spectrum store / load goes
-// through an LDS tile [kx][row] so that R consecutive y of one kx move as
-// one run.
+// for h = l + m L.  The pointwise work runs per pixel pair on the registers
+// between the inverse and the forward transform; the real <-> half-spectrum
+// step pairs bin k with M - k by a cross-lane shuffle (same pattern as the
+// packed column); the transposed spectrum load / store goes through an LDS
+// tile [kx][row] so that R consecutive y of one kx move as one run.
 // ---------------------------------------------------------------------------
 template <int M>
 struct RowLds {
-  // exchange areas of the R row groups, then the [kx][row] tile
+  // exchange areas of the R row groups, then the [kx][row] tile, then the
+  // twiddle table.  Rows of 1024 points let the tile overlie the exchange
+  // areas (a barrier more per component): 49 KB for four rows instead of
+  // 86 KB, so that a CU holds more than one work-group.
+  static constexpr bool ALIAS = M >= 1024;
   static __device__ __forceinline__ int tile_index(int k, int r, int R) { return k * (R + 1) + r; }
-  static size_t bytes(int R, size_t csize) {
-    return ((size_t)R * XArea<M>::size + (size_t)M * (R + 1)) * csize;
+  static __device__ __forceinline__ int table(int R) {
+    const int x = R * XArea<M>::size, t = M * (R + 1);
+    return ALIAS ? (x > t ? x : t) : x + t;
   }
 };
 
@@ -1327,11 +1402,27 @@ __device__ __forceinline__ void partner_bins(const cplx<real> (&v)[E], cplx<real
   }
 }
 
+// comp_update for a lane's pixel pairs of component c.
+template <typename real, int OP, int NQ, int OSTEP>
+__device__ __forceinline__ void row_comp(const RowCtx<real>& X, const SlotPtr<real>& F, int c, At o0,
+                                         cplx<real> (&v)[NQ]) {
+  real *pk = F.pm + c * X.n, *tk = F.theta + c * X.n;
+  constexpr int CH = NQ > 8 ? 8 : NQ;
+#pragma unroll
+  for (int i0 = 0; i0 < NQ; i0 += CH) {
+    CompIn<real> in[CH];
+    if (i0) asm volatile("" ::: "memory");
+    comp_load<real, OP, CH, OSTEP>(X, pk, tk, o0 + i0 * OSTEP, in);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) comp_update<real, OP>(X, pk, tk, o0 + (i0 + i) * OSTEP, in[i], v[i0 + i]);
+  }
+}
+
 template <typename real, int M, int E>
-__device__ __forceinline__ void k_rowfwdr_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
-                                               const SlotParam* __restrict__ prms, const CtrlArgs A,
-                                               const cplx<real>* __restrict__ twx, double* __restrict__ part,
-                                               int ny, int ngr) {
+__device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
+                                            const SlotParam* __restrict__ prms, const CtrlArgs A,
+                                            const cplx<real>* __restrict__ twx, double* __restrict__ part, int ny,
+                                            int ngr, const RowTimers T) {
   using C = cplx<real>;
   constexpr int L = M / E, nx = 2 * M;
   extern __shared__ unsigned char smem_raw[];
@@ -1341,171 +1432,73 @@ __device__ __forceinline__ void k_rowfwdr_body(const int* __restrict__ list, con
   row_coords(ngr, g, si);
   const int s = list[si];
   if (s < 0) return;
-  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl);
-  const SlotCtl& ctl = lctl;
-  const int phase = ctl.phase;
-  const int ncomp = phase_comps_row(phase);
-  if (phase != PH_AM_CHK && phase != PH_TD_RESTORE && ncomp == 0) return;
+  const int R = blockDim.x / L, logR = ilog2(R);
+  C* tile = reinterpret_cast<C*>(smem_raw) + (RowLds<M>::ALIAS ? 0 : R * XArea<M>::size);
+  C* tw = reinterpret_cast<C*>(smem_raw) + RowLds<M>::table(R);
+  TwLoad<real, M / 64> tl;
+  tl.load(twx, M);
+  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl, [&]() { tl.store(tw, M); });
   const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
-  const int R = blockDim.x / L;
+  const int n = nx * ny;
+  const RowCtx<real> X = row_ctx<real>(lctl, P, n);
+  if (X.op == RO_NONE) return;
   const int row = threadIdx.x / L, lane = threadIdx.x & (L - 1);
   const int y0 = g * R;
-  const int n = nx * ny;
   C* xa = reinterpret_cast<C*>(smem_raw) + row * XArea<M>::size;
-  C* tile = reinterpret_cast<C*>(smem_raw) + R * XArea<M>::size;
-  double acc[NP_ROW];
-#pragma unroll
-  for (int i = 0; i < NP_ROW; ++i) acc[i] = 0.0;
-  if (phase == PH_STATS) acc[3] = -1.0e300;
-  const RowCtx<real> X = row_ctx<real>(ctl, P, phase, ncomp, n);
+  C* spec = reinterpret_cast<C*>(F.spec);
 
-  C v[3][E];
-  {
-    real val[E][3][2];
-    row_prologue_n<real, E, 2 * L>(X, P, F.E, F.phi, F.phi_ref, F.eps, F.theta, F.rm, F.pm,
-                                   (y0 + row) * nx + 2 * lane, val, acc);
+  const At o0 = at<real>((y0 + row) * nx + 2 * lane);
+  // Each op has its own copy of the whole pass: values that merge before or
+  // after a switch over the ops cost a wavefront per SIMD (176 registers a
+  // lane instead of 138 for eight points per lane).
+  auto pass = [&](auto opc) {
+    constexpr int OP = decltype(opc)::value;
+    constexpr bool CG = OP == RO_RES_CG || OP == RO_CG_CG;
+    // a diagnostic operator's component count is known at run time
+    constexpr int NIN = op_comps_in(OP, PH_X_PROJ), NOUT = op_comps_out(OP, PH_X_PROJ);
+    C v[3][E];
+    double acc[NP_ROW];
+    init_acc(OP, acc);
+    // Few problems per launch (four points per lane): the group's tile
+    // entries of every component (E per thread and component: R rows x M
+    // bins over R L threads) are loaded up front, so that the components
+    // cost one memory round trip instead of one each
+    if constexpr (E == 4) {
 #pragma unroll
-    for (int m = 0; m < E; ++m)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) v[c][m] = mk<C>(val[m][c][0], val[m][c][1]);
-  }
-  if (ncomp > 0) {
-    C* spec = reinterpret_cast<C*>(F.spec);
-    const int logR = ilog2(R);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if (c < ncomp) {
-        reg_fft<real, false, M, E>(v[c], xa, lane, twx, 2);
-        // half spectrum of the real row: X[k] = e + w^k o (k > 0), bin 0
-        // packs X[0] + i X[M]
-        C pn[E];
-        partner_bins<real, E, L>(v[c], pn, lane);
-        __syncthreads();  // the tile is free
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-          const int k = lane + m * L;
-          C out;
-          if (k == 0) {
-            out = mk<C>(v[c][m].x + v[c][m].y, v[c][m].x - v[c][m].y);
-          } else {
-            const C zk = v[c][m], zm = cconj(pn[m]);
-            const C e = cscale(cadd(zk, zm), real(0.5));
-            const C od = cscale(cmulni(csub(zk, zm)), real(0.5));
-            out = cadd(e, cmul(twx[k], od));
-          }
-          tile[RowLds<M>::tile_index(k, row, R)] = out;
-        }
-        __syncthreads();
-        // transposed store: spec[c][kx][y0 + r], r fastest
-        for (int idx = threadIdx.x; idx < M * R; idx += blockDim.x) {
-          const int r = idx & (R - 1), k = idx >> logR;
-          stc<real>(spec + (size_t)(c * M + k) * ny + y0 + r, tile[RowLds<M>::tile_index(k, r, R)]);
-        }
-      }
-    }
-  }
-  block_reduce_store<NP_ROW>(acc, red, part + (size_t)s * NP_ROW * ngr + g, ngr, nacc_rowfwd(phase),
-                             phase == PH_STATS ? 3 : (phase == PH_PF_ASM ? 1 : -1));
-}
-
-template <typename real, int M, int E>
-__device__ __forceinline__ void k_rowinvr_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
-                                               const SlotParam* __restrict__ prms, const SlotCtl* __restrict__ ctls,
-                                               const cplx<real>* __restrict__ twx,
-                                               const double* __restrict__ part_row, double* __restrict__ part,
-                                               int ny, int ngr) {
-  using C = cplx<real>;
-  constexpr int L = M / E, nx = 2 * M;
-  extern __shared__ unsigned char smem_raw[];
-  __shared__ double red[(THREADS / 64) * NP_INV];
-  int g, si;
-  row_coords(ngr, g, si);
-  const int s = list[si];
-  if (s < 0) return;
-  const SlotCtl& ctl = ctls[s];
-  const int phase = ctl.phase;
-  int ncomp;
-  switch (phase) {
-    case PH_M_RES:
-    case PH_M_CG:
-    case PH_X_PROJ:
-    case PH_X_DISP:
-      ncomp = 3;
-      break;
-    case PH_PF_ASM:
-    case PH_PF_R:
-    case PH_X_LAP:
-      ncomp = 1;
-      break;
-    default:
-      return;
-  }
-  const SlotParam& P = prms[s];
-  const SlotPtr<real> F = ptrs[s];
-  const int R = blockDim.x / L;
-  const int row = threadIdx.x / L, lane = threadIdx.x & (L - 1);
-  const int y0 = g * R;
-  const int n = nx * ny;
-  const RowCtx<real> X = row_ctx<real>(ctl, P, phase, ncomp, n);
-  C* xa = reinterpret_cast<C*>(smem_raw) + row * XArea<M>::size;
-  C* tile = reinterpret_cast<C*>(smem_raw) + R * XArea<M>::size;
-  const C* spec = reinterpret_cast<const C*>(F.spec);
-  const int logR = ilog2(R);
-
-  // Few problems per launch (four points per lane): the group's tile entries
-  // of every component (E per thread and component: R rows x M bins over
-  // R L threads) are loaded up front, so that the components cost one
-  // memory round trip instead of one each
-  C pre[3][E];
-  if constexpr (E == 4) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if (c < ncomp) {
+      for (int c = 0; c < NIN; ++c) {
+        if (OP == RO_X_OUT && c >= X.nin) break;
 #pragma unroll
         for (int i = 0; i < E; ++i) {
           const int idx = threadIdx.x + i * blockDim.x;
           const int r = idx & (R - 1), k = idx >> logR;
-          pre[c][i] = ldc<real>(spec + (size_t)(c * M + k) * ny + y0 + r);
+          v[c][i] = ldc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r));
         }
       }
     }
-  }
-
-  // CG step length from this tick's row-forward partials (same fixed-order
-  // reduction as the controller)
-  __shared__ double scal[1];
-  real alpha = 0;
-  if (phase == PH_M_CG) {
-    if (threadIdx.x < 64) {
-      const double pcp = wave_reduce_partials(part_row + (size_t)s * NP_ROW * ngr, ngr);
-      if (threadIdx.x == 0) scal[0] = (pcp > 0.0 && isfinite(pcp)) ? ctl.rr / pcp : 0.0;
-    }
-    __syncthreads();
-    alpha = real(scal[0]);
-  }
-
-  C v[3][E];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (c < ncomp) {
+    for (int c = 0; c < NIN; ++c) {
+      if (OP == RO_X_OUT && c >= X.nin) break;
       if (c > 0) __syncthreads();  // the previous component's tile reads are done
+      const int tid = opaque(threadIdx.x), lane = tid & (L - 1);
       if constexpr (E == 4) {
 #pragma unroll
         for (int i = 0; i < E; ++i) {
-          const int idx = threadIdx.x + i * blockDim.x;
+          const int idx = tid + i * blockDim.x;
           const int r = idx & (R - 1), k = idx >> logR;
-          tile[RowLds<M>::tile_index(k, r, R)] = pre[c][i];
+          tile[RowLds<M>::tile_index(k, r, R)] = v[c][i];
         }
       } else {
-        for (int idx = threadIdx.x; idx < M * R; idx += blockDim.x) {
+        for (int idx = tid; idx < M * R; idx += blockDim.x) {
           const int r = idx & (R - 1), k = idx >> logR;
-          tile[RowLds<M>::tile_index(k, r, R)] = ldc<real>(spec + (size_t)(c * M + k) * ny + y0 + r);
+          tile[RowLds<M>::tile_index(k, r, R)] =
+              ldc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r));
         }
       }
       __syncthreads();
 #pragma unroll
       for (int m = 0; m < E; ++m) v[c][m] = tile[RowLds<M>::tile_index(lane + m * L, row, R)];
+      if constexpr (RowLds<M>::ALIAS) __syncthreads();
       // from the packed half spectrum to Z whose unnormalised inverse FFT
       // gives nx (x[2h] + i x[2h+1])
       C pn[E];
@@ -1518,158 +1511,97 @@ __device__ __forceinline__ void k_rowinvr_body(const int* __restrict__ list, con
         } else {
           const C xk = v[c][m], xm = cconj(pn[m]);
           const C a = cadd(xk, xm), b = csub(xk, xm);
-          v[c][m] = cadd(a, cmuli(cmul(cconj(twx[k]), b)));
+          v[c][m] = cadd(a, cmuli(cmul(cconj(tw[k]), b)));
         }
       }
-      reg_fft<real, true, M, E>(v[c], xa, lane, twx, 2);
+      reg_fft<real, true, M, E>(v[c], xa, lane, tw, 2);
+      if constexpr (CG) row_comp<real, OP, E, 2 * L>(X, F, c, o0, v[c]);
     }
-  }
-  double acc[NP_INV] = {0.0, 0.0, 0.0, 0.0};
-  if (phase == PH_PF_ASM) acc[1] = -1.0e300;  // max of -F_phi (near-equilibrium)
-  {
-    C q[E][3];
+    row_middle(T);
+    row_pairs<real, OP, E, E == 4 ? 4 : 2, 2 * L, E == 16>(X, P, F.E, F.phi, F.phi_ref, F.eps, F.theta, F.rm,
+                                                                F.pm, o0, v, acc);
 #pragma unroll
-    for (int m = 0; m < E; ++m)
+    for (int c = 0; c < NOUT; ++c) {
+      if (OP == RO_X_IN && c >= X.nout) break;
+      const int tid = opaque(threadIdx.x), lane = tid & (L - 1);
+      if constexpr (RowLds<M>::ALIAS) __syncthreads();
+      reg_fft<real, false, M, E>(v[c], xa, lane, tw, 2);
+      // half spectrum of the real row: X[k] = e + w^k o (k > 0), bin 0
+      // packs X[0] + i X[M]
+      C pn[E];
+      partner_bins<real, E, L>(v[c], pn, lane);
+      __syncthreads();  // the tile is free
 #pragma unroll
-      for (int c = 0; c < 3; ++c) q[m][c] = c < ncomp ? v[c][m] : mk<C>(real(0), real(0));
-    row_epilogue_n<real, E, 2 * L>(X, P, F.phi, F.phi_ref, F.theta, F.rm, F.pm, (y0 + row) * nx + 2 * lane, q,
-                                   alpha, acc);
-  }
-  block_reduce_store<NP_INV>(acc, red, part + (size_t)s * NP_INV * ngr + g, ngr, nacc_rowinv(phase),
-                             phase == PH_PF_ASM ? 1 : -1);
+      for (int m = 0; m < E; ++m) {
+        const int k = lane + m * L;
+        C out;
+        if (k == 0) {
+          out = mk<C>(v[c][m].x + v[c][m].y, v[c][m].x - v[c][m].y);
+        } else {
+          const C zk = v[c][m], zm = cconj(pn[m]);
+          const C e = cscale(cadd(zk, zm), real(0.5));
+          const C od = cscale(cmulni(csub(zk, zm)), real(0.5));
+          out = cadd(e, cmul(tw[k], od));
+        }
+        tile[RowLds<M>::tile_index(k, row, R)] = out;
+      }
+      __syncthreads();
+      // transposed store: spec[c][kx][y0 + r], r fastest
+      for (int idx = tid; idx < M * R; idx += blockDim.x) {
+        const int r = idx & (R - 1), k = idx >> logR;
+        stc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r), tile[RowLds<M>::tile_index(k, r, R)]);
+      }
+    }
+    block_reduce_store<NP_ROW>(acc, red, part + (size_t)s * NP_ROW * ngr + g, ngr, op_nacc(OP), op_maxslot(OP));
+    asm volatile("; end of row op %0" ::"i"(OP));  // keeps the copies apart
+  };
+#define SPFF_ROW_PASS(OPC) pass(std::integral_constant<int, OPC>{})
+  SPFF_ROW_SWITCH(X.op, SPFF_ROW_PASS)
+#undef SPFF_ROW_PASS
 }
 
-// ===========================================================================
-// Row-inverse kernel: transposed load -> C2R row FFTs -> epilogue (per
-// phase); FP64 partial sums per work-group.
-// ===========================================================================
-template <typename real>
-__device__ __forceinline__ void k_rowinv_body(const int* __restrict__ list,
-                                                    const SlotPtr<real>* __restrict__ ptrs,
-                                                    const SlotParam* __restrict__ prms,
-                                                    const SlotCtl* __restrict__ ctls,
-                                                    const cplx<real>* __restrict__ twx,
-                                                    const double* __restrict__ part_row,
-                                                    double* __restrict__ part, int nx, int ny, int R, int ngr) {
-  using C = cplx<real>;
-  extern __shared__ unsigned char smem_raw[];
-  __shared__ double red[(THREADS / 64) * NP_INV];
-  int g, si;
-  row_coords(ngr, g, si);
-  const int s = list[si];
-  if (s < 0) return;
-  const SlotCtl& ctl = ctls[s];
-  const int phase = ctl.phase;
-  int ncomp;
-  switch (phase) {
-    case PH_M_RES:
-    case PH_M_CG:
-    case PH_X_PROJ:
-    case PH_X_DISP:
-      ncomp = 3;
-      break;
-    case PH_PF_ASM:
-    case PH_PF_R:
-    case PH_X_LAP:
-      ncomp = 1;
-      break;
-    default:
-      return;
-  }
-  const SlotParam& P = prms[s];
-  const SlotPtr<real> F = ptrs[s];
-  const int M = nx >> 1, stride = M + PAD;
-  const int y0 = g * R;
-  const int n = nx * ny;
-  const RowCtx<real> X = row_ctx<real>(ctl, P, phase, ncomp, n);
-  C* buf = reinterpret_cast<C*>(smem_raw);
-  const C* spec = reinterpret_cast<const C*>(F.spec);
-
-  // CG step length from this tick's row-forward partials (same fixed-order
-  // reduction as the controller)
-  __shared__ double scal[1];
-  real alpha = 0;
-  if (phase == PH_M_CG) {
-    if (threadIdx.x < 64) {
-      const double pcp = wave_reduce_partials(part_row + (size_t)s * NP_ROW * ngr, ngr);
-      if (threadIdx.x == 0) scal[0] = (pcp > 0.0 && isfinite(pcp)) ? ctl.rr / pcp : 0.0;
-    }
-    __syncthreads();
-    alpha = real(scal[0]);
-  }
-
-  const int tot = ncomp * M * R;
-  const int logM = ilog2(M), logR = ilog2(R);
-  for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
-    const int r = idx & (R - 1);
-    const int rest = idx >> logR;
-    const int kx = rest & (M - 1), c = rest >> logM;
-    buf[(c * R + r) * stride + kx] = ldc<real>(spec + (size_t)rest * ny + y0 + r);
-  }
-  __syncthreads();
-  c2r_pre<real>(buf, M, ncomp * R, stride, twx);
-  fft_lds<real, true, MAXE>(buf, M, ncomp * R, stride, twx, 2);
-
-  double acc[NP_INV] = {0.0, 0.0, 0.0, 0.0};
-  if (phase == PH_PF_ASM) acc[1] = -1.0e300;  // max of -F_phi (near-equilibrium)
-  for (int idx = threadIdx.x; idx < R * M; idx += blockDim.x) {
-    const int r = idx >> logM, h = idx & (M - 1);
-    const int o = (y0 + r) * nx + 2 * h;
-    const int li = r * stride + h;
-    C q[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) q[c] = c < ncomp ? buf[c * R * stride + li] : mk<C>(real(0), real(0));
-    row_epilogue<real>(X, P, F.phi, F.phi_ref, F.theta, F.rm, F.pm, o, q, alpha, acc);
-  }
-  block_reduce_store<NP_INV>(acc, red, part + (size_t)s * NP_INV * ngr + g, ngr, nacc_rowinv(phase),
-                             phase == PH_PF_ASM ? 1 : -1);
-}
-
-// Algorithmic HBM bytes per pixel moved by the row-forward, column and
-// row-inverse kernels for the phase a slot executed (r = sizeof(real)):
-// every input plane read once, every output plane written once, half spectra
-// (nx/2 * ny complex values = r bytes per pixel per component) written by the
-// row-forward kernel, read and written by the column kernel, read by the
-// row-inverse kernel.
-__device__ inline void phase_bytes(int phase, int flags, int split, double r, double* b) {
+// Algorithmic HBM bytes per pixel moved by the row kernel's forward part,
+// the column kernel and the row kernel's inverse part in a tick that
+// finishes phase `inv` and starts `phase` (r = sizeof(real)): every input
+// plane read once, every output plane written once, half spectra (nx/2 * ny
+// complex values = r bytes per pixel per component) written by the forward
+// part, read and written by the column kernel, read by the inverse part.
+__device__ inline void phase_bytes(int inv, int phase, int flags, int split, double r, double* b) {
+  const int op = row_op(inv, phase);
   const double sp = r;  // half spectrum, per pixel per component
-  b[0] = b[1] = b[2] = 0.0;
-  switch (phase) {
-    case PH_M_RES:
-      b[0] = r * 5 + 3 * sp + ((flags & FL_THETA_PENDING) ? 6 * r : 0) + ((flags & FL_FIRST_OF_STEP) ? r : 0);
-      b[1] = 6 * sp;
-      b[2] = 3 * sp + 3 * r;
+  const double strain = split ? 3 : 0;
+  const bool first = flags & FL_THETA_FIRST;
+  const int nin = op_comps_in(op, inv), nout = op_comps_out(op, phase);
+  double planes = 0.0, bytes = 0.0;
+  switch (op) {
+    case RO_RES:
+      planes = 5 + ((flags & FL_FIRST_OF_STEP) ? 1 : 0) + ((flags & FL_THETA_PENDING) ? 6 + (first ? 0 : 3) : 0);
       break;
-    case PH_M_CG:
-      b[0] = r * (2 + 3 + ((flags & FL_CG_FIRST) ? 0 : 3) + (split ? 3 : 0) + 3) + 3 * sp;
-      b[1] = 6 * sp;
-      b[2] = 3 * sp + r * (3 + 3 + ((flags & FL_CG_FIRST) ? 0 : 3) + 6);
+    case RO_RES_CG: planes = 2 + strain + 3; break;
+    case RO_CG_CG: planes = 2 + strain + 3 + (first ? 0 : 3) + 6; break;
+    case RO_ASM: planes = 6 + 4 + ((flags & FL_NE_SCALE) ? 3 : 0); break;
+    case RO_ASM_PQ: planes = 4 + 1; break;
+    case RO_ASM_WAIT: planes = 4 + 2; break;
+    case RO_R_PQ:
+      planes = 6 + 1;
+      bytes = 1;
       break;
-    case PH_PF_ASM:
-      b[0] = r * (6 + 4) + sp + ((flags & FL_NE_SCALE) ? 3 * r : 0);
-      b[1] = 2 * sp;
-      b[2] = sp + r * (4 + 1) + 1 + ((flags & FL_NE_CHECK) ? r : 0);
+    case RO_PQ: planes = 2; break;
+    case RO_PFR:
+      planes = 3 + ((flags & FL_PF_FIRST) ? 0 : 1) + 2;
+      bytes = (flags & FL_PF_FIRST) ? 0 : 1;
       break;
-    case PH_PF_PQ:
-      b[0] = r * (2 + ((flags & FL_PF_FIRST) ? 0 : 1) + 1) + 1 + sp;
-      b[1] = sp;
-      break;
-    case PH_PF_R:
-      b[0] = r * (3 + 1) + sp;
-      b[1] = 2 * sp;
-      b[2] = sp + r * (5 + 1) + 1;
-      break;
-    case PH_AM_CHK:
-    case PH_TD_RESTORE:
-      b[0] = 2 * r;
-      break;
-    case PH_STATS:
-      b[0] = r * 5 + sp;
-      b[1] = sp;
-      break;
-    default:
-      break;
+    case RO_AM:
+    case RO_RESTORE: planes = 2; break;
+    case RO_STATS: planes = 5; break;
+    default: break;
   }
+  b[0] = planes * r + bytes + nout * sp;
+  // column kernel: spectra in, result out; mechanics: the residual's spectrum
+  // out, and in after the first
+  const bool mech = phase == PH_M_RES || phase == PH_M_CG;
+  b[1] = nout * sp * ((phase == PH_PF_PQ || phase == PH_STATS) ? 1.0 : (phase == PH_M_CG ? 4.0 : (mech ? 3.0 : 2.0)));
+  b[2] = nin * sp;
 }
 
 // ===========================================================================
@@ -1683,7 +1615,7 @@ __device__ __forceinline__ int wave_min_int(int v) {
 }
 
 // Near-equilibrium strain scaling (Sec. 3.2.2, Algorithm 4).  fm is the
-// largest -F_phi(phi_n, eps_n); the row-inverse kernel of the assembly kept
+// largest -F_phi(phi_n, eps_n); the row kernel that finished the assembly kept
 // the unmasked residual F_phi in rm[1] and its per-row-group maxima in
 // gmax[0 .. ngr).  x* is the first pixel (row-major) where -F_phi equals fm:
 // the first row group holding the maximum, then the first pixel of that
@@ -1731,37 +1663,42 @@ __device__ bool ne_gamma(const SlotPtr<real>& F, const SlotParam& P, const SlotC
 
 // The controller step of slot s after a tick: one wavefront reads the
 // tick's partial sums and the control block C, lane 0 writes the advanced
-// block back into C.  `writer`: this wavefront also records the step's
-// statistics (byte counters, finished load steps, the queue position); the
-// other wavefronts that run the same step on their own copy of C (every
-// row-forward work-group of the slot) only advance their copy.
+// block back into C: the phase that the next row kernel finishes (inv) and
+// the one that it starts (phase).  `writer`: this wavefront also records the
+// step's statistics (byte counters, finished load steps, the queue
+// position); the other wavefronts that run the same step on their own copy
+// of C (every row work-group of the slot) only advance their copy.
 template <typename real>
 __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict__ ptrs,
                                           const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
                                           const double* __restrict__ prow, const double* __restrict__ pcol,
-                                          const double* __restrict__ pinv, double* __restrict__ prof,
-                                          SlotSeq* __restrict__ seqs, StepRec* __restrict__ recs, int nx, int ny,
-                                          int ngr, int ngc) {
+                                          double* __restrict__ prof, SlotSeq* __restrict__ seqs,
+                                          StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc) {
   const double* pr = prow + (size_t)s * NP_ROW * ngr;
   const double* pc = pcol + (size_t)s * NP_COL * ngc;
-  const double* pi = pinv + (size_t)s * NP_INV * ngr;
-  const int phase = C.phase;
+  const int phase = uni(C.phase), inv = uni(C.inv);
   if (phase == PH_IDLE) return;
   if (threadIdx.x == 0 && C.ticks == 0 && C.t_start == 0) C.t_start = wall_clock64();
   const SlotParam& P = prms[s];
   if (prof && writer && threadIdx.x == 0) {
     double b[3];
-    phase_bytes(phase, C.flags, P.contact, double(sizeof(real)), b);
+    phase_bytes(inv, phase, C.flags, P.contact, double(sizeof(real)), b);
     const double npx = double(nx) * double(ny);
     prof[3 * s + 0] += b[0] * npx;
     prof[3 * s + 1] += b[1] * npx;
     prof[3 * s + 2] += b[2] * npx;
   }
   const double inv_n = 1.0 / (double(nx) * double(ny));
-  // all lanes compute the same values; lane 0 writes
-  double v[8];
-  int nphase = phase;
-  int flags = C.flags;
+  // the sums of the tick: those of the row kernel's op, and the column
+  // kernel's; all lanes compute the same values, lane 0 writes
+  double o[NP_ROW], oc;
+  {
+    const int op = row_op(inv, phase);
+    const bool col = phase == PH_M_RES || phase == PH_M_CG || phase == PH_PF_PQ || phase == PH_STATS;
+    reduce_partials(pr, ngr, op_nacc(op), op_maxslot(op), pc, col ? ngc : 0, o, &oc);
+  }
+  int nphase = phase, ninv = PH_IDLE;
+  int flags = uni(C.flags);
   int cg = C.cg, cg_newton = C.cg_newton, newton = C.newton, bccg = C.bccg, pf_it = C.pf_it, am = C.am;
   int newton_solve = C.newton_solve;
   int status = C.status;
@@ -1773,7 +1710,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
   int pf_best_it = C.pf_best_it;
   double eta_dt = C.eta_dt, dt = C.dt;
   int halvings = C.halvings, advance = C.advance;
-  double gamma = C.gamma, fmax_ne = C.fmax_ne;
+  double gamma = C.gamma, fmax_ne = C.fmax_ne, dmax = C.dmax;
   int ne_flag = C.ne_flag;
   bool scaled = false;
   bool bad = false;
@@ -1787,9 +1724,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
   };
   switch (phase) {
     case PH_M_RES: {
-      double o[3];
-      wave_reduce_partials_n<3>({pr, pr + 1 * ngr, pi}, {ngr, ngr, ngr}, o);
-      const double sh2 = o[0], sg2 = o[1], r2 = o[2];
+      const double sh2 = o[0], sg2 = o[1], r2 = oc * inv_n;  // Parseval
       bad = !isfinite(sh2) || !isfinite(r2) || !isfinite(sg2);
       mech_res = sqrt(r2);
       // G[sigma] cannot be evaluated more accurately than the rounding of
@@ -1802,97 +1737,133 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
         flags |= FL_MECH_STARTED;
         newton_solve = 0;
       }
-      flags &= ~(FL_FIRST_OF_STEP | FL_THETA_PENDING);
+      flags &= ~(FL_FIRST_OF_STEP | FL_THETA_PENDING | FL_THETA_FIRST);
       if (mech_res <= fmax(mech_target, mech_floor)) {
         nphase = PH_PF_ASM;
       } else if (newton_solve >= P.max_newton) {
         flags |= FL_NOT_CONVERGED;
         nphase = PH_PF_ASM;
       } else {
-        rr = r2;
         inner_tol = (P.contact == 0) ? fmax(mech_target, mech_floor)
                                    : fmax(0.1 * mech_res, fmax(mech_target, mech_floor));
+        rr = r2;
         cg_newton = 0;
-        flags |= FL_CG_FIRST;
+        ninv = PH_M_RES;
         nphase = PH_M_CG;
       }
       if (nphase == PH_PF_ASM) flags &= ~FL_MECH_STARTED;
       break;
     }
     case PH_M_CG: {
-      double o[2];
-      wave_reduce_partials_n<2>({pr, pi}, {ngr, ngr}, o);
-      const double pcp = o[0], r2 = o[1];
+      const double pcp = o[0], r2 = oc * inv_n;  // Parseval
       bad = !isfinite(pcp) || !isfinite(r2);
-      alpha_m = (pcp > 0.0) ? rr / pcp : 0.0;
+      alpha_m = cg_alpha(pcp, rr);
       ++cg;
       ++cg_newton;
-      flags &= ~FL_CG_FIRST;
+      flags &= ~FL_THETA_FIRST;
+      if (cg_newton == 1) flags |= FL_THETA_FIRST;
       beta_m = (rr > 0.0) ? r2 / rr : 0.0;
       rr = r2;
       if (sqrt(r2) <= inner_tol || cg_newton >= P.max_cg || pcp <= 0.0) {
+        // the next M_RES applies theta + alpha p
         if (sqrt(r2) > inner_tol) flags |= FL_NOT_CONVERGED;
         ++newton;
         ++newton_solve;
         flags |= FL_THETA_PENDING;
         nphase = PH_M_RES;
+      } else {
+        ninv = PH_M_CG;
+        nphase = PH_M_CG;
       }
       break;
     }
     case PH_PF_ASM: {
       flags &= ~FL_NE_SCALE;
+      bad = !isfinite(o[0]);
+      pf_bnorm = sqrt(o[0]);
+      dmax = o[1];
+      ninv = PH_PF_ASM;
       if (flags & FL_NE_CHECK) {
+        nphase = PH_PF_WAIT;
+      } else {
+        // the first direction is -r: start the first iteration with it
+        flags |= FL_PF_FIRST;
+        nphase = PH_PF_PQ;
+      }
+      break;
+    }
+    case PH_PF_WAIT:
+    case PH_PF_PQ: {
+      const double r2 = o[0];
+      if (phase == PH_PF_WAIT) {
         // Algorithm 4: -F_phi(phi_n, eps_n) and the crack driving force
         // -h'(phi_n) psi0+ were evaluated by this assembly
         flags &= ~FL_NE_CHECK;
-        double o[2];
-        wave_reduce_partials_n<2>({pi + 1 * ngr, pr + 1 * ngr}, {ngr, ngr}, o, 3u);
-        fmax_ne = o[0];
-        const double dmax = o[1];
+        fmax_ne = o[1];
         if (fmax_ne > P.fphi_max && dmax > P.drive_thr) ne_flag = 1;
         if (fmax_ne > P.fphi_max && ne_flag &&
-            ne_gamma<real>(ptrs[s], P, C, fmax_ne, pi + 1 * ngr, nx, ny, ngr, &gamma)) {
+            ne_gamma<real>(ptrs[s], P, C, fmax_ne, pr + 1 * ngr, nx, ny, ngr, &gamma)) {
           scaled = true;
           flags |= FL_NE_SCALE;
           nphase = PH_PF_ASM;  // assemble again at the scaled strain
           break;
         }
       }
-      double o[4];
-      wave_reduce_partials_n<4>({pr, pi, pi + 2 * ngr, pi + 3 * ngr}, {ngr, ngr, ngr, ngr}, o);
-      const double b2 = o[0], r2 = o[1], x2 = o[2], dx2 = o[3];
-      bad = !isfinite(b2) || !isfinite(r2);
-      pf_res = sqrt(r2);
-      pf_bnorm = sqrt(b2);
-      pf_ref = fmax(pf_bnorm, pf_res);
-      pf_target = P.tol_pf * pf_ref + P.tol_abs_pf;
-      // attainable accuracy of r = J phi - b in the working precision
-      pf_floor = P.floor_coef * (sqrt(dx2) + P.kappa * P.lap_rms * sqrt(x2) + pf_bnorm);
-      rr_pf = r2;
-      pf_it = 0;
-      pf_best = pf_res;
-      pf_best_it = 0;
-      if (pf_res <= fmax(pf_target, pf_floor)) {
-        pf_done();
-      } else {
-        flags |= FL_PF_FIRST;
-        nphase = PH_PF_PQ;
+      if (inv != PH_IDLE) {
+        // the residual that this tick's row kernel finished
+        bad = !isfinite(r2);
+        rr_pf = r2;
+        pf_res = sqrt(r2);
+        // attainable accuracy of r = J phi - b in the working precision
+        pf_floor = P.floor_coef * (sqrt(o[3]) + P.kappa * P.lap_rms * sqrt(o[2]) + pf_bnorm);
+        bool done = false;
+        if (inv == PH_PF_ASM) {
+          pf_ref = fmax(pf_bnorm, pf_res);
+          pf_target = P.tol_pf * pf_ref + P.tol_abs_pf;
+          pf_it = 0;
+          pf_best = pf_res;
+          pf_best_it = 0;
+          done = pf_res <= fmax(pf_target, pf_floor);
+        } else {
+          bad |= !isfinite(o[1]);
+          beta_pf = bccg_beta(r2, o[1], C);
+          ++pf_it;
+          ++bccg;
+          if (pf_res < pf_best) {
+            pf_best = pf_res;
+            pf_best_it = pf_it;
+          }
+          if (pf_res <= fmax(pf_target, pf_floor)) {
+            done = true;
+          } else if (P.stall_iters > 0 && pf_it - pf_best_it >= P.stall_iters) {
+            flags |= FL_STALLED;
+            done = true;
+          } else if (pf_it >= P.max_bccg) {
+            flags |= FL_NOT_CONVERGED;
+            done = true;
+          }
+        }
+        if (done) {
+          flags &= ~FL_PF_FIRST;
+          pf_done();
+          break;
+        }
+        if (phase == PH_PF_WAIT) {
+          flags |= FL_PF_FIRST;
+          nphase = PH_PF_PQ;
+          break;
+        }
       }
-      break;
-    }
-    case PH_PF_PQ: {
-      // sum d p^2, sum r p, sum L |p^|^2
-      double o[3];
-      wave_reduce_partials_n<3>({pr, pr + 1 * ngr, pc}, {ngr, ngr, ngc}, o);
-      v[0] = o[0];
-      v[1] = o[1];
-      v[2] = o[2];
-      bad = !isfinite(v[0]) || !isfinite(v[1]) || !isfinite(v[2]);
-      pq = v[0] + P.kappa * inv_n * v[2];
-      rp = v[1];
-      flags &= ~FL_PF_FIRST;
+      // p = -r + beta m p_old: sum d p^2 and r.p from the sums over r and
+      // m p_old, sum L |p^|^2 from the column kernel
+      const double b = (flags & FL_PF_FIRST) ? 0.0 : beta_pf;
+      const double dpp = o[4] - 2.0 * b * o[5] + b * b * o[6];
+      rp = -r2 + b * o[7];
+      bad |= !isfinite(dpp) || !isfinite(rp) || !isfinite(oc);
+      pq = dpp + P.kappa * inv_n * oc;
       if (!(pq > 0.0)) {
         flags |= FL_NOT_CONVERGED;
+        flags &= ~FL_PF_FIRST;
         pf_done();
       } else {
         alpha_pf = -rp / pq;
@@ -1900,36 +1871,13 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
       }
       break;
     }
-    case PH_PF_R: {
-      double o[4];
-      wave_reduce_partials_n<4>({pi, pi + 1 * ngr, pi + 2 * ngr, pi + 3 * ngr}, {ngr, ngr, ngr, ngr}, o);
-      const double r2 = o[0], rro = o[1], x2 = o[2], dx2 = o[3];
-      bad = !isfinite(r2) || !isfinite(rro);
-      beta_pf = (r2 - rro) / (alpha_pf * pq);
-      rr_pf = r2;
-      pf_res = sqrt(r2);
-      pf_floor = P.floor_coef * (sqrt(dx2) + P.kappa * P.lap_rms * sqrt(x2) + pf_bnorm);
-      ++pf_it;
-      ++bccg;
-      if (pf_res < pf_best) {
-        pf_best = pf_res;
-        pf_best_it = pf_it;
-      }
-      if (pf_res <= fmax(pf_target, pf_floor)) {
-        pf_done();
-      } else if (P.stall_iters > 0 && pf_it - pf_best_it >= P.stall_iters) {
-        flags |= FL_STALLED;
-        pf_done();
-      } else if (pf_it >= P.max_bccg) {
-        flags |= FL_NOT_CONVERGED;
-        pf_done();
-      } else {
-        nphase = PH_PF_PQ;
-      }
+    case PH_PF_R:
+      flags &= ~FL_PF_FIRST;
+      ninv = PH_PF_R;
+      nphase = PH_PF_PQ;
       break;
-    }
     case PH_AM_CHK: {
-      dphi = wave_reduce_partials(pr, ngr);
+      dphi = o[0];
       bad = !isfinite(dphi);
       ++am;
       if (P.evolution == 2) {
@@ -1968,26 +1916,24 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
     case PH_X_PROJ:
     case PH_X_DISP:
     case PH_X_LAP:
+      ninv = phase;
+      nphase = PH_X_END;
+      break;
+    case PH_X_END:
       nphase = PH_IDLE;
       break;
     case PH_STATS: {
-      double o[4];
-      wave_reduce_partials_n<4>({pr, pr + 1 * ngr, pr + 2 * ngr, pr + 3 * ngr}, {ngr, ngr, ngr, ngr}, o, 8u);
-      for (int i = 0; i < 4; ++i) v[i] = o[i];
-      wave_reduce_partials_n<4>({pr + 4 * ngr, pr + 5 * ngr, pr + 6 * ngr, pr + 7 * ngr}, {ngr, ngr, ngr, ngr}, o);
-      for (int i = 0; i < 4; ++i) v[4 + i] = o[i];
-      const double lg = wave_reduce_partials(pc, ngc);
       bad = false;
-      for (int i = 0; i < 8; ++i) bad |= !isfinite(v[i]);
+      for (int i = 0; i < 8; ++i) bad |= !isfinite(o[i]);
       if (threadIdx.x == 0) {
-        C.F_e = v[0];
-        C.F_f = P.cwl * (v[1] + P.ell * P.ell * inv_n * lg);
-        C.phi_sum = v[2];
-        C.phi_max = v[3];
-        C.crack_px = v[4];
-        C.sbar[0] = v[5] * inv_n;
-        C.sbar[1] = v[6] * inv_n;
-        C.sbar[2] = v[7] * inv_n;
+        C.F_e = o[0];
+        C.F_f = P.cwl * (o[1] + P.ell * P.ell * inv_n * oc);
+        C.phi_sum = o[2];
+        C.phi_max = o[3];
+        C.crack_px = o[4];
+        C.sbar[0] = o[5] * inv_n;
+        C.sbar[1] = o[6] * inv_n;
+        C.sbar[2] = o[7] * inv_n;
       }
       nphase = PH_IDLE;
       break;
@@ -2000,6 +1946,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
     status = -4;
     nphase = PH_IDLE;
   }
+  if (nphase == PH_IDLE) ninv = PH_IDLE;
   // a load step just ended: record it and start the next one of the queue
   bool restart = false;
   if (seqs && nphase == PH_IDLE && (phase == PH_STATS || bad) && !(flags & FL_INIT_SOLVE) && threadIdx.x == 0 &&
@@ -2056,6 +2003,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
       C.eps_bar[2] = q.eps_bar[pos][2];
     }
     C.phase = PH_M_RES;
+    C.inv = PH_IDLE;
     C.flags = FL_FIRST_OF_STEP | (P.evolution == 2 ? FL_NE_CHECK : 0);
     C.am = C.newton = C.cg = C.bccg = C.cg_newton = C.pf_it = C.newton_solve = 0;
     C.ticks = 0;
@@ -2073,6 +2021,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
   }
   if (threadIdx.x == 0) {
     C.phase = nphase;
+    C.inv = ninv;
     C.flags = flags;
     C.cg = cg;
     C.cg_newton = cg_newton;
@@ -2109,6 +2058,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
     C.advance = advance;
     C.gamma = gamma;
     C.fmax_ne = fmax_ne;
+    C.dmax = dmax;
     C.ne_flag = ne_flag;
     if (scaled) {
       C.eps_bar[0] *= gamma;
@@ -2137,11 +2087,11 @@ __device__ __forceinline__ void kt_end(KTime* kt) {
   }
 }
 
-// Folds the kernel times of one tick (kt[0..2]: row-forward, column,
-// row-inverse) into ktsum and resets the words for the tick after next; one
-// wavefront, lane l takes line l.  ktsum[j]: activity of kernel j (first
-// start to last end); ktsum[4 + j]: its span (first start to the first
-// start of the kernel after it; t_next for the row-inverse kernel).
+// Folds the times of one tick (kt[0..2]: row-forward part, column kernel,
+// row-inverse part) into ktsum and resets the words for the tick after next;
+// one wavefront, lane l takes line l.  ktsum[j]: activity of part j (first
+// start to last end); ktsum[4 + j]: its span (first start to the first start
+// of the part after it; t_next for the column kernel).
 __device__ __forceinline__ void kt_fold(KTime* kt, unsigned long long t_next, unsigned long long* ktsum) {
   const int l = threadIdx.x & 63;
   unsigned long long st[3], en[3];
@@ -2160,11 +2110,11 @@ __device__ __forceinline__ void kt_fold(KTime* kt, unsigned long long t_next, un
     en[j] = b;
   }
   if (l == 0) {
-    const unsigned long long nxt[3] = {st[1], st[2], t_next};
+    const unsigned long long nxt[3] = {st[1], t_next, st[0]};
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       if (en[j] > st[j]) ktsum[j] += en[j] - st[j];
-      if (nxt[j] > st[j] && st[j] != ~0ull) ktsum[4 + j] += nxt[j] - st[j];
+      if (nxt[j] > st[j] && nxt[j] != ~0ull) ktsum[4 + j] += nxt[j] - st[j];
     }
   }
 }
@@ -2182,12 +2132,12 @@ __device__ __forceinline__ unsigned long long kt_first_start(const KTime* kt) {
 // Timer bookkeeping of the column kernel: with timers on, the launch has one
 // extra row of work-groups; its group 0 folds the previous tick's times
 // (kt_prev, null for the first tick of a block) -- the previous tick ended
-// before this tick's row-forward kernel, whose first start (kt_row) closes
-// the previous row-inverse span -- and the other extra groups return.
+// before this tick's row kernel, whose first start (kt_row) closes the
+// previous column kernel's span -- and the other extra groups return.
 struct ColTimers {
   KTime* kt;             // this column kernel's stamps
-  KTime* kt_prev;        // the previous tick's three kernels
-  const KTime* kt_row;   // this tick's row-forward kernel
+  KTime* kt_prev;        // the previous tick's three parts
+  const KTime* kt_row;   // this tick's row kernel (its inverse part starts it)
   unsigned long long* ktsum;
 };
 __device__ __forceinline__ bool col_timer_group(const ColTimers& T) {
@@ -2196,25 +2146,45 @@ __device__ __forceinline__ bool col_timer_group(const ColTimers& T) {
   return true;
 }
 
+// Between the parts of a row kernel (every thread of a group that has work).
+__device__ __forceinline__ void row_middle(const RowTimers& T) {
+  if (T.inv) {
+    kt_end(T.inv);
+    kt_begin(T.fwd);
+  }
+}
+
 template <typename real>
-__global__ __launch_bounds__(THREADS) void k_rowfwd(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
-                                                    const SlotParam* __restrict__ prms, const CtrlArgs A,
-                                                    const cplx<real>* __restrict__ twx, double* __restrict__ part,
-                                                    int nx, int ny, int R, int ngr, KTime* kt) {
-  kt_begin(kt);
-  k_rowfwd_body<real>(list, ptrs, prms, A, twx, part, nx, ny, R, ngr);
-  kt_end(kt);
+__global__ __launch_bounds__(THREADS) void k_row(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
+                                                 const SlotParam* __restrict__ prms, const CtrlArgs A,
+                                                 const cplx<real>* __restrict__ twx, double* __restrict__ part,
+                                                 int nx, int ny, int R, int ngr, const RowTimers T) {
+  kt_begin(T.inv);
+  k_row_body<real>(list, ptrs, prms, A, twx, part, nx, ny, R, ngr, T);
+  kt_end(T.fwd);
+}
+
+template <typename real, int M, int E>
+__global__ __launch_bounds__(THREADS) void k_rowr(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
+                                                  const SlotParam* __restrict__ prms, const CtrlArgs A,
+                                                  const cplx<real>* __restrict__ twx, double* __restrict__ part,
+                                                  int ny, int ngr, const RowTimers T) {
+  kt_begin(T.inv);
+  k_rowr_body<real, M, E>(list, ptrs, prms, A, twx, part, ny, ngr, T);
+  kt_end(T.fwd);
 }
 
 template <typename real>
 __global__ __launch_bounds__(THREADS) void k_col(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                                  const SlotParam* __restrict__ prms,
                                                  const SlotCtl* __restrict__ ctls,
-                                                 const cplx<real>* __restrict__ twy, double* __restrict__ part,
-                                                 int nx, int ny, int W, int ngc, int nyq_free, const ColTimers T) {
+                                                 const cplx<real>* __restrict__ twy,
+                                                 const double* __restrict__ part_row, double* __restrict__ part,
+                                                 int nx, int ny, int W, int ngr, int ngc, int nyq_free,
+                                                 const ColTimers T) {
   if (col_timer_group(T)) return;
   kt_begin(T.kt);
-  k_col_body<real>(list, ptrs, prms, ctls, twy, part, nx, ny, W, ngc, nyq_free);
+  k_col_body<real>(list, ptrs, prms, ctls, twy, part_row, part, nx, ny, W, ngr, ngc, nyq_free);
   kt_end(T.kt);
 }
 
@@ -2222,49 +2192,13 @@ template <typename real, int N, int E>
 __global__ __launch_bounds__(THREADS) void k_colr(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                                   const SlotParam* __restrict__ prms,
                                                   const SlotCtl* __restrict__ ctls,
-                                                  const cplx<real>* __restrict__ twy, double* __restrict__ part,
-                                                  int nx, int ngc, int nyq_free, const ColTimers T) {
+                                                  const cplx<real>* __restrict__ twy,
+                                                  const double* __restrict__ part_row, double* __restrict__ part,
+                                                  int nx, int ngr, int ngc, int nyq_free, const ColTimers T) {
   if (col_timer_group(T)) return;
   kt_begin(T.kt);
-  k_colr_body<real, N, E>(list, ptrs, prms, ctls, twy, part, nx, ngc, nyq_free);
+  k_colr_body<real, N, E>(list, ptrs, prms, ctls, twy, part_row, part, nx, ngr, ngc, nyq_free);
   kt_end(T.kt);
-}
-
-template <typename real, int M, int E>
-__global__ __launch_bounds__(THREADS) void k_rowfwdr(const int* __restrict__ list,
-                                                     const SlotPtr<real>* __restrict__ ptrs,
-                                                     const SlotParam* __restrict__ prms, const CtrlArgs A,
-                                                     const cplx<real>* __restrict__ twx, double* __restrict__ part,
-                                                     int ny, int ngr, KTime* kt) {
-  kt_begin(kt);
-  k_rowfwdr_body<real, M, E>(list, ptrs, prms, A, twx, part, ny, ngr);
-  kt_end(kt);
-}
-
-template <typename real, int M, int E>
-__global__ __launch_bounds__(THREADS) void k_rowinvr(const int* __restrict__ list,
-                                                     const SlotPtr<real>* __restrict__ ptrs,
-                                                     const SlotParam* __restrict__ prms,
-                                                     const SlotCtl* __restrict__ ctls,
-                                                     const cplx<real>* __restrict__ twx,
-                                                     const double* __restrict__ part_row, double* __restrict__ part,
-                                                     int ny, int ngr, KTime* kt) {
-  kt_begin(kt);
-  k_rowinvr_body<real, M, E>(list, ptrs, prms, ctls, twx, part_row, part, ny, ngr);
-  kt_end(kt);
-}
-
-template <typename real>
-__global__ __launch_bounds__(THREADS) void k_rowinv(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
-                                                    const SlotParam* __restrict__ prms,
-                                                    const SlotCtl* __restrict__ ctls,
-                                                    const cplx<real>* __restrict__ twx,
-                                                    const double* __restrict__ part_row,
-                                                    double* __restrict__ part, int nx, int ny, int R, int ngr,
-                                                    KTime* kt) {
-  kt_begin(kt);
-  k_rowinv_body<real>(list, ptrs, prms, ctls, twx, part_row, part, nx, ny, R, ngr);
-  kt_end(kt);
 }
 
 // Closing kernel of a block of ticks: the controller step of the last tick,
@@ -2289,8 +2223,7 @@ __global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, con
   if (threadIdx.x < 64) {
     if (s >= 0) {
       if (lc.pending)
-        ctrl_slot<real>(s, ptrs, prms, lc, true, A.prow, A.pcol, A.pinv, A.prof, A.seqs, A.recs, nx, ny, ngr,
-                        A.ngc);
+        ctrl_slot<real>(s, ptrs, prms, lc, true, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc);
       if (threadIdx.x == 0) lc.pending = 0;
     }
   } else if (kt_last && blockIdx.x == 0) {
@@ -2357,17 +2290,16 @@ __global__ void k_fields(const SlotPtr<real>* __restrict__ ptrs, const SlotParam
 // ===========================================================================
 
 template <typename real>
-hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st) {
+hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st, bool row_only) {
   // tick i reads control block (i & 1) and the partials of tick i - 1
-  // (row partials double-buffered: this tick's row-forward kernel writes the
-  // other half while its groups reduce the previous one)
+  // (row partials double-buffered: this tick's row kernel writes the other
+  // half while its groups reduce the previous one)
   const int cur = i & 1, nxt = cur ^ 1;
   CtrlArgs A;
   A.ctl_in = B.ctl[cur];
   A.ctl_out = B.ctl[nxt];
   A.prow = B.prow[nxt];
   A.pcol = B.pcol;
-  A.pinv = B.pinv;
   A.prof = B.prof;
   A.seqs = B.seqs;
   A.recs = B.recs;
@@ -2380,51 +2312,52 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
   const auto* twy = B.twy;
   double* prow = B.prow[cur];
   double* pcol = B.pcol;
-  double* pinv = B.pinv;
   KTime* ktset = B.kt ? B.kt + 3 * cur : nullptr;
-  KTime* ktf = ktset;
-  KTime* kti = ktset ? ktset + 2 : nullptr;
+  RowTimers TR;
+  TR.fwd = ktset;
+  TR.inv = ktset ? ktset + 2 : nullptr;
   ColTimers T;
   T.kt = ktset ? ktset + 1 : nullptr;
   T.kt_prev = (B.kt && i > 0) ? B.kt + 3 * nxt : nullptr;
-  T.kt_row = ktf;
+  T.kt_row = TR.inv;
   T.ktsum = B.ktsum;
   dim3 grow(G.ngr, G.S), gcol(G.ngc, G.S + (B.kt ? 1 : 0));
   bool row_done = false;
   if constexpr (std::is_same<real, float>::value) {
     if (G.row_reg) {
       row_done = true;
-#define SPFF_ROWS_FWD(MM, EE)                                                                                   \
-  hipLaunchKernelGGL((k_rowfwdr<real, MM, EE>), grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, A, twx, \
-                     prow, G.ny, G.ngr, ktf)
+#define SPFF_ROWS(MM, EE)                                                                                    \
+  hipLaunchKernelGGL((k_rowr<real, MM, EE>), grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, A, twx, \
+                     prow, G.ny, G.ngr, TR)
       if (G.row_reg == 2) {
         switch (G.nx) {
-          case 128: SPFF_ROWS_FWD(64, 4); break;
-          case 256: SPFF_ROWS_FWD(128, 4); break;
-          default: SPFF_ROWS_FWD(256, 4); break;
+          case 128: SPFF_ROWS(64, 4); break;
+          case 256: SPFF_ROWS(128, 4); break;
+          default: SPFF_ROWS(256, 4); break;
         }
       } else {
         switch (G.nx) {
-          case 128: SPFF_ROWS_FWD(64, 8); break;
-          case 256: SPFF_ROWS_FWD(128, 8); break;
-          case 512: SPFF_ROWS_FWD(256, 8); break;
-          case 1024: SPFF_ROWS_FWD(512, 8); break;
-          default: SPFF_ROWS_FWD(1024, 16); break;
+          case 128: SPFF_ROWS(64, 8); break;
+          case 256: SPFF_ROWS(128, 8); break;
+          case 512: SPFF_ROWS(256, 8); break;
+          case 1024: SPFF_ROWS(512, 8); break;
+          default: SPFF_ROWS(1024, 16); break;
         }
       }
-#undef SPFF_ROWS_FWD
+#undef SPFF_ROWS
     }
   }
   if (!row_done)
-    hipLaunchKernelGGL(k_rowfwd<real>, grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, A, twx, prow,
-                       G.nx, G.ny, G.R, G.ngr, ktf);
+    hipLaunchKernelGGL(k_row<real>, grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, A, twx, prow, G.nx, G.ny,
+                       G.R, G.ngr, TR);
+  if (row_only) return hipGetLastError();
   bool col_done = false;
   if constexpr (std::is_same<real, float>::value) {
     if (G.col_reg) {
       col_done = true;
 #define SPFF_COLS(NN, EE)                                                                                           \
   hipLaunchKernelGGL((k_colr<real, NN, EE>), gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, \
-                     pcol, G.nx, G.ngc, G.nyq_free, T)
+                     prow, pcol, G.nx, G.ngr, G.ngc, G.nyq_free, T)
       switch (G.ny) {
         case 128: SPFF_COLS(128, 8); break;
         case 256: SPFF_COLS(256, 8); break;
@@ -2448,34 +2381,8 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
     }
   }
   if (!col_done)
-    hipLaunchKernelGGL(k_col<real>, gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, pcol,
-                       G.nx, G.ny, G.W, G.ngc, G.nyq_free, T);
-  if (row_done) {
-    if constexpr (std::is_same<real, float>::value) {
-#define SPFF_ROWS_INV(MM, EE)                                                                                   \
-  hipLaunchKernelGGL((k_rowinvr<real, MM, EE>), grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, ctls, twx, \
-                     prow, pinv, G.ny, G.ngr, kti)
-      if (G.row_reg == 2) {
-        switch (G.nx) {
-          case 128: SPFF_ROWS_INV(64, 4); break;
-          case 256: SPFF_ROWS_INV(128, 4); break;
-          default: SPFF_ROWS_INV(256, 4); break;
-        }
-      } else {
-        switch (G.nx) {
-          case 128: SPFF_ROWS_INV(64, 8); break;
-          case 256: SPFF_ROWS_INV(128, 8); break;
-          case 512: SPFF_ROWS_INV(256, 8); break;
-          case 1024: SPFF_ROWS_INV(512, 8); break;
-          default: SPFF_ROWS_INV(1024, 16); break;
-        }
-      }
-#undef SPFF_ROWS_INV
-    }
-  } else {
-    hipLaunchKernelGGL(k_rowinv<real>, grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, ctls, twx, prow,
-                       pinv, G.nx, G.ny, G.R, G.ngr, kti);
-  }
+    hipLaunchKernelGGL(k_col<real>, gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, prow, pcol,
+                       G.nx, G.ny, G.W, G.ngr, G.ngc, G.nyq_free, T);
   return hipGetLastError();
 }
 
@@ -2488,7 +2395,6 @@ hipError_t launch_close(const LaunchGeom& G, const TickBufs<real>& B, int k, hip
   A.ctl_out = B.ctl[0];
   A.prow = B.prow[last];
   A.pcol = B.pcol;
-  A.pinv = B.pinv;
   A.prof = B.prof;
   A.seqs = B.seqs;
   A.recs = B.recs;
@@ -2519,8 +2425,8 @@ hipError_t launch_fields(const SlotPtr<real>* ptrs, const SlotParam* prms, const
   return hipGetLastError();
 }
 
-template hipError_t launch_tick<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t);
-template hipError_t launch_tick<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t);
+template hipError_t launch_tick<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t, bool);
+template hipError_t launch_tick<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t, bool);
 template hipError_t launch_close<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t);
 template hipError_t launch_close<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t);
 template hipError_t launch_validate<float>(const float*, size_t, double, double, double, unsigned int*,

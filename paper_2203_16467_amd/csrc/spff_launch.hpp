@@ -33,21 +33,21 @@ struct TickBufs {
   SlotCtl* ctl[2];            // control blocks; the host reads and writes ctl[0]
   const typename HostCplx<real>::type* twx;
   const typename HostCplx<real>::type* twy;
-  double* prow[2];            // row-forward partials, alternating by tick
+  double* prow[2];            // row partials, alternating by tick
   double* pcol;
-  double* pinv;
   double* prof;               // per-slot byte counters, or null
   SlotSeq* seqs;              // device load-step queues, or null
   StepRec* recs;
-  KTime* kt;                  // six kernel timers (two ticks x three kernels), or null
-  unsigned long long* ktsum;  // folded kernel times
+  KTime* kt;                  // six timers (two ticks x three parts), or null
+  unsigned long long* ktsum;  // folded times
 };
 
 // Tick i (0-based) of a block of ticks over the listed slots.  Tick 0 reads
 // ctl[0], whose blocks must have no controller step pending (as the host
-// and launch_close leave them).
+// and launch_close leave them).  row_only: the row kernel alone, which
+// finishes the phase of tick i - 1.
 template <typename real>
-hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st);
+hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st, bool row_only = false);
 
 // Closes a block of k ticks: the controller step of tick k - 1, leaving
 // every listed slot's control block in ctl[0].
