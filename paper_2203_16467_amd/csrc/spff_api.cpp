@@ -120,14 +120,18 @@ spff_status check_config(const spff_config* c) {
 // auto_plan() is the built-in heuristic; the autotuner replaces it per
 // bucket through spff_set_plan().
 // ---------------------------------------------------------------------------
-bool reg_rows_ok(const spff_config* c, int kind = SPFF_FFT_REG) {
+// Sizes with register kernels, and those a plan of the C ABI may ask them
+// for (FP32).  FP64 problems take them as built in only: see auto_geom().
+bool reg_rows_size(const spff_config* c, int kind = SPFF_FFT_REG) {
   const int M = c->nx / 2;
-  return c->precision == SPFF_FP32 && M >= 64 && M <= (kind == SPFF_FFT_REG4 ? 256 : 1024);
+  const int most = c->precision == SPFF_FP64 ? 512 : 1024;
+  return M >= 64 && M <= (kind == SPFF_FFT_REG4 ? 256 : most);
 }
-bool reg_cols_ok(const spff_config* c) {
-  return c->precision == SPFF_FP32 &&
-         (c->ny == 128 || c->ny == 256 || c->ny == 512 || c->ny == 1024 || c->ny == 2048);
+bool reg_cols_size(const spff_config* c) { return c->ny >= 128; }
+bool reg_rows_ok(const spff_config* c, int kind = SPFF_FFT_REG) {
+  return c->precision == SPFF_FP32 && reg_rows_size(c, kind);
 }
+bool reg_cols_ok(const spff_config* c) { return c->precision == SPFF_FP32 && reg_cols_size(c); }
 // points per lane of the register kinds: 8 up to 512-point transforms, 16
 // for 1024 and 2048 (a 2048-point row is 1024 complex points: 64 lanes);
 // REG4 rows: 4
@@ -144,11 +148,74 @@ int reg_col_lanes(const spff_config* c, const spff_plan& pl) {
 int reg_cols_min(int Lc) { return Lc >= 64 ? 1 : 64 / Lc; }
 int reg_cols_max(int Lc) { return Lc > 64 ? 1 : THREADS / Lc; }
 
+// Register kernels of a built-in plan, where the grid has them.
+// at least ~TARGET_WG work-groups per launch when the batch allows it
+constexpr long TARGET_WG = 1024;
+void reg_plan(const spff_config* c, int S, spff_plan* pl) {
+  const int M = c->nx / 2;
+  // columns of 128..2048 points: register-resident transforms, a group
+  // of ny/8 lanes per column (8 points per lane), W columns per work-group
+  // (at least one wavefront, at most THREADS lanes); W is fixed by plan_cols
+  // if given so that the partial sums (hence the results) do not depend on
+  // the batch.  1024- and 2048-point columns take one column per group (the
+  // 16-point form of their lanes holds one wavefront per SIMD in registers);
+  // plan_cols > 1 asks a 1024-point column for that form, 16 points per lane
+  // with up to four columns per group.
+  if (reg_cols_size(c)) {
+    const bool wide = c->ny == 2048 || (c->ny == 1024 && c->plan_cols <= 1);
+    const int Lc = wide ? c->ny / 8 : c->ny / reg_points(c->ny);
+    const int wmin = reg_cols_min(Lc), wmax = reg_cols_max(Lc);
+    if (wmin <= M) {
+      int Wr = wmin;
+      if (c->plan_cols > 0) {
+        Wr = std::max(wmin, std::min(wmax, c->plan_cols));
+      } else {
+        while (Wr * 2 <= wmax && Wr * 2 <= M && (long)(M / (2 * Wr)) * S >= TARGET_WG) Wr *= 2;
+      }
+      if (Wr <= M) {
+        pl->col_kind = SPFF_FFT_REG;
+        pl->cols = Wr;
+        pl->col_threads = Wr * Lc;
+      }
+    }
+  }
+  // rows of 64..1024 complex points (nx = 128..2048; FP64 to 1024):
+  // register-resident transforms, a group of nx/16 (nx/32 for 2048) lanes per
+  // row, R rows per work-group (at least one wavefront, at most THREADS
+  // lanes); R fixed by plan_rows if given.  Below ~8 wavefronts per CU (a few
+  // problems of a small grid) rows of up to 256 points take 4 points per
+  // lane: twice the wavefronts to hide the latency of each.
+  const bool many_waves = (long)S * c->ny * (M / 8) / 64 >= 2048;
+  if (reg_rows_size(c) && (many_waves || c->plan_rows > 0 || !reg_rows_size(c, SPFF_FFT_REG4))) {
+    const int Lr = M / reg_points(M);
+    const int rmin = std::max(1, 64 / Lr), rmax = THREADS / Lr;
+    if (rmin <= c->ny) {
+      int Rr = rmin;
+      if (c->plan_rows > 0) {
+        Rr = std::max(rmin, std::min(rmax, c->plan_rows));
+      } else {
+        while (Rr * 2 <= rmax && Rr * 2 <= c->ny && (long)(c->ny / (2 * Rr)) * S >= TARGET_WG) Rr *= 2;
+      }
+      if (Rr <= c->ny) {
+        pl->row_kind = SPFF_FFT_REG;
+        pl->rows = Rr;
+        pl->row_threads = Rr * Lr;
+      }
+    }
+  } else if (reg_rows_size(c, SPFF_FFT_REG4) && c->plan_rows == 0) {
+    const int Lr = M / 4;
+    const int Rr = std::max(1, 64 / Lr);
+    if (Rr <= c->ny) {
+      pl->row_kind = SPFF_FFT_REG4;
+      pl->rows = Rr;
+      pl->row_threads = Rr * Lr;
+    }
+  }
+}
+
 spff_plan auto_plan(const spff_config* c, int S, size_t csize) {
   spff_plan pl{};
   const int M = c->nx / 2;
-  // at least ~TARGET_WG work-groups per launch when the batch allows it
-  const long TARGET_WG = 1024;
   int R = 1;
   while (R * 2 <= c->ny && 3 * (size_t)(2 * R) * (M + PAD) * csize <= LDS_TARGET &&
          (long)(c->ny / (2 * R)) * S >= TARGET_WG)
@@ -166,67 +233,7 @@ spff_plan auto_plan(const spff_config* c, int S, size_t csize) {
   pl.col_kind = SPFF_FFT_LDS;
   pl.cols = W;
   pl.col_threads = T;
-  // FP32 columns of 128..2048 points: register-resident transforms, a group
-  // of ny/8 lanes per column (8 points per lane), W columns per work-group
-  // (at least one wavefront, at most THREADS lanes); W is fixed by plan_cols
-  // if given so that the partial sums (hence the results) do not depend on
-  // the batch.  1024- and 2048-point columns take one column per group (the
-  // 16-point form of their lanes holds one wavefront per SIMD in registers);
-  // plan_cols > 1 asks a 1024-point column for that form, 16 points per lane
-  // with up to four columns per group.
-  if (reg_cols_ok(c)) {
-    const bool wide = c->ny == 2048 || (c->ny == 1024 && c->plan_cols <= 1);
-    const int Lc = wide ? c->ny / 8 : c->ny / reg_points(c->ny);
-    const int wmin = reg_cols_min(Lc), wmax = reg_cols_max(Lc);
-    if (wmin <= M) {
-      int Wr = wmin;
-      if (c->plan_cols > 0) {
-        Wr = std::max(wmin, std::min(wmax, c->plan_cols));
-      } else {
-        while (Wr * 2 <= wmax && Wr * 2 <= M && (long)(M / (2 * Wr)) * S >= TARGET_WG) Wr *= 2;
-      }
-      if (Wr <= M) {
-        pl.col_kind = SPFF_FFT_REG;
-        pl.cols = Wr;
-        pl.col_threads = Wr * Lc;
-      }
-    }
-  }
-  // FP32 rows of 64..1024 complex points (nx = 128..2048): register-resident
-  // transforms, a group of nx/16 (nx/32 for 2048) lanes per row, R rows per work-group (at
-  // least one wavefront, at most THREADS lanes); R fixed by plan_rows if
-  // given.  A lane walks 8 pixel pairs of its row one after the other, so
-  // the path needs enough wavefronts in flight to hide that: below ~8 per
-  // CU (a few problems of a small grid) the LDS row kernels, whose threads
-  // take one pixel pair each, finish sooner.
-  const bool many_waves = (long)S * c->ny * (M / 8) / 64 >= 2048;
-  if (reg_rows_ok(c) && (many_waves || c->plan_rows > 0)) {
-    const int Lr = M / reg_points(M);
-    const int rmin = std::max(1, 64 / Lr), rmax = THREADS / Lr;
-    if (rmin <= c->ny) {
-      int Rr = rmin;
-      if (c->plan_rows > 0) {
-        Rr = std::max(rmin, std::min(rmax, c->plan_rows));
-      } else {
-        while (Rr * 2 <= rmax && Rr * 2 <= c->ny && (long)(c->ny / (2 * Rr)) * S >= TARGET_WG) Rr *= 2;
-      }
-      if (Rr <= c->ny) {
-        pl.row_kind = SPFF_FFT_REG;
-        pl.rows = Rr;
-        pl.row_threads = Rr * Lr;
-      }
-    }
-  } else if (reg_rows_ok(c, SPFF_FFT_REG4) && c->plan_rows == 0) {
-    // few wavefronts: 4 points per lane (twice the lanes per row) hides the
-    // per-lane latency better than either 8 points per lane or the LDS path
-    const int Lr = M / 4;
-    const int Rr = std::max(1, 64 / Lr);
-    if (Rr <= c->ny) {
-      pl.row_kind = SPFF_FFT_REG4;
-      pl.rows = Rr;
-      pl.row_threads = Rr * Lr;
-    }
-  }
+  if (c->precision == SPFF_FP32) reg_plan(c, S, &pl);
   return pl;
 }
 
@@ -283,7 +290,7 @@ LaunchGeom geom_from_plan(const spff_config* c, int S, size_t csize, const spff_
   G.threads = pl.row_threads;
   G.row_reg = pl.row_kind == SPFF_FFT_REG ? 1 : (pl.row_kind == SPFF_FFT_REG4 ? 2 : 0);
   const size_t xch = (size_t)pl.rows * (M + M / 8), tile = (size_t)M * (pl.rows + 1);
-  G.lds_row = G.row_reg ? (M >= 1024 ? std::max(xch, tile) : xch + tile) * csize  // RowLds in spff_kernels.hip
+  G.lds_row = G.row_reg ? (M * csize >= 8192 ? std::max(xch, tile) : xch + tile) * csize  // RowLds in spff_kernels.hip
                         : 3 * (size_t)pl.rows * (M + PAD) * csize;
   if (G.row_reg) G.lds_row += (size_t)M * csize;  // twiddle factors
   G.W = pl.cols;
@@ -296,6 +303,15 @@ LaunchGeom geom_from_plan(const spff_config* c, int S, size_t csize, const spff_
                         : 3 * (size_t)pl.cols * (c->ny + PAD) * csize;
   if (G.col_reg) G.lds_col += (size_t)(c->ny / 2) * csize;
   return G;
+}
+
+// Geometry of a bucket's built-in plan.  FP64 problems without overrides take
+// the register kernels too (512^2 load step: 1.05 ms against 0.77 ms), while the plan
+// they report, and may be given, keeps to the LDS kind.
+LaunchGeom auto_geom(const spff_config* c, int S, size_t csize) {
+  spff_plan pl = auto_plan(c, S, csize);
+  if (c->precision == SPFF_FP64 && c->plan_rows == 0 && c->plan_cols == 0 && c->plan_threads == 0) reg_plan(c, S, &pl);
+  return geom_from_plan(c, S, csize, pl);
 }
 
 // scratch_only: slots hold solver scratch only; the resident planes
@@ -859,7 +875,7 @@ spff_status engine_create(const spff_config* cfg, int32_t nbatch, const void* E_
   std::vector<spff_plan> plans;
   for (int v : bsize) {
     spff_plan pl = auto_plan(cfg, v, 2 * rsize);
-    LaunchGeom G = geom_from_plan(cfg, v, 2 * rsize, pl);
+    LaunchGeom G = auto_geom(cfg, v, 2 * rsize);
     if (G.lds_row > LDS_MAX || G.lds_col > LDS_MAX) return fail(SPFF_E_INVALID, "grid too large for LDS tiles");
     geoms.push_back(G);
     plans.push_back(pl);
@@ -1277,7 +1293,7 @@ spff_status spff_set_plan(spff_problem* p, int32_t bucket, spff_plan* plan) {
   if (st != SPFF_OK) return st;
   HIP_TRY(hipStreamSynchronize(p->stream));
   p->plans[bucket] = pl;
-  p->geoms[bucket] = geom_from_plan(&p->cfg, v, csize, pl);
+  p->geoms[bucket] = plan ? geom_from_plan(&p->cfg, v, csize, pl) : auto_geom(&p->cfg, v, csize);
   if (p->graphs[bucket]) {
     HIP_TRY(hipGraphExecDestroy(p->graphs[bucket]));
     p->graphs[bucket] = nullptr;
@@ -1424,8 +1440,7 @@ spff_status spff_load_step_static(const spff_config* cfg, const void* E_dev, voi
   if (L.total > SPFF_STATIC_SCRATCH_BYTES)
     return fail(SPFF_E_INVALID, "a %d x %d %s problem needs %zu bytes of scratch; the static scratch holds %zu",
                 cfg->nx, cfg->ny, rsize == 8 ? "FP64" : "FP32", L.total, (size_t)SPFF_STATIC_SCRATCH_BYTES);
-  const spff_plan pl = auto_plan(cfg, 1, 2 * rsize);
-  const LaunchGeom G = geom_from_plan(cfg, 1, 2 * rsize, pl);
+  const LaunchGeom G = auto_geom(cfg, 1, 2 * rsize);
   if (G.lds_row > LDS_MAX || G.lds_col > LDS_MAX) return fail(SPFF_E_INVALID, "grid too large for LDS tiles");
   void* ws = nullptr;
   hipError_t e = static_scratch(&ws);

@@ -1372,13 +1372,13 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
 // packed column); the transposed spectrum load / store goes through an LDS
 // tile [kx][row] so that R consecutive y of one kx move as one run.
 // ---------------------------------------------------------------------------
-template <int M>
+template <typename real, int M>
 struct RowLds {
   // exchange areas of the R row groups, then the [kx][row] tile, then the
-  // twiddle table.  Rows of 1024 points let the tile overlie the exchange
-  // areas (a barrier more per component): 49 KB for four rows instead of
-  // 86 KB, so that a CU holds more than one work-group.
-  static constexpr bool ALIAS = M >= 1024;
+  // twiddle table.  Rows of 8 KB (1024 points, 512 in FP64) let the tile
+  // overlie the exchange areas (a barrier more per component): 49 KB for
+  // four rows instead of 86 KB, so that a CU holds more than one work-group.
+  static constexpr bool ALIAS = M * sizeof(cplx<real>) >= 8192;
   static __device__ __forceinline__ int tile_index(int k, int r, int R) { return k * (R + 1) + r; }
   static __device__ __forceinline__ int table(int R) {
     const int x = R * XArea<M>::size, t = M * (R + 1);
@@ -1433,8 +1433,8 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
   const int s = list[si];
   if (s < 0) return;
   const int R = blockDim.x / L, logR = ilog2(R);
-  C* tile = reinterpret_cast<C*>(smem_raw) + (RowLds<M>::ALIAS ? 0 : R * XArea<M>::size);
-  C* tw = reinterpret_cast<C*>(smem_raw) + RowLds<M>::table(R);
+  C* tile = reinterpret_cast<C*>(smem_raw) + (RowLds<real, M>::ALIAS ? 0 : R * XArea<M>::size);
+  C* tw = reinterpret_cast<C*>(smem_raw) + RowLds<real, M>::table(R);
   TwLoad<real, M / 64> tl;
   tl.load(twx, M);
   tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl, [&]() { tl.store(tw, M); });
@@ -1486,19 +1486,19 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
         for (int i = 0; i < E; ++i) {
           const int idx = tid + i * blockDim.x;
           const int r = idx & (R - 1), k = idx >> logR;
-          tile[RowLds<M>::tile_index(k, r, R)] = v[c][i];
+          tile[RowLds<real, M>::tile_index(k, r, R)] = v[c][i];
         }
       } else {
         for (int idx = tid; idx < M * R; idx += blockDim.x) {
           const int r = idx & (R - 1), k = idx >> logR;
-          tile[RowLds<M>::tile_index(k, r, R)] =
+          tile[RowLds<real, M>::tile_index(k, r, R)] =
               ldc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r));
         }
       }
       __syncthreads();
 #pragma unroll
-      for (int m = 0; m < E; ++m) v[c][m] = tile[RowLds<M>::tile_index(lane + m * L, row, R)];
-      if constexpr (RowLds<M>::ALIAS) __syncthreads();
+      for (int m = 0; m < E; ++m) v[c][m] = tile[RowLds<real, M>::tile_index(lane + m * L, row, R)];
+      if constexpr (RowLds<real, M>::ALIAS) __syncthreads();
       // from the packed half spectrum to Z whose unnormalised inverse FFT
       // gives nx (x[2h] + i x[2h+1])
       C pn[E];
@@ -1524,7 +1524,7 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
     for (int c = 0; c < NOUT; ++c) {
       if (OP == RO_X_IN && c >= X.nout) break;
       const int tid = opaque(threadIdx.x), lane = tid & (L - 1);
-      if constexpr (RowLds<M>::ALIAS) __syncthreads();
+      if constexpr (RowLds<real, M>::ALIAS) __syncthreads();
       reg_fft<real, false, M, E>(v[c], xa, lane, tw, 2);
       // half spectrum of the real row: X[k] = e + w^k o (k > 0), bin 0
       // packs X[0] + i X[M]
@@ -1543,13 +1543,13 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
           const C od = cscale(cmulni(csub(zk, zm)), real(0.5));
           out = cadd(e, cmul(tw[k], od));
         }
-        tile[RowLds<M>::tile_index(k, row, R)] = out;
+        tile[RowLds<real, M>::tile_index(k, row, R)] = out;
       }
       __syncthreads();
       // transposed store: spec[c][kx][y0 + r], r fastest
       for (int idx = tid; idx < M * R; idx += blockDim.x) {
         const int r = idx & (R - 1), k = idx >> logR;
-        stc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r), tile[RowLds<M>::tile_index(k, r, R)]);
+        stc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r), tile[RowLds<real, M>::tile_index(k, r, R)]);
       }
     }
     block_reduce_store<NP_ROW>(acc, red, part + (size_t)s * NP_ROW * ngr + g, ngr, op_nacc(OP), op_maxslot(OP));
@@ -2322,67 +2322,62 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
   T.kt_row = TR.inv;
   T.ktsum = B.ktsum;
   dim3 grow(G.ngr, G.S), gcol(G.ngc, G.S + (B.kt ? 1 : 0));
-  bool row_done = false;
-  if constexpr (std::is_same<real, float>::value) {
-    if (G.row_reg) {
-      row_done = true;
 #define SPFF_ROWS(MM, EE)                                                                                    \
   hipLaunchKernelGGL((k_rowr<real, MM, EE>), grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, A, twx, \
                      prow, G.ny, G.ngr, TR)
-      if (G.row_reg == 2) {
-        switch (G.nx) {
-          case 128: SPFF_ROWS(64, 4); break;
-          case 256: SPFF_ROWS(128, 4); break;
-          default: SPFF_ROWS(256, 4); break;
-        }
-      } else {
-        switch (G.nx) {
-          case 128: SPFF_ROWS(64, 8); break;
-          case 256: SPFF_ROWS(128, 8); break;
-          case 512: SPFF_ROWS(256, 8); break;
-          case 1024: SPFF_ROWS(512, 8); break;
-          default: SPFF_ROWS(1024, 16); break;
-        }
-      }
-#undef SPFF_ROWS
+  if (G.row_reg == 2) {
+    switch (G.nx) {
+      case 128: SPFF_ROWS(64, 4); break;
+      case 256: SPFF_ROWS(128, 4); break;
+      case 512: SPFF_ROWS(256, 4); break;
+      default: return hipErrorInvalidValue;
     }
-  }
-  if (!row_done)
+  } else if (G.row_reg == 1) {
+    switch (G.nx) {
+      case 128: SPFF_ROWS(64, 8); break;
+      case 256: SPFF_ROWS(128, 8); break;
+      case 512: SPFF_ROWS(256, 8); break;
+      case 1024: SPFF_ROWS(512, 8); break;
+      default:
+        // FP64 has no register kernel for 2048-point rows
+        if constexpr (std::is_same<real, float>::value)
+          SPFF_ROWS(1024, 16);
+        else
+          return hipErrorInvalidValue;
+        break;
+    }
+  } else {
     hipLaunchKernelGGL(k_row<real>, grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, A, twx, prow, G.nx, G.ny,
                        G.R, G.ngr, TR);
+  }
+#undef SPFF_ROWS
   if (row_only) return hipGetLastError();
-  bool col_done = false;
-  if constexpr (std::is_same<real, float>::value) {
-    if (G.col_reg) {
-      col_done = true;
 #define SPFF_COLS(NN, EE)                                                                                           \
   hipLaunchKernelGGL((k_colr<real, NN, EE>), gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, \
                      prow, pcol, G.nx, G.ngr, G.ngc, G.nyq_free, T)
-      switch (G.ny) {
-        case 128: SPFF_COLS(128, 8); break;
-        case 256: SPFF_COLS(256, 8); break;
-        case 512: SPFF_COLS(512, 8); break;
-        case 1024:
-          if (G.col_pts == 8) {
-            SPFF_COLS(1024, 8);
-          } else {
-            SPFF_COLS(1024, 16);
-          }
-          break;
-        default:
-          if (G.col_pts == 8) {
-            SPFF_COLS(2048, 8);
-          } else {
-            SPFF_COLS(2048, 16);
-          }
-          break;
-      }
-#undef SPFF_COLS
+  if (G.col_reg && G.col_pts == 8) {
+    switch (G.ny) {
+      case 128: SPFF_COLS(128, 8); break;
+      case 256: SPFF_COLS(256, 8); break;
+      case 512: SPFF_COLS(512, 8); break;
+      case 1024: SPFF_COLS(1024, 8); break;
+      default: SPFF_COLS(2048, 8); break;
     }
-  }
-  if (!col_done)
+  } else if (G.col_reg) {
+    // 16 points per lane: plans of FP32 problems only
+    if constexpr (std::is_same<real, float>::value) {
+      if (G.ny == 1024)
+        SPFF_COLS(1024, 16);
+      else
+        SPFF_COLS(2048, 16);
+    } else {
+      return hipErrorInvalidValue;
+    }
+  } else {
     hipLaunchKernelGGL(k_col<real>, gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, prow, pcol,
                        G.nx, G.ny, G.W, G.ngr, G.ngc, G.nyq_free, T);
+  }
+#undef SPFF_COLS
   return hipGetLastError();
 }
 
