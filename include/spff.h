@@ -117,8 +117,8 @@ typedef struct spff_config {
   double tol_pf, tol_abs_pf;     /* phase field: ||r|| <= tol*max(||b||,||r0||) + tol_abs */
   double tol_am;           /* AM stop: sum |phi_n+1 - phi_n| < tol_am (pixel units); <0: 1e-3 ell^2 */
   int32_t max_cg, max_newton, max_bccg, max_am; /* iteration caps */
-  int32_t ticks_per_sync;  /* solver ticks enqueued between host status checks (>= 1) */
-  int32_t use_graph;       /* 1: replay the tick block as a captured HIP graph */
+  int32_t ticks_per_sync;  /* most solver ticks in a block, the unit the host enqueues and checks (>= 1) */
+  int32_t use_graph;       /* 1: replay the tick block as a captured HIP graph (of an even number of ticks) */
   /* Attainable-accuracy floor (not in the paper): a residual evaluated in the
    * working precision u carries rounding noise of about u sqrt(log2(nx ny))
    * times the norm of the terms it is computed from, so a sub-solve also
@@ -292,34 +292,38 @@ spff_status spff_set_state(spff_problem* p, const void* src_dev, const double* e
 enum { SPFF_OP_PROJECT = 0, SPFF_OP_NEG_LAPLACIAN = 1, SPFF_OP_DISPLACEMENT = 2 };
 spff_status spff_apply_operator(spff_problem* p, int32_t op, const void* in_dev, void* out_dev);
 
-/* Kernel profiling.  A tick is three kernels: row-forward FFT (which first
- * runs the controller step of the previous tick), column FFT and
- * row-inverse FFT; a block of ticks ends with a closing controller kernel.
- * While enabled, every work-group of the three FFT kernels stamps its first
- * and last device wall-clock reading, and an extra work-group of the next
- * tick's column kernel (the closing kernel, for a block's last tick)
- * accumulates per FFT kernel
+/* Kernel profiling.  A tick is two kernels: the row kernel, which first runs
+ * the controller step of the previous tick, then finishes that tick's phase
+ * (inverse row transforms: its inverse part) and starts the next one (forward
+ * row transforms: its forward part), and the column kernel.  While enabled,
+ * blocks have ticks_per_sync ticks, each ends with a closing controller
+ * kernel and a host check, and every work-group stamps the device wall clock
+ * at the start of both kernels, between the row kernel's parts and at both
+ * ends; an extra work-group of the next tick's column kernel (the closing
+ * kernel, for a block's last tick) accumulates per part (index 0: row kernel,
+ * forward part; 1: column kernel; 2: row kernel, inverse part)
  *   kernel_ms       its activity: first work-group start to last end;
  *   kernel_span_ms  its span: first start to the first start of the next
- *                   kernel (activity plus the dead time of its drain,
- *                   end-of-kernel write-back and the next dispatch);
+ *                   part (for the column kernel activity plus the dead time
+ *                   of its drain, end-of-kernel write-back and the next
+ *                   dispatch);
  * a profiler's kernel trace, which also counts dispatch and write-back,
- * falls between the two.  Works inside captured graphs, without host
- * events; index 3 stays zero.  The controller step also accumulates each
- * kernel's algorithmic HBM bytes for the phase every problem executed
- * (inputs read once, outputs written once, half spectra round-tripped).
- * Enabling resets the totals. */
+ * falls between the two for the column kernel.  Works inside captured
+ * graphs, without host events; index 3 stays zero.  The controller step also
+ * accumulates each part's algorithmic HBM bytes for the phases every problem
+ * executed (inputs read once, outputs written once, half spectra
+ * round-tripped).  Enabling resets the totals. */
 typedef struct spff_profile {
-  double kernel_ms[4];       /* summed activity per kernel */
-  int64_t launches[4];       /* launches per kernel */
-  double alg_bytes[4];       /* summed algorithmic bytes per kernel */
+  double kernel_ms[4];       /* summed activity per part */
+  int64_t launches[4];       /* launches of its kernel */
+  double alg_bytes[4];       /* summed algorithmic bytes per part */
   int64_t ticks;
-  double kernel_span_ms[4];  /* summed span per kernel */
+  double kernel_span_ms[4];  /* summed span per part */
 } spff_profile;
 spff_status spff_profile_enable(spff_problem* p, int32_t enable);
 spff_status spff_profile_read(spff_problem* p, spff_profile* out);
 
-/* Launch plans of the three FFT kernels, one per bucket of active problems
+/* Launch plans of the FFT kernels, one per bucket of active problems
  * (the launch covers a power-of-two number of problem slots: bucket i has
  * min(2^i, nbatch) slots).  The handle starts with a built-in heuristic
  * plan per bucket; an autotuner may time alternatives and install the
@@ -378,7 +382,7 @@ spff_status spff_destroy_problem(spff_problem* p);
  * (admission by HBM footprint).  A request is one load step (Algorithm 2) of
  * one problem; requests of one problem run in submission order, one at a time.
  * spff_server_progress admits queued requests into free slots between tick
- * blocks, so requests that arrive while others run join the batch as slots
+ * blocks of their class, so requests that arrive while others run join the batch as slots
  * free up (their work overlaps on the device).  A problem's result does not
  * depend on what else runs (fixed-order reductions); with fixed launch-plan
  * overrides it is bitwise identical to running the problem alone.
@@ -405,8 +409,9 @@ spff_status spff_server_register(spff_server* sv, const spff_config* cfg, const 
 /* Queue one load step of problem id at eps_bar (host double[3]). */
 spff_status spff_server_submit(spff_server* sv, int32_t id, const double eps_bar[3], uint64_t* ticket);
 
-/* Drive the device: up to max_rounds rounds of (admit, launch one tick block
- * per busy class, collect finished requests).  *completed receives the number
+/* Drive the device: up to max_rounds rounds of (admit, enqueue tick blocks of
+ * every busy class, wait for the end of some class's block, collect finished
+ * requests).  *completed receives the number
  * of requests finished during the call, *pending the number still queued or
  * running. */
 spff_status spff_server_progress(spff_server* sv, int32_t max_rounds, int32_t* completed, int32_t* pending);

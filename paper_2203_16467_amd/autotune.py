@@ -1,6 +1,6 @@
 """Autotuner for the FFT launch plans.
 
-A handle launches its three FFT kernels (row-forward, column, row-inverse)
+A handle launches its two FFT kernels (row, column)
 over a power-of-two bucket of active problem slots; for every bucket the
 library holds a launch plan (``spff_plan``): the kind of FFT kernel for rows
 and for columns (LDS Stockham radix-4/2 with one point pair per thread, or
@@ -17,7 +17,7 @@ every load step runs both the mechanics CG (three-component ticks) and the
 phase-field BCCG (one-component ticks).  Each candidate runs the same capped
 load step from the same saved state, once to warm up (graph capture), once
 timed with the library's device-clock kernel timers.  Row plans are ranked by
-row-forward + row-inverse time per tick, column plans by column time per
+the time of the row kernel (both parts) per tick, column plans by column time per
 tick (the kernels are timed apart, so the two searches are independent).
 Results are kept in a JSON cache keyed by grid, precision and bucket size.
 """

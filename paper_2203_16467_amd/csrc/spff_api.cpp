@@ -48,6 +48,16 @@ constexpr int PAD = 1;
 constexpr size_t LDS_TARGET = 60 * 1024;
 constexpr size_t LDS_MAX = 150 * 1024;
 
+// Blocks of ticks: at most BLOCK_TICKS ticks each, and ticks_per_sync: short,
+// so that few idle ticks follow a run's last one.  A captured block costs a
+// gap of its own and is twice as long (13 x 256^2 evolution: 8.0 ms with
+// captured blocks of 4 ticks, 7.7 with 8, 7.6 launched eagerly by 4; 2048^2
+// step: 2.68, 2.72, 2.66 ms, and 2.85 with captured blocks of 32).
+constexpr int BLOCK_TICKS = 4;
+constexpr int GRAPH_TICKS = 8;
+constexpr int BLOCKS_AHEAD = 2;
+constexpr int LIST_RING = 4;
+
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 inline bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
@@ -380,9 +390,26 @@ struct spff_problem {
   std::vector<spff_plan> plans;  // per bucket, geoms[i] derived from plans[i]
   std::vector<hipGraphExec_t> graphs;  // one captured tick block per bucket (lazy)
   int cur_bucket = -1;
-  int32_t* host_list = nullptr;  // pinned staging of the device slot list
+  // pinned staging of the device slot list: uploads of LIST_RING successive
+  // lists, of which at most BLOCKS_AHEAD + 1 can be in flight
+  int32_t* host_list = nullptr;
+  int list_at = 0;
   std::vector<int32_t> cur_list;
-  SlotCtl* host_ctl;  // pinned mirror
+  SlotCtl* host_ctl;  // pinned mirror (S blocks), and a second copy for run_begin()'s upload
+  // progress words that the row kernels post (pinned), see run_slots()
+  unsigned long long* host_post = nullptr;
+  // pinned staging of the step queues and their records (allocated by the
+  // first call that queues more than one step)
+  SlotSeq* host_seq = nullptr;
+  StepRec* host_rec = nullptr;  // host_rec_len per slot
+  int host_rec_len = 0;
+  struct Block {
+    std::vector<std::pair<int32_t, uint32_t>> upto;  // listed slots, their row kernels enqueued up to this block
+  };
+  std::deque<Block> ahead;           // enqueued blocks the host has not seen the end of
+  std::vector<int32_t> listed;       // slots of the next block
+  std::vector<uint32_t> enqueued;    // row kernels enqueued per slot since it started
+  int run_ticks = 0, run_bucket = -1;  // ticks since the last closing kernel, their bucket
   std::vector<SlotParam> prm;
   std::vector<double> last_eps_bar;
   std::vector<int> last_advance;  // advance flag of each problem's last step (1 before the first)
@@ -426,21 +453,22 @@ TickBufs<real> tick_bufs(const spff_problem* p) {
   B.prof = p->prof_on ? p->d_prof() : nullptr;
   B.seqs = p->d_seq();
   B.recs = p->d_rec();
+  B.post = p->prof_on ? nullptr : p->host_post;
+  B.mirror = p->host_ctl;
   B.kt = p->prof_on ? p->d_kt() : nullptr;
   B.ktsum = p->prof_on ? p->d_ktsum() : nullptr;
   return B;
 }
 
-// k ticks and the closing controller step (leaves the control blocks in
-// the host-visible buffer)
+// ticks t0 .. t0 + k - 1 of a run
 template <typename real>
-hipError_t enqueue_block(spff_problem* p, int k, hipStream_t st, int b) {
+hipError_t enqueue_block(spff_problem* p, int t0, int k, hipStream_t st, int b) {
   const TickBufs<real> B = tick_bufs<real>(p);
   for (int i = 0; i < k; ++i) {
-    hipError_t e = launch_tick<real>(p->geoms[b], B, i, st);
+    hipError_t e = launch_tick<real>(p->geoms[b], B, t0 + i, st);
     if (e != hipSuccess) return e;
   }
-  return launch_close<real>(p->geoms[b], B, k, st);
+  return hipSuccess;
 }
 
 // one tick of a diagnostic phase and the row kernel that finishes it (the
@@ -452,9 +480,26 @@ hipError_t enqueue_operator(spff_problem* p, hipStream_t st, int b) {
   return e != hipSuccess ? e : launch_tick<real>(p->geoms[b], B, 1, st, true);
 }
 
-hipError_t enqueue_ticks(spff_problem* p, int k, hipStream_t st, int b) {
-  return p->cfg.precision == SPFF_FP64 ? enqueue_block<double>(p, k, st, b) : enqueue_block<float>(p, k, st, b);
+hipError_t enqueue_ticks(spff_problem* p, int t0, int k, hipStream_t st, int b) {
+  return p->cfg.precision == SPFF_FP64 ? enqueue_block<double>(p, t0, k, st, b) : enqueue_block<float>(p, t0, k, st, b);
 }
+
+hipError_t enqueue_close(spff_problem* p, int k, hipStream_t st, int b, int slots) {
+  return p->cfg.precision == SPFF_FP64
+             ? launch_close<double>(p->geoms[b], tick_bufs<double>(p), k, st, slots)
+             : launch_close<float>(p->geoms[b], tick_bufs<float>(p), k, st, slots);
+}
+
+// Ticks of one block.  A captured block has an even number (it starts at the
+// buffers of tick 0) and, with timers on, ends with the closing kernel.
+int block_ticks(const spff_problem* p) {
+  const int K = p->cfg.ticks_per_sync;
+  if (p->prof_on) return K;
+  if (!p->cfg.use_graph) return std::min(K, BLOCK_TICKS);
+  return K >= GRAPH_TICKS ? GRAPH_TICKS : (K % 2 ? 2 * K : K);
+}
+
+int blocks_ahead(const spff_problem* p) { return block_ticks(p) > 1 ? 1 : BLOCKS_AHEAD; }
 
 // After a synchronised block of k ticks: count the launches (the kernel
 // times are accumulated on the device): k of each FFT kernel, one closing
@@ -467,14 +512,15 @@ void collect_profile(spff_problem* p, int k) {
 }
 
 spff_status build_graph(spff_problem* p, int b) {
-  const int K = p->cfg.ticks_per_sync;
+  const int K = block_ticks(p);
   if (p->graphs[b]) {
     HIP_TRY(hipGraphExecDestroy(p->graphs[b]));
     p->graphs[b] = nullptr;
   }
   if (!p->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking));
   HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = enqueue_ticks(p, K, p->cap_stream, b);
+  hipError_t e = enqueue_ticks(p, 0, K, p->cap_stream, b);
+  if (e == hipSuccess && p->prof_on) e = enqueue_close(p, K, p->cap_stream, b, 0);
   hipGraph_t graph = nullptr;
   hipError_t e2 = hipStreamEndCapture(p->cap_stream, &graph);
   if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick capture failed: %s", hipGetErrorString(e));
@@ -497,11 +543,12 @@ spff_status set_list(spff_problem* p, const std::vector<int32_t>& active, int b)
   std::vector<int32_t> lst(active);
   lst.resize(p->bucket_size[b], -1);
   if (lst == p->cur_list) return SPFF_OK;
-  // the previous upload was followed by a synchronisation, so the pinned
-  // staging buffer is free
-  std::copy(lst.begin(), lst.end(), p->host_list);
-  HIP_TRY(hipMemcpyAsync(p->d_list(), p->host_list, sizeof(int32_t) * lst.size(), hipMemcpyHostToDevice,
-                         p->stream));
+  // a staging buffer is used again only LIST_RING uploads later: at most one
+  // upload a block, and the blocks before the last BLOCKS_AHEAD + 1 have run
+  int32_t* stage = p->host_list + (size_t)p->list_at * p->S;
+  p->list_at = (p->list_at + 1) % LIST_RING;
+  std::copy(lst.begin(), lst.end(), stage);
+  HIP_TRY(hipMemcpyAsync(p->d_list(), stage, sizeof(int32_t) * lst.size(), hipMemcpyHostToDevice, p->stream));
   p->cur_list.swap(lst);
   return SPFF_OK;
 }
@@ -512,20 +559,51 @@ int bucket_for(const spff_problem* p, int nactive) {
   return b;
 }
 
-// Enqueue one block of ticks over the slots that are not idle (host mirror)
-// with the launch plan of their count.  Returns SPFF_OK without launching
-// when no slot is active.
-spff_status launch_block(spff_problem* p, bool* launched, int* nticks) {
-  std::vector<int32_t> active;
-  for (int s = 0; s < p->S; ++s)
-    if (p->host_ctl[s].phase != PH_IDLE) active.push_back(s);
-  *launched = false;
-  *nticks = 0;
-  if (active.empty()) return SPFF_OK;
-  const int b = bucket_for(p, (int)active.size());
-  spff_status st = set_list(p, active, b);
+// Runs blocks of ticks_per_sync ticks until every slot is idle, with a
+// closing kernel and a host check after each (the timers count closed blocks).
+spff_status run_timed(spff_problem* p, const char* more) {
+  for (;;) {
+    std::vector<int32_t> active;
+    bool stop = false;
+    for (int s = 0; s < p->S; ++s) {
+      if (p->host_ctl[s].phase != PH_IDLE) active.push_back(s);
+      stop |= more && more[s] && p->host_ctl[s].phase == PH_IDLE;
+    }
+    if (active.empty() || stop) return SPFF_OK;
+    const int b = bucket_for(p, (int)active.size());
+    spff_status st = set_list(p, active, b);
+    if (st != SPFF_OK) return st;
+    const int K = p->cfg.ticks_per_sync;
+    if (p->cfg.use_graph) {
+      if (!p->graphs[b]) {
+        st = build_graph(p, b);
+        if (st != SPFF_OK) return st;
+      }
+      HIP_TRY(hipGraphLaunch(p->graphs[b], p->stream));
+    } else {
+      hipError_t e = enqueue_ticks(p, 0, K, p->stream, b);
+      if (e == hipSuccess) e = enqueue_close(p, K, p->stream, b, 0);
+      if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick launch failed: %s", hipGetErrorString(e));
+    }
+    HIP_TRY(hipStreamSynchronize(p->stream));
+    collect_profile(p, K);
+  }
+}
+
+// Enqueue one block of ticks over the listed slots, with the launch plan of
+// their number.
+spff_status enqueue_run_block(spff_problem* p) {
+  const int b = bucket_for(p, (int)p->listed.size());
+  if (p->run_bucket >= 0 && b != p->run_bucket && p->run_ticks > 0) {
+    // another plan reduces other partial sums: finish the last controller
+    // step under the plan that wrote them
+    HIP_TRY(enqueue_close(p, p->run_ticks, p->stream, p->run_bucket, 0));
+    p->run_ticks = 0;
+  }
+  p->run_bucket = b;
+  spff_status st = set_list(p, p->listed, b);
   if (st != SPFF_OK) return st;
-  const int K = p->cfg.ticks_per_sync;
+  const int k = block_ticks(p);
   if (p->cfg.use_graph) {
     if (!p->graphs[b]) {
       st = build_graph(p, b);
@@ -533,28 +611,115 @@ spff_status launch_block(spff_problem* p, bool* launched, int* nticks) {
     }
     HIP_TRY(hipGraphLaunch(p->graphs[b], p->stream));
   } else {
-    hipError_t e = enqueue_ticks(p, K, p->stream, b);
+    hipError_t e = enqueue_ticks(p, p->run_ticks, k, p->stream, b);
     if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick launch failed: %s", hipGetErrorString(e));
   }
-  *launched = true;
-  *nticks = K;
+  // only the parity and whether there were any matter
+  p->run_ticks = (p->run_ticks + k) % 2 ? 1 : 2;
+  spff_problem::Block blk;
+  blk.upto.reserve(p->listed.size());
+  for (int s : p->listed) {
+    p->enqueued[s] += (uint32_t)k;
+    blk.upto.push_back({s, p->enqueued[s]});
+  }
+  p->ahead.push_back(std::move(blk));
   return SPFF_OK;
 }
 
-// Run ticks until every slot is idle.
-spff_status run_until_idle(spff_problem* p) {
-  const size_t cbytes = sizeof(SlotCtl) * p->S;
-  for (;;) {
-    bool launched;
-    int k;
-    spff_status st = launch_block(p, &launched, &k);
-    if (st != SPFF_OK) return st;
-    if (!launched) break;
-    HIP_TRY(hipMemcpyAsync(p->host_ctl, p->d_ctl(), cbytes, hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
-    collect_profile(p, k);
+// Start of a run over the slots that are not idle in the host mirror:
+// uploads the control blocks (to both buffers: the closing kernel reads the
+// one that the run's parity gives, also for slots that never were listed).
+// The device is idle.
+spff_status run_begin(spff_problem* p) {
+  p->listed.clear();
+  p->enqueued.assign(p->S, 0);
+  p->ahead.clear();
+  p->run_ticks = 0;
+  p->run_bucket = -1;
+  for (int s = 0; s < p->S; ++s) {
+    SlotCtl& c = p->host_ctl[s];
+    c.tick_no = c.idle_at = 0;
+    c.pending = 0;
+    p->host_post[s] = 0;
+    if (c.phase != PH_IDLE) p->listed.push_back(s);
+  }
+  std::copy(p->host_ctl, p->host_ctl + p->S, p->host_ctl + p->S);
+  HIP_TRY(hipMemcpyAsync(p->d_ctl(), p->host_ctl, 2 * sizeof(SlotCtl) * p->S, hipMemcpyHostToDevice, p->stream));
+  return SPFF_OK;
+}
+
+// Whether the oldest enqueued block has been posted by all of its slots.
+bool run_seen(const spff_problem* p) {
+  const volatile unsigned long long* post = p->host_post;
+  for (const auto& [s, n] : p->ahead.front().upto)
+    if ((uint32_t)post[s] < n) return false;
+  return true;
+}
+
+// Retires the oldest block (which run_seen() has confirmed): slots that were
+// idle by its end leave the list.  What is known at a block's end does not
+// depend on how far the device has got since, so neither does the list (and
+// with it the launch plan) of a later block.  A slot that was idle in a
+// tick has both of its control buffers idle after the next one: the blocks
+// enqueued since contain it.
+void run_retire(spff_problem* p) {
+  for (const auto& [s, n] : p->ahead.front().upto) {
+    const uint32_t idle = (uint32_t)(p->host_post[s] >> 32);
+    if (idle != 0 && idle <= n && p->enqueued[s] > idle)
+      p->listed.erase(std::remove(p->listed.begin(), p->listed.end(), s), p->listed.end());
+  }
+  p->ahead.pop_front();
+}
+
+// Waits for the oldest block.  The words are posted while later blocks are
+// already in the stream, so the wait ends in time to enqueue the next one;
+// the stream is asked now and then, so that a failed device ends it too.
+spff_status run_wait(spff_problem* p) {
+  for (unsigned spin = 1; !run_seen(p); ++spin) {
+    if (spin % 4096) continue;
+    const hipError_t e = hipStreamQuery(p->stream);
+    if (e == hipErrorNotReady) continue;
+    if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick block failed: %s", hipGetErrorString(e));
+    if (!run_seen(p)) return fail(SPFF_E_DEVICE, "a tick block ended without its progress being posted");
   }
   return SPFF_OK;
+}
+
+// End of a run: the last controller step, every slot's control block into
+// buffer 0 and the host mirror.  Synchronises the stream.
+spff_status run_end(spff_problem* p) {
+  if (p->run_ticks > 0) HIP_TRY(enqueue_close(p, p->run_ticks, p->stream, p->run_bucket, p->S));
+  HIP_TRY(hipStreamSynchronize(p->stream));
+  p->ahead.clear();
+  p->run_ticks = 0;
+  return SPFF_OK;
+}
+
+// Runs blocks of ticks, from the control blocks of the host mirror, until
+// every slot is idle -- or one of those in `more` (per slot, may be null),
+// which have further work.  blocks_ahead() blocks are enqueued beyond the one
+// whose end the host watches (a host round trip per block left the device
+// idle for 16 us: the closing kernel, a copy, a synchronisation and the next
+// launch); the ticks enqueued after the last slot has gone idle do nothing.
+spff_status run_until_idle(spff_problem* p, const char* more = nullptr) {
+  spff_status st = run_begin(p);
+  if (st != SPFF_OK) return st;
+  if (p->prof_on) return run_timed(p, more);
+  bool stop = false;
+  while (!p->listed.empty() && !stop) {
+    st = enqueue_run_block(p);
+    if (st != SPFF_OK) break;
+    if ((int)p->ahead.size() <= blocks_ahead(p)) continue;
+    st = run_wait(p);
+    if (st != SPFF_OK) break;
+    const auto upto = p->ahead.front().upto;
+    run_retire(p);
+    if (more)
+      for (const auto& [s, n] : upto)
+        stop |= more[s] && std::find(p->listed.begin(), p->listed.end(), s) == p->listed.end();
+  }
+  const spff_status end = run_end(p);
+  return st != SPFF_OK ? st : end;
 }
 
 template <typename real>
@@ -905,10 +1070,12 @@ spff_status engine_create(const spff_config* cfg, int32_t nbatch, const void* E_
     spff_destroy_problem(p);
     return s;
   };
-  if (hipHostMalloc(reinterpret_cast<void**>(&p->host_ctl), sizeof(SlotCtl) * nbatch, hipHostMallocDefault) !=
+  if (hipHostMalloc(reinterpret_cast<void**>(&p->host_ctl), 2 * sizeof(SlotCtl) * nbatch, hipHostMallocDefault) !=
           hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&p->host_list), sizeof(int32_t) * nbatch, hipHostMallocDefault) !=
-          hipSuccess)
+      hipHostMalloc(reinterpret_cast<void**>(&p->host_list), sizeof(int32_t) * nbatch * LIST_RING,
+                    hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&p->host_post), sizeof(unsigned long long) * nbatch,
+                    hipHostMallocDefault) != hipSuccess)
     return cleanup(fail(SPFF_E_DEVICE, "pinned host allocation failed"));
   for (int s = 0; s < nbatch; ++s) reset_ctl(p, s);
   st = cfg->precision == SPFF_FP64 ? init_device<double>(p, E_dev, phi_init_dev)
@@ -926,7 +1093,7 @@ spff_status engine_create(const spff_config* cfg, int32_t nbatch, const void* E_
       hipSuccess)
     return cleanup(fail(SPFF_E_DEVICE, "control upload failed"));
   if (phi_init_dev) {
-    st = run_until_idle(p);
+    st = run_until_idle(p);  // (uploads the control blocks itself)
     if (st != SPFF_OK) return cleanup(st);
   }
   if (hipStreamSynchronize(p->stream) != hipSuccess) return cleanup(fail(SPFF_E_DEVICE, "stream sync failed"));
@@ -961,6 +1128,37 @@ spff_status spff_run_evolution(spff_problem* p, int32_t nsteps, const double* de
   return run_queue(p, nsteps, deps, stats, true);
 }
 
+// The control-block view of a recorded step, for fill_stats().
+static SlotCtl rec_ctl(const StepRec& r) {
+  SlotCtl c{};
+  c.am = r.am;
+  c.newton = r.newton;
+  c.cg = r.cg;
+  c.bccg = r.bccg;
+  c.ticks = r.ticks;
+  c.status = r.status;
+  c.dt = r.dt;
+  c.halvings = r.halvings;
+  c.advance = r.advance;
+  c.gamma = r.gamma;
+  c.fmax_ne = r.fmax_ne;
+  c.ne_flag = r.ne_flag;
+  c.flags = r.flags;
+  c.dphi = r.dphi;
+  c.mech_res = r.mech_res;
+  c.pf_res = r.pf_res;
+  c.F_e = r.F_e;
+  c.F_f = r.F_f;
+  for (int m = 0; m < 3; ++m) {
+    c.sbar[m] = r.sbar[m];
+    c.eps_bar[m] = r.eps_bar[m];
+  }
+  c.phi_sum = r.phi_sum;
+  c.phi_max = r.phi_max;
+  c.crack_px = r.crack_px;
+  return c;
+}
+
 // Device step queues: per problem, steps at the given macroscopic strains
 // (incr = false) or, for the time-discretized / near-equilibrium evolution,
 // steps that continue from the previous step's final strain plus the given
@@ -980,110 +1178,114 @@ static spff_status run_queue(spff_problem* p, int32_t nsteps, const double* eps_
     p->clock_khz = khz > 0 ? (double)khz : 1e5;
   }
   // Steps are handed to the device in chunks of at most SEQ_MAX per slot; the
-  // controller chains the steps of a chunk on the device.
-  std::vector<int> next(S, 0);      // first step of the slot's current chunk
-  std::vector<int> clen(S, 0);      // length of the slot's current chunk
-  std::vector<SlotSeq> q(1);
-  std::vector<StepRec> rec(SEQ_MAX);
-  auto upload_chunk = [&](int s) -> spff_status {
-    const int len = std::min(SEQ_MAX, nsteps - next[s]);
-    SlotSeq& h = q[0];
-    h.len = len;
-    h.pos = 0;
-    h.incr = incr ? 1 : 0;
-    for (int k = 0; k < len; ++k)
-      for (int c = 0; c < 3; ++c) h.eps_bar[k][c] = eps_bar[3 * ((size_t)s * nsteps + next[s] + k) + c];
-    HIP_TRY(hipMemcpyAsync(p->d_seq() + s, &h, sizeof(SlotSeq), hipMemcpyHostToDevice, p->stream));
-    // the staging struct is reused for the next slot: wait for this copy
-    HIP_TRY(hipStreamSynchronize(p->stream));
-    clen[s] = len;
-    double eb[3];
-    for (int c = 0; c < 3; ++c)
-      eb[c] = incr ? p->last_eps_bar[3 * s + c] + (p->last_advance[s] ? h.eps_bar[0][c] : 0.0) : h.eps_bar[0][c];
-    start_step(p, s, eb, p->cfg);
-    return SPFF_OK;
-  };
-  for (int s = 0; s < S; ++s) {
-    spff_status st = upload_chunk(s);
-    if (st != SPFF_OK) return st;
+  // controller chains the steps of a chunk on the device.  A single step
+  // needs no queue: its result is the slot's control block.
+  const bool queue = nsteps > 1;
+  const int most = std::min(SEQ_MAX, nsteps);
+  if (queue && p->host_rec_len < most) {
+    if (p->host_rec) HIP_TRY(hipHostFree(p->host_rec));
+    p->host_rec = nullptr;
+    if (!p->host_seq)
+      HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&p->host_seq), sizeof(SlotSeq) * S, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&p->host_rec), sizeof(StepRec) * most * S, hipHostMallocDefault));
+    p->host_rec_len = most;
   }
-  HIP_TRY(hipMemcpyAsync(p->d_ctl(), p->host_ctl, sizeof(SlotCtl) * S, hipMemcpyHostToDevice, p->stream));
   spff_status worst = SPFF_OK;
-  int remaining = S;
-  const size_t cbytes = sizeof(SlotCtl) * S;
-  while (remaining > 0) {
-    bool launched;
-    int k;
-    spff_status bst = launch_block(p, &launched, &k);
-    if (bst != SPFF_OK) return bst;
-    HIP_TRY(hipMemcpyAsync(p->host_ctl, p->d_ctl(), cbytes, hipMemcpyDeviceToHost, p->stream));
-    HIP_TRY(hipStreamSynchronize(p->stream));
-    collect_profile(p, k);
-    bool dirty = false;
+  auto note = [&](spff_status ss) {
+    if (ss < 0 && (worst >= 0 || ss < worst)) worst = ss;
+    if (ss > 0 && worst == SPFF_OK) worst = ss;
+  };
+  std::vector<int> next(S, 0), clen(S, 0);  // first step and length of the slot's current chunk
+  std::vector<char> more(S, 0);             // it is not the slot's last
+  std::vector<int32_t> start(S);
+  for (int s = 0; s < S; ++s) start[s] = s;
+  const double t0 = now_ms();
+  for (;;) {
+    for (int s : start) {
+      const int len = clen[s] = std::min(SEQ_MAX, nsteps - next[s]);
+      more[s] = next[s] + len < nsteps;
+      const double* e = eps_bar + 3 * ((size_t)s * nsteps + next[s]);
+      double eb[3];
+      for (int c = 0; c < 3; ++c)
+        eb[c] = incr ? p->last_eps_bar[3 * s + c] + (p->last_advance[s] ? e[c] : 0.0) : e[c];
+      start_step(p, s, eb, p->cfg);
+      if (!queue) {
+        p->host_ctl[s].seq_pos = SEQ_MAX;  // past the end of whatever queue the slot had
+        continue;
+      }
+      SlotSeq& h = p->host_seq[s];
+      h.len = len;
+      h.pos = 0;
+      h.incr = incr ? 1 : 0;
+      for (int k = 0; k < len; ++k)
+        for (int c = 0; c < 3; ++c) h.eps_bar[k][c] = e[3 * k + c];
+      if ((int)start.size() < S)
+        HIP_TRY(hipMemcpyAsync(p->d_seq() + s, &h, offsetof(SlotSeq, eps_bar) + sizeof(double) * 3 * len,
+                               hipMemcpyHostToDevice, p->stream));
+    }
+    if (queue && (int)start.size() == S)
+      HIP_TRY(hipMemcpy2DAsync(p->d_seq(), sizeof(SlotSeq), p->host_seq, sizeof(SlotSeq),
+                               offsetof(SlotSeq, eps_bar) + sizeof(double) * 3 * most, S, hipMemcpyHostToDevice,
+                               p->stream));
+    spff_status st = run_until_idle(p, nsteps > SEQ_MAX ? more.data() : nullptr);
+    if (st != SPFF_OK) return st;
+    // the device is idle and the mirror current: collect the chunks that ended
+    start.clear();
+    bool running = false;
+    std::vector<int32_t> ended;
     for (int s = 0; s < S; ++s) {
-      if (clen[s] == 0 || p->host_ctl[s].phase != PH_IDLE) continue;
-      // the slot's chunk has ended (all steps done, or a step failed)
-      HIP_TRY(hipMemcpyAsync(rec.data(), p->d_rec() + (size_t)s * SEQ_MAX, sizeof(StepRec) * clen[s],
-                             hipMemcpyDeviceToHost, p->stream));
-      HIP_TRY(hipMemcpyAsync(&q[0], p->d_seq() + s, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, p->stream));
+      if (clen[s] == 0) continue;
+      if (p->host_ctl[s].phase == PH_IDLE)
+        ended.push_back(s);
+      else
+        running = true;
+    }
+    if (queue) {
+      const size_t rp = sizeof(StepRec) * p->host_rec_len;
+      if ((int)ended.size() == S) {
+        HIP_TRY(hipMemcpy2DAsync(p->host_rec, rp, p->d_rec(), sizeof(StepRec) * SEQ_MAX, sizeof(StepRec) * most, S,
+                                 hipMemcpyDeviceToHost, p->stream));
+        HIP_TRY(hipMemcpy2DAsync(p->host_seq, sizeof(SlotSeq), p->d_seq(), sizeof(SlotSeq), 2 * sizeof(int32_t), S,
+                                 hipMemcpyDeviceToHost, p->stream));
+      } else {
+        for (int s : ended) {
+          HIP_TRY(hipMemcpyAsync(p->host_rec + (size_t)s * p->host_rec_len, p->d_rec() + (size_t)s * SEQ_MAX,
+                                 sizeof(StepRec) * clen[s], hipMemcpyDeviceToHost, p->stream));
+          HIP_TRY(hipMemcpyAsync(p->host_seq + s, p->d_seq() + s, 2 * sizeof(int32_t), hipMemcpyDeviceToHost,
+                                 p->stream));
+        }
+      }
       HIP_TRY(hipStreamSynchronize(p->stream));
-      const int done = q[0].pos;
+    }
+    for (int s : ended) {
+      const int done = queue ? p->host_seq[s].pos : 1;
       bool failed = done < clen[s];
       for (int j = 0; j < done; ++j) {
-        const StepRec& r = rec[j];
         SlotCtl c{};
-        c.am = r.am;
-        c.newton = r.newton;
-        c.cg = r.cg;
-        c.bccg = r.bccg;
-        c.ticks = r.ticks;
-        c.status = r.status;
-        c.dt = r.dt;
-        c.halvings = r.halvings;
-        c.advance = r.advance;
-        c.gamma = r.gamma;
-        c.fmax_ne = r.fmax_ne;
-        c.ne_flag = r.ne_flag;
-        c.flags = r.flags;
-        c.dphi = r.dphi;
-        c.mech_res = r.mech_res;
-        c.pf_res = r.pf_res;
-        c.F_e = r.F_e;
-        c.F_f = r.F_f;
-        for (int m = 0; m < 3; ++m) {
-          c.sbar[m] = r.sbar[m];
-          c.eps_bar[m] = r.eps_bar[m];
+        double ms;
+        if (queue) {
+          const StepRec& r = p->host_rec[(size_t)s * p->host_rec_len + j];
+          c = rec_ctl(r);
+          ms = (double)(r.t_end - r.t_start) / p->clock_khz;
+        } else {
+          c = p->host_ctl[s];
+          ms = now_ms() - t0;
         }
-        c.phi_sum = r.phi_sum;
-        c.phi_max = r.phi_max;
-        c.crack_px = r.crack_px;
         const spff_status ss = slot_status(c);
-        if (ss < 0 && (worst >= 0 || ss < worst)) worst = ss;
-        if (ss > 0 && worst == SPFF_OK) worst = ss;
-        if (ss < 0) failed = true;
-        const double ms = (double)(r.t_end - r.t_start) / p->clock_khz;
+        note(ss);
+        failed |= ss < 0;
         if (stats) fill_stats(p->n(), c, stats[(size_t)s * nsteps + next[s] + j], ms);
-        for (int m = 0; m < 3; ++m) p->last_eps_bar[3 * s + m] = r.eps_bar[m];
-        p->last_advance[s] = r.advance;
+        for (int m = 0; m < 3; ++m) p->last_eps_bar[3 * s + m] = c.eps_bar[m];
+        p->last_advance[s] = c.advance;
       }
-      if (done == 0 && p->host_ctl[s].status < 0) {
-        // failed before its record was written
-        const spff_status ss = (spff_status)p->host_ctl[s].status;
-        if (worst >= 0 || ss < worst) worst = ss;
-        failed = true;
-      }
+      // failed before its record was written
+      if (done == 0 && p->host_ctl[s].status < 0) note((spff_status)p->host_ctl[s].status);
       next[s] += clen[s];
       clen[s] = 0;
-      if (!failed && next[s] < nsteps) {
-        spff_status st = upload_chunk(s);
-        if (st != SPFF_OK) return st;
-        dirty = true;
-      } else {
-        --remaining;
-      }
+      more[s] = 0;
+      if (!failed && next[s] < nsteps) start.push_back(s);
     }
-    // the device is idle here (synchronised), so the whole mirror is current
-    if (dirty) HIP_TRY(hipMemcpyAsync(p->d_ctl(), p->host_ctl, cbytes, hipMemcpyHostToDevice, p->stream));
+    if (start.empty() && !running) break;
   }
   if (worst < 0) g_last_error = "a problem of the batch failed (see per-problem status)";
   return worst;
@@ -1319,6 +1521,9 @@ spff_status spff_destroy_problem(spff_problem* p) {
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   if (p->host_ctl) (void)hipHostFree(p->host_ctl);
   if (p->host_list) (void)hipHostFree(p->host_list);
+  if (p->host_post) (void)hipHostFree(p->host_post);
+  if (p->host_seq) (void)hipHostFree(p->host_seq);
+  if (p->host_rec) (void)hipHostFree(p->host_rec);
   delete p;
   return SPFF_OK;
 }
@@ -1404,15 +1609,16 @@ spff_status static_step(const spff_config* cfg, const Layout& L, const LaunchGeo
   B.prow[0] = reinterpret_cast<double*>(ws + L.prow);
   B.prow[1] = reinterpret_cast<double*>(ws + L.prow1);
   B.pcol = reinterpret_cast<double*>(ws + L.pcol);
+  // blocks of ticks_per_sync ticks; the host reads the block that the last
+  // row kernel left (no closing kernel in between: the next tick takes the
+  // controller step up)
   const int K = cfg->ticks_per_sync;
-  for (;;) {
-    for (int i = 0; i < K; ++i) {
-      hipError_t e = launch_tick<real>(G, B, i, st);
+  for (int t = 0;; t = t % 2 ? 1 : 2) {
+    for (int i = 0; i < K; ++i, ++t) {
+      hipError_t e = launch_tick<real>(G, B, t, st);
       if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick launch failed: %s", hipGetErrorString(e));
     }
-    hipError_t e = launch_close<real>(G, B, K, st);
-    if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick launch failed: %s", hipGetErrorString(e));
-    HIP_TRY(hipMemcpyAsync(&ctl, d_ctl, sizeof(ctl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(&ctl, B.ctl[t & 1], sizeof(ctl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (ctl.phase == PH_IDLE) break;
   }
@@ -1484,10 +1690,9 @@ struct SrvClass {
   int nx, ny, precision, nyquist;
   spff_problem* eng = nullptr;
   hipStream_t stream = nullptr;
-  hipEvent_t done_ev = nullptr;
   std::vector<int> owner;  // problem id per slot, -1 free
   std::deque<int> ready;   // problems with a request waiting for a slot
-  bool inflight = false;
+  bool running = false;    // blocks of ticks are enqueued (run_begin() to run_end())
   std::vector<int> members;
 };
 
@@ -1544,7 +1749,6 @@ spff_status class_start(spff_server* sv, int c) {
   const size_t bytes = layout(&ec, S, rsize, true).total;
   unsigned char* ws = arena_take(sv, bytes);
   HIP_TRY(hipStreamCreateWithFlags(&C.stream, hipStreamNonBlocking));
-  HIP_TRY(hipEventCreateWithFlags(&C.done_ev, hipEventDisableTiming));
   spff_status st = engine_create(&ec, S, nullptr, nullptr, ws, bytes, C.stream, true, &C.eng);
   if (st != SPFF_OK) return st;
   sv->scratch_used += bytes;
@@ -1683,62 +1887,94 @@ spff_status spff_server_submit(spff_server* sv, int32_t id, const double eps_bar
 spff_status spff_server_progress(spff_server* sv, int32_t max_rounds, int32_t* completed, int32_t* pending) {
   if (!sv) return fail(SPFF_E_INVALID, "server is NULL");
   int done_count = 0;
+  // ends a class's run and collects its finished requests; a request
+  // completes when the host has seen the end of its class's blocks
+  auto collect = [&](SrvClass& C) -> spff_status {
+    spff_problem* e = C.eng;
+    const spff_status st = run_end(e);
+    C.running = false;
+    if (st != SPFF_OK) return st;
+    const double t = now_ms();
+    for (int s = 0; s < e->S; ++s) {
+      const int id = C.owner[s];
+      if (id < 0 || e->host_ctl[s].phase != PH_IDLE) continue;
+      SrvProblem& P = sv->probs[id];
+      spff_step_stats o;
+      fill_stats(e->n(), e->host_ctl[s], o, t - P.t_submit);
+      P.dt = e->host_ctl[s].dt;
+      P.ne_flag = e->host_ctl[s].ne_flag;
+      sv->done[P.ticket] = o;
+      sv->live.erase(P.ticket);
+      P.running = false;
+      C.owner[s] = -1;
+      ++done_count;
+      if (!P.queue.empty()) C.ready.push_back(id);
+    }
+    return SPFF_OK;
+  };
   for (int round = 0; round < max_rounds; ++round) {
-    bool any = false;
     // 1. admit and launch, class by class (each on its own stream)
+    bool any = false;
     for (size_t c = 0; c < sv->classes.size(); ++c) {
       SrvClass& C = sv->classes[c];
-      if (C.ready.empty() && (!C.eng || std::all_of(C.owner.begin(), C.owner.end(), [](int o) { return o < 0; })))
-        continue;
+      const bool busy = C.eng && std::any_of(C.owner.begin(), C.owner.end(), [](int o) { return o >= 0; });
+      if (C.ready.empty() && !busy) continue;
       if (!C.eng) {
         spff_status st = class_start(sv, (int)c);
         if (st != SPFF_OK) return st;
       }
       spff_problem* e = C.eng;
-      bool dirty = false;
-      for (int s = 0; s < e->S && !C.ready.empty(); ++s) {
-        if (C.owner[s] >= 0) continue;
-        const int id = C.ready.front();
-        C.ready.pop_front();
-        spff_status st = class_admit(sv, C, s, id);
+      const bool admits =
+          !C.ready.empty() && std::any_of(C.owner.begin(), C.owner.end(), [](int o) { return o < 0; });
+      if (C.running && admits) {
+        // the control blocks are written between runs
+        spff_status st = collect(C);
         if (st != SPFF_OK) return st;
-        dirty = true;
       }
-      if (dirty)
-        HIP_TRY(hipMemcpyAsync(e->d_ctl(), e->host_ctl, sizeof(SlotCtl) * e->S, hipMemcpyHostToDevice, C.stream));
-      bool launched;
-      int k;
-      spff_status st = launch_block(e, &launched, &k);
-      if (st != SPFF_OK) return st;
-      if (!launched) continue;
-      HIP_TRY(hipMemcpyAsync(e->host_ctl, e->d_ctl(), sizeof(SlotCtl) * e->S, hipMemcpyDeviceToHost, C.stream));
-      HIP_TRY(hipEventRecord(C.done_ev, C.stream));
-      C.inflight = true;
+      if (!C.running) {
+        for (int s = 0; s < e->S && !C.ready.empty(); ++s) {
+          if (C.owner[s] >= 0) continue;
+          const int id = C.ready.front();
+          C.ready.pop_front();
+          spff_status st = class_admit(sv, C, s, id);
+          if (st != SPFF_OK) return st;
+        }
+        spff_status st = run_begin(e);
+        if (st != SPFF_OK) return st;
+        C.running = true;
+      }
+      while (!e->listed.empty() && (int)e->ahead.size() <= blocks_ahead(e)) {
+        spff_status st = enqueue_run_block(e);
+        if (st != SPFF_OK) return st;
+      }
       any = true;
     }
     if (!any) break;
-    // 2. collect finished requests; a request completes when the host has
-    // seen the end of its class's tick block
-    for (SrvClass& C : sv->classes) {
-      if (!C.inflight) continue;
-      HIP_TRY(hipEventSynchronize(C.done_ev));
-      const double t = now_ms();
-      C.inflight = false;
-      spff_problem* e = C.eng;
-      for (int s = 0; s < e->S; ++s) {
-        const int id = C.owner[s];
-        if (id < 0 || e->host_ctl[s].phase != PH_IDLE) continue;
-        SrvProblem& P = sv->probs[id];
-        spff_step_stats o;
-        fill_stats(e->n(), e->host_ctl[s], o, t - P.t_submit);
-        P.dt = e->host_ctl[s].dt;
-        P.ne_flag = e->host_ctl[s].ne_flag;
-        sv->done[P.ticket] = o;
-        sv->live.erase(P.ticket);
-        P.running = false;
-        C.owner[s] = -1;
-        ++done_count;
-        if (!P.queue.empty()) C.ready.push_back(id);
+    // 2. wait for the end of some class's block -- not for the slowest class:
+    // a class of small grids runs as many blocks as fit beside one block of
+    // a large one -- and collect the requests that finished
+    for (unsigned spin = 1, seen = 0; !seen; ++spin) {
+      for (SrvClass& C : sv->classes) {
+        if (!C.running) continue;
+        spff_problem* e = C.eng;
+        if (e->ahead.empty() || !run_seen(e)) {
+          if (spin % 4096 == 0 && !e->ahead.empty()) {
+            const hipError_t q = hipStreamQuery(C.stream);
+            if (q != hipErrorNotReady && !run_seen(e))
+              return fail(SPFF_E_DEVICE, "tick block failed: %s", hipGetErrorString(q));
+          }
+          if (!e->ahead.empty()) continue;
+        } else {
+          const size_t before = e->listed.size();
+          run_retire(e);
+          if (e->listed.size() == before) {
+            seen = 1;
+            continue;
+          }
+        }
+        spff_status st = collect(C);
+        if (st != SPFF_OK) return st;
+        seen = 1;
       }
     }
   }
@@ -1793,7 +2029,6 @@ spff_status spff_server_destroy(spff_server* sv) {
   for (SrvClass& C : sv->classes) {
     if (C.stream) (void)hipStreamSynchronize(C.stream);
     if (C.eng) spff_destroy_problem(C.eng);
-    if (C.done_ev) (void)hipEventDestroy(C.done_ev);
     if (C.stream) (void)hipStreamDestroy(C.stream);
   }
   if (sv->setup) (void)hipStreamDestroy(sv->setup);

@@ -32,8 +32,10 @@
 // reads block (i & 1), the group of row block 0 writes the advanced one to
 // block ((i + 1) & 1), which the column kernel of tick i reads.  Ticks
 // contain no host round trip, so blocks of ticks can be replayed as a
-// captured HIP graph; the host polls phases between blocks (the closing
-// kernel leaves the current block in buffer 0).
+// captured HIP graph.  The row kernel of a tick posts the slot's progress
+// to pinned host memory, which the host watches while later blocks are
+// already enqueued; a closing kernel after the last block leaves the current
+// control blocks in buffer 0 and in the host's mirror.
 #pragma once
 #include <stdint.h>
 
@@ -106,6 +108,9 @@ struct SlotCtl {
   int32_t inv, pad1;                // phase that the row kernel finishes before it starts `phase` (0: none)
   uint64_t t_start;                 // device wall clock at the start of the step
   int32_t ticks, status;
+  // row kernels the slot has been through since the host wrote the block, and
+  // the first of them that found it idle (0: none): what is posted to the host
+  uint32_t tick_no, idle_at;
   double eps_bar[3];
   // mechanics
   double mech_ref, mech_target, mech_res, rr, inner_tol, alpha_m, beta_m;

@@ -630,6 +630,8 @@ struct CtrlArgs {
   double* prof;
   SlotSeq* seqs;
   StepRec* recs;
+  unsigned long long* post;  // progress word per slot in pinned host memory, or null
+  SlotCtl* mirror;           // host mirror of the control blocks (closing kernel), or null
   int ngc;
 };
 
@@ -701,7 +703,15 @@ __device__ __forceinline__ void tick_control(int s, bool writer, const CtrlArgs&
     if (lc.pending)
       ctrl_slot<real>(s, ptrs, prms, lc, writer, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc);
     // the slot's controller step after this tick is pending if it works
-    if (threadIdx.x == 0) lc.pending = lc.phase != PH_IDLE ? 1 : 0;
+    if (threadIdx.x == 0) {
+      lc.pending = lc.phase != PH_IDLE ? 1 : 0;
+      const uint32_t no = ++lc.tick_no;
+      if (lc.phase == PH_IDLE && lc.idle_at == 0) lc.idle_at = no;
+      // one word, so that the host needs no ordering between two
+      if (writer && A.post)
+        __hip_atomic_store(A.post + s, ((unsigned long long)lc.idle_at << 32) | no, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
   also();
   __syncthreads();
@@ -2201,10 +2211,9 @@ __global__ __launch_bounds__(THREADS) void k_colr(const int* __restrict__ list, 
   kt_end(T.kt);
 }
 
-// Closing kernel of a block of ticks: the controller step of the last tick,
-// one work-group per listed slot, from A.ctl_in into A.ctl_out (buffer 0,
-// possibly the same block), so that the host reads every slot's current
-// block in buffer 0.  With timers on, the second wavefront of group 0 folds
+// Closing kernel of a run of ticks: the controller step of the last tick,
+// one work-group per listed slot (list null: every slot), from A.ctl_in into
+// A.ctl_out (buffer 0, possibly the same block) and the host's mirror.  With timers on, the second wavefront of group 0 folds
 // the last tick's kernel times meanwhile.
 template <typename real>
 __global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
@@ -2213,7 +2222,7 @@ __global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, con
   constexpr int NW = (int)(sizeof(SlotCtl) / sizeof(int));
   __shared__ SlotCtl lc;
   const unsigned long long t_close = wall_clock64();
-  const int s = list[blockIdx.x];
+  const int s = list ? list[blockIdx.x] : (int)blockIdx.x;
   int* w = reinterpret_cast<int*>(&lc);
   if (s >= 0) {
     const int* src = reinterpret_cast<const int*>(A.ctl_in + s);
@@ -2232,7 +2241,11 @@ __global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, con
   __syncthreads();
   if (s >= 0) {
     int* out = reinterpret_cast<int*>(A.ctl_out + s);
-    for (int i = threadIdx.x; i < NW; i += blockDim.x) out[i] = w[i];
+    int* host = A.mirror ? reinterpret_cast<int*>(A.mirror + s) : nullptr;
+    for (int i = threadIdx.x; i < NW; i += blockDim.x) {
+      out[i] = w[i];
+      if (host) host[i] = w[i];
+    }
   }
 }
 
@@ -2303,6 +2316,8 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
   A.prof = B.prof;
   A.seqs = B.seqs;
   A.recs = B.recs;
+  A.post = B.post;
+  A.mirror = nullptr;
   A.ngc = G.ngc;
   const int* list = B.list;
   const SlotPtr<real>* ptrs = B.ptrs;
@@ -2382,7 +2397,7 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
 }
 
 template <typename real>
-hipError_t launch_close(const LaunchGeom& G, const TickBufs<real>& B, int k, hipStream_t st) {
+hipError_t launch_close(const LaunchGeom& G, const TickBufs<real>& B, int k, hipStream_t st, int slots) {
   // after ticks 0..k-1 the latest control blocks are in buffer (k & 1)
   const int last = (k - 1) & 1;
   CtrlArgs A;
@@ -2393,9 +2408,11 @@ hipError_t launch_close(const LaunchGeom& G, const TickBufs<real>& B, int k, hip
   A.prof = B.prof;
   A.seqs = B.seqs;
   A.recs = B.recs;
+  A.post = nullptr;
+  A.mirror = B.mirror;
   A.ngc = G.ngc;
-  hipLaunchKernelGGL(k_close<real>, dim3(G.S), dim3(128), 0, st, B.list, B.ptrs, B.prms, A, G.nx, G.ny, G.ngr,
-                     B.kt ? B.kt + 3 * last : nullptr, B.ktsum);
+  hipLaunchKernelGGL(k_close<real>, dim3(slots > 0 ? slots : G.S), dim3(128), 0, st, slots > 0 ? nullptr : B.list,
+                     B.ptrs, B.prms, A, G.nx, G.ny, G.ngr, B.kt ? B.kt + 3 * last : nullptr, B.ktsum);
   return hipGetLastError();
 }
 
@@ -2422,8 +2439,8 @@ hipError_t launch_fields(const SlotPtr<real>* ptrs, const SlotParam* prms, const
 
 template hipError_t launch_tick<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t, bool);
 template hipError_t launch_tick<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t, bool);
-template hipError_t launch_close<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t);
-template hipError_t launch_close<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t);
+template hipError_t launch_close<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t, int);
+template hipError_t launch_close<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t, int);
 template hipError_t launch_validate<float>(const float*, size_t, double, double, double, unsigned int*,
                                            hipStream_t);
 template hipError_t launch_validate<double>(const double*, size_t, double, double, double, unsigned int*,

@@ -38,21 +38,24 @@ struct TickBufs {
   double* prof;               // per-slot byte counters, or null
   SlotSeq* seqs;              // device load-step queues, or null
   StepRec* recs;
+  unsigned long long* post;   // progress words in pinned host memory, or null
+  SlotCtl* mirror;            // host mirror of the control blocks, or null
   KTime* kt;                  // six timers (two ticks x three parts), or null
   unsigned long long* ktsum;  // folded times
 };
 
-// Tick i (0-based) of a block of ticks over the listed slots.  Tick 0 reads
+// Tick i (0-based) of a run of ticks over the listed slots.  Tick 0 reads
 // ctl[0], whose blocks must have no controller step pending (as the host
 // and launch_close leave them).  row_only: the row kernel alone, which
 // finishes the phase of tick i - 1.
 template <typename real>
 hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st, bool row_only = false);
 
-// Closes a block of k ticks: the controller step of tick k - 1, leaving
-// every listed slot's control block in ctl[0].
+// Closes a run of k ticks under one geometry: the controller step of tick
+// k - 1, leaving the control blocks of the listed slots (slots > 0: of all
+// `slots` slots) in ctl[0] and the mirror.
 template <typename real>
-hipError_t launch_close(const LaunchGeom& G, const TickBufs<real>& B, int k, hipStream_t st);
+hipError_t launch_close(const LaunchGeom& G, const TickBufs<real>& B, int k, hipStream_t st, int slots = 0);
 
 template <typename real>
 hipError_t launch_validate(const real* a, size_t n, double lo_excl, double lo_incl, double hi_incl,

@@ -103,7 +103,7 @@ FFT_LDS, FFT_REG, FFT_REG4 = 1, 2, 3
 
 
 class Plan(ctypes.Structure):
-    """spff_plan: launch plan of the three FFT kernels for one bucket."""
+    """spff_plan: launch plan of the FFT kernels for one bucket."""
     _fields_ = [("row_kind", ctypes.c_int32), ("rows", ctypes.c_int32), ("row_threads", ctypes.c_int32),
                 ("col_kind", ctypes.c_int32), ("cols", ctypes.c_int32), ("col_threads", ctypes.c_int32)]
 

@@ -39,3 +39,31 @@ def test_fp64_register_kernels_match_oracle_and_lds_kernels(nx, ny, B):
         again = p.apply_operator(op, xt if op != spff.OP_NEG_LAPLACIAN else xt[:, 0]).cpu().numpy()
         assert rel_l2(again, g) < 1e-12
     p.close()
+
+
+@pytest.mark.parametrize("K,graph", [(1, 0), (2, 0), (3, 1), (32, 0), (32, 1)])
+def test_blocks_in_flight_give_the_problems_alone(K, graph):
+    """Blocks of ticks are enqueued ahead of the host's checks; problems of a
+    batch finish at different times, so that the bucket (launch size) shrinks
+    while blocks are in flight.  With the plan fixed, every problem's steps
+    are bit for bit those of the problem alone, at any block length."""
+    import torch
+    n, B = 64, 5
+    E = np.stack([si.young_modulus(n, 3.0, 0.05 + 0.06 * b, 90 + b) for b in range(B)])
+    ramp = si.uniaxial_ramp(12, 0.2, 2.0)[4:7]
+    kw = dict(at=2, plan_rows=2, plan_cols=2)
+    p = spff.Problem(torch.from_numpy(E).to(device()), cfg_for(n, use_graph=graph, ticks_per_sync=K, **kw))
+    _, stats = p.run_sequence(ramp)
+    f = p.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+    ticks = [sum(s["ticks"] for s in row) for row in stats]
+    assert len(set(ticks)) > 1  # they do not finish together
+    for b in range(B):
+        q = spff.Problem(torch.from_numpy(E[b]).to(device()), cfg_for(n, **kw))
+        alone = [q.load_step(e)[1][0] for e in ramp]
+        g = q.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+        for k in f:
+            assert torch.equal(f[k][b], g[k][0]), (b, k)
+        for s, a in zip(stats[b], alone):
+            assert all(s[k] == a[k] for k in ("cg_iters", "bccg_iters", "am_iters", "ticks", "F_e", "F_f"))
+        q.close()
+    p.close()
