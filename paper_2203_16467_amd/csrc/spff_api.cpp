@@ -64,7 +64,8 @@ inline bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 struct Layout {
   // ctl: two control blocks per slot (ticks alternate; the host uses the
   // first); prow: two halves of row partials (ticks alternate)
-  size_t ctl, prm, ptr, twx, twy, prow, prow1, pcol, list, bad, prof, seq, rec, kt, ktsum;
+  // op*: control blocks, pointers and list of a diagnostic operator
+  size_t ctl, prm, ptr, twx, twy, prow, prow1, pcol, list, bad, prof, seq, rec, kt, ktsum, octl, optr, olist;
   size_t slot0, slot_bytes;
   // offsets inside a slot
   size_t E, phi, phi_ref, eps, theta, rm, pm, spec;
@@ -351,6 +352,9 @@ Layout layout(const spff_config* c, int S, size_t rsize, bool scratch_only = fal
   L.kt = take(sizeof(KTime) * 6);
   L.ktsum = take(sizeof(unsigned long long) * 8);
   L.rec = take(sizeof(StepRec) * SEQ_MAX * S);
+  L.octl = take(2 * sizeof(SlotCtl) * S);
+  L.optr = take(sizeof(SlotPtr<double>) * S);
+  L.olist = take(sizeof(int32_t) * S);
   L.slot0 = off;
   size_t so = 0;
   auto stake = [&](size_t bytes) {
@@ -398,6 +402,8 @@ struct spff_problem {
   SlotCtl* host_ctl;  // pinned mirror (S blocks), and a second copy for run_begin()'s upload
   // progress words that the row kernels post (pinned), see run_slots()
   unsigned long long* host_post = nullptr;
+  unsigned* host_refused = nullptr;  // pinned: whether the last state given was refused
+  unsigned state_token = 0;
   // pinned staging of the step queues and their records (allocated by the
   // first call that queues more than one step)
   SlotSeq* host_seq = nullptr;
@@ -471,13 +477,36 @@ hipError_t enqueue_block(spff_problem* p, int t0, int k, hipStream_t st, int b) 
   return hipSuccess;
 }
 
-// one tick of a diagnostic phase and the row kernel that finishes it (the
-// caller restores the control blocks)
+int bucket_for(const spff_problem* p, int nactive) {
+  int b = 0;
+  while (p->bucket_size[b] < nactive) ++b;
+  return b;
+}
+
+// Diagnostic operator `phase` over slots s0 .. s0 + count - 1: one tick and
+// the row kernel that finishes it, on control blocks, pointers and a list of
+// its own (the slots' are left alone).  in, out: see launch_op_setup().
 template <typename real>
-hipError_t enqueue_operator(spff_problem* p, hipStream_t st, int b) {
-  const TickBufs<real> B = tick_bufs<real>(p);
-  hipError_t e = launch_tick<real>(p->geoms[b], B, 0, st);
-  return e != hipSuccess ? e : launch_tick<real>(p->geoms[b], B, 1, st, true);
+hipError_t enqueue_operator(spff_problem* p, int phase, int s0, int count, const void* in, size_t in_stride, void* out,
+                            size_t out_stride) {
+  const int b = bucket_for(p, count);
+  TickBufs<real> B = tick_bufs<real>(p);
+  SlotCtl* ctl = reinterpret_cast<SlotCtl*>(p->ws + p->L.octl);
+  SlotPtr<real>* ptr = reinterpret_cast<SlotPtr<real>*>(p->ws + p->L.optr);
+  int32_t* list = reinterpret_cast<int32_t*>(p->ws + p->L.olist);
+  hipError_t e = launch_op_setup<real>(list, ctl, ptr, B.ptrs, s0, count, p->bucket_size[b], phase, in, in_stride, out,
+                                       out_stride, p->stream);
+  if (e != hipSuccess) return e;
+  B.list = list;
+  B.ptrs = ptr;
+  B.ctl[0] = ctl;
+  B.ctl[1] = ctl + p->S;
+  B.post = nullptr;
+  B.prof = nullptr;
+  B.kt = nullptr;
+  B.ktsum = nullptr;
+  e = launch_tick<real>(p->geoms[b], B, 0, p->stream);
+  return e != hipSuccess ? e : launch_tick<real>(p->geoms[b], B, 1, p->stream, true);
 }
 
 hipError_t enqueue_ticks(spff_problem* p, int t0, int k, hipStream_t st, int b) {
@@ -548,15 +577,9 @@ spff_status set_list(spff_problem* p, const std::vector<int32_t>& active, int b)
   int32_t* stage = p->host_list + (size_t)p->list_at * p->S;
   p->list_at = (p->list_at + 1) % LIST_RING;
   std::copy(lst.begin(), lst.end(), stage);
-  HIP_TRY(hipMemcpyAsync(p->d_list(), stage, sizeof(int32_t) * lst.size(), hipMemcpyHostToDevice, p->stream));
+  HIP_TRY(launch_upload(stage, p->d_list(), sizeof(int32_t) * lst.size(), p->stream));
   p->cur_list.swap(lst);
   return SPFF_OK;
-}
-
-int bucket_for(const spff_problem* p, int nactive) {
-  int b = 0;
-  while (p->bucket_size[b] < nactive) ++b;
-  return b;
 }
 
 // Runs blocks of ticks_per_sync ticks until every slot is idle, with a
@@ -644,7 +667,7 @@ spff_status run_begin(spff_problem* p) {
     if (c.phase != PH_IDLE) p->listed.push_back(s);
   }
   std::copy(p->host_ctl, p->host_ctl + p->S, p->host_ctl + p->S);
-  HIP_TRY(hipMemcpyAsync(p->d_ctl(), p->host_ctl, 2 * sizeof(SlotCtl) * p->S, hipMemcpyHostToDevice, p->stream));
+  HIP_TRY(launch_upload(p->host_ctl, p->d_ctl(), 2 * sizeof(SlotCtl) * p->S, p->stream));
   return SPFF_OK;
 }
 
@@ -784,7 +807,6 @@ SlotParam make_param(const spff_config* c) {
 template <typename real>
 spff_status init_device(spff_problem* p, const void* E_dev, const void* phi_init_dev) {
   const size_t n = p->n();
-  const size_t rb = sizeof(real) * n;
   static_assert(sizeof(SlotPtr<real>) == sizeof(SlotPtr<double>), "pointer tables differ");
   p->host_ptrs.assign(p->S, SlotPtr<double>{});
   for (int s = 0; s < p->S; ++s) {
@@ -815,38 +837,17 @@ spff_status init_device(spff_problem* p, const void* E_dev, const void* phi_init
 
   HIP_TRY(hipMemsetAsync(p->d_seq(), 0, sizeof(SlotSeq) * p->S, p->stream));
   if (p->scratch_only) {
-    for (int s = 0; s < p->S; ++s) {
-      unsigned char* b = p->slot(s);
-      HIP_TRY(hipMemsetAsync(b + p->L.theta, 0, 9 * rb, p->stream));
-    }
+    HIP_TRY(launch_init<real>(p->slot(0) + p->L.theta, p->L.slot_bytes, nullptr, nullptr, p->S, (int)n, 9, nullptr,
+                              p->stream));
     HIP_TRY(hipStreamSynchronize(p->stream));
     return SPFF_OK;
   }
-  // inputs and zeroed state
+  // inputs and zeroed state and scratch: E, phi, phi_ref, eps*, theta, r and p
+  // follow one another in a slot
   unsigned int* bad = reinterpret_cast<unsigned int*>(p->ws + p->L.bad);
-  HIP_TRY(hipMemsetAsync(bad, 0, 2 * sizeof(unsigned int), p->stream));
-  for (int s = 0; s < p->S; ++s) {
-    unsigned char* b = p->slot(s);
-    HIP_TRY(hipMemcpyAsync(b + p->L.E, static_cast<const unsigned char*>(E_dev) + s * rb, rb,
-                           hipMemcpyDeviceToDevice, p->stream));
-    HIP_TRY(hipMemsetAsync(b + p->L.eps, 0, 3 * rb, p->stream));
-    HIP_TRY(hipMemsetAsync(b + p->L.theta, 0, 3 * rb, p->stream));
-    HIP_TRY(hipMemsetAsync(b + p->L.rm, 0, 3 * rb, p->stream));
-    HIP_TRY(hipMemsetAsync(b + p->L.pm, 0, 3 * rb, p->stream));
-    if (phi_init_dev) {
-      const unsigned char* src = static_cast<const unsigned char*>(phi_init_dev) + s * rb;
-      HIP_TRY(hipMemcpyAsync(b + p->L.phi, src, rb, hipMemcpyDeviceToDevice, p->stream));
-      HIP_TRY(hipMemcpyAsync(b + p->L.phi_ref, src, rb, hipMemcpyDeviceToDevice, p->stream));
-    } else {
-      HIP_TRY(hipMemsetAsync(b + p->L.phi, 0, rb, p->stream));
-      HIP_TRY(hipMemsetAsync(b + p->L.phi_ref, 0, rb, p->stream));
-    }
-    HIP_TRY(launch_validate<real>(reinterpret_cast<const real*>(b + p->L.E), n, 0.0, -1e300, 1e300, bad,
-                                  p->stream));
-    if (phi_init_dev)
-      HIP_TRY(launch_validate<real>(reinterpret_cast<const real*>(b + p->L.phi), n, -1e300, 0.0, 1.0, bad + 1,
-                                    p->stream));
-  }
+  HIP_TRY(hipMemsetAsync(bad, 0, 64, p->stream));
+  HIP_TRY(launch_init<real>(p->slot(0) + p->L.E, p->L.slot_bytes, E_dev, phi_init_dev, p->S, (int)n, 15, bad,
+                            p->stream));
   unsigned int hbad[2] = {0, 0};
   HIP_TRY(hipMemcpyAsync(hbad, bad, sizeof(hbad), hipMemcpyDeviceToHost, p->stream));
   HIP_TRY(hipStreamSynchronize(p->stream));
@@ -924,41 +925,42 @@ double now_ms() {
   return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
 }
 
-// One diagnostic tick (PH_X_PROJ, PH_X_LAP or PH_X_DISP) over the slots
-// `slots`: copies pin planes from src(s) into the slot's theta planes, runs
-// the tick with the plan of the slot count's bucket, copies pout planes of
-// rm to dst(s), and restores the control blocks (step statistics stay
-// readable).  Every listed slot must be idle.
-template <typename Src, typename Dst>
-spff_status run_diag(spff_problem* p, int phase, const std::vector<int32_t>& slots, int pin, int pout, Src src,
-                     Dst dst) {
+// Diagnostic operator `phase` over slots s0 .. s0 + count - 1: pin planes from
+// src (src_stride bytes per slot) to pout planes of dst.  The kernels read and
+// write the buffers themselves where they are aligned to a pixel pair;
+// otherwise copies through the slots' scratch stand between.  Every slot
+// must be idle.  The caller synchronises the stream.
+spff_status run_diag(spff_problem* p, int phase, int s0, int count, int pin, int pout, const unsigned char* src,
+                     size_t src_stride, unsigned char* dst) {
   const size_t rb = p->rsize * p->n();
-  for (int s : slots)
+  for (int s = s0; s < s0 + count; ++s)
     if (p->host_ctl[s].phase != PH_IDLE) return fail(SPFF_E_BUSY, "slot %d is not idle", s);
-  if (slots.empty()) return SPFF_OK;
-  for (int s : slots)
-    HIP_TRY(hipMemcpyAsync(p->slot(s) + p->L.theta, src(s), pin * rb, hipMemcpyDeviceToDevice, p->stream));
-  std::vector<SlotCtl> saved(p->host_ctl, p->host_ctl + p->S);
-  for (int s : slots) p->host_ctl[s].phase = phase;
-  HIP_TRY(hipMemcpyAsync(p->d_ctl(), p->host_ctl, sizeof(SlotCtl) * p->S, hipMemcpyHostToDevice, p->stream));
-  const int b = bucket_for(p, (int)slots.size());
-  spff_status lst = set_list(p, slots, b);
-  if (lst != SPFF_OK) return lst;
-  const bool prof = p->prof_on;
-  p->prof_on = false;
-  hipError_t e = p->cfg.precision == SPFF_FP64 ? enqueue_operator<double>(p, p->stream, b)
-                                               : enqueue_operator<float>(p, p->stream, b);
-  p->prof_on = prof;
+  const uintptr_t pair = 2 * p->rsize;
+  const bool in_place = reinterpret_cast<uintptr_t>(src) % pair == 0, out_place = reinterpret_cast<uintptr_t>(dst) % pair == 0;
+  if (!in_place)
+    for (int j = 0; j < count; ++j)
+      HIP_TRY(hipMemcpyAsync(p->slot(s0 + j) + p->L.theta, src + j * src_stride, pin * rb, hipMemcpyDeviceToDevice,
+                             p->stream));
+  const void* in = in_place ? src : nullptr;
+  void* out = out_place ? dst : nullptr;
+  const size_t is = src_stride / p->rsize, os = pout * p->n();
+  const hipError_t e = p->cfg.precision == SPFF_FP64 ? enqueue_operator<double>(p, phase, s0, count, in, is, out, os)
+                                                     : enqueue_operator<float>(p, phase, s0, count, in, is, out, os);
   if (e != hipSuccess) return fail(SPFF_E_DEVICE, "operator launch failed: %s", hipGetErrorString(e));
-  for (int s : slots)
-    HIP_TRY(hipMemcpyAsync(dst(s), p->slot(s) + p->L.rm, pout * rb, hipMemcpyDeviceToDevice, p->stream));
-  // the pinned mirror is the source of the pending upload above: wait before
-  // reusing it, then restore the control blocks
-  HIP_TRY(hipStreamSynchronize(p->stream));
-  std::copy(saved.begin(), saved.end(), p->host_ctl);
-  HIP_TRY(hipMemcpyAsync(p->d_ctl(), p->host_ctl, sizeof(SlotCtl) * p->S, hipMemcpyHostToDevice, p->stream));
-  HIP_TRY(hipStreamSynchronize(p->stream));
+  if (!out_place)
+    for (int j = 0; j < count; ++j)
+      HIP_TRY(hipMemcpyAsync(dst + j * pout * rb, p->slot(s0 + j) + p->L.rm, pout * rb, hipMemcpyDeviceToDevice,
+                             p->stream));
   return SPFF_OK;
+}
+
+// out: buffers in the bit order of SPFF_FIELD_*
+template <typename real>
+hipError_t enqueue_fields(spff_problem* p, int s0, int count, void* const* out) {
+  auto at = [&](int f) { return static_cast<real*>(out[f]); };
+  const FieldOut<real> O = {at(0), at(1), at(2), at(3), at(4), at(5)};
+  return launch_fields<real>(reinterpret_cast<const SlotPtr<real>*>(p->d_ptr()), p->d_prm(), p->d_ctl(), s0, count,
+                             (int)p->n(), O, p->stream);
 }
 
 }  // namespace
@@ -1075,7 +1077,8 @@ spff_status engine_create(const spff_config* cfg, int32_t nbatch, const void* E_
       hipHostMalloc(reinterpret_cast<void**>(&p->host_list), sizeof(int32_t) * nbatch * LIST_RING,
                     hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&p->host_post), sizeof(unsigned long long) * nbatch,
-                    hipHostMallocDefault) != hipSuccess)
+                    hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&p->host_refused), sizeof(unsigned), hipHostMallocDefault) != hipSuccess)
     return cleanup(fail(SPFF_E_DEVICE, "pinned host allocation failed"));
   for (int s = 0; s < nbatch; ++s) reset_ctl(p, s);
   st = cfg->precision == SPFF_FP64 ? init_device<double>(p, E_dev, phi_init_dev)
@@ -1306,7 +1309,6 @@ spff_status spff_get_fields(spff_problem* p, int32_t index, uint32_t mask, void*
   if (index < -1 || index >= p->S) return fail(SPFF_E_INVALID, "index out of range");
   if (mask & ~0x7Fu) return fail(SPFF_E_INVALID, "unknown field bits");
   if (mask && !dst) return fail(SPFF_E_INVALID, "dst is NULL");
-  const size_t n = p->n(), rb = p->rsize * n;
   const int s0 = index < 0 ? 0 : index, s1 = index < 0 ? p->S : index + 1;
   int k = 0;
   void* out[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -1315,37 +1317,16 @@ spff_status spff_get_fields(spff_problem* p, int32_t index, uint32_t mask, void*
       if (!dst[k]) return fail(SPFF_E_INVALID, "dst[%d] is NULL", k);
       out[b] = dst[k++];
     }
-  const size_t planes[7] = {1, 1, 3, 3, 1, 3, 2};
   if (out[6]) {
-    // displacement u* of eps*: one diagnostic tick over the selected slots
-    std::vector<int32_t> sl;
-    for (int s = s0; s < s1; ++s) sl.push_back(s);
-    spff_status st = run_diag(
-        p, PH_X_DISP, sl, 3, 2, [&](int s) { return static_cast<const unsigned char*>(p->slot(s) + p->L.eps); },
-        [&](int s) { return static_cast<unsigned char*>(out[6]) + (size_t)(s - s0) * 2 * rb; });
+    // displacement u* of eps*
+    spff_status st = run_diag(p, PH_X_DISP, s0, s1 - s0, 3, 2, p->slot(s0) + p->L.eps, p->L.slot_bytes,
+                              static_cast<unsigned char*>(out[6]));
     if (st != SPFF_OK) return st;
   }
-  for (int s = s0; s < s1; ++s) {
-    const int j = s - s0;
-    unsigned char* b = p->slot(s);
-    auto at = [&](int f) { return static_cast<unsigned char*>(out[f]) + (size_t)j * planes[f] * rb; };
-    if (out[0]) HIP_TRY(hipMemcpyAsync(at(0), b + p->L.phi, rb, hipMemcpyDeviceToDevice, p->stream));
-    if (out[1]) HIP_TRY(hipMemcpyAsync(at(1), b + p->L.phi_ref, rb, hipMemcpyDeviceToDevice, p->stream));
-    if (out[5]) HIP_TRY(hipMemcpyAsync(at(5), b + p->L.eps, 3 * rb, hipMemcpyDeviceToDevice, p->stream));
-    if (out[2] || out[3] || out[4]) {
-      hipError_t e;
-      if (p->cfg.precision == SPFF_FP64)
-        e = launch_fields<double>(reinterpret_cast<const SlotPtr<double>*>(p->d_ptr()), p->d_prm(), p->d_ctl(), s,
-                                  (int)n, reinterpret_cast<double*>(out[2] ? at(2) : nullptr),
-                                  reinterpret_cast<double*>(out[3] ? at(3) : nullptr),
-                                  reinterpret_cast<double*>(out[4] ? at(4) : nullptr), p->stream);
-      else
-        e = launch_fields<float>(reinterpret_cast<const SlotPtr<float>*>(p->d_ptr()), p->d_prm(), p->d_ctl(), s,
-                                 (int)n, reinterpret_cast<float*>(out[2] ? at(2) : nullptr),
-                                 reinterpret_cast<float*>(out[3] ? at(3) : nullptr),
-                                 reinterpret_cast<float*>(out[4] ? at(4) : nullptr), p->stream);
-      if (e != hipSuccess) return fail(SPFF_E_DEVICE, "field kernel failed: %s", hipGetErrorString(e));
-    }
+  if (mask & ~(uint32_t)SPFF_FIELD_DISP) {
+    const hipError_t e = p->cfg.precision == SPFF_FP64 ? enqueue_fields<double>(p, s0, s1 - s0, out)
+                                                       : enqueue_fields<float>(p, s0, s1 - s0, out);
+    if (e != hipSuccess) return fail(SPFF_E_DEVICE, "field kernel failed: %s", hipGetErrorString(e));
   }
   HIP_TRY(hipStreamSynchronize(p->stream));
   return SPFF_OK;
@@ -1353,17 +1334,24 @@ spff_status spff_get_fields(spff_problem* p, int32_t index, uint32_t mask, void*
 
 size_t spff_state_bytes(const spff_problem* p) { return p ? (size_t)p->S * 5 * p->rsize * p->n() : 0; }
 
+// All slots' state from `in` (refused as a whole if a value is not finite:
+// host_refused) or to `out`.
+static hipError_t move_state(spff_problem* p, const void* in, void* out) {
+  // the flag word is compared with a new token each time, never cleared
+  unsigned* flag = reinterpret_cast<unsigned*>(p->ws + p->L.bad) + 8;
+  const unsigned token = in ? ++p->state_token : 0u;
+  const Layout& L = p->L;
+  return p->cfg.precision == SPFF_FP64
+             ? launch_state<double>(p->slot(0), L.slot_bytes, L.eps, L.phi, L.phi_ref, p->S, (int)p->n(), in, out, flag,
+                                    token, p->host_refused, p->stream)
+             : launch_state<float>(p->slot(0), L.slot_bytes, L.eps, L.phi, L.phi_ref, p->S, (int)p->n(), in, out, flag,
+                                   token, p->host_refused, p->stream);
+}
+
 spff_status spff_get_state(spff_problem* p, void* dst_dev, double* eps_bar_host) {
   if (!p) return fail(SPFF_E_INVALID, "problem is NULL");
   if (!dst_dev) return fail(SPFF_E_INVALID, "dst is NULL");
-  const size_t rb = p->rsize * p->n();
-  for (int s = 0; s < p->S; ++s) {
-    unsigned char* d = static_cast<unsigned char*>(dst_dev) + (size_t)s * 5 * rb;
-    unsigned char* b = p->slot(s);
-    HIP_TRY(hipMemcpyAsync(d, b + p->L.eps, 3 * rb, hipMemcpyDeviceToDevice, p->stream));
-    HIP_TRY(hipMemcpyAsync(d + 3 * rb, b + p->L.phi, rb, hipMemcpyDeviceToDevice, p->stream));
-    HIP_TRY(hipMemcpyAsync(d + 4 * rb, b + p->L.phi_ref, rb, hipMemcpyDeviceToDevice, p->stream));
-  }
+  HIP_TRY(move_state(p, nullptr, dst_dev));
   HIP_TRY(hipStreamSynchronize(p->stream));
   if (eps_bar_host) std::copy(p->last_eps_bar.begin(), p->last_eps_bar.end(), eps_bar_host);
   return SPFF_OK;
@@ -1375,10 +1363,13 @@ spff_status spff_set_state(spff_problem* p, const void* src_dev, const double* e
   if (eps_bar_host)
     for (int k = 0; k < 3 * p->S; ++k)
       if (!std::isfinite(eps_bar_host[k])) return fail(SPFF_E_INVALID, "eps_bar must be finite");
-  const size_t rb = p->rsize * p->n();
-  // every value finite (checked before anything is copied: an error leaves
-  // the state unchanged)
-  {
+  // every value finite: the check is enqueued before the copy, which it
+  // stops, so that an error leaves the state unchanged
+  volatile unsigned* refused = p->host_refused;
+  *refused = 1u;
+  HIP_TRY(move_state(p, src_dev, nullptr));
+  HIP_TRY(hipStreamSynchronize(p->stream));
+  if (*refused) {
     unsigned int* bad = reinterpret_cast<unsigned int*>(p->ws + p->L.bad);
     const size_t cnt = (size_t)p->S * 5 * p->n();
     HIP_TRY(hipMemsetAsync(bad, 0, sizeof(unsigned int), p->stream));
@@ -1391,23 +1382,16 @@ spff_status spff_set_state(spff_problem* p, const void* src_dev, const double* e
     unsigned int hbad = 0;
     HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(hbad), hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(hipStreamSynchronize(p->stream));
-    if (hbad) return fail(SPFF_E_INVALID, "state has %u non-finite entries", hbad);
-  }
-  for (int s = 0; s < p->S; ++s) {
-    const unsigned char* d = static_cast<const unsigned char*>(src_dev) + (size_t)s * 5 * rb;
-    unsigned char* b = p->slot(s);
-    HIP_TRY(hipMemcpyAsync(b + p->L.eps, d, 3 * rb, hipMemcpyDeviceToDevice, p->stream));
-    HIP_TRY(hipMemcpyAsync(b + p->L.phi, d + 3 * rb, rb, hipMemcpyDeviceToDevice, p->stream));
-    HIP_TRY(hipMemcpyAsync(b + p->L.phi_ref, d + 4 * rb, rb, hipMemcpyDeviceToDevice, p->stream));
+    return fail(SPFF_E_INVALID, "state has %u non-finite entries", hbad);
   }
   if (eps_bar_host) {
     std::copy(eps_bar_host, eps_bar_host + 3 * p->S, p->last_eps_bar.begin());
-  std::fill(p->last_advance.begin(), p->last_advance.end(), 1);
+    std::fill(p->last_advance.begin(), p->last_advance.end(), 1);
     for (int s = 0; s < p->S; ++s)
       for (int k = 0; k < 3; ++k) p->host_ctl[s].eps_bar[k] = eps_bar_host[3 * s + k];
-    HIP_TRY(hipMemcpyAsync(p->d_ctl(), p->host_ctl, sizeof(SlotCtl) * p->S, hipMemcpyHostToDevice, p->stream));
+    HIP_TRY(launch_upload(p->host_ctl, p->d_ctl(), sizeof(SlotCtl) * p->S, p->stream));
+    HIP_TRY(hipStreamSynchronize(p->stream));
   }
-  HIP_TRY(hipStreamSynchronize(p->stream));
   return SPFF_OK;
 }
 
@@ -1419,10 +1403,11 @@ spff_status spff_apply_operator(spff_problem* p, int32_t op, const void* in_dev,
   const int pin = op == SPFF_OP_NEG_LAPLACIAN ? 1 : 3;
   const int pout = op == SPFF_OP_NEG_LAPLACIAN ? 1 : (op == SPFF_OP_DISPLACEMENT ? 2 : 3);
   const int phase = op == SPFF_OP_PROJECT ? PH_X_PROJ : (op == SPFF_OP_DISPLACEMENT ? PH_X_DISP : PH_X_LAP);
-  std::vector<int32_t> all(p->S);
-  for (int s = 0; s < p->S; ++s) all[s] = s;
-  return run_diag(p, phase, all, pin, pout, [&](int s) { return static_cast<const unsigned char*>(in_dev) + (size_t)s * pin * p->rsize * p->n(); },
-                  [&](int s) { return static_cast<unsigned char*>(out_dev) + (size_t)s * pout * p->rsize * p->n(); });
+  spff_status st = run_diag(p, phase, 0, p->S, pin, pout, static_cast<const unsigned char*>(in_dev),
+                            pin * p->rsize * p->n(), static_cast<unsigned char*>(out_dev));
+  if (st != SPFF_OK) return st;
+  HIP_TRY(hipStreamSynchronize(p->stream));
+  return SPFF_OK;
 }
 
 spff_status spff_profile_enable(spff_problem* p, int32_t enable) {
@@ -1522,6 +1507,7 @@ spff_status spff_destroy_problem(spff_problem* p) {
   if (p->host_ctl) (void)hipHostFree(p->host_ctl);
   if (p->host_list) (void)hipHostFree(p->host_list);
   if (p->host_post) (void)hipHostFree(p->host_post);
+  if (p->host_refused) (void)hipHostFree(p->host_refused);
   if (p->host_seq) (void)hipHostFree(p->host_seq);
   if (p->host_rec) (void)hipHostFree(p->host_rec);
   delete p;
@@ -1831,17 +1817,12 @@ spff_status spff_server_register(spff_server* sv, const spff_config* cfg, const 
     sv->used = used0;
     return fail(SPFF_E_NOMEM, "arena full");
   }
-  HIP_TRY(hipMemcpyAsync(P.E, E_dev, rb, hipMemcpyDeviceToDevice, sv->setup));
-  HIP_TRY(hipMemsetAsync(P.phi, 0, rb, sv->setup));
-  HIP_TRY(hipMemsetAsync(P.phi_ref, 0, rb, sv->setup));
-  HIP_TRY(hipMemsetAsync(P.eps, 0, 3 * rb, sv->setup));
   HIP_TRY(hipMemsetAsync(bad, 0, 64, sv->setup));
-  const size_t n = (size_t)cfg->nx * cfg->ny;
+  const int n = cfg->nx * cfg->ny;
+  // E, phi, phi_ref and eps* were taken one after another
   hipError_t e = cfg->precision == SPFF_FP64
-                     ? launch_validate<double>(reinterpret_cast<const double*>(P.E), n, 0.0, -1e300, 1e300,
-                                               reinterpret_cast<unsigned int*>(bad), sv->setup)
-                     : launch_validate<float>(reinterpret_cast<const float*>(P.E), n, 0.0, -1e300, 1e300,
-                                              reinterpret_cast<unsigned int*>(bad), sv->setup);
+                     ? launch_init<double>(P.E, 0, E_dev, nullptr, 1, n, 6, reinterpret_cast<unsigned*>(bad), sv->setup)
+                     : launch_init<float>(P.E, 0, E_dev, nullptr, 1, n, 6, reinterpret_cast<unsigned*>(bad), sv->setup);
   if (e != hipSuccess) return fail(SPFF_E_DEVICE, "validation launch failed: %s", hipGetErrorString(e));
   unsigned int hbad = 0;
   HIP_TRY(hipMemcpyAsync(&hbad, bad, sizeof(hbad), hipMemcpyDeviceToHost, sv->setup));

@@ -17,6 +17,7 @@
 // components; a column kernel work-group owns W consecutive kx columns.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -179,7 +180,7 @@ __device__ __forceinline__ constexpr int op_comps_in(int op, int inv) {
     case RO_ASM_PQ:
     case RO_ASM_WAIT:
     case RO_R_PQ: return 1;
-    case RO_X_OUT: return inv == PH_X_LAP ? 1 : 3;
+    case RO_X_OUT: return inv == PH_X_LAP ? 1 : (inv == PH_X_DISP ? 2 : 3);
     default: return 0;
   }
 }
@@ -2265,36 +2266,191 @@ __global__ void k_validate(const real* __restrict__ a, size_t n, real lo_excl, r
   if (cnt) atomicAdd(bad, cnt);
 }
 
-// Pointwise output fields of one slot (see SPFF_FIELD_*).
+// Whole-handle moves between the slots' planes and the caller's buffers: one
+// launch for all slots (blockIdx.y).  A copy and a kernel per slot and plane
+// cost 8 us of gap each: 1.9 ms to restore and 1.3 ms to read out the state
+// of 64 problems of 512^2 that move in 0.2 ms.  VEC values per access: 16
+// bytes where every caller buffer is aligned to them, else one.
+template <typename real, int VEC>
+struct VecOf {
+  typedef real type __attribute__((ext_vector_type(VEC)));
+};
 template <typename real>
+struct VecOf<real, 1> {
+  typedef real type;
+};
+
+// Slot planes of the resident state.
+template <typename real>
+struct StatePlanes {
+  unsigned char* base;  // slot 0
+  size_t slot_bytes;
+  size_t eps, phi, phi_ref;  // byte offsets in a slot
+  __device__ __forceinline__ real* plane(int s, int k, int n) const {
+    unsigned char* b = base + (size_t)s * slot_bytes;
+    return k < 3 ? reinterpret_cast<real*>(b + eps) + (size_t)k * n
+                 : reinterpret_cast<real*>(b + (k == 3 ? phi : phi_ref));
+  }
+};
+
+// *flag = token if a value is not finite.
+template <typename real>
+__global__ void k_check_finite(const real* __restrict__ a, size_t n, unsigned* __restrict__ flag, unsigned token) {
+  bool bad = false;
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+    bad |= !isfinite(a[i]);
+  if (bad) *flag = token;
+}
+
+// State (eps*[3], phi, phi_ref per slot) in (PUT; not if *flag is token) or
+// out; *refused tells the host which.
+template <typename real, int VEC, bool PUT>
+__global__ void k_state(const StatePlanes<real> P, real* __restrict__ ext, int n, const unsigned* __restrict__ flag,
+                        unsigned token, unsigned* __restrict__ refused) {
+  using V = typename VecOf<real, VEC>::type;
+  const int s = blockIdx.y;
+  if constexpr (PUT) {
+    const bool no = *flag == token;
+    if (blockIdx.x == 0 && s == 0 && threadIdx.x == 0) *refused = no ? 1u : 0u;
+    if (no) return;
+  }
+  for (int k = 0; k < 5; ++k) {
+    V* in = reinterpret_cast<V*>(P.plane(s, k, n));
+    V* out = reinterpret_cast<V*>(ext + ((size_t)s * 5 + k) * n);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n / VEC; i += gridDim.x * blockDim.x) {
+      if constexpr (PUT)
+        in[i] = out[i];
+      else
+        out[i] = in[i];
+    }
+  }
+}
+
+// Output fields (see SPFF_FIELD_*) of slots s0 + blockIdx.y; out[f] null: not
+// asked for.
+template <typename real, int VEC>
 __global__ void k_fields(const SlotPtr<real>* __restrict__ ptrs, const SlotParam* __restrict__ prms,
-                         const SlotCtl* __restrict__ ctls, int slot, int n, real* __restrict__ strain,
-                         real* __restrict__ stress_out, real* __restrict__ psi_out) {
+                         const SlotCtl* __restrict__ ctls, int s0, int n, const FieldOut<real> O) {
+  using V = typename VecOf<real, VEC>::type;
+  const int slot = s0 + blockIdx.y;
   const SlotPtr<real> F = ptrs[slot];
   const SlotParam& P = prms[slot];
   const SlotCtl& C = ctls[slot];
   const real lt = real(P.lam_t), mt = real(P.mu_t), kres = real(P.k_res);
+  const size_t j = blockIdx.y;
+  auto ld = [](const real* p, int i, real* x) {
+    V v = reinterpret_cast<const V*>(p)[i];
+    __builtin_memcpy(x, &v, sizeof(v));
+  };
+  auto st = [](real* p, int i, const real* x) {
+    V v;
+    __builtin_memcpy(&v, x, sizeof(v));
+    reinterpret_cast<V*>(p)[i] = v;
+  };
+  const bool law = O.strain || O.stress || O.psi, need_eps = law || O.eps, need_phi = O.phi || O.stress;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n / VEC; i += gridDim.x * blockDim.x) {
+    real ph[VEC], x[3][VEC];
+    if (need_phi) ld(F.phi, i, ph);
+    if (O.phi) st(O.phi + j * n, i, ph);
+    if (O.phi_ref) {
+      real r[VEC];
+      ld(F.phi_ref, i, r);
+      st(O.phi_ref + j * n, i, r);
+    }
+    if (!need_eps) continue;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      ld(F.eps + (size_t)k * n, i, x[k]);
+      if (O.eps) st(O.eps + (j * 3 + k) * n, i, x[k]);
+    }
+    if (!law) continue;
+    real E[VEC], psi[VEC], sg[3][VEC];
+    if (O.stress || O.psi) ld(F.E, i, E);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) x[k][v] = real(C.eps_bar[k]) + x[k][v];
+      const Sym<real> e = {x[0][v], x[1][v], x[2][v]};
+      if (O.stress || O.psi) {
+        const real lam = lt * E[v], mu = mt * E[v];
+        if (O.stress) {
+          const real hk = (real(1) - ph[v]) * (real(1) - ph[v]) + kres;
+          const Sym<real> t = stress(e, lam, mu, hk, P.contact);
+          sg[0][v] = t.xx;
+          sg[1][v] = t.yy;
+          sg[2][v] = t.xy;
+        }
+        if (O.psi) {
+          real pm;
+          energies(e, lam, mu, P.split, &psi[v], &pm);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (O.strain) st(O.strain + (j * 3 + k) * n, i, x[k]);
+      if (O.stress) st(O.stress + (j * 3 + k) * n, i, sg[k]);
+    }
+    if (O.psi) st(O.psi + j * n, i, psi);
+  }
+}
+
+// Fills nplanes planes of each slot: plane 0 from E (zero without), planes 1
+// and 2 from phi (zero without), the rest with zeros; counts the values of E
+// that are not positive and finite in bad[0], those of phi outside [0, 1] in
+// bad[1].
+template <typename real>
+__global__ void k_init(unsigned char* __restrict__ base, size_t slot_bytes, const real* __restrict__ E,
+                       const real* __restrict__ phi, int n, int nplanes, unsigned* __restrict__ bad) {
+  const int s = blockIdx.y;
+  real* dst = reinterpret_cast<real*>(base + (size_t)s * slot_bytes);
+  unsigned bad_e = 0, bad_p = 0;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const Sym<real> e = {real(C.eps_bar[0]) + F.eps[i], real(C.eps_bar[1]) + F.eps[n + i],
-                         real(C.eps_bar[2]) + F.eps[2 * n + i]};
-    const real E = F.E[i], ph = F.phi[i];
-    const real lam = lt * E, mu = mt * E, hk = (real(1) - ph) * (real(1) - ph) + kres;
-    if (strain) {
-      strain[i] = e.xx;
-      strain[n + i] = e.yy;
-      strain[2 * n + i] = e.xy;
+    real e = 0, f = 0;
+    if (E) {
+      e = E[(size_t)s * n + i];
+      bad_e += (isfinite(e) && e > real(0)) ? 0u : 1u;
     }
-    if (stress_out) {
-      const Sym<real> sg = stress(e, lam, mu, hk, P.contact);
-      stress_out[i] = sg.xx;
-      stress_out[n + i] = sg.yy;
-      stress_out[2 * n + i] = sg.xy;
+    if (phi) {
+      f = phi[(size_t)s * n + i];
+      bad_p += (isfinite(f) && f >= real(0) && f <= real(1)) ? 0u : 1u;
     }
-    if (psi_out) {
-      real pp, pm;
-      energies(e, lam, mu, P.split, &pp, &pm);
-      psi_out[i] = pp;
-    }
+    dst[i] = e;
+    for (int k = 1; k < nplanes; ++k) dst[(size_t)k * n + i] = k < 3 ? f : real(0);
+  }
+  if (bad_e) atomicAdd(bad, bad_e);
+  if (bad_p) atomicAdd(bad + 1, bad_p);
+}
+
+// Words from pinned host memory to the device: a small upload without the
+// gaps of a copy command (8 to 12 us on either side).
+__global__ void k_upload(const int* __restrict__ src, int* __restrict__ dst, int n) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) dst[i] = src[i];
+}
+
+// Sets up a diagnostic operator (phase) over `count` slots from s0, padded
+// to `listed` list entries: list, control blocks and pointer table of its
+// own, with the caller's buffers as the planes it reads (theta) and writes
+// (rm).
+template <typename real>
+__global__ void k_op_setup(int* __restrict__ list, SlotCtl* __restrict__ ctl, SlotPtr<real>* __restrict__ optr,
+                           const SlotPtr<real>* __restrict__ ptrs, int s0, int count, int listed, int phase,
+                           const real* __restrict__ in, size_t in_stride, real* __restrict__ out, size_t out_stride) {
+  const int j = blockIdx.x;
+  if (j >= count) {
+    if (threadIdx.x == 0) list[j] = -1;
+    return;
+  }
+  int* c = reinterpret_cast<int*>(ctl + s0 + j);
+  for (int i = threadIdx.x; i < (int)(sizeof(SlotCtl) / sizeof(int)); i += blockDim.x) c[i] = 0;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    list[j] = s0 + j;
+    ctl[s0 + j].phase = phase;
+    SlotPtr<real> F = ptrs[s0 + j];
+    if (in) F.theta = const_cast<real*>(in) + j * in_stride;
+    if (out) F.rm = out + j * out_stride;
+    optr[s0 + j] = F;
   }
 }
 
@@ -2427,13 +2583,82 @@ hipError_t launch_validate(const real* a, size_t n, double lo_excl, double lo_in
   return hipGetLastError();
 }
 
+namespace {
+// blocks of 256 threads over `count` items per slot, about 4096 in all
+dim3 slot_grid(size_t count, int slots) {
+  size_t bx = (count + 255) / 256;
+  const size_t most = std::max<size_t>(8, 4096 / (size_t)slots);
+  return dim3((unsigned)std::min(bx, most), (unsigned)slots);
+}
 template <typename real>
-hipError_t launch_fields(const SlotPtr<real>* ptrs, const SlotParam* prms, const SlotCtl* ctls, int slot, int n,
-                         real* strain, real* stress_out, real* psi, hipStream_t st) {
-  int blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_fields<real>, dim3(blocks), dim3(256), 0, st, ptrs, prms, ctls, slot, n, strain,
-                     stress_out, psi);
+constexpr int VEC16 = 16 / (int)sizeof(real);
+bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+}  // namespace
+
+template <typename real>
+hipError_t launch_fields(const SlotPtr<real>* ptrs, const SlotParam* prms, const SlotCtl* ctls, int s0, int slots,
+                         int n, const FieldOut<real>& O, hipStream_t st) {
+  const bool wide = aligned16(O.phi) && aligned16(O.phi_ref) && aligned16(O.strain) && aligned16(O.stress) &&
+                    aligned16(O.psi) && aligned16(O.eps);
+  if (wide)
+    hipLaunchKernelGGL((k_fields<real, VEC16<real>>), slot_grid(n / VEC16<real>, slots), dim3(256), 0, st, ptrs, prms,
+                       ctls, s0, n, O);
+  else
+    hipLaunchKernelGGL((k_fields<real, 1>), slot_grid(n, slots), dim3(256), 0, st, ptrs, prms, ctls, s0, n, O);
+  return hipGetLastError();
+}
+
+template <typename real>
+hipError_t launch_state(unsigned char* base, size_t slot_bytes, size_t eps, size_t phi, size_t phi_ref, int slots,
+                        int n, const void* in, void* out, unsigned* flag, unsigned token, unsigned* refused,
+                        hipStream_t st) {
+  const StatePlanes<real> P = {base, slot_bytes, eps, phi, phi_ref};
+  constexpr int V = VEC16<real>;
+  if (in) {
+    const real* a = static_cast<const real*>(in);
+    real* ext = const_cast<real*>(a);  // only read
+    const size_t cnt = (size_t)slots * 5 * n;
+    const size_t blocks = std::min<size_t>((cnt + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_check_finite<real>, dim3((unsigned)blocks), dim3(256), 0, st, a, cnt, flag, token);
+    if (aligned16(in))
+      hipLaunchKernelGGL((k_state<real, V, true>), slot_grid(n / V, slots), dim3(256), 0, st, P, ext, n, flag, token,
+                         refused);
+    else
+      hipLaunchKernelGGL((k_state<real, 1, true>), slot_grid(n, slots), dim3(256), 0, st, P, ext, n, flag, token,
+                         refused);
+  } else {
+    real* ext = static_cast<real*>(out);
+    if (aligned16(out))
+      hipLaunchKernelGGL((k_state<real, V, false>), slot_grid(n / V, slots), dim3(256), 0, st, P, ext, n, flag, token,
+                         refused);
+    else
+      hipLaunchKernelGGL((k_state<real, 1, false>), slot_grid(n, slots), dim3(256), 0, st, P, ext, n, flag, token,
+                         refused);
+  }
+  return hipGetLastError();
+}
+
+template <typename real>
+hipError_t launch_init(unsigned char* base, size_t slot_bytes, const void* E, const void* phi, int slots, int n,
+                       int nplanes, unsigned* bad, hipStream_t st) {
+  hipLaunchKernelGGL(k_init<real>, slot_grid(n, slots), dim3(256), 0, st, base, slot_bytes,
+                     static_cast<const real*>(E), static_cast<const real*>(phi), n, nplanes, bad);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(const void* pinned, void* dst, size_t bytes, hipStream_t st) {
+  const int n = (int)(bytes / sizeof(int));
+  hipLaunchKernelGGL(k_upload, dim3(std::min((n + 255) / 256, 64)), dim3(256), 0, st, static_cast<const int*>(pinned),
+                     static_cast<int*>(dst), n);
+  return hipGetLastError();
+}
+
+template <typename real>
+hipError_t launch_op_setup(int* list, SlotCtl* ctl, SlotPtr<real>* optr, const SlotPtr<real>* ptrs, int s0, int count,
+                           int listed, int phase, const void* in, size_t in_stride, void* out, size_t out_stride,
+                           hipStream_t st) {
+  hipLaunchKernelGGL(k_op_setup<real>, dim3(listed), dim3(64), 0, st, list, ctl, optr, ptrs, s0, count, listed, phase,
+                     static_cast<const real*>(in), in_stride, static_cast<real*>(out), out_stride);
   return hipGetLastError();
 }
 
@@ -2445,11 +2670,18 @@ template hipError_t launch_validate<float>(const float*, size_t, double, double,
                                            hipStream_t);
 template hipError_t launch_validate<double>(const double*, size_t, double, double, double, unsigned int*,
                                             hipStream_t);
-template hipError_t launch_fields<float>(const SlotPtr<float>*, const SlotParam*, const SlotCtl*, int, int,
-                                         float*, float*, float*, hipStream_t);
-template hipError_t launch_fields<double>(const SlotPtr<double>*, const SlotParam*, const SlotCtl*, int, int,
-                                          double*, double*, double*, hipStream_t);
-
+#define SPFF_INSTANTIATE(R)                                                                                          \
+  template hipError_t launch_fields<R>(const SlotPtr<R>*, const SlotParam*, const SlotCtl*, int, int, int,           \
+                                       const FieldOut<R>&, hipStream_t);                                             \
+  template hipError_t launch_state<R>(unsigned char*, size_t, size_t, size_t, size_t, int, int, const void*, void*,  \
+                                      unsigned*, unsigned, unsigned*, hipStream_t);                                  \
+  template hipError_t launch_init<R>(unsigned char*, size_t, const void*, const void*, int, int, int, unsigned*,     \
+                                     hipStream_t);                                                                   \
+  template hipError_t launch_op_setup<R>(int*, SlotCtl*, SlotPtr<R>*, const SlotPtr<R>*, int, int, int, int,         \
+                                         const void*, size_t, void*, size_t, hipStream_t);
+SPFF_INSTANTIATE(float)
+SPFF_INSTANTIATE(double)
+#undef SPFF_INSTANTIATE
 
 // ===========================================================================
 // Library-owned scratch of the allocation-free entry point

@@ -61,9 +61,43 @@ template <typename real>
 hipError_t launch_validate(const real* a, size_t n, double lo_excl, double lo_incl, double hi_incl,
                            unsigned int* bad, hipStream_t st);
 
+// Caller buffers of the output fields ([slots][planes][n] each), null: not
+// asked for.
 template <typename real>
-hipError_t launch_fields(const SlotPtr<real>* ptrs, const SlotParam* prms, const SlotCtl* ctls, int slot, int n,
-                         real* strain, real* stress_out, real* psi, hipStream_t st);
+struct FieldOut {
+  real *phi, *phi_ref, *strain, *stress, *psi, *eps;
+};
+
+// Output fields of slots s0 .. s0 + slots - 1.
+template <typename real>
+hipError_t launch_fields(const SlotPtr<real>* ptrs, const SlotParam* prms, const SlotCtl* ctls, int s0, int slots,
+                         int n, const FieldOut<real>& O, hipStream_t st);
+
+// State planes of all slots (byte offsets eps, phi, phi_ref in a slot) from
+// `in` (real[slots][5][n]; nothing is copied if a value is not finite:
+// *flag = token then, and *refused, in pinned host memory, tells), or to
+// `out` if in is null.
+template <typename real>
+hipError_t launch_state(unsigned char* base, size_t slot_bytes, size_t eps, size_t phi, size_t phi_ref, int slots,
+                        int n, const void* in, void* out, unsigned* flag, unsigned token, unsigned* refused,
+                        hipStream_t st);
+
+// First nplanes planes of every slot: E, phi, phi (null: zeros), zeros;
+// counts bad values of E and phi in bad[0], bad[1].
+template <typename real>
+hipError_t launch_init(unsigned char* base, size_t slot_bytes, const void* E, const void* phi, int slots, int n,
+                       int nplanes, unsigned* bad, hipStream_t st);
+
+// bytes (a multiple of 4) from pinned host memory to the device
+hipError_t launch_upload(const void* pinned, void* dst, size_t bytes, hipStream_t st);
+
+// Control blocks, pointer table and list of a diagnostic operator over
+// `count` slots from s0; in / out (elements per slot apart) take the place
+// of the planes it reads and writes where they are not null.
+template <typename real>
+hipError_t launch_op_setup(int* list, SlotCtl* ctl, SlotPtr<real>* optr, const SlotPtr<real>* ptrs, int s0, int count,
+                           int listed, int phase, const void* in, size_t in_stride, void* out, size_t out_stride,
+                           hipStream_t st);
 
 // Address of the current device's copy of the library-owned scratch array
 // (SPFF_STATIC_SCRATCH_BYTES bytes, 256-byte aligned).

@@ -67,3 +67,63 @@ def test_blocks_in_flight_give_the_problems_alone(K, graph):
             assert all(s[k] == a[k] for k in ("cg_iters", "bccg_iters", "am_iters", "ticks", "F_e", "F_f"))
         q.close()
     p.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("shift", [0, 1, 2])
+def test_operators_and_state_with_shifted_buffers(precision, shift):
+    """Caller buffers at any element offset: operators read and write them
+    directly where they are aligned to a pixel pair and through the scratch
+    otherwise; states and fields move 16 bytes at a time or one value."""
+    import ctypes
+    import torch
+    n, B = 32, 3
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    E = torch.from_numpy(np.stack([si.young_modulus(n, 3.0, 0.1, 7 + b) for b in range(B)])).to(device(), dt)
+    p = spff.Problem(E, cfg_for(n, precision=precision))
+    p.load_step((0.0, 0.1, 0.02))
+    g = torch.Generator(device="cpu").manual_seed(3)
+    x = torch.randn(B, 3, n, n, generator=g, dtype=torch.float64).to(device(), dt)
+    L = spff.lib()
+
+    def shifted(shape):
+        t = torch.empty(int(np.prod(shape)) + 8, dtype=dt, device=device())
+        return t[shift:shift + int(np.prod(shape))].view(shape)
+
+    for op, pin, pout in ((spff.OP_PROJECT, 3, 3), (spff.OP_NEG_LAPLACIAN, 1, 1), (spff.OP_DISPLACEMENT, 3, 2)):
+        src = shifted((B, pin, n, n))
+        src.copy_(x[:, :pin])
+        want = p.apply_operator(op, x if pin == 3 else x[:, 0])
+        dst = shifted((B, pout, n, n))
+        assert L.spff_apply_operator(p.handle, op, ctypes.c_void_p(src.data_ptr()),
+                                     ctypes.c_void_p(dst.data_ptr())) == 0
+        assert torch.equal(dst.view(want.shape), want)
+    st, eb = p.get_state()
+    f = p.get_fields(0x7F)
+    again = shifted(tuple(st.shape))
+    assert L.spff_get_state(p.handle, ctypes.c_void_p(again.data_ptr()), None) == 0
+    assert torch.equal(again, st)
+    other = torch.zeros_like(st)
+    other[:, 3:] = 0.25
+    p.set_state(other, np.zeros(3))
+    assert float(p.get_fields(spff.FIELD_PHI)["phi"].min()) == 0.25
+    assert L.spff_set_state(p.handle, ctypes.c_void_p(again.data_ptr()), eb.ctypes.data_as(
+        ctypes.POINTER(ctypes.c_double))) == 0
+    g2 = {}
+    ptrs = []
+    for bit in sorted(spff.FIELD_PLANES):
+        g2[spff.FIELD_NAMES[bit]] = t = shifted((B, spff.FIELD_PLANES[bit], n, n))
+        ptrs.append(t.data_ptr())
+    assert L.spff_get_fields(p.handle, -1, 0x7F, (ctypes.c_void_p * len(ptrs))(*ptrs)) == 0
+    for k in f:
+        assert torch.equal(g2[k], f[k]), k
+    one = p.get_fields(0x7F, index=1)
+    for k in f:
+        assert torch.equal(one[k], f[k][1]), k
+    # a state with one bad value is refused as a whole
+    bad = again.clone()
+    bad[2, 4, n - 1, n - 1] = float("nan")
+    with pytest.raises(spff.SpffError):
+        p.set_state(bad)
+    assert torch.equal(p.get_state()[0], st)
+    p.close()
