@@ -519,88 +519,60 @@ __device__ __forceinline__ real ddot(const Sym<real>& a, const Sym<real>& b) {
   return a.xx * b.xx + a.yy * b.yy + real(2) * a.xy * b.xy;
 }
 
-// Split part (sign > 0: positive, < 0: negative) of the stress and, if
-// `dp` is non-null, its directional derivative along *dp.
-template <typename real, int SIGN>
-__device__ __forceinline__ void spectral_part(const Sym<real>& e, real lam, real mu, Sym<real>* sig, real* psi,
-                                              const Sym<real>* dp, Sym<real>* dsig) {
-  const real m = real(0.5) * (e.xx + e.yy);
-  const real d0 = real(0.5) * (e.xx - e.yy);
+// Weight of a positive, negative or vanishing eigenvalue (or trace): h, 1, 0.
+template <typename real>
+__device__ __forceinline__ real ramp(real v, real hk) {
+  return v > real(0) ? hk : (v < real(0) ? real(1) : real(0));
+}
+
+// Strain-spectral stress hk sigma0+ + sigma0- and its derivative along p
+// (TANGENT) in the eigenbasis: eigenvalue e_i carries w_i (ramp above), the
+// shear between the two the divided difference (w1 e1 - w2 e2) / (e1 - e2).
+// One square root and one division for both signs; without branches, so that
+// the pixels of a wavefront need not agree on theirs.  Where both eigenvalues
+// weigh the same the law is isotropic, and the unit direction D / r (0/0 at
+// r = 0) does not enter.
+template <typename real, bool TANGENT>
+__device__ __forceinline__ Sym<real> spectral_law(const Sym<real>& e, const Sym<real>& p, real lam, real mu, real hk) {
+  const real tr = e.xx + e.yy, m = real(0.5) * tr, d0 = real(0.5) * (e.xx - e.yy);
   const real r = sqrt(d0 * d0 + e.xy * e.xy);
   const real e1 = m + r, e2 = m - r;  // e1 >= e2
-  const real tr = e.xx + e.yy;
-  const bool trpos = SIGN > 0 ? (tr > real(0)) : (tr < real(0));
-  const real trp = trpos ? tr : real(0);
-  // Cases: both in the part, one (the larger for +, the smaller for -), none.
-  const bool both = SIGN > 0 ? (e2 > real(0)) : (e1 < real(0));
-  const bool one = SIGN > 0 ? (e1 > real(0)) : (e2 < real(0));
-  real s = 0, qd_scale = 0;  // q*D = qd_scale * (D / r) in the mixed case, or 2*D when both
-  real ea = 0;               // the eigenvalue in the part (mixed case)
-  if (both) {
-    s = tr;
-  } else if (one) {
-    ea = SIGN > 0 ? e1 : e2;
-    s = ea;
+  const real w1 = ramp(e1, hk), w2 = ramp(e2, hk);
+  const real inv = real(1) / (r > real(0) ? r : real(1));
+  const real ux = d0 * inv, uy = e.xy * inv;
+  const bool same = w1 == w2;
+  const real q0 = w1 * e1 - w2 * e2;
+  Sym<real> o;
+  if (TANGENT) {
+    const real dtr = p.xx + p.yy, dm = real(0.5) * dtr, dd = real(0.5) * (p.xx - p.yy);
+    const real iso = lam * ramp(tr, hk) * dtr;
+    const real along = ux * dd + uy * p.xy, across = ux * p.xy - uy * dd;
+    const real d1 = w1 * (dm + along), d2 = w2 * (dm - along);
+    const real s = d1 + d2, q = d1 - d2, sh = q0 * inv * across;  // 2 w12 across, w12 = q0 / (2 r)
+    const real w = real(2) * mu * w1;
+    o.xx = iso + (same ? w * p.xx : mu * (s + q * ux - sh * uy));
+    o.yy = iso + (same ? w * p.yy : mu * (s - q * ux + sh * uy));
+    o.xy = same ? w * p.xy : mu * (q * uy + sh * ux);
+  } else {
+    const real iso = lam * ramp(tr, hk) * tr;
+    const real s = w1 * e1 + w2 * e2, w = real(2) * mu * w1;
+    o.xx = iso + (same ? w * e.xx : mu * (s + q0 * ux));
+    o.yy = iso + (same ? w * e.yy : mu * (s - q0 * ux));
+    o.xy = same ? w * e.xy : mu * (q0 * uy);
   }
-  if (sig) {
-    Sym<real> o;
-    const real iso = lam * trp + mu * s;
-    if (both) {
-      o.xx = iso + real(2) * mu * d0;
-      o.yy = iso - real(2) * mu * d0;
-      o.xy = real(2) * mu * e.xy;
-    } else if (one) {
-      // q D = (ea / r) D, |q| <= 2 ; SIGN<0: q = -e2/r
-      const real qa = SIGN > 0 ? ea : -ea;  // q * r
-      const real ux = d0 / r, uy = e.xy / r;
-      o.xx = iso + mu * qa * ux;
-      o.yy = iso - mu * qa * ux;
-      o.xy = mu * qa * uy;
-    } else {
-      o.xx = iso;
-      o.yy = iso;
-      o.xy = 0;
-    }
-    *sig = o;
-  }
-  if (psi) {
-    real p = real(0.5) * lam * trp * trp;
-    if (both)
-      p += mu * (e1 * e1 + e2 * e2);
-    else if (one)
-      p += mu * ea * ea;
-    *psi = p;
-  }
-  if (dp) {
-    const Sym<real>& p = *dp;
-    const real dtr = p.xx + p.yy, dm = real(0.5) * dtr, dd0 = real(0.5) * (p.xx - p.yy);
-    Sym<real> o;
-    const real liso = lam * (trpos ? dtr : real(0));
-    if (both) {
-      o.xx = liso + mu * dtr + real(2) * mu * dd0;
-      o.yy = liso + mu * dtr - real(2) * mu * dd0;
-      o.xy = real(2) * mu * p.xy;
-    } else if (one) {
-      const real ux = d0 / r, uy = e.xy / r;
-      const real dr = ux * dd0 + uy * p.xy;         // derivative of r
-      const real ds = SIGN > 0 ? (dm + dr) : (dm - dr);  // derivative of ea
-      // q D = (+-ea) (D/r):  d(qD) = (+-d ea) (D/r) + (+-ea) d(D/r),
-      // d(D/r) = (dD - (D/r) dr) / r, dD = (dd0, -dd0, p.xy)
-      const real sg = SIGN > 0 ? real(1) : real(-1);
-      const real qa = sg * ea;
-      const real cr = qa / r;  // in [0, 2]
-      const real base = lam * (trpos ? dtr : real(0)) + mu * ds;
-      const real t1 = sg * ds - cr * dr;  // coefficient of D/r
-      o.xx = base + mu * (t1 * ux + cr * dd0);
-      o.yy = base + mu * (-t1 * ux - cr * dd0);
-      o.xy = mu * (t1 * uy + cr * p.xy);
-    } else {
-      o.xx = liso;
-      o.yy = liso;
-      o.xy = 0;
-    }
-    *dsig = o;
-  }
+  return o;
+}
+
+// psi0+ and psi0- of the strain-spectral split.
+template <typename real>
+__device__ __forceinline__ void spectral_energies(const Sym<real>& e, real lam, real mu, real* pp, real* pm) {
+  const real tr = e.xx + e.yy, m = real(0.5) * tr, d0 = real(0.5) * (e.xx - e.yy);
+  const real r = sqrt(d0 * d0 + e.xy * e.xy);
+  const real e1 = m + r, e2 = m - r;
+  const real t1 = fmax(tr, real(0)), t2 = fmin(tr, real(0));
+  const real a1 = fmax(e1, real(0)), a2 = fmax(e2, real(0)), b1 = fmin(e1, real(0)), b2 = fmin(e2, real(0));
+  *pp = real(0.5) * lam * t1 * t1 + mu * (a1 * a1 + a2 * a2);
+  *pm = real(0.5) * lam * t2 * t2 + mu * (b1 * b1 + b2 * b2);
 }
 
 // Volumetric-deviatoric split (plane strain, zero out-of-plane strain):
@@ -646,13 +618,7 @@ __device__ __forceinline__ Sym<real> stress(const Sym<real>& e, real lam, real m
     o.xy = hk * (real(2) * mu * e.xy);
     return o;
   }
-  Sym<real> sp, sm;
-  spectral_part<real, +1>(e, lam, mu, &sp, nullptr, nullptr, nullptr);
-  spectral_part<real, -1>(e, lam, mu, &sm, nullptr, nullptr, nullptr);
-  o.xx = hk * sp.xx + sm.xx;
-  o.yy = hk * sp.yy + sm.yy;
-  o.xy = hk * sp.xy + sm.xy;
-  return o;
+  return spectral_law<real, false>(e, e, lam, mu, hk);
 }
 
 // Tangent action C : p at strain e.
@@ -668,13 +634,7 @@ __device__ __forceinline__ Sym<real> tangent(const Sym<real>& e, const Sym<real>
     o.xy = hk * (real(2) * mu * p.xy);
     return o;
   }
-  Sym<real> dp, dm;
-  spectral_part<real, +1>(e, lam, mu, nullptr, nullptr, &p, &dp);
-  spectral_part<real, -1>(e, lam, mu, nullptr, nullptr, &p, &dm);
-  o.xx = hk * dp.xx + dm.xx;
-  o.yy = hk * dp.yy + dm.yy;
-  o.xy = hk * dp.xy + dm.xy;
-  return o;
+  return spectral_law<real, true>(e, p, lam, mu, hk);
 }
 
 // psi0+ and psi0- (isotropic model: psi0+ = full energy, psi0- = 0).
@@ -694,8 +654,7 @@ __device__ __forceinline__ void energies(const Sym<real>& e, real lam, real mu, 
     *pm = 0;
     return;
   }
-  spectral_part<real, +1>(e, lam, mu, nullptr, pp, nullptr, nullptr);
-  spectral_part<real, -1>(e, lam, mu, nullptr, pm, nullptr, nullptr);
+  spectral_energies(e, lam, mu, pp, pm);
 }
 
 }  // namespace spff
