@@ -159,30 +159,28 @@ int reg_col_lanes(const spff_config* c, const spff_plan& pl) {
 int reg_cols_min(int Lc) { return Lc >= 64 ? 1 : 64 / Lc; }
 int reg_cols_max(int Lc) { return Lc > 64 ? 1 : THREADS / Lc; }
 
-// Register kernels of a built-in plan, where the grid has them.
-// at least ~TARGET_WG work-groups per launch when the batch allows it
+// LDS kinds: at least ~TARGET_WG work-groups per launch when the batch allows it
 constexpr long TARGET_WG = 1024;
+constexpr long ROW_WG = 512;  // register rows: longer runs of the spectrum are worth more than groups
+// Register kernels of a built-in plan, where the grid has them.
 void reg_plan(const spff_config* c, int S, spff_plan* pl) {
   const int M = c->nx / 2;
   // columns of 128..2048 points: register-resident transforms, a group
-  // of ny/8 lanes per column (8 points per lane), W columns per work-group
-  // (at least one wavefront, at most THREADS lanes); W is fixed by plan_cols
-  // if given so that the partial sums (hence the results) do not depend on
-  // the batch.  1024- and 2048-point columns take one column per group (the
-  // 16-point form of their lanes holds one wavefront per SIMD in registers);
-  // plan_cols > 1 asks a 1024-point column for that form, 16 points per lane
-  // with up to four columns per group.
+  // of ny/8 lanes per column (8 points per lane), as many columns per
+  // work-group as fill a wavefront: a single wavefront waits for no other at
+  // its exchanges (64 x 256^2: 25.9 us a launch against 27.1 with four,
+  // 64 x 512^2 75.4 against 76.9, 1 x 256^2 8.5 against 9.2).  W is fixed by
+  // plan_cols if given.  1024- and 2048-point columns take one column per
+  // group (the 16-point form of their lanes holds one wavefront per SIMD in
+  // registers); plan_cols > 1 asks a 1024-point column for that form, 16
+  // points per lane with up to four columns per group.
   if (reg_cols_size(c)) {
     const bool wide = c->ny == 2048 || (c->ny == 1024 && c->plan_cols <= 1);
     const int Lc = wide ? c->ny / 8 : c->ny / reg_points(c->ny);
     const int wmin = reg_cols_min(Lc), wmax = reg_cols_max(Lc);
     if (wmin <= M) {
       int Wr = wmin;
-      if (c->plan_cols > 0) {
-        Wr = std::max(wmin, std::min(wmax, c->plan_cols));
-      } else {
-        while (Wr * 2 <= wmax && Wr * 2 <= M && (long)(M / (2 * Wr)) * S >= TARGET_WG) Wr *= 2;
-      }
+      if (c->plan_cols > 0) Wr = std::max(wmin, std::min(wmax, c->plan_cols));
       if (Wr <= M) {
         pl->col_kind = SPFF_FFT_REG;
         pl->cols = Wr;
@@ -193,11 +191,20 @@ void reg_plan(const spff_config* c, int S, spff_plan* pl) {
   // rows of 64..1024 complex points (nx = 128..2048; FP64 to 1024):
   // register-resident transforms, a group of nx/16 (nx/32 for 2048) lanes per
   // row, R rows per work-group (at least one wavefront, at most THREADS
-  // lanes); R fixed by plan_rows if given.  Below ~8 wavefronts per CU (a few
-  // problems of a small grid) rows of up to 256 points take 4 points per
-  // lane: twice the wavefronts to hide the latency of each.
-  const bool many_waves = (long)S * c->ny * (M / 8) / 64 >= 2048;
-  if (reg_rows_size(c) && (many_waves || c->plan_rows > 0 || !reg_rows_size(c, SPFF_FFT_REG4))) {
+  // lanes and eight rows -- 64-byte runs of the transposed spectrum -- and at
+  // least ROW_WG work-groups: 64 x 512^2 200 us with 8 rows, 204 with 4, 230
+  // with 2; 64 x 256^2 53.1 with 8, 53.9 with 16); R fixed by plan_rows if
+  // given.
+  // Below ~8 wavefronts per CU (a few problems of a small grid) rows of up to
+  // 256 points take 4 points per lane: twice the wavefronts to hide the
+  // latency of each; longer rows keep to the LDS kind (a thread per pixel
+  // pair) below 512 (1024 points: 1024) rows: 1024 x 128 17.7 us a tick
+  // against 19.4, 2048 x 512 34 against 42, 2048 x 1024 47.7 against 46.7,
+  // 1024 x 1024 30.6 against 25.9.
+  const long rows = (long)S * c->ny;
+  const bool many_waves = rows * (M / 8) / 64 >= 2048;
+  const bool few4 = reg_rows_size(c, SPFF_FFT_REG4) && c->plan_rows == 0 && !many_waves;
+  if (reg_rows_size(c) && !few4 && (c->plan_rows > 0 || M <= 256 || rows >= M)) {
     const int Lr = M / reg_points(M);
     const int rmin = std::max(1, 64 / Lr), rmax = THREADS / Lr;
     if (rmin <= c->ny) {
@@ -205,7 +212,7 @@ void reg_plan(const spff_config* c, int S, spff_plan* pl) {
       if (c->plan_rows > 0) {
         Rr = std::max(rmin, std::min(rmax, c->plan_rows));
       } else {
-        while (Rr * 2 <= rmax && Rr * 2 <= c->ny && (long)(c->ny / (2 * Rr)) * S >= TARGET_WG) Rr *= 2;
+        while (Rr * 2 <= std::min(rmax, 8) && Rr * 2 <= c->ny && rows / (2 * Rr) >= ROW_WG) Rr *= 2;
       }
       if (Rr <= c->ny) {
         pl->row_kind = SPFF_FFT_REG;
@@ -213,9 +220,12 @@ void reg_plan(const spff_config* c, int S, spff_plan* pl) {
         pl->row_threads = Rr * Lr;
       }
     }
-  } else if (reg_rows_size(c, SPFF_FFT_REG4) && c->plan_rows == 0) {
+  } else if (few4) {
+    // two rows (four) where that leaves a work-group (two) per CU: 16-byte
+    // (32-byte) runs of the transposed spectrum (1 x 512^2: 12.7 us a tick
+    // with two, 14.1 with one; 4 x 512^2 20.0 with two, 19.3 with four)
     const int Lr = M / 4;
-    const int Rr = std::max(1, 64 / Lr);
+    const int Rr = std::max(rows >= 2048 ? 4 : rows >= 512 ? 2 : 1, 64 / Lr);
     if (Rr <= c->ny) {
       pl->row_kind = SPFF_FFT_REG4;
       pl->rows = Rr;
@@ -300,8 +310,9 @@ LaunchGeom geom_from_plan(const spff_config* c, int S, size_t csize, const spff_
   G.ngr = c->ny / pl.rows;
   G.threads = pl.row_threads;
   G.row_reg = pl.row_kind == SPFF_FFT_REG ? 1 : (pl.row_kind == SPFF_FFT_REG4 ? 2 : 0);
+  const size_t nc = G.row_reg == 2 && csize == 8 ? 3 : 1;
   const size_t xch = (size_t)pl.rows * (M + M / 8), tile = (size_t)M * (pl.rows + 1);
-  G.lds_row = G.row_reg ? (M * csize >= 8192 ? std::max(xch, tile) : xch + tile) * csize  // RowLds in spff_kernels.hip
+  G.lds_row = G.row_reg ? (M * csize >= 8192 ? std::max(xch, tile) : nc * (xch + tile)) * csize  // RowLds in spff_kernels.hip
                         : 3 * (size_t)pl.rows * (M + PAD) * csize;
   if (G.row_reg) G.lds_row += (size_t)M * csize;  // twiddle factors
   G.W = pl.cols;

@@ -249,7 +249,8 @@ __device__ __forceinline__ void dft_small(V (&u)[RD]) {
   }
 }
 
-template <typename real, bool INV, int N, int E, int RD, int NS>
+// WRITE_ONLY: the caller reads the outputs of a pass back (not the last one's).
+template <typename real, bool INV, int N, int E, int RD, int NS, bool WRITE_ONLY = false>
 __device__ __forceinline__ void reg_pass(cplx<real> (&v)[E], cplx<real>* x, int lane,
                                          const cplx<real>* __restrict__ tw, int twmul) {
   using V = cplx<real>;
@@ -300,7 +301,7 @@ __device__ __forceinline__ void reg_pass(cplx<real> (&v)[E], cplx<real>* x, int 
   if constexpr (LAST) {
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = o[m];
-  } else {
+  } else if constexpr (!WRITE_ONLY) {
     group_sync<L>();
     static_assert(L % 8 == 0, "a lane's inputs are a whole number of pad groups apart");
     const cplx<real>* rd = x + xpad(lane);
@@ -320,6 +321,33 @@ __device__ __forceinline__ void reg_fft(cplx<real> (&v)[E], cplx<real>* x, int l
     constexpr int RD = RD0 > 8 ? 8 : RD0;
     reg_pass<real, INV, N, E, RD, NS>(v, x, lane, tw, twmul);
     reg_fft<real, INV, N, E, NS * RD>(v, x, lane, tw, twmul);
+  }
+}
+
+// NC transforms of a group at once, pass by pass, transform c exchanging
+// through x + c xstride: with few wavefronts on a SIMD an exchange's latency
+// is the transform's time, and this pays it once per pass instead of NC
+// times.
+template <typename real, bool INV, int N, int E, int NC, int NS = 1>
+__device__ __forceinline__ void reg_fft_n(cplx<real> (&v)[3][E], cplx<real>* x, int xstride, int lane,
+                                          const cplx<real>* __restrict__ tw, int twmul) {
+  if constexpr (NS < N) {
+    constexpr int L = N / E;
+    constexpr int RD0 = (N / NS) >= E ? E : (N / NS);
+    constexpr int RD = RD0 > 8 ? 8 : RD0;
+    constexpr bool LAST = NS * RD == N;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) reg_pass<real, INV, N, E, RD, NS, true>(v[c], x + c * xstride, lane, tw, twmul);
+    if constexpr (!LAST) {
+      group_sync<L>();
+      const cplx<real>* rd = x + xpad(lane);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[c][m] = rd[c * xstride + m * (L + L / 8)];
+      group_sync<L>();
+    }
+    reg_fft_n<real, INV, N, E, NC, NS * RD>(v, x, xstride, lane, tw, twmul);
   }
 }
 
@@ -450,6 +478,23 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[NP], double* re
   }
 }
 
+// The first 256 values of a slot's first two arrays of row sums and of its
+// column sums, loaded along with its control block: before that says which
+// are needed.
+struct EarlyPartials {
+  double r[2][4], c[4];
+  __device__ __forceinline__ void load(const double* __restrict__ pr, int ngr, const double* __restrict__ pc,
+                                       int ngc) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = (threadIdx.x & 63) + 64 * k;
+      r[0][k] = i < ngr ? pr[i] : 0.0;
+      r[1][k] = i < ngr ? pr[ngr + i] : 0.0;
+      c[k] = i < ngc ? pc[i] : 0.0;
+    }
+  }
+};
+
 // Sums over the work-groups' partials by one wavefront, in a fixed order:
 // lane l runs through p[l], p[l + 64], ... in index order, then the
 // wavefront combines; every lane returns the same values.  Array j of the
@@ -461,8 +506,8 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[NP], double* re
 // work-group, and its instructions are fetched cold in each launch).
 template <int NP>
 __device__ __forceinline__ void reduce_partials(const double* __restrict__ pr, int ngr, int nrow, int maxslot,
-                                                const double* __restrict__ pc, int ncol, double (&out)[NP],
-                                                double* outc) {
+                                                const double* __restrict__ pc, int ncol, const EarlyPartials& early,
+                                                double (&out)[NP], double* outc) {
   const int lane = threadIdx.x & 63;
   constexpr int NK = 4;
   double s[NP], sc = 0.0;
@@ -472,13 +517,23 @@ __device__ __forceinline__ void reduce_partials(const double* __restrict__ pr, i
   for (int base = lane; base < cmax; base += 64 * NK) {
     double a[NP][NK], c[NK];
 #pragma unroll
-    for (int k = 0; k < NK; ++k) c[k] = base + 64 * k < ncol ? pc[base + 64 * k] : 0.0;
+    for (int k = 0; k < NK; ++k) {
+      if (base < 64)
+        c[k] = base + 64 * k < ncol ? early.c[k] : 0.0;
+      else
+        c[k] = base + 64 * k < ncol ? pc[base + 64 * k] : 0.0;
+    }
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
       if (j < nrow) {
 #pragma unroll
-        for (int k = 0; k < NK; ++k)
-          a[j][k] = base + 64 * k < ngr ? pr[j * ngr + base + 64 * k] : (j == maxslot ? -1.0e300 : 0.0);
+        for (int k = 0; k < NK; ++k) {
+          const double none = j == maxslot ? -1.0e300 : 0.0;
+          if (j < 2 && base < 64)
+            a[j][k] = base + 64 * k < ngr ? early.r[j < 2 ? j : 0][k] : none;
+          else
+            a[j][k] = base + 64 * k < ngr ? pr[j * ngr + base + 64 * k] : none;
+        }
       }
     }
 #pragma unroll

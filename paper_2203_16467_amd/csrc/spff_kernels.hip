@@ -641,7 +641,8 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
                                           const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
                                           const double* __restrict__ prow, const double* __restrict__ pcol,
                                           double* __restrict__ prof, SlotSeq* __restrict__ seqs,
-                                          StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc);
+                                          StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc,
+                                          const EarlyPartials& early);
 
 // Timers of a row kernel's two parts (null when profiling is off).
 struct RowTimers {
@@ -698,11 +699,25 @@ __device__ __forceinline__ void tick_control(int s, bool writer, const CtrlArgs&
   static_assert(sizeof(SlotCtl) % sizeof(int) == 0, "the control block is copied as words");
   const int* src = reinterpret_cast<const int*>(A.ctl_in + s);
   int* dst = reinterpret_cast<int*>(&lc);
-  for (int i = threadIdx.x; i < NW; i += blockDim.x) dst[i] = src[i];
+  EarlyPartials early;
+  int w[2];  // NW words by at least 64 threads
+  static_assert(NW <= 128, "two words per thread hold the control block");
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = threadIdx.x + k * blockDim.x;
+    if (i < NW) w[k] = src[i];
+  }
+  if (threadIdx.x < 64)
+    early.load(A.prow + (size_t)s * NP_ROW * ngr, ngr, A.pcol + (size_t)s * NP_COL * A.ngc, A.ngc);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = threadIdx.x + k * blockDim.x;
+    if (i < NW) dst[i] = w[k];
+  }
   __syncthreads();
   if (threadIdx.x < 64) {
     if (lc.pending)
-      ctrl_slot<real>(s, ptrs, prms, lc, writer, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc);
+      ctrl_slot<real>(s, ptrs, prms, lc, writer, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc, early);
     // the slot's controller step after this tick is pending if it works
     if (threadIdx.x == 0) {
       lc.pending = lc.phase != PH_IDLE ? 1 : 0;
@@ -913,19 +928,46 @@ __device__ __forceinline__ double cg_alpha(double pcp, double rr) {
 }
 
 // The coefficient of a CM_CG (alpha) or combining CM_SUM (beta) column kernel
-// from this tick's row partials, for every thread of the group (which it
-// synchronises); the controller reduces the same partials in the same order
-// and gets the same value.
-__device__ __forceinline__ double col_coef(const double* __restrict__ pr, int ngr, const SlotCtl& ctl, bool combine) {
-  __shared__ double coef;
-  if (threadIdx.x < 64) {
-    double o[2], oc;
-    reduce_partials<2>(pr, ngr, combine ? 2 : 1, -1, nullptr, 0, o, &oc);
-    if (threadIdx.x == 0) coef = combine ? bccg_beta(o[0], o[1], ctl) : cg_alpha(o[0], ctl.rr);
+// from this tick's row partials; the controller reduces the same partials in
+// the same order and gets the same value.  load() issues the loads of the
+// first 256 work-groups' partials (the first wavefront), get() returns the
+// value in every thread of the group (which it synchronises).
+struct ColCoef {
+  double a[2][4];
+  __device__ __forceinline__ void load(const double* __restrict__ pr, int ngr, bool combine) {
+    if (threadIdx.x < 64) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (j == 0 || combine) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int i = threadIdx.x + 64 * k;
+            a[j][k] = i < ngr ? pr[j * ngr + i] : 0.0;
+          }
+        }
+      }
+    }
   }
-  __syncthreads();
-  return coef;
-}
+  __device__ __forceinline__ double get(const double* __restrict__ pr, int ngr, const SlotCtl& ctl, bool combine) {
+    __shared__ double coef;
+    if (threadIdx.x < 64) {
+      double o[2] = {0.0, 0.0};
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (j == 0 || combine) {
+          double v = 0.0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v += a[j][k];
+          for (int i = threadIdx.x + 256; i < ngr; i += 64) v += pr[j * ngr + i];
+          o[j] = wave_sum(v);
+        }
+      }
+      if (threadIdx.x == 0) coef = combine ? bccg_beta(o[0], o[1], ctl) : cg_alpha(o[0], ctl.rr);
+    }
+    __syncthreads();
+    return coef;
+  }
+};
 
 // The mechanics residual of a mode (three components a, packed or not):
 // r = -a, or r - alpha a with the stored r; stores r, leaves r / n in a and
@@ -979,9 +1021,12 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
   const int tot = ncomp * W * ny;
   const int logny = ilog2(ny), logW = ilog2(W);
   const bool mech = mode == CM_RES || mode == CM_CG;
-  const real coef = (op.combine || mode == CM_CG)
-                        ? real(col_coef(part_row + (size_t)s * NP_ROW * ngr, ngr, ctl, op.combine))
-                        : real(0);
+  real coef = 0;
+  if (op.combine || mode == CM_CG) {
+    ColCoef cc;
+    cc.load(part_row + (size_t)s * NP_ROW * ngr, ngr, op.combine);
+    coef = real(cc.get(part_row + (size_t)s * NP_ROW * ngr, ngr, ctl, op.combine));
+  }
   C* rhat = reinterpret_cast<C*>(F.rm);
   // one mode of the mechanics residual
   auto mech_mode = [&](C* a, int kx, int ky) {
@@ -1154,7 +1199,7 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
 // LDS, inside the group.  The packed column kx = 0 (X[0] + i X[nx/2]) takes
 // the partner mode -ky from lane (L - l) mod L by a cross-lane shuffle
 // (through LDS where the group spans several wavefronts).
-template <typename real, int N, int E>
+template <typename real, int N, int E, bool AHEAD>
 __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                             const SlotParam* __restrict__ prms, const SlotCtl* __restrict__ ctls,
                                             const cplx<real>* __restrict__ twy, const double* __restrict__ part_row,
@@ -1207,17 +1252,40 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
   }
   const bool mech = mode == CM_RES || mode == CM_CG;
   real coef = 0;
-  if (op.combine || mode == CM_CG)
-    coef = real(col_coef(part_row + (size_t)s * NP_ROW * ngr, ngr, ctl, op.combine));
+  ColCoef cc;
+  const double* pr = part_row + (size_t)s * NP_ROW * ngr;
+  if (op.combine || mode == CM_CG) cc.load(pr, ngr, op.combine);
+  C* rhat = reinterpret_cast<C*>(F.rm);
+  // The stored residual.  AHEAD (launches of few wavefronts): that of the
+  // first half of the modes is loaded before the transforms, the rest after
+  // them, all before the first store: one memory round trip less, at a
+  // wavefront per SIMD less.  Otherwise four modes at a time.
+  constexpr int HR = AHEAD ? E / 2 : 0;
+  C r0[3][E];
+  if (AHEAD && mode == CM_CG) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int m = 0; m < HR; ++m) r0[c][m] = ldc<real>(rhat + (size_t)c * M * N, at, m * L);
+  }
   if (op.combine) {
+    coef = real(cc.get(pr, ngr, ctl, true));
 #pragma unroll
     for (int m = 0; m < E; ++m) v[0][m] = mk<C>(coef * v[1][m].x - v[0][m].x, coef * v[1][m].y - v[0][m].y);
   }
-  C* rhat = reinterpret_cast<C*>(F.rm);
   __syncthreads();  // the twiddle table
 #pragma unroll
   for (int c = 0; c < 3; ++c)
     if (c < ncomp) reg_fft<real, false, N, E>(v[c], x, lane, tw, 1);
+  if (mode == CM_CG) {
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int m = HR; m < E; ++m) r0[c][m] = ldc<real>(rhat + (size_t)c * M * N, at, m * L);
+    }
+    coef = real(cc.get(pr, ngr, ctl, false));
+  }
 
   double acc[NP_COL] = {0.0, 0.0};
   if (kx > 0) {
@@ -1335,24 +1403,20 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
     // (a packed column's norm is that of its two halves: the cross terms of
     // the Hermitian A and B cancel over +-ky)
     const double w = kx > 0 ? 2.0 : 1.0;
-    constexpr int CH = 4;  // modes whose residual is loaded ahead
 #pragma unroll
-    for (int m0 = 0; m0 < E; m0 += CH) {
-      C r0[CH][3];
-      if (mode == CM_CG) {
+    for (int m = 0; m < E; ++m) {
+      if (!AHEAD && mode == CM_CG && m % 4 == 0) {
 #pragma unroll
-        for (int i = 0; i < CH; ++i)
+        for (int i = m; i < m + 4; ++i)
 #pragma unroll
-          for (int c = 0; c < 3; ++c) r0[i][c] = ldc<real>(rhat + (size_t)c * M * N, at, (m0 + i) * L);
+          for (int c = 0; c < 3; ++c) r0[c][i] = ldc<real>(rhat + (size_t)c * M * N, at, i * L);
       }
+      C a[3] = {v[0][m], v[1][m], v[2][m]};
+      const C r[3] = {r0[0][m], r0[1][m], r0[2][m]};
+      acc[0] += w * col_residual<real>(a, rhat, at, m * L, (size_t)M * N, mode == CM_CG, coef, r, inv_n);
 #pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        C a[3] = {v[0][m0 + i], v[1][m0 + i], v[2][m0 + i]};
-        acc[0] += w * col_residual<real>(a, rhat, at, (m0 + i) * L, (size_t)M * N, mode == CM_CG, coef, r0[i], inv_n);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) v[c][m0 + i] = a[c];
-      }
-      settle(acc, 0, 1);
+      for (int c = 0; c < 3; ++c) v[c][m] = a[c];
+      if (m % 4 == 3) settle(acc, 0, 1);
     }
   } else if (mode == CM_PROJECT) {
 #pragma unroll
@@ -1383,17 +1447,20 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
 // packed column); the transposed spectrum load / store goes through an LDS
 // tile [kx][row] so that R consecutive y of one kx move as one run.
 // ---------------------------------------------------------------------------
-template <typename real, int M>
+template <typename real, int M, int E = 8>
 struct RowLds {
   // exchange areas of the R row groups, then the [kx][row] tile, then the
-  // twiddle table.  Rows of 8 KB (1024 points, 512 in FP64) let the tile
-  // overlie the exchange areas (a barrier more per component): 49 KB for
+  // twiddle table.  FP32 rows with four points per lane hold areas and tiles
+  // of all three components.  Rows of 8 KB (1024 points, 512 in FP64) let the
+  // tile overlie the exchange areas (a barrier more per component): 49 KB for
   // four rows instead of 86 KB, so that a CU holds more than one work-group.
   static constexpr bool ALIAS = M * sizeof(cplx<real>) >= 8192;
+  static constexpr int NC = E == 4 && sizeof(real) == 4 ? 3 : 1;
   static __device__ __forceinline__ int tile_index(int k, int r, int R) { return k * (R + 1) + r; }
+  static __device__ __forceinline__ int tile(int R) { return ALIAS ? 0 : NC * R * XArea<M>::size; }
   static __device__ __forceinline__ int table(int R) {
     const int x = R * XArea<M>::size, t = M * (R + 1);
-    return ALIAS ? (x > t ? x : t) : x + t;
+    return ALIAS ? (x > t ? x : t) : NC * (x + t);
   }
 };
 
@@ -1413,17 +1480,66 @@ __device__ __forceinline__ void partner_bins(const cplx<real> (&v)[E], cplx<real
   }
 }
 
-// comp_update for a lane's pixel pairs of component c.
-template <typename real, int OP, int NQ, int OSTEP>
+// From a row's packed half spectrum (bin k = lane + m L; bin 0 holds X[0] + i
+// X[M]) to Z whose unnormalised inverse transform gives nx (x[2h] +
+// i x[2h+1]), in place; and from the transform of a real row to its half
+// spectrum.
+template <typename real, int M, int E>
+__device__ __forceinline__ void c2r_bins(cplx<real> (&v)[E], const cplx<real>* tw, int lane) {
+  using C = cplx<real>;
+  constexpr int L = M / E;
+  C pn[E];
+  partner_bins<real, E, L>(v, pn, lane);
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    const int k = lane + m * L;
+    if (k == 0) {
+      v[m] = mk<C>(v[m].x + v[m].y, v[m].x - v[m].y);
+    } else {
+      const C xk = v[m], xm = cconj(pn[m]);
+      const C a = cadd(xk, xm), b = csub(xk, xm);
+      v[m] = cadd(a, cmuli(cmul(cconj(tw[k]), b)));
+    }
+  }
+}
+template <typename real, int M, int E>
+__device__ __forceinline__ void r2c_bins(const cplx<real> (&v)[E], cplx<real> (&out)[E], const cplx<real>* tw,
+                                         int lane) {
+  using C = cplx<real>;
+  constexpr int L = M / E;
+  C pn[E];
+  partner_bins<real, E, L>(v, pn, lane);
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    const int k = lane + m * L;
+    if (k == 0) {
+      out[m] = mk<C>(v[m].x + v[m].y, v[m].x - v[m].y);
+    } else {
+      const C zk = v[m], zm = cconj(pn[m]);
+      const C e = cscale(cadd(zk, zm), real(0.5));
+      const C od = cscale(cmulni(csub(zk, zm)), real(0.5));
+      out[m] = cadd(e, cmul(tw[k], od));
+    }
+  }
+}
+
+// comp_update for a lane's pixel pairs of component c; in: their inputs,
+// where they are loaded already (PRE).
+template <typename real, int OP, int NQ, int OSTEP, bool PRE>
 __device__ __forceinline__ void row_comp(const RowCtx<real>& X, const SlotPtr<real>& F, int c, At o0,
-                                         cplx<real> (&v)[NQ]) {
+                                         const CompIn<real> (&pre)[NQ], cplx<real> (&v)[NQ]) {
   real *pk = F.pm + c * X.n, *tk = F.theta + c * X.n;
   constexpr int CH = NQ > 8 ? 8 : NQ;
 #pragma unroll
   for (int i0 = 0; i0 < NQ; i0 += CH) {
     CompIn<real> in[CH];
-    if (i0) asm volatile("" ::: "memory");
-    comp_load<real, OP, CH, OSTEP>(X, pk, tk, o0 + i0 * OSTEP, in);
+    if constexpr (PRE) {
+#pragma unroll
+      for (int i = 0; i < CH; ++i) in[i] = pre[i0 + i];
+    } else {
+      if (i0) asm volatile("" ::: "memory");
+      comp_load<real, OP, CH, OSTEP>(X, pk, tk, o0 + i0 * OSTEP, in);
+    }
 #pragma unroll
     for (int i = 0; i < CH; ++i) comp_update<real, OP>(X, pk, tk, o0 + (i0 + i) * OSTEP, in[i], v[i0 + i]);
   }
@@ -1444,13 +1560,14 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
   const int s = list[si];
   if (s < 0) return;
   const int R = blockDim.x / L, logR = ilog2(R);
-  C* tile = reinterpret_cast<C*>(smem_raw) + (RowLds<real, M>::ALIAS ? 0 : R * XArea<M>::size);
-  C* tw = reinterpret_cast<C*>(smem_raw) + RowLds<real, M>::table(R);
+  C* tile = reinterpret_cast<C*>(smem_raw) + RowLds<real, M, E>::tile(R);
+  C* tw = reinterpret_cast<C*>(smem_raw) + RowLds<real, M, E>::table(R);
+  const int tsize = M * (R + 1);
   TwLoad<real, M / 64> tl;
   tl.load(twx, M);
-  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl, [&]() { tl.store(tw, M); });
-  const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
+  const SlotParam& P = prms[s];
+  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl, [&]() { tl.store(tw, M); });
   const int n = nx * ny;
   const RowCtx<real> X = row_ctx<real>(lctl, P, n);
   if (X.op == RO_NONE) return;
@@ -1471,10 +1588,19 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
     C v[3][E];
     double acc[NP_ROW];
     init_acc(OP, acc);
-    // Few problems per launch (four points per lane): the group's tile
-    // entries of every component (E per thread and component: R rows x M
-    // bins over R L threads) are loaded up front, so that the components
-    // cost one memory round trip instead of one each
+    // Four points per lane is the kernel of few wavefronts: it loads the tile
+    // entries of every component up front (E per thread and component: R rows
+    // x M bins over R L threads) and, in FP32, takes the three transforms
+    // through their passes together (ILV), which pays each memory round trip,
+    // exchange and barrier once instead of three times: 11.4 -> 10.6 us a CG
+    // tick at 1 x 256^2, 18.3 -> 17.7 at 13 x 256^2, 13.5 -> 12.7 at 1 x 512^2.
+    // (Loading the pixel fields ahead of the transforms too gave 0.2 us at one
+    // problem and took 0.4 at three: more loads in flight than the CU queues.)
+    // Up to eight points per lane load a component's CG vectors before its
+    // transform.
+    constexpr int CH = E == 4 ? 4 : 2;
+    constexpr bool ILV = E == 4 && std::is_same<real, float>::value, PREC = E <= 8;
+    CompIn<real> ci[3][E];
     if constexpr (E == 4) {
 #pragma unroll
       for (int c = 0; c < NIN; ++c) {
@@ -1487,6 +1613,33 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
         }
       }
     }
+    if constexpr (ILV && NIN > 0) {
+      // every component at once, through tiles and exchange areas of its own
+#pragma unroll
+      for (int c = 0; c < NIN; ++c)
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          const int idx = threadIdx.x + i * blockDim.x;
+          const int r = idx & (R - 1), k = idx >> logR;
+          tile[c * tsize + RowLds<real, M>::tile_index(k, r, R)] = v[c][i];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < NIN; ++c) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[c][m] = tile[c * tsize + RowLds<real, M>::tile_index(lane + m * L, row, R)];
+        c2r_bins<real, M, E>(v[c], tw, lane);
+      }
+      if constexpr (CG) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) comp_load<real, OP, E, 2 * L>(X, F.pm + c * n, F.theta + c * n, o0, ci[c]);
+      }
+      reg_fft_n<real, true, M, E, NIN>(v, xa, R * XArea<M>::size, lane, tw, 2);
+      if constexpr (CG) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) row_comp<real, OP, E, 2 * L, true>(X, F, c, o0, ci[c], v[c]);
+      }
+    } else {
 #pragma unroll
     for (int c = 0; c < NIN; ++c) {
       if (OP == RO_X_OUT && c >= X.nin) break;
@@ -1510,58 +1663,56 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
 #pragma unroll
       for (int m = 0; m < E; ++m) v[c][m] = tile[RowLds<real, M>::tile_index(lane + m * L, row, R)];
       if constexpr (RowLds<real, M>::ALIAS) __syncthreads();
-      // from the packed half spectrum to Z whose unnormalised inverse FFT
-      // gives nx (x[2h] + i x[2h+1])
-      C pn[E];
-      partner_bins<real, E, L>(v[c], pn, lane);
-#pragma unroll
-      for (int m = 0; m < E; ++m) {
-        const int k = lane + m * L;
-        if (k == 0) {
-          v[c][m] = mk<C>(v[c][m].x + v[c][m].y, v[c][m].x - v[c][m].y);
-        } else {
-          const C xk = v[c][m], xm = cconj(pn[m]);
-          const C a = cadd(xk, xm), b = csub(xk, xm);
-          v[c][m] = cadd(a, cmuli(cmul(cconj(tw[k]), b)));
-        }
-      }
+      c2r_bins<real, M, E>(v[c], tw, lane);
+      if constexpr (CG && PREC)
+        comp_load<real, OP, E, 2 * L>(X, F.pm + c * n, F.theta + c * n, o0, ci[c]);
       reg_fft<real, true, M, E>(v[c], xa, lane, tw, 2);
-      if constexpr (CG) row_comp<real, OP, E, 2 * L>(X, F, c, o0, v[c]);
+      if constexpr (CG) row_comp<real, OP, E, 2 * L, PREC>(X, F, c, o0, ci[c], v[c]);
+    }
     }
     row_middle(T);
-    row_pairs<real, OP, E, E == 4 ? 4 : 2, 2 * L, E == 16>(X, P, F.E, F.phi, F.phi_ref, F.eps, F.theta, F.rm,
-                                                                F.pm, o0, v, acc);
+    row_pairs<real, OP, E, CH, 2 * L, E == 16>(X, P, F.E, F.phi, F.phi_ref, F.eps, F.theta, F.rm, F.pm, o0, v, acc);
+    if constexpr (ILV && NOUT > 0) {
+      reg_fft_n<real, false, M, E, NOUT>(v, xa, R * XArea<M>::size, lane, tw, 2);
+      __syncthreads();  // the tiles are free
+#pragma unroll
+      for (int c = 0; c < NOUT; ++c) {
+        C out[E];
+        r2c_bins<real, M, E>(v[c], out, tw, lane);
+#pragma unroll
+        for (int m = 0; m < E; ++m) tile[c * tsize + RowLds<real, M>::tile_index(lane + m * L, row, R)] = out[m];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < NOUT; ++c) {
+        if (OP == RO_X_IN && c >= X.nout) break;
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          const int idx = threadIdx.x + i * blockDim.x;
+          const int r = idx & (R - 1), k = idx >> logR;
+          stc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r),
+                    tile[c * tsize + RowLds<real, M>::tile_index(k, r, R)]);
+        }
+      }
+    } else {
 #pragma unroll
     for (int c = 0; c < NOUT; ++c) {
       if (OP == RO_X_IN && c >= X.nout) break;
       const int tid = opaque(threadIdx.x), lane = tid & (L - 1);
       if constexpr (RowLds<real, M>::ALIAS) __syncthreads();
       reg_fft<real, false, M, E>(v[c], xa, lane, tw, 2);
-      // half spectrum of the real row: X[k] = e + w^k o (k > 0), bin 0
-      // packs X[0] + i X[M]
-      C pn[E];
-      partner_bins<real, E, L>(v[c], pn, lane);
+      C out[E];
+      r2c_bins<real, M, E>(v[c], out, tw, lane);
       __syncthreads();  // the tile is free
 #pragma unroll
-      for (int m = 0; m < E; ++m) {
-        const int k = lane + m * L;
-        C out;
-        if (k == 0) {
-          out = mk<C>(v[c][m].x + v[c][m].y, v[c][m].x - v[c][m].y);
-        } else {
-          const C zk = v[c][m], zm = cconj(pn[m]);
-          const C e = cscale(cadd(zk, zm), real(0.5));
-          const C od = cscale(cmulni(csub(zk, zm)), real(0.5));
-          out = cadd(e, cmul(tw[k], od));
-        }
-        tile[RowLds<real, M>::tile_index(k, row, R)] = out;
-      }
+      for (int m = 0; m < E; ++m) tile[RowLds<real, M>::tile_index(lane + m * L, row, R)] = out[m];
       __syncthreads();
       // transposed store: spec[c][kx][y0 + r], r fastest
       for (int idx = tid; idx < M * R; idx += blockDim.x) {
         const int r = idx & (R - 1), k = idx >> logR;
         stc<real>(spec + (size_t)c * M * ny, (unsigned)(k * ny + y0 + r), tile[RowLds<real, M>::tile_index(k, r, R)]);
       }
+    }
     }
     block_reduce_store<NP_ROW>(acc, red, part + (size_t)s * NP_ROW * ngr + g, ngr, op_nacc(OP), op_maxslot(OP));
     asm volatile("; end of row op %0" ::"i"(OP));  // keeps the copies apart
@@ -1691,7 +1842,8 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
                                           const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
                                           const double* __restrict__ prow, const double* __restrict__ pcol,
                                           double* __restrict__ prof, SlotSeq* __restrict__ seqs,
-                                          StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc) {
+                                          StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc,
+                                          const EarlyPartials& early) {
   const double* pr = prow + (size_t)s * NP_ROW * ngr;
   const double* pc = pcol + (size_t)s * NP_COL * ngc;
   const int phase = uni(C.phase), inv = uni(C.inv);
@@ -1713,7 +1865,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
   {
     const int op = row_op(inv, phase);
     const bool col = phase == PH_M_RES || phase == PH_M_CG || phase == PH_PF_PQ || phase == PH_STATS;
-    reduce_partials(pr, ngr, op_nacc(op), op_maxslot(op), pc, col ? ngc : 0, o, &oc);
+    reduce_partials(pr, ngr, op_nacc(op), op_maxslot(op), pc, col ? ngc : 0, early, o, &oc);
   }
   int nphase = phase, ninv = PH_IDLE;
   int flags = uni(C.flags);
@@ -2206,7 +2358,7 @@ __global__ __launch_bounds__(THREADS) void k_col(const int* __restrict__ list, c
   kt_end(T.kt);
 }
 
-template <typename real, int N, int E>
+template <typename real, int N, int E, bool AHEAD>
 __global__ __launch_bounds__(THREADS) void k_colr(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                                   const SlotParam* __restrict__ prms,
                                                   const SlotCtl* __restrict__ ctls,
@@ -2215,7 +2367,7 @@ __global__ __launch_bounds__(THREADS) void k_colr(const int* __restrict__ list, 
                                                   int nx, int ngr, int ngc, int nyq_free, const ColTimers T) {
   if (col_timer_group(T)) return;
   kt_begin(T.kt);
-  k_colr_body<real, N, E>(list, ptrs, prms, ctls, twy, part_row, part, nx, ngr, ngc, nyq_free);
+  k_colr_body<real, N, E, AHEAD>(list, ptrs, prms, ctls, twy, part_row, part, nx, ngr, ngc, nyq_free);
   kt_end(T.kt);
 }
 
@@ -2239,8 +2391,11 @@ __global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, con
   __syncthreads();
   if (threadIdx.x < 64) {
     if (s >= 0) {
-      if (lc.pending)
-        ctrl_slot<real>(s, ptrs, prms, lc, true, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc);
+      if (lc.pending) {
+        EarlyPartials early;
+        early.load(A.prow + (size_t)s * NP_ROW * ngr, ngr, A.pcol + (size_t)s * NP_COL * A.ngc, A.ngc);
+        ctrl_slot<real>(s, ptrs, prms, lc, true, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc, early);
+      }
       if (threadIdx.x == 0) lc.pending = 0;
     }
   } else if (kt_last && blockIdx.x == 0) {
@@ -2530,24 +2685,33 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
   }
 #undef SPFF_ROWS
   if (row_only) return hipGetLastError();
-#define SPFF_COLS(NN, EE)                                                                                           \
-  hipLaunchKernelGGL((k_colr<real, NN, EE>), gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, \
+#define SPFF_COLS(NN, EE, AA)                                                                                           \
+  hipLaunchKernelGGL((k_colr<real, NN, EE, AA>), gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, \
                      prow, pcol, G.nx, G.ngr, G.ngc, G.nyq_free, T)
+#define SPFF_COLS8(NN)        \
+  if (ahead)                  \
+    SPFF_COLS(NN, 8, true);   \
+  else                        \
+    SPFF_COLS(NN, 8, false);
+  // at most one wavefront per SIMD (FP32: two): registers for loads ahead
+  // cost nothing
+  const long col_waves = (long)G.ngc * G.S * (G.threads_col / 64);
+  const bool ahead = col_waves <= (sizeof(real) == 8 ? 1024 : 2048);
   if (G.col_reg && G.col_pts == 8) {
     switch (G.ny) {
-      case 128: SPFF_COLS(128, 8); break;
-      case 256: SPFF_COLS(256, 8); break;
-      case 512: SPFF_COLS(512, 8); break;
-      case 1024: SPFF_COLS(1024, 8); break;
-      default: SPFF_COLS(2048, 8); break;
+      case 128: SPFF_COLS8(128) break;
+      case 256: SPFF_COLS8(256) break;
+      case 512: SPFF_COLS8(512) break;
+      case 1024: SPFF_COLS8(1024) break;
+      default: SPFF_COLS8(2048) break;
     }
   } else if (G.col_reg) {
     // 16 points per lane: plans of FP32 problems only
     if constexpr (std::is_same<real, float>::value) {
       if (G.ny == 1024)
-        SPFF_COLS(1024, 16);
+        SPFF_COLS(1024, 16, false);
       else
-        SPFF_COLS(2048, 16);
+        SPFF_COLS(2048, 16, false);
     } else {
       return hipErrorInvalidValue;
     }
@@ -2555,6 +2719,7 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
     hipLaunchKernelGGL(k_col<real>, gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, prow, pcol,
                        G.nx, G.ny, G.W, G.ngr, G.ngc, G.nyq_free, T);
   }
+#undef SPFF_COLS8
 #undef SPFF_COLS
   return hipGetLastError();
 }
