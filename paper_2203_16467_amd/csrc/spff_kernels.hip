@@ -1826,9 +1826,10 @@ __device__ bool ne_gamma(const SlotPtr<real>& F, const SlotParam& P, const SlotC
 // The mechanics residual's norm is summed in Fourier space: it leaves out the
 // rounding of the transform back, which adds up to 1% to the norm of the
 // field near the FP32 tolerance (measured on the two against each other).  The
-// stops keep a margin for it, so that no solve ends earlier than by the
+// FP32 stops keep a margin for it, so that no solve ends earlier than by the
 // norm of the field.
-constexpr double MECH_MARGIN = 0.97;
+template <typename real>
+constexpr double MECH_MARGIN = std::is_same<real, float>::value ? 0.97 : 1.0;
 
 // The controller step of slot s after a tick: one wavefront reads the
 // tick's partial sums and the control block C, lane 0 writes the advanced
@@ -1903,7 +1904,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
       if (!(flags & FL_MECH_STARTED)) {
         // first residual of this mechanics solve fixes the reference norm
         mech_ref = fmax(sqrt(sh2), mech_res);
-        mech_target = MECH_MARGIN * (P.tol_mech * mech_ref + P.tol_abs_mech);
+        mech_target = MECH_MARGIN<real> * (P.tol_mech * mech_ref + P.tol_abs_mech);
         flags |= FL_MECH_STARTED;
         newton_solve = 0;
       }
@@ -1915,7 +1916,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
         nphase = PH_PF_ASM;
       } else {
         inner_tol = (P.contact == 0) ? fmax(mech_target, mech_floor)
-                                   : fmax(0.1 * MECH_MARGIN * mech_res, fmax(mech_target, mech_floor));
+                                   : fmax(0.1 * MECH_MARGIN<real> * mech_res, fmax(mech_target, mech_floor));
         rr = r2;
         cg_newton = 0;
         ninv = PH_M_RES;
@@ -2334,8 +2335,15 @@ __global__ __launch_bounds__(THREADS) void k_row(const int* __restrict__ list, c
   kt_end(T.fwd);
 }
 
+// Wavefronts per SIMD that the register rows are compiled for.  Eight FP32
+// points per lane want 131 to 134 registers; held to 128 (15 of them kept in
+// scratch memory at 256 points) a CU takes four work-groups instead of three:
+// 64 x 512^2 119 us a tick's part against 125.  512 points would not gain a
+// group (LDS), and 16 points per lane lose 2% at three wavefronts.
 template <typename real, int M, int E>
-__global__ __launch_bounds__(THREADS) void k_rowr(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
+constexpr int ROW_WAVES = std::is_same<real, float>::value && E == 8 && M <= 256 ? 4 : 1;
+template <typename real, int M, int E>
+__global__ __launch_bounds__(THREADS, (ROW_WAVES<real, M, E>)) void k_rowr(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                                   const SlotParam* __restrict__ prms, const CtrlArgs A,
                                                   const cplx<real>* __restrict__ twx, double* __restrict__ part,
                                                   int ny, int ngr, const RowTimers T) {
