@@ -1,15 +1,16 @@
 """Autotuner for the FFT launch plans.
 
-A handle launches its two FFT kernels (row, column)
-over a power-of-two bucket of active problem slots; for every bucket the
-library holds a launch plan (``spff_plan``): the kind of FFT kernel for rows
-and for columns (LDS Stockham radix-4/2 with one point pair per thread, or
-register-resident radix-8 with eight points per lane -- sixteen for
-1024- and 2048-point transforms, columns of those sizes also eight --, or for
-rows radix-4 with four), rows / columns per work-group and threads per
-work-group.  The built-in plans come from a
-heuristic; this module times the alternatives on the device and installs the
-fastest.
+A handle launches its two FFT kernels (row, column) over a power-of-two
+bucket of active problem slots; for every bucket the library holds a launch
+plan (``spff_plan``): the kind of FFT kernel for rows and for columns (LDS
+Stockham radix-4/2 with one point pair per thread, or register-resident
+radix-8 with eight points per lane -- sixteen for 1024- and 2048-point
+transforms, columns of those sizes also eight --, or for rows radix-4 with
+four), rows / columns per work-group and threads per work-group.  The
+built-in plans come from a heuristic; this module times the alternatives on
+the device and installs the fastest.  FP64 plans name the LDS kind only; the
+built-in FP64 geometry takes register kernels, and is the faster from about
+256 x 256 on.
 
 Method: for a bucket of v slots a tuning handle holds v identical copies of
 a synthetic microstructure (so that all v stay active together), AT2 so that

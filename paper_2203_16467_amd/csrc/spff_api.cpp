@@ -173,8 +173,14 @@ void reg_plan(const spff_config* c, int S, spff_plan* pl) {
   // plan_cols if given.  1024- and 2048-point columns take one column per
   // group (the 16-point form of their lanes holds one wavefront per SIMD in
   // registers); plan_cols > 1 asks a 1024-point column for that form, 16
-  // points per lane with up to four columns per group.
-  if (reg_cols_size(c)) {
+  // points per lane with up to four columns per group.  FP64 columns of up to
+  // 256 points stay with the LDS kind (256 threads a column) below 512 of
+  // them, where a lane's chain of FP64 operations is the launch: 128 x 128
+  // 9.6 us against 12.7, 8 x 128 x 128 11.1 against 13.4, 256 x 256 11.5
+  // against 12.8, 4 x 256 x 256 14.8 against 15.0, 16 x 256 x 256 34.4
+  // against 26.1.
+  const bool few64 = c->precision == SPFF_FP64 && c->ny <= 256 && (long)M * S < 512;
+  if (reg_cols_size(c) && !few64) {
     const bool wide = c->ny == 2048 || (c->ny == 1024 && c->plan_cols <= 1);
     const int Lc = wide ? c->ny / 8 : c->ny / reg_points(c->ny);
     const int wmin = reg_cols_min(Lc), wmax = reg_cols_max(Lc);
@@ -517,7 +523,7 @@ hipError_t enqueue_operator(spff_problem* p, int phase, int s0, int count, const
   B.kt = nullptr;
   B.ktsum = nullptr;
   e = launch_tick<real>(p->geoms[b], B, 0, p->stream);
-  return e != hipSuccess ? e : launch_tick<real>(p->geoms[b], B, 1, p->stream, true);
+  return e != hipSuccess ? e : launch_tick<real>(p->geoms[b], B, 1, p->stream, TICK_ROW);
 }
 
 hipError_t enqueue_ticks(spff_problem* p, int t0, int k, hipStream_t st, int b) {
@@ -1606,16 +1612,23 @@ spff_status static_step(const spff_config* cfg, const Layout& L, const LaunchGeo
   B.prow[0] = reinterpret_cast<double*>(ws + L.prow);
   B.prow[1] = reinterpret_cast<double*>(ws + L.prow1);
   B.pcol = reinterpret_cast<double*>(ws + L.pcol);
-  // blocks of ticks_per_sync ticks; the host reads the block that the last
-  // row kernel left (no closing kernel in between: the next tick takes the
-  // controller step up)
-  const int K = cfg->ticks_per_sync;
+  // Blocks of at most ticks_per_sync ticks, cut after a row kernel: that has
+  // taken the controller step of the tick before it, so no tick runs to find
+  // out that the last one ended the step.  A check (30 to 40 us) costs a few
+  // ticks that find nothing to do (6 to 12 us each), so the blocks after the
+  // first are no longer than a quarter of the ticks so far (but four): a
+  // 256 x 256 FP64 step of 17 ticks in blocks of 16 takes 690 us instead of 855.
+  int done = 0;
+  hipError_t e = launch_tick<real>(G, B, 0, st, TICK_ROW);
   for (int t = 0;; t = t % 2 ? 1 : 2) {
-    for (int i = 0; i < K; ++i, ++t) {
-      hipError_t e = launch_tick<real>(G, B, t, st);
-      if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick launch failed: %s", hipGetErrorString(e));
+    const int K = done ? std::min(cfg->ticks_per_sync, std::max(done / 4, 4)) : cfg->ticks_per_sync;
+    for (int i = 0; i < K && e == hipSuccess; ++i) {
+      e = launch_tick<real>(G, B, t, st, TICK_COL);
+      if (e == hipSuccess) e = launch_tick<real>(G, B, ++t, st, TICK_ROW);
     }
-    HIP_TRY(hipMemcpyAsync(&ctl, B.ctl[t & 1], sizeof(ctl), hipMemcpyDeviceToHost, st));
+    done += K;
+    if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick launch failed: %s", hipGetErrorString(e));
+    HIP_TRY(hipMemcpyAsync(&ctl, B.ctl[(t & 1) ^ 1], sizeof(ctl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (ctl.phase == PH_IDLE) break;
   }

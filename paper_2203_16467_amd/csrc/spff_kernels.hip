@@ -2629,7 +2629,7 @@ __global__ void k_op_setup(int* __restrict__ list, SlotCtl* __restrict__ ctl, Sl
 // ===========================================================================
 
 template <typename real>
-hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st, bool row_only) {
+hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st, int kernels) {
   // tick i reads control block (i & 1) and the partials of tick i - 1
   // (row partials double-buffered: this tick's row kernel writes the other
   // half while its groups reduce the previous one)
@@ -2666,7 +2666,8 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
 #define SPFF_ROWS(MM, EE)                                                                                    \
   hipLaunchKernelGGL((k_rowr<real, MM, EE>), grow, dim3(G.threads), G.lds_row, st, list, ptrs, prms, A, twx, \
                      prow, G.ny, G.ngr, TR)
-  if (G.row_reg == 2) {
+  if (!(kernels & TICK_ROW)) {
+  } else if (G.row_reg == 2) {
     switch (G.nx) {
       case 128: SPFF_ROWS(64, 4); break;
       case 256: SPFF_ROWS(128, 4); break;
@@ -2692,7 +2693,7 @@ hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipS
                        G.R, G.ngr, TR);
   }
 #undef SPFF_ROWS
-  if (row_only) return hipGetLastError();
+  if (!(kernels & TICK_COL)) return hipGetLastError();
 #define SPFF_COLS(NN, EE, AA)                                                                                           \
   hipLaunchKernelGGL((k_colr<real, NN, EE, AA>), gcol, dim3(G.threads_col), G.lds_col, st, list, ptrs, prms, ctls, twy, \
                      prow, pcol, G.nx, G.ngr, G.ngc, G.nyq_free, T)
@@ -2842,8 +2843,8 @@ hipError_t launch_op_setup(int* list, SlotCtl* ctl, SlotPtr<real>* optr, const S
   return hipGetLastError();
 }
 
-template hipError_t launch_tick<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t, bool);
-template hipError_t launch_tick<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t, bool);
+template hipError_t launch_tick<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t, int);
+template hipError_t launch_tick<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t, int);
 template hipError_t launch_close<float>(const LaunchGeom&, const TickBufs<float>&, int, hipStream_t, int);
 template hipError_t launch_close<double>(const LaunchGeom&, const TickBufs<double>&, int, hipStream_t, int);
 template hipError_t launch_validate<float>(const float*, size_t, double, double, double, unsigned int*,

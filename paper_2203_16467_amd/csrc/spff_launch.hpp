@@ -46,10 +46,12 @@ struct TickBufs {
 
 // Tick i (0-based) of a run of ticks over the listed slots.  Tick 0 reads
 // ctl[0], whose blocks must have no controller step pending (as the host
-// and launch_close leave them).  row_only: the row kernel alone, which
-// finishes the phase of tick i - 1.
+// and launch_close leave them).  kernels: which of the two to launch; the row
+// kernel alone finishes the phase of tick i - 1.
+enum { TICK_ROW = 1, TICK_COL = 2 };
 template <typename real>
-hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st, bool row_only = false);
+hipError_t launch_tick(const LaunchGeom& G, const TickBufs<real>& B, int i, hipStream_t st,
+                       int kernels = TICK_ROW | TICK_COL);
 
 // Closes a run of k ticks under one geometry: the controller step of tick
 // k - 1, leaving the control blocks of the listed slots (slots > 0: of all

@@ -127,3 +127,88 @@ def test_operators_and_state_with_shifted_buffers(precision, shift):
         p.set_state(bad)
     assert torch.equal(p.get_state()[0], st)
     p.close()
+
+
+@pytest.mark.parametrize("nx,ny,B", [(128, 128, 136), (256, 256, 34)])
+def test_column_loads_ahead_leave_the_results(nx, ny, B):
+    """Launches of at most 2048 column wavefronts load the residual ahead of
+    the transform.  With the plan fixed the batch, which has more, and the
+    problem alone, which has fewer, agree bit for bit."""
+    import torch
+    distinct = 2
+    E = np.stack([si.young_modulus(nx, 3.0, 0.1 + 0.05 * b, 40 + b, ny=ny) for b in range(distinct)])
+    kw = dict(plan_rows=4 if nx == 256 else 8, plan_cols=4)
+    eps = si.uniaxial_ramp(12, 0.2, 2.0)[5]
+    Et = torch.from_numpy(E).to(device())
+    p = spff.Problem(Et.repeat(B // distinct, 1, 1).contiguous(), cfg_for(nx, ny, **kw))
+    _, stats = p.load_step(eps)
+    f = p.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+    for b in range(distinct):
+        q = spff.Problem(Et[b], cfg_for(nx, ny, **kw))
+        _, alone = q.load_step(eps)
+        g = q.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+        for k in f:
+            assert torch.equal(f[k][b], g[k][0]) and torch.equal(f[k][B - distinct + b], g[k][0]), k
+        assert stats[b]["cg_iters"] == alone[0]["cg_iters"] > 0
+        q.close()
+    p.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_static_step_is_the_same_at_any_block_length(precision):
+    """The static step's blocks are cut after a row kernel and shrink after
+    the first: no block length changes its result or its tick count."""
+    import torch
+    n = 64
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    E = torch.from_numpy(si.young_modulus(n, 3.0, 0.2, 5)).to(device(), dt).contiguous()
+    want = None
+    for K in (1, 2, 5, 64):
+        state = torch.zeros((5, n, n), dtype=dt, device=device())
+        _, s = spff.load_step_static(cfg_for(n, precision=precision, at=2, ticks_per_sync=K), E, state,
+                                     (0.0, 0.2, 0.03))
+        got = (state, s["ticks"], s["cg_iters"], s["F_e"], s["F_f"])
+        want = want or got
+        assert torch.equal(got[0], want[0]) and got[1:] == want[1:], K
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_spectral_stress_and_energy_at_its_corners(precision):
+    """Vanishing, equal, opposite and barely different eigenvalues, either
+    sign: the stress and the driving energy of the strain-spectral split are
+    the oracle's to 16 roundings of the largest term."""
+    import torch
+    n = 16
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    corners = [(0, 0, 0), (1, 1, 0), (-1, -1, 0), (1, -1, 0), (1, 0, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1),
+               (1, 1, 1), (-1, -1, 1), (1, 1 + 1e-6, 0), (1e-6, -1, 0), (1, -1e-6, 1e-6), (2, 0.5, 1), (-2, -0.5, -1),
+               (1e-12, 1e-12, 0)]
+    x = np.array(corners, dtype=np.float64) * 1e-2
+    eps = np.zeros((3, n * n))
+    phi = np.zeros(n * n)
+    for i in range(n * n):
+        eps[:, i] = x[i % len(x)]
+        phi[i] = (i // len(x)) / 16.0
+    # the fluctuations are stored in the problem's precision; the mean is 0
+    eps = torch.from_numpy(eps.reshape(3, n, n)).to(dt)
+    phi = torch.from_numpy(phi.reshape(n, n)).to(dt)
+    E = torch.ones((n, n), dtype=dt, device=device())
+    cfg = cfg_for(n, precision=precision, split="spectral")
+    p = spff.Problem(E, cfg)
+    state = torch.cat([eps, phi[None], phi[None]]).to(device())
+    p.set_state(state[None].contiguous(), np.zeros(3))
+    f = p.get_fields(spff.FIELD_STRESS | spff.FIELD_PSI_PLUS)
+    nu = cfg.nu
+    lam, mu = nu / ((1 + nu) * (1 - 2 * nu)), 1 / (2 * (1 + nu))
+    t = planes_to_tensor(eps.double().numpy())
+    sp, sm = oracle.constitutive.sigma0(t, np.full((n, n), lam), np.full((n, n), mu), "spectral")
+    h = ((1 - phi.double().numpy()) ** 2 + cfg.k_res)[..., None, None]
+    want = tensor_to_planes(h * sp + sm)
+    got = f["stress"][0].double().cpu().numpy()
+    u = np.finfo(np.float64 if precision == "fp64" else np.float32).eps
+    scale = (lam + 2 * mu) * np.abs(eps.double().numpy()).sum(axis=0)
+    assert np.all(np.abs(got - want) <= 16 * u * scale[None] + 1e-300)
+    pp = oracle.constitutive.psi0(t, np.full((n, n), lam), np.full((n, n), mu), "spectral")[0]
+    gpp = f["psi_plus"][0].double().cpu().numpy()
+    assert np.all(np.abs(gpp - pp) <= 16 * u * (lam + 2 * mu) * np.abs(eps.double().numpy()).sum(axis=0) ** 2 + 1e-300)
+    p.close()
