@@ -637,8 +637,7 @@ struct CtrlArgs {
 };
 
 template <typename real>
-__device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict__ ptrs,
-                                          const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
+__device__ __forceinline__ void ctrl_slot(int s, const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
                                           const double* __restrict__ prow, const double* __restrict__ pcol,
                                           double* __restrict__ prof, SlotSeq* __restrict__ seqs,
                                           StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc,
@@ -692,7 +691,6 @@ struct TwLoad {
 // runs in every thread before the last synchronisation.
 template <typename real, typename Also>
 __device__ __forceinline__ void tick_control(int s, bool writer, const CtrlArgs& A,
-                                             const SlotPtr<real>* __restrict__ ptrs,
                                              const SlotParam* __restrict__ prms, int nx, int ny, int ngr,
                                              SlotCtl& lc, Also also) {
   constexpr int NW = (int)(sizeof(SlotCtl) / sizeof(int));
@@ -717,7 +715,7 @@ __device__ __forceinline__ void tick_control(int s, bool writer, const CtrlArgs&
   __syncthreads();
   if (threadIdx.x < 64) {
     if (lc.pending)
-      ctrl_slot<real>(s, ptrs, prms, lc, writer, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc, early);
+      ctrl_slot<real>(s, prms, lc, writer, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc, early);
     // the slot's controller step after this tick is pending if it works
     if (threadIdx.x == 0) {
       lc.pending = lc.phase != PH_IDLE ? 1 : 0;
@@ -757,7 +755,7 @@ __device__ __forceinline__ void k_row_body(const int* __restrict__ list, const S
   if (s < 0) return;
   const int M = nx >> 1, stride = M + PAD;
   C* buf = reinterpret_cast<C*>(smem_raw);
-  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl, []() {});
+  tick_control<real>(s, g == 0, A, prms, nx, ny, ngr, lctl, []() {});
   const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
   const int n = nx * ny;
@@ -992,6 +990,77 @@ __device__ __forceinline__ double col_residual(cplx<real>* a, cplx<real>* rhat, 
   return w;
 }
 
+__device__ __forceinline__ int wave_min_int(int v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
+  return v;
+}
+
+// Near-equilibrium strain scaling (Sec. 3.2.2, Algorithm 4).  fm is the
+// largest -F_phi(phi_n, eps_n); the row kernel that finished the assembly kept
+// the unmasked residual F_phi in rm[1] and its per-row-group maxima in
+// gmax[0 .. ngr).  x* is the first pixel (row-major) where -F_phi equals fm:
+// the first row group holding the maximum, then the first pixel of that
+// group's rows.  With d = -h'(phi_n) psi0+ at x*, gamma^2 =
+// (fphi_max - (fm - d)) / d (psi0+ is degree-two homogeneous in the strain),
+// clamped at 0 and capped at 1 + deps_max / max|eps_bar|.  Returns false
+// (no scaling) when x* is not found or d is not positive.  One wavefront.
+template <typename real>
+__device__ bool ne_gamma(const SlotPtr<real>& F, const SlotParam& P, const SlotCtl& C, double fm,
+                         const double* __restrict__ gmax, int nx, int ny, int ngr, double* gamma) {
+  const int lane = threadIdx.x & 63;
+  int gs = ngr;
+  for (int i = lane; i < ngr; i += 64)
+    if (gmax[i] == fm) {
+      gs = i;
+      break;
+    }
+  gs = wave_min_int(gs);
+  if (gs >= ngr) return false;
+  const int n = nx * ny, rows = ny / ngr;
+  const int base = gs * rows * nx, cnt = rows * nx;
+  const real* fr = F.rm + n;
+  int xi = n;
+  for (int i = lane; i < cnt; i += 64)
+    if (-double(fr[base + i]) == fm) {
+      xi = base + i;
+      break;
+    }
+  xi = wave_min_int(xi);
+  if (xi >= n) return false;
+  const real E = F.E[xi], ph = F.phi_ref[xi];
+  const real lam = real(P.lam_t) * E, mu = real(P.mu_t) * E;
+  const Sym<real> e = {real(C.eps_bar[0]) + F.eps[xi], real(C.eps_bar[1]) + F.eps[n + xi],
+                       real(C.eps_bar[2]) + F.eps[2 * n + xi]};
+  real pp, pm;
+  energies(e, lam, mu, P.split, &pp, &pm);
+  const double d = double(real(2) * (real(1) - ph) * pp);
+  if (!(d > 0.0)) return false;
+  double g = sqrt(fmax((P.fphi_max - (fm - d)) / d, 0.0));
+  const double eb = fmax(fabs(C.eps_bar[0]), fmax(fabs(C.eps_bar[1]), fabs(C.eps_bar[2])));
+  if (eb > 0.0) g = fmin(g, 1.0 + P.deps_max / eb);
+  *gamma = g;
+  return true;
+}
+
+// The scaling factor of a near-equilibrium check (PF_WAIT), by one wavefront
+// of the column kernel of its tick, into the first column partial: -1 if the
+// strain is not to be scaled.  That kernel has no other work then and writes
+// no plane.  The controller step cannot evaluate it: it runs at the start of
+// every row work-group, and the row kernel that it opens stores the scaled
+// strain, so a group that starts after x*'s owner has stored would read
+// gamma eps* and take another factor.
+template <typename real>
+__device__ __forceinline__ void col_ne_gamma(const SlotPtr<real>& F, const SlotParam& P, const SlotCtl& C,
+                                             const double* __restrict__ pr, double* __restrict__ out, int nx, int ny,
+                                             int ngr) {
+  double fm = -1.0e300, gamma = -1.0;
+  for (int i = threadIdx.x; i < ngr; i += 64) fm = fmax(fm, pr[ngr + i]);
+  fm = wave_max(fm);
+  if (fm > P.fphi_max) ne_gamma<real>(F, P, C, fm, pr + ngr, nx, ny, ngr, &gamma);
+  if (threadIdx.x == 0) *out = gamma;
+}
+
 template <typename real>
 __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
                                                  const SlotParam* __restrict__ prms,
@@ -1006,7 +1075,12 @@ __device__ __forceinline__ void k_col_body(const int* __restrict__ list, const S
   if (s < 0) return;
   const SlotCtl& ctl = ctls[s];
   const ColOp op = col_op(ctl);
-  if (op.ncomp == 0) return;
+  if (op.ncomp == 0) {
+    if (ctl.phase == PH_PF_WAIT && g == 0 && threadIdx.x < 64)
+      col_ne_gamma<real>(ptrs[s], prms[s], ctl, part_row + (size_t)s * NP_ROW * ngr, part + (size_t)s * NP_COL * ngc,
+                         nx, ny, ngr);
+    return;
+  }
   const int phase = ctl.phase, ncomp = op.ncomp, mode = op.mode;
   const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
@@ -1221,7 +1295,12 @@ __device__ __forceinline__ void k_colr_body(const int* __restrict__ list, const 
   if (s < 0) return;
   const SlotCtl& ctl = ctls[s];
   const ColOp op = col_op(ctl);
-  if (op.ncomp == 0) return;
+  if (op.ncomp == 0) {
+    if (ctl.phase == PH_PF_WAIT && g == 0 && threadIdx.x < 64)
+      col_ne_gamma<real>(ptrs[s], prms[s], ctl, part_row + (size_t)s * NP_ROW * ngr, part + (size_t)s * NP_COL * ngc,
+                         nx, N, ngr);
+    return;
+  }
   const int phase = ctl.phase, ncomp = op.ncomp, mode = op.mode;
   const SlotParam& P = prms[s];
   const SlotPtr<real> F = ptrs[s];
@@ -1567,7 +1646,7 @@ __device__ __forceinline__ void k_rowr_body(const int* __restrict__ list, const 
   tl.load(twx, M);
   const SlotPtr<real> F = ptrs[s];
   const SlotParam& P = prms[s];
-  tick_control<real>(s, g == 0, A, ptrs, prms, nx, ny, ngr, lctl, [&]() { tl.store(tw, M); });
+  tick_control<real>(s, g == 0, A, prms, nx, ny, ngr, lctl, [&]() { tl.store(tw, M); });
   const int n = nx * ny;
   const RowCtx<real> X = row_ctx<real>(lctl, P, n);
   if (X.op == RO_NONE) return;
@@ -1769,60 +1848,8 @@ __device__ inline void phase_bytes(int inv, int phase, int flags, int split, dou
 // ===========================================================================
 // Controller of one slot, run by one wavefront.  Reduces the tick's partials
 // in a fixed order, updates FP64 scalars and moves the slot's state machine.
+// It reads no plane: other groups of its launch may be writing them already.
 // ===========================================================================
-__device__ __forceinline__ int wave_min_int(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
-  return v;
-}
-
-// Near-equilibrium strain scaling (Sec. 3.2.2, Algorithm 4).  fm is the
-// largest -F_phi(phi_n, eps_n); the row kernel that finished the assembly kept
-// the unmasked residual F_phi in rm[1] and its per-row-group maxima in
-// gmax[0 .. ngr).  x* is the first pixel (row-major) where -F_phi equals fm:
-// the first row group holding the maximum, then the first pixel of that
-// group's rows.  With d = -h'(phi_n) psi0+ at x*, gamma^2 =
-// (fphi_max - (fm - d)) / d (psi0+ is degree-two homogeneous in the strain),
-// clamped at 0 and capped at 1 + deps_max / max|eps_bar|.  Returns false
-// (no scaling) when x* is not found or d is not positive.  One wavefront.
-template <typename real>
-__device__ bool ne_gamma(const SlotPtr<real>& F, const SlotParam& P, const SlotCtl& C, double fm,
-                         const double* __restrict__ gmax, int nx, int ny, int ngr, double* gamma) {
-  const int lane = threadIdx.x & 63;
-  int gs = ngr;
-  for (int i = lane; i < ngr; i += 64)
-    if (gmax[i] == fm) {
-      gs = i;
-      break;
-    }
-  gs = wave_min_int(gs);
-  if (gs >= ngr) return false;
-  const int n = nx * ny, rows = ny / ngr;
-  const int base = gs * rows * nx, cnt = rows * nx;
-  const real* fr = F.rm + n;
-  int xi = n;
-  for (int i = lane; i < cnt; i += 64)
-    if (-double(fr[base + i]) == fm) {
-      xi = base + i;
-      break;
-    }
-  xi = wave_min_int(xi);
-  if (xi >= n) return false;
-  const real E = F.E[xi], ph = F.phi_ref[xi];
-  const real lam = real(P.lam_t) * E, mu = real(P.mu_t) * E;
-  const Sym<real> e = {real(C.eps_bar[0]) + F.eps[xi], real(C.eps_bar[1]) + F.eps[n + xi],
-                       real(C.eps_bar[2]) + F.eps[2 * n + xi]};
-  real pp, pm;
-  energies(e, lam, mu, P.split, &pp, &pm);
-  const double d = double(real(2) * (real(1) - ph) * pp);
-  if (!(d > 0.0)) return false;
-  double g = sqrt(fmax((P.fphi_max - (fm - d)) / d, 0.0));
-  const double eb = fmax(fabs(C.eps_bar[0]), fmax(fabs(C.eps_bar[1]), fabs(C.eps_bar[2])));
-  if (eb > 0.0) g = fmin(g, 1.0 + P.deps_max / eb);
-  *gamma = g;
-  return true;
-}
-
 // The mechanics residual's norm is summed in Fourier space: it leaves out the
 // rounding of the transform back, which adds up to 1% to the norm of the
 // field near the FP32 tolerance (measured on the two against each other).  The
@@ -1839,8 +1866,7 @@ constexpr double MECH_MARGIN = std::is_same<real, float>::value ? 0.97 : 1.0;
 // position); the other wavefronts that run the same step on their own copy
 // of C (every row work-group of the slot) only advance their copy.
 template <typename real>
-__device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict__ ptrs,
-                                          const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
+__device__ __forceinline__ void ctrl_slot(int s, const SlotParam* __restrict__ prms, SlotCtl& C, bool writer,
                                           const double* __restrict__ prow, const double* __restrict__ pcol,
                                           double* __restrict__ prof, SlotSeq* __restrict__ seqs,
                                           StepRec* __restrict__ recs, int nx, int ny, int ngr, int ngc,
@@ -1972,8 +1998,9 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotPtr<real>* __restrict
         flags &= ~FL_NE_CHECK;
         fmax_ne = o[1];
         if (fmax_ne > P.fphi_max && dmax > P.drive_thr) ne_flag = 1;
-        if (fmax_ne > P.fphi_max && ne_flag &&
-            ne_gamma<real>(ptrs[s], P, C, fmax_ne, pr + 1 * ngr, nx, ny, ngr, &gamma)) {
+        // the factor that the column kernel left (col_ne_gamma), below 0: none
+        if (fmax_ne > P.fphi_max && ne_flag && pc[0] >= 0.0) {
+          gamma = pc[0];
           scaled = true;
           flags |= FL_NE_SCALE;
           nphase = PH_PF_ASM;  // assemble again at the scaled strain
@@ -2384,9 +2411,9 @@ __global__ __launch_bounds__(THREADS) void k_colr(const int* __restrict__ list, 
 // A.ctl_out (buffer 0, possibly the same block) and the host's mirror.  With timers on, the second wavefront of group 0 folds
 // the last tick's kernel times meanwhile.
 template <typename real>
-__global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, const SlotPtr<real>* __restrict__ ptrs,
-                                              const SlotParam* __restrict__ prms, const CtrlArgs A, int nx, int ny,
-                                              int ngr, KTime* kt_last, unsigned long long* __restrict__ ktsum) {
+__global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, const SlotParam* __restrict__ prms,
+                                              const CtrlArgs A, int nx, int ny, int ngr, KTime* kt_last,
+                                              unsigned long long* __restrict__ ktsum) {
   constexpr int NW = (int)(sizeof(SlotCtl) / sizeof(int));
   __shared__ SlotCtl lc;
   const unsigned long long t_close = wall_clock64();
@@ -2402,7 +2429,7 @@ __global__ __launch_bounds__(128) void k_close(const int* __restrict__ list, con
       if (lc.pending) {
         EarlyPartials early;
         early.load(A.prow + (size_t)s * NP_ROW * ngr, ngr, A.pcol + (size_t)s * NP_COL * A.ngc, A.ngc);
-        ctrl_slot<real>(s, ptrs, prms, lc, true, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc, early);
+        ctrl_slot<real>(s, prms, lc, true, A.prow, A.pcol, A.prof, A.seqs, A.recs, nx, ny, ngr, A.ngc, early);
       }
       if (threadIdx.x == 0) lc.pending = 0;
     }
@@ -2749,7 +2776,7 @@ hipError_t launch_close(const LaunchGeom& G, const TickBufs<real>& B, int k, hip
   A.mirror = B.mirror;
   A.ngc = G.ngc;
   hipLaunchKernelGGL(k_close<real>, dim3(slots > 0 ? slots : G.S), dim3(128), 0, st, slots > 0 ? nullptr : B.list,
-                     B.ptrs, B.prms, A, G.nx, G.ny, G.ngr, B.kt ? B.kt + 3 * last : nullptr, B.ktsum);
+                     B.prms, A, G.nx, G.ny, G.ngr, B.kt ? B.kt + 3 * last : nullptr, B.ktsum);
   return hipGetLastError();
 }
 

@@ -212,3 +212,43 @@ def test_spectral_stress_and_energy_at_its_corners(precision):
     gpp = f["psi_plus"][0].double().cpu().numpy()
     assert np.all(np.abs(gpp - pp) <= 16 * u * (lam + 2 * mu) * np.abs(eps.double().numpy()).sum(axis=0) ** 2 + 1e-300)
     p.close()
+
+
+@pytest.mark.parametrize("n,B,rows", [(512, 32, 2), (64, 128, 1)])
+def test_near_equilibrium_scaling_is_one_factor_with_many_row_groups(n, B, rows):
+    """Algorithm 4's strain scaling in launches of 8192 row groups, of which
+    the GPU holds a part at once: every row of a problem is scaled by the one
+    factor that its statistics report (eps* is that factor, in the working
+    precision, times the strain of the same step without scaling), and the
+    batch agrees bit for bit with the problems alone."""
+    import torch
+    distinct = 4
+    print(f"scaling {B} x {n}", flush=True)
+    E = np.stack([si.young_modulus(n, n / 32.0, 0.2, 60 + b) for b in range(distinct)])
+    Et = torch.from_numpy(E).to(device())
+    eps = (0.0, 0.5, 0.0)
+    kw = dict(evolution=spff.EVOL_NEAR_EQ, drive_threshold=0.0, deps_max=1e-3, eta=0.0, plan_rows=rows, plan_cols=1,
+              max_bccg=20)
+    free = spff.Problem(Et, cfg_for(n, fphi_max=1e30, **kw))
+    free.load_step(eps)
+    before = free.get_fields(spff.FIELD_EPS_STAR)["eps_star"].cpu().numpy()
+    free.close()
+    cfg = cfg_for(n, fphi_max=0.05, **kw)
+    p = spff.Problem(Et.repeat(B // distinct, 1, 1).contiguous(), cfg)
+    _, stats = p.load_step(eps)
+    f = p.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+    got = f["eps_star"].cpu().numpy()
+    for b in range(B):
+        g = stats[b]["gamma"]
+        assert 0.0 < g < 1.0 and stats[b]["ne_flag"] == 1
+        assert stats[b]["eps_bar"][1] == g * eps[1]
+        assert np.array_equal(got[b], np.float32(g) * before[b % distinct]), b
+    for b in range(distinct):
+        q = spff.Problem(Et[b], cfg)
+        _, alone = q.load_step(eps)
+        one = q.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+        for i in range(b, B, distinct):
+            assert stats[i]["gamma"] == alone[0]["gamma"]
+            assert all(torch.equal(f[k][i], one[k][0]) for k in f), i
+        q.close()
+    p.close()
