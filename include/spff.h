@@ -182,7 +182,8 @@ typedef struct spff_step_stats {
   double C_bar;            /* sigma_bar_ij / eps_bar_ij at the largest |eps_bar_ij| */
   double phi_max, phi_mean;
   int64_t crack_px;        /* pixels with phi > 0.9 */
-  double wall_ms;          /* host wall time from enqueueing the step to observing its end */
+  double wall_ms;          /* device time of this problem's step, from its first tick to its last;
+                              static step: host time of the call; served: submit to completion */
   double dt;               /* SPFF_EVOL_TIME: dt for the next step */
   int32_t halvings;        /* SPFF_EVOL_TIME: dt halvings in this step */
   int32_t advance;         /* SPFF_EVOL_TIME / _NEAR_EQ: 1 if the algorithm increments the load now */

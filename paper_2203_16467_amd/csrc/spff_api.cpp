@@ -1157,6 +1157,8 @@ static SlotCtl rec_ctl(const StepRec& r) {
   c.bccg = r.bccg;
   c.ticks = r.ticks;
   c.status = r.status;
+  c.t_start = r.t_start;
+  c.t_end = r.t_end;
   c.dt = r.dt;
   c.halvings = r.halvings;
   c.advance = r.advance;
@@ -1219,7 +1221,6 @@ static spff_status run_queue(spff_problem* p, int32_t nsteps, const double* eps_
   std::vector<char> more(S, 0);             // it is not the slot's last
   std::vector<int32_t> start(S);
   for (int s = 0; s < S; ++s) start[s] = s;
-  const double t0 = now_ms();
   for (;;) {
     for (int s : start) {
       const int len = clen[s] = std::min(SEQ_MAX, nsteps - next[s]);
@@ -1281,16 +1282,8 @@ static spff_status run_queue(spff_problem* p, int32_t nsteps, const double* eps_
       const int done = queue ? p->host_seq[s].pos : 1;
       bool failed = done < clen[s];
       for (int j = 0; j < done; ++j) {
-        SlotCtl c{};
-        double ms;
-        if (queue) {
-          const StepRec& r = p->host_rec[(size_t)s * p->host_rec_len + j];
-          c = rec_ctl(r);
-          ms = (double)(r.t_end - r.t_start) / p->clock_khz;
-        } else {
-          c = p->host_ctl[s];
-          ms = now_ms() - t0;
-        }
+        const SlotCtl c = queue ? rec_ctl(p->host_rec[(size_t)s * p->host_rec_len + j]) : p->host_ctl[s];
+        const double ms = (double)(c.t_end - c.t_start) / p->clock_khz;
         const spff_status ss = slot_status(c);
         note(ss);
         failed |= ss < 0;

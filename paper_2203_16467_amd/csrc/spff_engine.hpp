@@ -106,7 +106,7 @@ struct SlotCtl {
   int32_t newton_solve;             // Newton steps of the current mechanics solve
   int32_t pending;                  // the controller step of the last tick is still to run
   int32_t inv, pad1;                // phase that the row kernel finishes before it starts `phase` (0: none)
-  uint64_t t_start;                 // device wall clock at the start of the step
+  uint64_t t_start, t_end;          // device wall clock at the start and the end of the step
   int32_t ticks, status;
   // row kernels the slot has been through since the host wrote the block, and
   // the first of them that found it idle (0: none): what is posted to the host

@@ -2144,7 +2144,11 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotParam* __restrict__ p
     status = -4;
     nphase = PH_IDLE;
   }
-  if (nphase == PH_IDLE) ninv = PH_IDLE;
+  uint64_t t_end = C.t_end;
+  if (nphase == PH_IDLE) {
+    ninv = PH_IDLE;
+    t_end = wall_clock64();
+  }
   // a load step just ended: record it and start the next one of the queue
   bool restart = false;
   if (seqs && nphase == PH_IDLE && (phase == PH_STATS || bad) && !(flags & FL_INIT_SOLVE) && threadIdx.x == 0 &&
@@ -2166,7 +2170,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotParam* __restrict__ p
       r.fmax_ne = fmax_ne;
       r.ne_flag = ne_flag;
       r.t_start = C.t_start;
-      r.t_end = wall_clock64();
+      r.t_end = t_end;
       r.dphi = dphi;
       r.mech_res = mech_res;
       r.pf_res = pf_res;
@@ -2264,6 +2268,7 @@ __device__ __forceinline__ void ctrl_slot(int s, const SlotParam* __restrict__ p
       C.eps_bar[2] *= gamma;
     }
     C.ticks = C.ticks + 1;
+    C.t_end = t_end;
   }
 }
 

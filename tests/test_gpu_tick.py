@@ -252,3 +252,20 @@ def test_near_equilibrium_scaling_is_one_factor_with_many_row_groups(n, B, rows)
             assert all(torch.equal(f[k][i], one[k][0]) for k in f), i
         q.close()
     p.close()
+
+
+def test_wall_time_is_that_of_each_problem():
+    """A step's wall_ms is the time of that problem's step: of two problems
+    in one batch, a homogeneous one that takes a few ticks reports less than
+    half of what one that takes many times as many does, also where the two
+    are queued."""
+    import torch
+    n = 64
+    E = np.stack([np.ones((n, n), dtype=np.float32), si.young_modulus(n, 3.0, 0.3, 5)])
+    ramp = si.uniaxial_ramp(12, 0.2, 2.0)[3:6]
+    p = spff.Problem(torch.from_numpy(E).to(device()), cfg_for(n, tol=1e-6))
+    for k, rows in enumerate((p.load_step(ramp[0])[1], [r[0] for r in p.run_sequence(ramp[1:])[1]])):
+        quick, slow = rows
+        assert 4 * quick["ticks"] <= slow["ticks"], k
+        assert 0.0 < quick["wall_ms"] < 0.5 * slow["wall_ms"] < 1e3, k
+    p.close()
