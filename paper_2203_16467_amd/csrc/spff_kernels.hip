@@ -2495,12 +2495,19 @@ struct StatePlanes {
   }
 };
 
-// *flag = token if a value is not finite.
+// Values that the library takes as input: finite, and in FP64 at most 1e300
+// in size (any finite FP32 value: 1e300 rounds to infinity there).
+template <typename real>
+__device__ __forceinline__ bool acceptable(real v) {
+  return isfinite(v) && fabs(v) <= real(1e300);
+}
+
+// *flag = token if a value is not acceptable.
 template <typename real>
 __global__ void k_check_finite(const real* __restrict__ a, size_t n, unsigned* __restrict__ flag, unsigned token) {
   bool bad = false;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    bad |= !isfinite(a[i]);
+    bad |= !acceptable(a[i]);
   if (bad) *flag = token;
 }
 
@@ -2599,8 +2606,8 @@ __global__ void k_fields(const SlotPtr<real>* __restrict__ ptrs, const SlotParam
 
 // Fills nplanes planes of each slot: plane 0 from E (zero without), planes 1
 // and 2 from phi (zero without), the rest with zeros; counts the values of E
-// that are not positive and finite in bad[0], those of phi outside [0, 1] in
-// bad[1].
+// that are not positive and acceptable in bad[0], those of phi outside [0, 1]
+// in bad[1].
 template <typename real>
 __global__ void k_init(unsigned char* __restrict__ base, size_t slot_bytes, const real* __restrict__ E,
                        const real* __restrict__ phi, int n, int nplanes, unsigned* __restrict__ bad) {
@@ -2611,7 +2618,7 @@ __global__ void k_init(unsigned char* __restrict__ base, size_t slot_bytes, cons
     real e = 0, f = 0;
     if (E) {
       e = E[(size_t)s * n + i];
-      bad_e += (isfinite(e) && e > real(0)) ? 0u : 1u;
+      bad_e += (acceptable(e) && e > real(0)) ? 0u : 1u;
     }
     if (phi) {
       f = phi[(size_t)s * n + i];

@@ -269,3 +269,41 @@ def test_wall_time_is_that_of_each_problem():
         assert 4 * quick["ticks"] <= slow["ticks"], k
         assert 0.0 < quick["wall_ms"] < 0.5 * slow["wall_ms"] < 1e3, k
     p.close()
+
+
+def test_fp64_values_beyond_1e300_are_refused():
+    """Finite FP64 inputs beyond 1e300 are refused like non-finite ones, by
+    every entry point that takes a field, and a refused state leaves the old
+    one; 1e300 itself and any finite FP32 value are accepted as states."""
+    import torch
+    n = 16
+    E = torch.ones((n, n), dtype=torch.float64, device=device())
+    big = E.clone()
+    big[3, 5] = 2e300
+    with pytest.raises(spff.SpffError) as e:
+        spff.Problem(big, cfg_for(n, precision="fp64"))
+    assert e.value.status == spff.E_INVALID
+    sv = spff.Server(64 << 20)
+    with pytest.raises(spff.SpffError) as e:
+        sv.register(cfg_for(n, precision="fp64"), big)
+    assert e.value.status == spff.E_INVALID
+    sv.close()
+    p = spff.Problem(E, cfg_for(n, precision="fp64"))
+    st = torch.full_like(p.get_state()[0], 0.5)
+    p.set_state(st)
+    for v in (2e300, -2e300, float("inf"), float("nan")):
+        other = torch.zeros_like(st)
+        other[0, 1, 2, 3] = v
+        with pytest.raises(spff.SpffError) as e:
+            p.set_state(other)
+        assert e.value.status == spff.E_INVALID and torch.equal(p.get_state()[0], st)
+    other[0, 1, 2, 3] = -1e300
+    p.set_state(other)
+    assert torch.equal(p.get_state()[0], other)
+    p.close()
+    q = spff.Problem(E.float(), cfg_for(n))
+    st = torch.zeros_like(q.get_state()[0])
+    st[0, 0, 0, 0] = 3e38
+    q.set_state(st)
+    assert torch.equal(q.get_state()[0], st)
+    q.close()
