@@ -1207,6 +1207,7 @@ static spff_status run_queue(spff_problem* p, int32_t nsteps, const double* eps_
   if (queue && p->host_rec_len < most) {
     if (p->host_rec) HIP_TRY(hipHostFree(p->host_rec));
     p->host_rec = nullptr;
+    p->host_rec_len = 0;  // an allocation below may fail
     if (!p->host_seq)
       HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&p->host_seq), sizeof(SlotSeq) * S, hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&p->host_rec), sizeof(StepRec) * most * S, hipHostMallocDefault));

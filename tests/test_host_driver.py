@@ -1,0 +1,79 @@
+"""The host driver (spff_api.cpp) against a stand-in device: launch plans,
+step queues and blocks of ticks, without a GPU."""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2203_16467_amd import spff
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = "/opt/rocm/include"
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    """The driver compiled for the host and linked with tests/fake_device.cpp."""
+    cxx = shutil.which("g++")
+    if cxx is None or not os.path.exists(os.path.join(ROCM, "hip", "hip_runtime.h")):
+        pytest.skip("needs g++ and the HIP headers")
+    csrc = os.path.join(ROOT, "paper_2203_16467_amd", "csrc")
+    out = str(tmp_path_factory.mktemp("driver") / "driver.so")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-I", ROCM, "-I",
+                    os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "spff_api.cpp"),
+                    os.path.join(ROOT, "tests", "fake_device.cpp"), "-Wl,-z,defs", "-Wl,-Bsymbolic",
+                    "-o", out], check=True)
+    L = ctypes.CDLL(out)
+    for name, (res, args) in spff._SIGS.items():
+        getattr(L, name).restype, getattr(L, name).argtypes = res, args
+    return L
+
+
+class Handle:
+    """A handle of the driver over host memory."""
+
+    def __init__(self, L, B=1, **kw):
+        L.fake_reset()
+        self.L, self.B, self.cfg = L, B, spff.default_config(**kw)
+        n = ctypes.c_size_t()
+        assert L.spff_workspace_bytes(ctypes.byref(self.cfg), B, ctypes.byref(n)) == 0
+        self.mem = ctypes.create_string_buffer(n.value + 512)
+        ws = (ctypes.addressof(self.mem) + 255) // 256 * 256
+        self.h = ctypes.c_void_p()
+        assert L.spff_create_batch(ctypes.byref(self.cfg), B, ctypes.c_void_p(ws), None, ctypes.c_void_p(ws), n.value,
+                                   None, ctypes.byref(self.h)) == 0
+
+    def need(self, *ticks):
+        self.L.fake_need(len(ticks), (ctypes.c_int * len(ticks))(*ticks))
+
+    def counts(self):
+        c = (ctypes.c_int * 3)()
+        self.L.fake_counts(c)
+        return list(c)
+
+    def sequence(self, K):
+        stats = (spff.StepStats * (self.B * K))()
+        st = self.L.spff_run_sequence(self.h, K, (ctypes.c_double * (3 * self.B * K))(), stats)
+        return st, [[stats[b * K + k].to_dict() for k in range(K)] for b in range(self.B)]
+
+    def close(self):
+        self.L.spff_destroy_problem(self.h)
+
+
+def test_step_records_survive_a_failed_allocation(driver):
+    """The pinned staging of step records grows with the queue.  If its
+    allocation fails the call reports it, and a later queue no longer than
+    an earlier one works."""
+    p = Handle(driver, 2)
+    p.need(3, 5)
+    assert p.sequence(2)[0] == 0
+    driver.fake_fail_alloc(1)
+    assert p.sequence(6)[0] == spff.E_DEVICE
+    st, s = p.sequence(2)
+    assert st == 0 and [[x["ticks"] for x in row] for row in s] == [[3, 3], [5, 5]]
+    st, s = p.sequence(6)
+    assert st == 0 and [len(row) for row in s] == [6, 6] and s[1][5]["ticks"] == 5
+    p.close()
