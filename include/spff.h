@@ -357,7 +357,11 @@ typedef struct spff_plan {
 } spff_plan;
 /* Number of buckets and their slot counts (sizes may be NULL). */
 spff_status spff_plan_buckets(const spff_problem* p, int32_t* count, int32_t* sizes);
-/* The plan in use for bucket `bucket`. */
+/* The plan in use for bucket `bucket`.  FP64 problems report the LDS plan of
+ * the built-in rule for it, although their built-in geometry takes register
+ * kernels where the grid has them (rows: 128 <= nx <= 1024, columns: ny in
+ * {128, ..., 2048}); installing that plan keeps the built-in geometry, any
+ * other LDS plan gives the LDS kernels it names. */
 spff_status spff_get_plan(const spff_problem* p, int32_t bucket, spff_plan* out);
 /* Install a plan for bucket `bucket` (NULL restores the heuristic).  The
  * plan is validated (SPFF_E_INVALID on a bad plan, state unchanged) and the

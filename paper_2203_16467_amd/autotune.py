@@ -8,9 +8,10 @@ radix-8 with eight points per lane -- sixteen for 1024- and 2048-point
 transforms, columns of those sizes also eight --, or for rows radix-4 with
 four), rows / columns per work-group and threads per work-group.  The
 built-in plans come from a heuristic; this module times the alternatives on
-the device and installs the fastest.  FP64 plans name the LDS kind only; the
-built-in FP64 geometry takes register kernels, and is the faster from about
-256 x 256 on.
+the device and installs the fastest.  FP64 plans name the LDS kind only, while
+the built-in FP64 geometry takes register kernels; the plan that stands for it
+(the one a handle reports before any is installed) is timed like the others
+and kept unless a candidate is faster.
 
 Method: for a bucket of v slots a tuning handle holds v identical copies of
 a synthetic microstructure (so that all v stay active together), AT2 so that
@@ -123,6 +124,7 @@ def tune_bucket(nx, ny, v, precision=spff.FP32, seed=7, log=None):
     eps = ramp[10]
     bidx = prob.plan_buckets().index(v)
     base = prob.get_plan(bidx)
+    t_base = sum(_time_plan(prob, bidx, base, state, eps))
     best_row, best_col = None, None
     for kind, R, T in row_candidates(cfg):
         plan = dict(base, row_kind=kind, rows=R, row_threads=T)
@@ -145,10 +147,16 @@ def tune_bucket(nx, ny, v, precision=spff.FP32, seed=7, log=None):
             log(f"[autotune] {nx}x{ny} b{v} cols kind {kind} W {W} T {T}: {tc * 1e3:.1f} us/tick")
         if best_col is None or tc < best_col[0]:
             best_col = (tc, kind, W, T)
-    prob.close()
     plan = dict(row_kind=best_row[1], rows=best_row[2], row_threads=best_row[3], col_kind=best_col[1],
                 cols=best_col[2], col_threads=best_col[3])
-    return plan, {"row_us_per_tick": best_row[0] * 1e3, "col_us_per_tick": best_col[0] * 1e3}
+    # the two searches vary one half of the built-in plan at a time, and in
+    # FP64 a half of it stands for a register kernel only beside the other
+    tr, tc = _time_plan(prob, bidx, plan, state, eps)
+    if t_base <= tr + tc:
+        plan = dict(base)
+        tr, tc = _time_plan(prob, bidx, plan, state, eps)
+    prob.close()
+    return plan, {"row_us_per_tick": tr * 1e3, "col_us_per_tick": tc * 1e3}
 
 
 DEFAULT_CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "plans_gfx950.json")

@@ -334,12 +334,22 @@ LaunchGeom geom_from_plan(const spff_config* c, int S, size_t csize, const spff_
 }
 
 // Geometry of a bucket's built-in plan.  FP64 problems without overrides take
-// the register kernels too (512^2 load step: 1.05 ms against 0.77 ms), while the plan
-// they report, and may be given, keeps to the LDS kind.
+// the register kernels too (512^2 load step: 0.77 ms against 1.05 ms with the
+// LDS kind).  A plan names register kinds for FP32 only, so the plan that FP64
+// problems report is the LDS one of the same rule, and stands for the built-in
+// geometry: given to spff_set_plan() it keeps that (plan_geom()), as any other
+// plan is taken literally.
 LaunchGeom auto_geom(const spff_config* c, int S, size_t csize) {
   spff_plan pl = auto_plan(c, S, csize);
   if (c->precision == SPFF_FP64 && c->plan_rows == 0 && c->plan_cols == 0 && c->plan_threads == 0) reg_plan(c, S, &pl);
   return geom_from_plan(c, S, csize, pl);
+}
+
+LaunchGeom plan_geom(const spff_config* c, int S, size_t csize, const spff_plan& pl) {
+  const spff_plan a = auto_plan(c, S, csize);
+  const bool built_in = pl.row_kind == a.row_kind && pl.rows == a.rows && pl.row_threads == a.row_threads &&
+                        pl.col_kind == a.col_kind && pl.cols == a.cols && pl.col_threads == a.col_threads;
+  return built_in ? auto_geom(c, S, csize) : geom_from_plan(c, S, csize, pl);
 }
 
 // scratch_only: slots hold solver scratch only; the resident planes
@@ -1491,7 +1501,7 @@ spff_status spff_set_plan(spff_problem* p, int32_t bucket, spff_plan* plan) {
   if (st != SPFF_OK) return st;
   HIP_TRY(hipStreamSynchronize(p->stream));
   p->plans[bucket] = pl;
-  p->geoms[bucket] = plan ? geom_from_plan(&p->cfg, v, csize, pl) : auto_geom(&p->cfg, v, csize);
+  p->geoms[bucket] = plan_geom(&p->cfg, v, csize, pl);
   if (p->graphs[bucket]) {
     HIP_TRY(hipGraphExecDestroy(p->graphs[bucket]));
     p->graphs[bucket] = nullptr;

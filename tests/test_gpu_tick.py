@@ -307,3 +307,17 @@ def test_fp64_values_beyond_1e300_are_refused():
     q.set_state(st)
     assert torch.equal(q.get_state()[0], st)
     q.close()
+
+
+def test_autotuner_keeps_the_faster_built_in_fp64_geometry():
+    """FP64 plans name LDS kernels, the built-in geometry takes register
+    kernels, which are a quarter faster at 512 x 512: the tuner returns the
+    plan that stands for it."""
+    from paper_2203_16467_amd import autotune
+    plan, t = autotune.tune_bucket(512, 512, 1, precision=spff.FP64)
+    import torch
+    E = torch.ones((512, 512), dtype=torch.float64, device=device())
+    p = spff.Problem(E, cfg_for(512, precision="fp64"))
+    assert plan == p.get_plan(0), (plan, t)
+    assert t["row_us_per_tick"] > 0 and t["col_us_per_tick"] > 0
+    p.close()

@@ -77,3 +77,36 @@ def test_step_records_survive_a_failed_allocation(driver):
     st, s = p.sequence(6)
     assert st == 0 and [len(row) for row in s] == [6, 6] and s[1][5]["ticks"] == 5
     p.close()
+
+
+@pytest.mark.parametrize("nx,ny,B", [(512, 512, 1), (256, 128, 8), (64, 1024, 3), (1024, 64, 1), (32, 32, 2)])
+@pytest.mark.parametrize("precision", [spff.FP32, spff.FP64])
+def test_installing_the_reported_plan_changes_nothing(driver, nx, ny, B, precision):
+    """The plan that a handle reports, given back, leaves the geometry that
+    it launches as it was; any other LDS plan is launched as it says, and
+    removing the plan restores the built-in geometry."""
+    p = Handle(driver, B, nx=nx, ny=ny, precision=precision)
+
+    def launched():
+        g = (ctypes.c_int * 6)()
+        p.sequence(1)
+        driver.fake_geom(g)
+        return list(g)
+
+    count = ctypes.c_int32()
+    driver.spff_plan_buckets(p.h, ctypes.byref(count), None)
+    last = count.value - 1
+    built_in = launched()
+    if precision == spff.FP64 and nx == ny == 512:
+        assert built_in[0] and built_in[3]  # register kernels
+    plan = spff.Plan()
+    assert driver.spff_get_plan(p.h, last, ctypes.byref(plan)) == 0
+    assert driver.spff_set_plan(p.h, last, ctypes.byref(plan)) == 0
+    assert launched() == built_in
+    other = spff.Plan.from_dict(dict(row_kind=spff.FFT_LDS, rows=1, row_threads=128, col_kind=spff.FFT_LDS, cols=1,
+                                     col_threads=128))
+    assert driver.spff_set_plan(p.h, last, ctypes.byref(other)) == 0
+    assert launched() == [0, 1, 128, 0, 1, 128]
+    assert driver.spff_set_plan(p.h, last, None) == 0
+    assert launched() == built_in
+    p.close()
