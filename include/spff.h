@@ -117,7 +117,8 @@ typedef struct spff_config {
   double tol_pf, tol_abs_pf;     /* phase field: ||r|| <= tol*max(||b||,||r0||) + tol_abs */
   double tol_am;           /* AM stop: sum |phi_n+1 - phi_n| < tol_am (pixel units); <0: 1e-3 ell^2 */
   int32_t max_cg, max_newton, max_bccg, max_am; /* iteration caps */
-  int32_t ticks_per_sync;  /* most solver ticks in a block, the unit the host enqueues and checks (>= 1) */
+  int32_t ticks_per_sync;  /* most solver ticks in a block, the unit the host enqueues and checks (>= 1);
+                              the static step's first block has one more */
   int32_t use_graph;       /* 1: replay the tick block as a captured HIP graph (of an even number of ticks) */
   /* Attainable-accuracy floor (not in the paper): a residual evaluated in the
    * working precision u carries rounding noise of about u sqrt(log2(nx ny))

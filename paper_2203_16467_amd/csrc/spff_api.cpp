@@ -1616,21 +1616,29 @@ spff_status static_step(const spff_config* cfg, const Layout& L, const LaunchGeo
   B.prow[0] = reinterpret_cast<double*>(ws + L.prow);
   B.prow[1] = reinterpret_cast<double*>(ws + L.prow1);
   B.pcol = reinterpret_cast<double*>(ws + L.pcol);
-  // Blocks of at most ticks_per_sync ticks, cut after a row kernel: that has
-  // taken the controller step of the tick before it, so no tick runs to find
-  // out that the last one ended the step.  A check (30 to 40 us) costs a few
-  // ticks that find nothing to do (6 to 12 us each), so the blocks after the
-  // first are no longer than a quarter of the ticks so far (but four): a
-  // 256 x 256 FP64 step of 17 ticks in blocks of 16 takes 690 us instead of 855.
+  // Blocks of ticks_per_sync ticks, cut after a row kernel: that has taken the
+  // controller step of the tick before it, so no tick runs to find out that
+  // the last one ended the step.  The first block has a tick more, for the one
+  // in which a phase-field solve finds that it has converged: a step whose
+  // other ticks fill a block must not pay for a second one (256 x 256 FP64,
+  // 19 ticks: 669 us in blocks of 18, 728 with a second block).  A check costs
+  // 20 us, a tick that finds nothing to do 5 to 7, so of blocks of sixteen or
+  // more ticks the second is checked after a quarter too (256 x 256 FP32, 20
+  // ticks: 635 us in blocks of 16, 676 when checked halfway).
+  const int K = cfg->ticks_per_sync;
   int done = 0;
   hipError_t e = launch_tick<real>(G, B, 0, st, TICK_ROW);
   for (int t = 0;; t = t % 2 ? 1 : 2) {
-    const int K = done ? std::min(cfg->ticks_per_sync, std::max(done / 4, 4)) : cfg->ticks_per_sync;
-    for (int i = 0; i < K && e == hipSuccess; ++i) {
+    int k = K;
+    if (!done)
+      k = K + 1;
+    else if (K >= 16 && done <= 2 * K)
+      k = done == K + 1 ? K / 4 : 2 * K + 1 - done;
+    for (int i = 0; i < k && e == hipSuccess; ++i) {
       e = launch_tick<real>(G, B, t, st, TICK_COL);
       if (e == hipSuccess) e = launch_tick<real>(G, B, ++t, st, TICK_ROW);
     }
-    done += K;
+    done += k;
     if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick launch failed: %s", hipGetErrorString(e));
     HIP_TRY(hipMemcpyAsync(&ctl, B.ctl[(t & 1) ^ 1], sizeof(ctl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));

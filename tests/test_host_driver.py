@@ -110,3 +110,26 @@ def test_installing_the_reported_plan_changes_nothing(driver, nx, ny, B, precisi
     assert driver.spff_set_plan(p.h, last, None) == 0
     assert launched() == built_in
     p.close()
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 8, 12, 16, 64])
+def test_static_step_checks_no_oftener_than_its_blocks(driver, K):
+    """A phase-field solve ends with a tick that finds it converged, so a
+    step whose other ticks fill m blocks of ticks_per_sync takes one tick
+    more.  It must not cost a block: the static step checks m times (once
+    more where it splits a long second block), and enqueues no tick beyond
+    the blocks."""
+    for m in (1, 2, 3, 7):
+        T = m * K + 1
+        driver.fake_reset()
+        driver.fake_need(1, (ctypes.c_int * 1)(T))
+        cfg = spff.default_config(nx=16, ny=16, ticks_per_sync=K)
+        buf = ctypes.create_string_buffer(16 * 16 * 4 * 6)
+        stats, c = spff.StepStats(), (ctypes.c_int * 3)()
+        assert driver.spff_load_step_static(ctypes.byref(cfg), buf, ctypes.addressof(buf), (ctypes.c_double * 3)(),
+                                            ctypes.byref(stats), None) == 0
+        driver.fake_counts(c)
+        checks, rows, cols = c[0] - 2, c[1], c[2]  # two synchronisations of uploads
+        assert stats.ticks == T
+        assert checks <= m + (K >= 16 and m > 1), (m, checks)
+        assert cols == T and rows == T + 1
