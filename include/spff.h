@@ -113,7 +113,8 @@ typedef struct spff_config {
   double crack_set_threshold; /* crack-set constraint: phi_ref >= threshold (0.9) */
   double k_res;            /* residual stiffness added to h(phi); 0 in the paper */
   double eta_over_dt;      /* viscous term eta/dt; 0 = alternating minimisation */
-  double tol_mech, tol_abs_mech; /* mechanics: ||G[sigma]|| <= tol*max(||sigma_hom||,||R0||) + tol_abs */
+  double tol_mech, tol_abs_mech; /* mechanics: ||G[sigma]|| <= tol*max(||sigma_hom||,||R0||) + tol_abs
+                                    (FP32 solves stop at 0.97 of the right side) */
   double tol_pf, tol_abs_pf;     /* phase field: ||r|| <= tol*max(||b||,||r0||) + tol_abs */
   double tol_am;           /* AM stop: sum |phi_n+1 - phi_n| < tol_am (pixel units); <0: 1e-3 ell^2 */
   int32_t max_cg, max_newton, max_bccg, max_am; /* iteration caps */
@@ -176,7 +177,7 @@ typedef struct spff_step_stats {
   int32_t bccg_iters;      /* phase-field BCCG iterations (sum) */
   int32_t ticks;           /* solver ticks the step took */
   double dphi_l1;          /* last ||phi_n+1 - phi_n||_1 */
-  double mech_residual;    /* last ||G[sigma]||_2 */
+  double mech_residual;    /* last ||G[sigma]||_2, summed over its Fourier modes */
   double pf_residual;      /* last BCCG ||r||_2 */
   double F_e, F_f;         /* elastic and fracture energy (pixel area 1) */
   double sigma_bar[3];     /* mean stress (xx, yy, xy) */

@@ -321,3 +321,37 @@ def test_autotuner_keeps_the_faster_built_in_fp64_geometry():
     assert plan == p.get_plan(0), (plan, t)
     assert t["row_us_per_tick"] > 0 and t["col_us_per_tick"] > 0
     p.close()
+
+
+@pytest.mark.parametrize("nx,ny,precision", [(64, 64, "fp32"), (256, 128, "fp32"), (512, 512, "fp32"),
+                                             (64, 64, "fp64"), (256, 512, "fp64")])
+@pytest.mark.parametrize("split,nyquist", [("none", spff.NYQ_ZERO), ("spectral", spff.NYQ_FREE)])
+def test_mechanics_residual_is_the_norm_of_the_projected_stress(nx, ny, precision, split, nyquist):
+    """mech_residual, a sum over Fourier modes, is the norm of the field
+    G[sigma] of the returned stress (an elastic step: phi stays 0), and lies
+    within the tolerance, in FP32 within 0.97 of it.  Rounding of the stress
+    adds u ||sigma|| to a residual of 1e-3 ||sigma|| at most; 8 of that are
+    allowed."""
+    import torch
+    tol, eps = 1e-3, (0.0, 0.1, 0.03)
+    E = torch.from_numpy(si.young_modulus(nx, 4.0, 0.25, 3, ny=ny)).to(device())
+    if precision == "fp64":
+        E = E.double()
+    cfg = cfg_for(nx, ny, precision, split=split, nyquist=nyquist, tol=tol)
+    p = spff.Problem(E, cfg)
+    _, s = p.load_step(eps)
+    f = p.get_fields(spff.FIELD_STRESS | spff.FIELD_PHI)
+    assert float(f["phi"].max()) == 0.0 and s[0]["cg_iters"] > 0
+    g = p.apply_operator(spff.OP_PROJECT, f["stress"])[0].double().cpu().numpy()
+    sg = f["stress"][0].double().cpu().numpy()
+
+    def norm(a):
+        return float(np.sqrt((a[0] ** 2 + a[1] ** 2 + 2 * a[2] ** 2).sum()))
+
+    u = 2.0 ** -24 if precision == "fp32" else 2.0 ** -53
+    assert abs(norm(g) - s[0]["mech_residual"]) <= 8 * u * norm(sg)
+    lam, mu = cfg.nu / ((1 + cfg.nu) * (1 - 2 * cfg.nu)), 1 / (2 * (1 + cfg.nu))
+    Ef = E.double().cpu().numpy()
+    hom = norm(np.stack([lam * eps[1] * Ef, (lam + 2 * mu) * eps[1] * Ef, 2 * mu * eps[2] * Ef]))
+    assert 0.0 < s[0]["mech_residual"] <= (0.97 if precision == "fp32" else 1.0) * tol * hom * (1 + 1e-6)
+    p.close()
