@@ -420,7 +420,6 @@ struct spff_problem {
   std::vector<LaunchGeom> geoms;
   std::vector<spff_plan> plans;  // per bucket, geoms[i] derived from plans[i]
   std::vector<hipGraphExec_t> graphs;  // one captured tick block per bucket (lazy)
-  int cur_bucket = -1;
   // pinned staging of the device slot list: uploads of LIST_RING successive
   // lists, of which at most BLOCKS_AHEAD + 1 can be in flight
   int32_t* host_list = nullptr;
@@ -1099,13 +1098,13 @@ spff_status engine_create(const spff_config* cfg, int32_t nbatch, const void* E_
     spff_destroy_problem(p);
     return s;
   };
-  if (hipHostMalloc(reinterpret_cast<void**>(&p->host_ctl), 2 * sizeof(SlotCtl) * nbatch, hipHostMallocDefault) !=
-          hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&p->host_list), sizeof(int32_t) * nbatch * LIST_RING,
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&p->host_post), sizeof(unsigned long long) * nbatch,
-                    hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&p->host_refused), sizeof(unsigned), hipHostMallocDefault) != hipSuccess)
+  // kernels read and write these while the host does (the progress words
+  // while it waits for them): coherent whatever the process's default is
+  auto pinned = [](auto** ptr, size_t bytes) {
+    return hipHostMalloc(reinterpret_cast<void**>(ptr), bytes, hipHostMallocCoherent) == hipSuccess;
+  };
+  if (!pinned(&p->host_ctl, 2 * sizeof(SlotCtl) * nbatch) || !pinned(&p->host_list, sizeof(int32_t) * nbatch * LIST_RING) ||
+      !pinned(&p->host_post, sizeof(unsigned long long) * nbatch) || !pinned(&p->host_refused, sizeof(unsigned)))
     return cleanup(fail(SPFF_E_DEVICE, "pinned host allocation failed"));
   for (int s = 0; s < nbatch; ++s) reset_ctl(p, s);
   st = cfg->precision == SPFF_FP64 ? init_device<double>(p, E_dev, phi_init_dev)

@@ -133,3 +133,12 @@ def test_static_step_checks_no_oftener_than_its_blocks(driver, K):
         assert stats.ticks == T
         assert checks <= m + (K >= 16 and m > 1), (m, checks)
         assert cols == T and rows == T + 1
+
+
+def test_memory_that_kernels_post_to_is_coherent(driver):
+    """The progress words are read while the kernel that posts them runs, so
+    the pinned memory asks for coherence (0x40000000, hipHostMallocCoherent)
+    instead of relying on the process's default."""
+    p = Handle(driver, 3)
+    assert driver.fake_alloc_flags() & 0x40000000
+    p.close()
