@@ -355,3 +355,100 @@ def test_mechanics_residual_is_the_norm_of_the_projected_stress(nx, ny, precisio
     hom = norm(np.stack([lam * eps[1] * Ef, (lam + 2 * mu) * eps[1] * Ef, 2 * mu * eps[2] * Ef]))
     assert 0.0 < s[0]["mech_residual"] <= (0.97 if precision == "fp32" else 1.0) * tol * hom * (1 + 1e-6)
     p.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_spectral_tangent_at_its_corners(precision):
+    """One CG iteration from eps* = 0 at a uniform strain with equal,
+    vanishing, opposite or barely different eigenvalues and h(phi) < 1 takes
+    eps* to alpha p, p = -G[sigma], alpha = p.p / p.C p: the oracle's with
+    its tangent.  p carries the rounding of two transforms and of the stress
+    (16 u of its norm), alpha that of p twice and of the products (32 u over
+    the smallest h, 1/100); the two together are below 1e4 u."""
+    import torch
+    n, nu = 16, 0.2
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    corners = [(1, 1, 0), (-1, -1, 0), (1, -1, 0), (1, 0, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1), (1, 1 + 1e-6, 0),
+               (1e-6, -1, 0), (1, -1e-6, 1e-6), (2, 0.5, 0.7), (-2, -0.5, -0.7), (1, 0.2, 1), (-1, 0.3, 0.1)]
+    phi = torch.from_numpy(np.random.default_rng(4).uniform(0.0, 0.9, (n, n))).to(dt)
+    state = torch.zeros((1, 5, n, n), dtype=dt, device=device())
+    state[0, 3] = state[0, 4] = phi.to(device())
+    cfg = cfg_for(n, precision=precision, split="spectral", max_newton=1, max_cg=1, max_am=1, max_bccg=1, nu=nu)
+    E = si.young_modulus(n, 3.0, 0.2, 6)
+    p = spff.Problem(torch.from_numpy(E).to(device(), dt), cfg)
+    lam, mu = oracle.constitutive.lame(E, nu)
+    ph = phi.double().numpy()
+    u = 2.0 ** -24 if precision == "fp32" else 2.0 ** -53
+    for c in corners:
+        e = 1e-2 * np.array(c, dtype=np.float64)
+        p.set_state(state, np.zeros(3))
+        _, s = p.load_step(e)
+        assert s[0]["cg_iters"] == 1, c
+        eps = oracle.constitutive.sym_tensor(*[np.full((n, n), v) for v in e])
+        r = -osp.project(oracle.constitutive.stress(eps, ph, lam, mu, "spectral"))
+        cp = oracle.constitutive.tangent_action(eps, r, ph, lam, mu, "spectral")
+        want = tensor_to_planes((r * r).sum() / (r * cp).sum() * r)
+        got = p.get_fields(spff.FIELD_EPS_STAR)["eps_star"][0].double().cpu().numpy()
+        assert rel_l2(got, want) < 1e4 * u, (c, rel_l2(got, want) / u)
+    p.close()
+
+
+@pytest.mark.parametrize("nx,ny,B", [(256, 128, 1), (512, 256, 1), (1024, 512, 1), (64, 1024, 1), (128, 2048, 1),
+                                     (256, 256, 9), (256, 256, 20), (512, 512, 5), (512, 512, 8), (256, 256, 32),
+                                     (128, 128, 128), (256, 1024, 5), (256, 2048, 5)])
+def test_fp64_solver_register_against_lds_kernels(nx, ny, B):
+    """FP64 load steps (AT2, strain-spectral split: CG and BCCG) with the
+    built-in kernels -- register rows of four and eight points per lane,
+    register columns with and without loads ahead -- and with an LDS plan
+    take the same iterations to the same state.  The iterations are capped,
+    so the two differ by the rounding of some 60 of them only: 1e-9 of a
+    state is 1e7 roundings."""
+    import torch
+    print(f"fp64 steps {B} x {nx}x{ny}", flush=True)
+    distinct = min(B, 2)
+    E = torch.from_numpy(np.stack([si.young_modulus(nx, 4.0, 0.2, 70 + b, ny=ny) for b in range(distinct)]))
+    E = E.double().to(device()).repeat((B + distinct - 1) // distinct, 1, 1)[:B].contiguous()
+    cfg = cfg_for(nx, ny, "fp64", at=2, max_am=2, max_newton=2, max_cg=8, max_bccg=12, use_graph=1, ticks_per_sync=16)
+    p = spff.Problem(E, cfg)
+    eps = si.uniaxial_ramp(12, 0.2, 2.0)[5]
+    start, eb = p.get_state()
+    got = []
+    for plan in (None, dict(row_kind=spff.FFT_LDS, rows=1, row_threads=128, col_kind=spff.FFT_LDS, cols=1,
+                            col_threads=256)):
+        for b in range(len(p.plan_buckets())):
+            p.set_plan(b, plan)
+        p.set_state(start, eb)
+        _, s = p.load_step(eps)
+        got.append((p.get_state()[0].cpu().numpy(), s))
+    for b in range(B):
+        for k in ("am_iters", "newton_iters", "cg_iters", "bccg_iters", "ticks"):
+            assert got[0][1][b][k] == got[1][1][b][k], (b, k)
+        assert got[0][1][b]["bccg_iters"] > 0 and got[0][1][b]["cg_iters"] > 0
+        assert rel_l2(got[0][0][b, :3], got[1][0][b, :3]) < 1e-9
+        assert rel_l2(got[0][0][b, 3], got[1][0][b, 3]) < 1e-9
+        assert abs(got[0][1][b]["F_e"] - got[1][1][b]["F_e"]) <= 1e-9 * got[1][1][b]["F_e"]
+    p.close()
+
+
+@pytest.mark.parametrize("nx,ny,B", [(512, 512, 10), (256, 1024, 10), (256, 2048, 6)])
+def test_column_loads_ahead_leave_the_results_of_long_columns(nx, ny, B):
+    """As above for columns of 512 to 2048 points: with the plan fixed the
+    batch, above 2048 column wavefronts, and the problem alone, below, agree
+    bit for bit."""
+    import torch
+    kw = dict(plan_rows=4, plan_cols=1, max_am=2, max_cg=12, max_bccg=6, at=2)
+    Et = torch.from_numpy(np.stack([si.young_modulus(nx, 4.0, 0.15 + 0.05 * b, 30 + b, ny=ny) for b in range(2)]))
+    Et = Et.to(device())
+    eps = si.uniaxial_ramp(12, 0.2, 2.0)[5]
+    p = spff.Problem(Et.repeat(B // 2, 1, 1).contiguous(), cfg_for(nx, ny, **kw))
+    _, stats = p.load_step(eps)
+    f = p.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+    for b in range(2):
+        q = spff.Problem(Et[b], cfg_for(nx, ny, **kw))
+        _, alone = q.load_step(eps)
+        g = q.get_fields(spff.FIELD_PHI | spff.FIELD_EPS_STAR)
+        for k in f:
+            assert torch.equal(f[k][b], g[k][0]) and torch.equal(f[k][B - 2 + b], g[k][0]), k
+        assert stats[b]["cg_iters"] == alone[0]["cg_iters"] > 0 and stats[b]["bccg_iters"] > 0
+        q.close()
+    p.close()

@@ -142,3 +142,19 @@ def test_memory_that_kernels_post_to_is_coherent(driver):
     p = Handle(driver, 3)
     assert driver.fake_alloc_flags() & 0x40000000
     p.close()
+
+
+@pytest.mark.parametrize("nx,ny,B,row,col", [
+    (256, 128, 1, 2, 0), (512, 256, 1, 2, 0), (1024, 512, 1, 1, 1), (1024, 256, 1, 0, 1), (64, 1024, 1, 0, 1),
+    (512, 512, 5, 2, 1), (512, 512, 8, 1, 1), (256, 256, 9, 2, 1), (256, 256, 32, 1, 1), (128, 128, 128, 1, 1)])
+def test_fp64_built_in_kernels(driver, nx, ny, B, row, col):
+    """Which kernels FP64 batches run as built in (rows: 0 LDS, 1 eight, 2
+    four points per lane; columns: 0 LDS, 1 registers): the sizes at which
+    the GPU tests compare them."""
+    p = Handle(driver, B, nx=nx, ny=ny, precision=spff.FP64)
+    p.need(*[3] * B)
+    g = (ctypes.c_int * 6)()
+    p.sequence(1)
+    driver.fake_geom(g)
+    assert [g[0], g[3]] == [row, col]
+    p.close()
