@@ -251,12 +251,27 @@ spff_plan auto_plan(const spff_config* c, int S, size_t csize) {
   while (W * 2 <= M && 3 * (size_t)(2 * W) * (c->ny + PAD) * csize <= LDS_TARGET &&
          (long)(M / (2 * W)) * S >= TARGET_WG)
     W *= 2;
+  const int T = c->plan_threads > 0 ? c->plan_threads : THREADS;
+  int TR = T;
+  if (M < 64 && c->plan_rows == 0 && c->plan_threads == 0) {
+    // Rows of 4 to 32 pixel pairs: one wavefront a group.  Every group runs
+    // the controller step first, by one wavefront while its others wait, and
+    // that step's time grows with the partial sums, one per group: up to 256
+    // groups a problem and 2048 in all (4096 from four rows a group on).  Us a
+    // tick of an AT2 step, with 256 threads before: 64 x 512 21.7 -> 18.9,
+    // 64 x 1024 28.1 -> 22.4, 16 x 64 x 64 24.6 -> 21.4, 64 x 64 x 64 29.6 ->
+    // 26.6, 13 x 64 x 512 39.8 -> 27.1, 64 x 64 x 512 96 -> 73 (AT1), FP64
+    // 9 x 32 x 128 30.9 -> 22.1, 64 x 256 21.8 -> 21.0.
+    const long rows = (long)c->ny * S;
+    TR = 64;
+    R = 1;
+    while (R * 2 <= c->ny && ((R < 4 && (c->ny / R > 256 || rows / R > 2048)) || (R == 4 && rows / R > 4096))) R *= 2;
+  }
   if (c->plan_rows > 0) R = c->plan_rows;
   if (c->plan_cols > 0) W = c->plan_cols;
-  const int T = c->plan_threads > 0 ? c->plan_threads : THREADS;
   pl.row_kind = SPFF_FFT_LDS;
   pl.rows = R;
-  pl.row_threads = T;
+  pl.row_threads = TR;
   pl.col_kind = SPFF_FFT_LDS;
   pl.cols = W;
   pl.col_threads = T;

@@ -158,3 +158,23 @@ def test_fp64_built_in_kernels(driver, nx, ny, B, row, col):
     driver.fake_geom(g)
     assert [g[0], g[3]] == [row, col]
     p.close()
+
+
+@pytest.mark.parametrize("nx,ny,B,rows", [(64, 64, 1, 1), (64, 256, 1, 1), (64, 512, 1, 2), (32, 1024, 1, 4),
+                                          (64, 2048, 1, 4), (64, 64, 32, 1), (64, 64, 33, 2), (64, 512, 13, 4),
+                                          (64, 512, 64, 8), (8, 8, 512, 2), (8, 8, 8192, 8)])
+@pytest.mark.parametrize("precision", [spff.FP32, spff.FP64])
+def test_short_rows_take_one_wavefront_a_group(driver, nx, ny, B, rows, precision):
+    """Rows below 64 pixel pairs: 64 threads a group, at most 256 groups a
+    problem and 2048 (with four or more rows a group 4096) in all, up to
+    eight rows a group; explicit overrides stand."""
+    p = Handle(driver, B, nx=nx, ny=ny, precision=precision)
+    count, plan = ctypes.c_int32(), spff.Plan()
+    driver.spff_plan_buckets(p.h, ctypes.byref(count), None)
+    assert driver.spff_get_plan(p.h, count.value - 1, ctypes.byref(plan)) == 0
+    assert (plan.row_kind, plan.rows, plan.row_threads) == (spff.FFT_LDS, rows, 64)
+    p.close()
+    p = Handle(driver, 1, nx=nx, ny=ny, precision=precision, plan_rows=2)
+    assert driver.spff_get_plan(p.h, 0, ctypes.byref(plan)) == 0
+    assert (plan.rows, plan.row_threads) == (2, 256)
+    p.close()
