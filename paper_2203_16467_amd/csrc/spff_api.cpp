@@ -735,18 +735,45 @@ void run_retire(spff_problem* p) {
   p->ahead.pop_front();
 }
 
-// Waits for the oldest block.  The words are posted while later blocks are
-// already in the stream, so the wait ends in time to enqueue the next one;
-// the stream is asked now and then, so that a failed device ends it too.
-spff_status run_wait(spff_problem* p) {
-  for (unsigned spin = 1; !run_seen(p); ++spin) {
+// Waits until done() holds of the progress words; the stream is asked now and
+// then, so that a failed device ends the wait too.
+template <typename Done>
+spff_status run_poll(spff_problem* p, Done done) {
+  for (unsigned spin = 1; !done(); ++spin) {
     if (spin % 4096) continue;
     const hipError_t e = hipStreamQuery(p->stream);
     if (e == hipErrorNotReady) continue;
     if (e != hipSuccess) return fail(SPFF_E_DEVICE, "tick block failed: %s", hipGetErrorString(e));
-    if (!run_seen(p)) return fail(SPFF_E_DEVICE, "a tick block ended without its progress being posted");
+    if (!done()) return fail(SPFF_E_DEVICE, "a tick block ended without its progress being posted");
   }
   return SPFF_OK;
+}
+
+// Waits for the oldest block.
+spff_status run_wait(spff_problem* p) {
+  return run_poll(p, [p] { return run_seen(p); });
+}
+
+// Waits until the newest block is in its last tick (a block of one tick: is
+// next), which leaves the host time to enqueue another without a gap, or until
+// its slots are all idle: then none is needed.  A block enqueued any earlier
+// ran for nothing wherever a step ended inside the one before it (64 x 256
+// FP64 step of 15 ticks in captured blocks of 8: 535 us, 480 so; blocks of one
+// tick: 3240 us a 256 x 256 AT2 step two ahead, 3160 one ahead, 3560 none).
+// Which slots a block lists does not depend on this.
+spff_status run_pause(spff_problem* p, bool* idle) {
+  const volatile unsigned long long* post = p->host_post;
+  return run_poll(p, [p, post, idle] {
+    const uint32_t left = block_ticks(p) > 1 ? 0 : 1;
+    bool last = true;
+    *idle = true;
+    for (const auto& [s, n] : p->ahead.back().upto) {
+      const unsigned long long w = post[s];
+      last = last && (uint32_t)w + left >= n;
+      *idle = *idle && (w >> 32) != 0;
+    }
+    return last || *idle;
+  });
 }
 
 // End of a run: the last controller step, every slot's control block into
@@ -761,16 +788,22 @@ spff_status run_end(spff_problem* p) {
 
 // Runs blocks of ticks, from the control blocks of the host mirror, until
 // every slot is idle -- or one of those in `more` (per slot, may be null),
-// which have further work.  blocks_ahead() blocks are enqueued beyond the one
-// whose end the host watches (a host round trip per block left the device
-// idle for 16 us: the closing kernel, a copy, a synchronisation and the next
-// launch); the ticks enqueued after the last slot has gone idle do nothing.
+// which have further work.  Blocks are enqueued while the one before is in its
+// last tick (a host round trip per block left the device idle for 16 us: the
+// closing kernel, a copy, a synchronisation and the next launch), with the
+// slots that were not idle by the end of the block blocks_ahead() before it;
+// the ticks enqueued after the last slot has gone idle do nothing.
 spff_status run_until_idle(spff_problem* p, const char* more = nullptr) {
   spff_status st = run_begin(p);
   if (st != SPFF_OK) return st;
   if (p->prof_on) return run_timed(p, more);
   bool stop = false;
   while (!p->listed.empty() && !stop) {
+    if (!p->ahead.empty()) {
+      bool idle = false;
+      st = run_pause(p, &idle);
+      if (st != SPFF_OK || idle) break;
+    }
     st = enqueue_run_block(p);
     if (st != SPFF_OK) break;
     if ((int)p->ahead.size() <= blocks_ahead(p)) continue;

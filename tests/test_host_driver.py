@@ -178,3 +178,21 @@ def test_short_rows_take_one_wavefront_a_group(driver, nx, ny, B, rows, precisio
     assert driver.spff_get_plan(p.h, 0, ctypes.byref(plan)) == 0
     assert (plan.rows, plan.row_threads) == (2, 256)
     p.close()
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 16])
+@pytest.mark.parametrize("need", [(6,), (7,), (8,), (15,), (3, 10), (21, 4, 9)])
+def test_no_block_runs_after_every_problem_is_idle(driver, K, need):
+    """A problem's end is known from the row kernel after its last tick.  The
+    driver enqueues no block once that has been seen for every problem; with
+    a device that runs each block at once, the row kernels are those of the
+    blocks that hold the last end."""
+    p = Handle(driver, len(need), ticks_per_sync=K)
+    p.need(*need)
+    p.counts()
+    st, s = p.sequence(1)
+    assert st == 0 and [row[0]["ticks"] for row in s] == list(need)
+    k = min(K, 4)
+    _, rows, cols = p.counts()
+    assert rows == cols == -(-(max(need) + 1) // k) * k
+    p.close()
