@@ -175,7 +175,9 @@ typedef struct spff_step_stats {
   int32_t newton_iters;    /* mechanics Newton steps (sum over AM iterations) */
   int32_t cg_iters;        /* mechanics CG iterations (sum) */
   int32_t bccg_iters;      /* phase-field BCCG iterations (sum) */
-  int32_t ticks;           /* solver ticks the step took */
+  int32_t ticks;           /* solver ticks the step took: two per BCCG iteration, one per CG iteration,
+                              mechanics residual, phase-field assembly and end of a phase-field
+                              solve, convergence check and statistics */
   double dphi_l1;          /* last ||phi_n+1 - phi_n||_1 */
   double mech_residual;    /* last ||G[sigma]||_2, summed over its Fourier modes */
   double pf_residual;      /* last BCCG ||r||_2 */

@@ -50,9 +50,10 @@ constexpr size_t LDS_MAX = 150 * 1024;
 
 // Blocks of ticks: at most BLOCK_TICKS ticks each, and ticks_per_sync: short,
 // so that few idle ticks follow a run's last one.  A captured block costs a
-// gap of its own and is twice as long (13 x 256^2 evolution: 8.0 ms with
-// captured blocks of 4 ticks, 7.7 with 8, 7.6 launched eagerly by 4; 2048^2
-// step: 2.68, 2.72, 2.66 ms, and 2.85 with captured blocks of 32).
+// gap of its own and is twice as long (13 x 256^2 evolution: 7.57 ms with
+// captured blocks of 4 ticks, 7.23 with 8, 7.16 with 16, 7.17 launched eagerly
+// by 4; 256^2 AT2 step 3.25, 3.02, 2.97, 3.07, and 3.36 eagerly by 2; 2048^2
+// step 2.54, 2.54, 2.61, 2.50 ms).
 constexpr int BLOCK_TICKS = 4;
 constexpr int GRAPH_TICKS = 8;
 constexpr int BLOCKS_AHEAD = 2;
@@ -441,7 +442,7 @@ struct spff_problem {
   int list_at = 0;
   std::vector<int32_t> cur_list;
   SlotCtl* host_ctl;  // pinned mirror (S blocks), and a second copy for run_begin()'s upload
-  // progress words that the row kernels post (pinned), see run_slots()
+  // progress words that the row kernels post (pinned), see run_poll()
   unsigned long long* host_post = nullptr;
   unsigned* host_refused = nullptr;  // pinned: whether the last state given was refused
   unsigned state_token = 0;

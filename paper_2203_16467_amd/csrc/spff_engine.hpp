@@ -33,8 +33,8 @@
 // block ((i + 1) & 1), which the column kernel of tick i reads.  Ticks
 // contain no host round trip, so blocks of ticks can be replayed as a
 // captured HIP graph.  The row kernel of a tick posts the slot's progress
-// to pinned host memory, which the host watches while later blocks are
-// already enqueued; a closing kernel after the last block leaves the current
+// to pinned host memory, which the host watches to enqueue the next block in
+// the last tick of the newest one; a closing kernel after the last block leaves the current
 // control blocks in buffer 0 and in the host's mirror.
 #pragma once
 #include <stdint.h>
@@ -192,7 +192,8 @@ struct KTime {
   unsigned long long end[KT_LINES * KT_STRIDE];
 };
 
-// Number of FP64 partials per work-group written by each kernel.
+// Number of FP64 partials per work-group written by each kernel.  (The column
+// kernel of a PF_WAIT tick leaves the strain's scaling factor in the first.)
 constexpr int NP_ROW = 8;
 constexpr int NP_COL = 2;
 
