@@ -1152,7 +1152,8 @@ spff_status engine_create(const spff_config* cfg, int32_t nbatch, const void* E_
   auto pinned = [](auto** ptr, size_t bytes) {
     return hipHostMalloc(reinterpret_cast<void**>(ptr), bytes, hipHostMallocCoherent) == hipSuccess;
   };
-  if (!pinned(&p->host_ctl, 2 * sizeof(SlotCtl) * nbatch) || !pinned(&p->host_list, sizeof(int32_t) * nbatch * LIST_RING) ||
+  if (!pinned(&p->host_ctl, 2 * sizeof(SlotCtl) * nbatch) ||
+      !pinned(&p->host_list, sizeof(int32_t) * nbatch * LIST_RING) ||
       !pinned(&p->host_post, sizeof(unsigned long long) * nbatch) || !pinned(&p->host_refused, sizeof(unsigned)))
     return cleanup(fail(SPFF_E_DEVICE, "pinned host allocation failed"));
   for (int s = 0; s < nbatch; ++s) reset_ctl(p, s);
